@@ -295,7 +295,7 @@ qgx_status qgx_eg_step(qgx_ctx* ctx, int half, const qgx_stream* cur, const qgx_
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
  * same kernels, same results bit for bit as qgx_eg_step; the one difference is where the second
  * half-step keeps its scratch, the per-chunk partial sums of S: not in memory that qgx_create allocated
- * but in a fixed array inside the library's device image (8 * QGX_STATIC_MAX_CHUNKS = 512 KiB per GPU,
+ * but in a fixed array inside the library's device image (16 * QGX_STATIC_MAX_CHUNKS = 1 MiB per GPU,
  * held until the process ends; its address on a device is looked up once, in the first qgx_create on
  * that device).  The call itself allocates and frees nothing.
  *   - QGX_ERR_CAPACITY if the layout has more than QGX_STATIC_MAX_CHUNKS chunks per worker (qgx_eg_step

@@ -3,105 +3,157 @@
 // (Section 3.2 / Appendix J for the decoding; Algorithm 1 and eq. (Q-GenX) for the updates;
 // Theorem 3 for gamma_t.)
 //
-// One wave per chunk position.  The wave copies a worker's chunk from the payload into LDS with
-// coalesced 16-byte loads, then every lane parses its own 64 coordinates, that is two sub-chunks of
-// 32, each starting at the bit offset the sub-chunk table gives: a 64-bit window from three LDS words
-// per three symbols, one table look-up by the next 13 (or 11) stream bits for each symbol's length and
-// level, the sign bit, one multiply by the bucket norm.  A symbol's length decides where the next one
-// starts, so a parse is one long dependent chain of LDS look-ups; what a lane can do about that is to
-// follow several chains at once: its two sub-chunks, of one stream or (second half-step) of both.
-// The K decoded values of a coordinate are summed in registers, so decoded vectors never go to HBM in
-// the fused modes.  Chunk positions with fewer than 4096 coordinates are few and have a body of their
-// own (decode_ragged_body), which spreads a position's workers over the waves of a workgroup; it runs
-// in the same launch as the full positions' body when a layout has both.
+// A wave's task is half a chunk position: 2048 coordinates, of which every lane parses one run of 32
+// (a sub-chunk), starting at the bit offset the sub-chunk table gives.  The wave copies its half of a
+// worker's chunk from the payload into LDS with coalesced 16-byte loads, then every lane parses its
+// run: a 64-bit window from three LDS words per three symbols, one table look-up by the next 13 (or 11)
+// stream bits for each symbol's length and level, the sign bit, one multiply by the bucket norm.  A symbol's
+// length decides where the next one starts, so a parse is one long dependent chain of LDS look-ups.
+// The K decoded values of a coordinate are summed in registers in worker order, so decoded vectors
+// never go to HBM in the fused modes.
+//
+// Two shapes, eight chains per SIMD either way (LDS holds no more):
+//   one stream (mean, first half-step): one chain per lane, 64 registers, eight waves per SIMD, whose
+//     loads, parses and updates cover each other;
+//   two streams (second half-step): two chains per lane, a worker's two streams, 128 registers, four waves
+//     per SIMD; the next worker's half chunks travel ahead in registers.  Plain decoding has this shape too,
+//     with two workers' chunks.
+// Why half a position: a wave per whole position held 64 sums per lane, which left four (one stream) or two
+// (two streams) waves per SIMD, and a launch of a round or two of equal waves in step.  Measured, whole position
+// -> half: second half-step of 16 x 2^26 coordinates 1.246 -> 1.02 ms, of 8 x 9.86 M 0.150 -> 0.115 ms; first
+// half-step 0.593 -> 0.535 and 0.085 -> 0.057 ms.
+// Positions of fewer than 4096 coordinates are the same tasks with some lanes' symbols masked out; a half
+// without coordinates is no task at all.  (A workgroup per such position, its workers spread over the waves, took
+// 0.168 ms for the second half-step of 5 x 3 M coordinates in buckets of 6000, this takes 0.035.)
 #include "qgx_device.h"
 
 namespace qgx {
 
-constexpr int kPre = kChunkWordsMax / (kWave * 4);   // 7 x uint4 per lane cover a worst-case chunk
-constexpr int kDecWaves = 8;                          // waves per workgroup: they share the decode table
+constexpr int kHalfCoords = kChunk / 2;               // coordinates of a task, a run of kSub per lane
+constexpr int kPre = 3;                               // uint4 per lane that travel ahead: 768 words, 12 bits per coordinate
+static_assert(kHalfCoords * kMaxSymBits / 32 + 8 <= (kPre + 1) * kWave * 4, "one more covers any half chunk");
+template <DecMode MODE, bool PREV> constexpr bool two_chains() { return PREV || MODE == DecMode::Decode; }
+template <DecMode MODE, bool PREV> constexpr int most_waves() { return two_chains<MODE, PREV>() ? 8 : 16; }   // per workgroup: they share the decode table
+static_assert(kSub * kWave == kHalfCoords && kSubs == 2 * kWave, "a sub-chunk per lane, two tasks per chunk");
 
-// Staged chunk layout in LDS.  Lane j parses the j-th run of 64 coordinates, whose bits start roughly
-// 64 * (bits per coordinate) / 32 words after lane j-1's: a power-of-two stride that would put all
-// lanes on a few banks.  So two pad words are inserted after every 32 words (word i lives at
-// i + 2 (i / 32)), and the pad slots repeat the two words that follow them, so that a lane always
-// finds the three words of its 64-bit window next to each other.
+// Staged words in LDS.  Lane j parses the j-th run of the half, whose bits start roughly bits-per-coordinate
+// words after lane j-1's: often a stride that would put all lanes on a few banks.  So two pad words
+// are inserted after every 32 words (word i lives at i + 2 (i / 32)), and the pad slots repeat the two
+// words that follow them, so that a lane always finds the three words of its 64-bit window next to
+// each other.
 __device__ __forceinline__ uint32_t staged(uint32_t i) { return i + ((i >> 5) << 1); }
 
-struct ChunkRef {            // where one worker's chunk lives and how long it is
-    const uint4* src;
-    uint32_t words;          // multiple of 4, 0 when the tables are inconsistent
+// A load through the scalar cache, of what an earlier launch wrote and this one only reads: a wave's tables of
+// extents cost no vector registers and no wait on the vector loads in flight.
+__device__ __forceinline__ uint32_t scalar_load(const void* p)
+{
+    return *reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// One worker's stream as this wave reads it (wave-uniform): its chunk's entry in the offset table, its row of
+// sub-chunk ends, its norms and its payload; stepped from worker to worker.
+struct StreamAt {
+    const uint32_t* off;
+    const uint16_t* ends;
+    const float* norms;
+    const uint32_t* payload;
 };
 
-// A chunk's size comes from its bit length (last sub-chunk entry), so compact and slotted
-// placements read alike; its start comes from the offset table.
-__device__ __forceinline__ ChunkRef chunk_ref(const uint32_t* payload, uint64_t cap, const uint32_t* chunk_off,
-                                              const uint16_t* sub_end, uint32_t k, uint32_t c, uint32_t NC,
-                                              uint32_t max_words, Scalars* sc)
+__device__ __forceinline__ StreamAt stream_at(const uint32_t* chunk_off, const uint16_t* sub_end, const float* norms,
+                                              const uint32_t* payload, uint64_t cap, uint32_t k, uint32_t c, const Layout& lay)
 {
-    const uint32_t off = chunk_off[(size_t)k * (NC + 1) + c];
-    const uint32_t bits = sub_end[((size_t)k * NC + c) * kSubs + (kSubs - 1)];
-    ChunkRef r;
-    r.src = reinterpret_cast<const uint4*>(payload + (size_t)k * cap + off);
-    r.words = (((bits + 31u) >> 5) + 3u) & ~3u;
-    if (r.words > max_words || (off & 3u) || (uint64_t)off + r.words > cap) {
+    return StreamAt{chunk_off + (size_t)k * (lay.NC + 1) + c, sub_end + ((size_t)k * lay.NC + c) * kSubs,
+                    norms + (size_t)k * lay.NB, payload + (size_t)k * cap};
+}
+
+__device__ __forceinline__ void step_workers(StreamAt& s, uint64_t cap, uint32_t n, const Layout& lay)
+{
+    s.off += (size_t)n * (lay.NC + 1);
+    s.ends += (size_t)n * lay.NC * kSubs;
+    s.norms += (size_t)n * lay.NB;
+    s.payload += (size_t)n * cap;
+}
+
+// Where half a chunk lies (wave-uniform): the chunk's first word in the worker's payload, and the bits of
+// the chunk at which the half starts and ends.
+struct Extent { uint32_t off, start, end; };
+
+__device__ __forceinline__ Extent load_extent(const StreamAt& s, uint32_t half)
+{
+    Extent x;                                             // (rows of 256 bytes: pairs of entries are words)
+    x.off = scalar_load(s.off);
+    x.start = half ? scalar_load(s.ends + kWave - 2) >> 16 : 0u;
+    x.end = scalar_load(s.ends + kWave * (half + 1u) - 2u) >> 16;
+    return x;
+}
+
+// What a lane needs of it: where its run ends (the lane before it: where it starts), and its bucket's norm.
+struct RunMeta { uint32_t hi; float n; };
+
+// The words that hold the half's bits.  A half's extent comes from the sub-chunk table, so
+// compact and slotted placements read alike; words counts from w0, both multiples of 4.
+struct HalfRef {
+    const uint4* src;
+    uint32_t w0, words, start;
+};
+
+__device__ __forceinline__ HalfRef half_ref(const uint32_t* payload, uint64_t cap, const Extent& x, uint32_t max_words, Scalars* sc)
+{
+    HalfRef r;
+    r.start = x.start;
+    r.w0 = (x.start >> 5) & ~3u;
+    r.words = ((((x.end + 31u) >> 5) + 3u) & ~3u) - r.w0;      // (an end before the start: beyond max_words, or an empty run)
+    uint64_t at = (uint64_t)x.off + r.w0;
+    if (r.words > max_words || (x.off & 3u) || at + r.words > cap) {
         if (lane_id() == 0) raise_error(sc, QGX_EBIT_STREAM);
-        r.words = 0;
+        r.words = 0;                                      // nothing is staged: what was staged before is parsed
+        at = 0;
     }
+    r.src = reinterpret_cast<const uint4*>(payload + at);
     return r;
 }
 
-__device__ __forceinline__ void prefetch_chunk(const ChunkRef& cr, uint4 (&pre)[kPre])
+// Lanes past the half's words read its last piece once more (no branch per load); nobody stages it.  With no words
+// at all that is the first piece of the worker's payload, which holds at least one.
+__device__ __forceinline__ void prefetch_half(const HalfRef& hr, uint4 (&pre)[kPre], uint32_t lane)
 {
-    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t last = max(hr.words >> 2, 1u) - 1u;
 #pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const uint32_t i = lane + (uint32_t)q * kWave;
-        pre[q] = (i < (cr.words >> 2)) ? nt_load4u(cr.src + i) : make_uint4(0, 0, 0, 0);
-    }
+    for (int q = 0; q < kPre; ++q) pre[q] = nt_load4u(hr.src + min(lane + (uint32_t)q * kWave, last));
 }
 
-__device__ __forceinline__ void commit_chunk(uint32_t* stage, const uint4 (&pre)[kPre], uint32_t stage_words)
-{
-    const uint32_t lane = (uint32_t)lane_id();
-#pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        const uint32_t i0 = (lane + (uint32_t)q * kWave) * 4u;
-        if (i0 < stage_words) {
-            uint2* at = reinterpret_cast<uint2*>(stage + staged(i0));          // even slot: 8-byte aligned
-            at[0] = make_uint2(pre[q].x, pre[q].y);
-            at[1] = make_uint2(pre[q].z, pre[q].w);
-            if ((i0 & 31u) == 0u && i0 != 0u) at[-1] = make_uint2(pre[q].x, pre[q].y);   // pads repeat their successors
-        }
-    }
-}
-
-// The chunk back to front, for the parse of the full positions: stream bit t goes to bit
+// The half chunk goes to LDS back to front: its bit t (counted from word w0) goes to bit
 // 32 (kTail + stage_words) - 1 - t of the buffer (word w to place kTail + stage_words - 1 - w, its bits
 // turned round), so that a plain funnel shift of buffer words gives a window with the FIRST stream bit on
 // top, which is how the decode tables are indexed, and no window has to be turned round when it is read:
 // a word is turned once here instead of twice per three symbols there.  kTail zero words lie below the
-// chunk's end (the windows of its last symbols reach there), and the buffer's slack above its first word
-// stays zero as well (a cursor may point one bit before the chunk).  The pads are as in the forward layout.
-// `words`: the chunk's own size; pieces of 256 words that lie beyond it are left as they are (a valid
+// end (the windows of the last symbols reach there), and the buffer's slack above the first word
+// stays zero as well (a cursor may point one bit before it).
+// `words`: the half's own size; pieces of 256 words that lie beyond it are left as they are (a valid
 // stream's symbols never depend on what follows its last bit).
 constexpr int kTail = 4;
-__device__ __forceinline__ void commit_chunk_reversed(uint32_t* stage, const uint4 (&pre)[kPre], uint32_t stage_words,
-                                                      uint32_t words)
+__device__ __forceinline__ void commit_half(uint32_t* stage, const uint4 (&pre)[kPre], const HalfRef& hr, uint32_t stage_words,
+                                            uint32_t lane)
 {
-    static_assert(kTail % 4 == 0 && kChunkWordsMax % 4 == 0, "16-byte pieces stay aligned");
-    const uint32_t lane = (uint32_t)lane_id();
+    static_assert(kTail % 4 == 0, "16-byte pieces stay aligned");
+    constexpr uint32_t kStep = kWave * 4u + kWave * 4u / 16u;                 // a piece of 256 words and its pads
+    const uint32_t j0 = (uint32_t)kTail + stage_words - 4u - 4u * lane;       // place of the lane's LAST word of piece 0
+    uint32_t* at0 = stage + (int)staged(j0);                                  // (piece q: whole steps of 32 words below)
+    const bool pads = (j0 & 31u) == 0u;
 #pragma unroll
-    for (int q = 0; q < kPre; ++q) {
-        if ((uint32_t)q * (kWave * 4u) >= words) break;                       // (wave-uniform)
-        const uint32_t i0 = (lane + (uint32_t)q * kWave) * 4u;
-        if (i0 < stage_words) {
-            const uint32_t j0 = (uint32_t)kTail + stage_words - 4u - i0;      // place of the piece's LAST word
-            uint2* at = reinterpret_cast<uint2*>(stage + staged(j0));
-            const uint2 low = make_uint2(__brev(pre[q].w), __brev(pre[q].z));
+    for (int q = 0; q <= kPre; ++q) {
+        const uint32_t left = hr.words - (uint32_t)q * (kWave * 4u);          // words from this piece on
+        if ((int)left <= 0) break;                                            // (wave-uniform)
+        uint4 x;
+        if (q < kPre) x = pre[q < kPre ? q : 0];
+        // the end of a half chunk of the longest codes: asked for only here (its registers are better spent)
+        else x = nt_load4u(hr.src + min(lane + (uint32_t)q * kWave, (hr.words >> 2) - 1u));
+        if (4u * lane < left) {
+            uint2* at = reinterpret_cast<uint2*>(at0 - q * (int)kStep);
+            const uint2 low = make_uint2(__brev(x.w), __brev(x.z));
             at[0] = low;
-            at[1] = make_uint2(__brev(pre[q].y), __brev(pre[q].x));
-            if ((j0 & 31u) == 0u) at[-1] = low;                               // (j0 >= kTail: never the buffer's first word)
+            at[1] = make_uint2(__brev(x.y), __brev(x.x));
+            if (pads) at[-1] = low;                                           // (j0 - 256 q >= kTail: never the buffer's first word)
         }
     }
 }
@@ -112,44 +164,23 @@ constexpr int kTabLvalBytes = kSymMax * 4;
 constexpr int kTabBytes = kTabLvalBytes + kDlut * 2;
 
 // Symbols are parsed in groups of up to three from one 64-bit window (three LDS words): a symbol
-// takes at most 15 bits with its sign, so the third one still starts inside the first word.  A table
-// entry is a bit count | 4 idx << 4 with bits 4 and 5 clear (the 13-bit table counts the symbol's bits
-// incl. sign less one, the 8-byte table all of them), so sums of entries carry the consumed bits in
-// their low six bits and an entry can be used as a shift count as it is.
-// The three steps are separate so that the caller can issue the next group's window reads before
-// it turns the current group's entries into values.
+// takes at most 15 bits with its sign, so the third one still starts inside the first word.  An entry of the
+// 13-bit table is the symbol's bits incl. sign less one | 4 idx << 4 with bits 4 and 5 clear, so sums of entries
+// carry the consumed bits in their low six bits; the 8-byte table's entries are minus the symbol's bits.
 struct Window { uint32_t w0, w1, w2; };
 
 __device__ __forceinline__ Window read_window(const uint32_t* stage, uint32_t p)
 {
-    const uint32_t* wp = stage + (p >> 5) + ((p >> 10) << 1);
-    return Window{wp[0], wp[1], wp[2]};
+    // (the two shift-and-adds spelled out: the compiler would shift and mask each part, an instruction more)
+    uint32_t at = lds_address(stage);
+    asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(p) : "v"(p >> 10), "v"(p >> 5));
+    asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(at) : "v"(p), "s"(at));
+    return Window{lds_load_u32(at), lds_load_u32(at + 4u), lds_load_u32(at + 8u)};
 }
 
-// The dependent chain: window i needs the lengths of the symbols before it.  Advances the cursor.
-// The 64 bits are turned so that the first stream bit is on top: a window is then a funnel shift
-// away, its top 13 bits index the table, and a symbol's last bit (the sign) reaches bit 31 by a left
-// shift of (symbol bits - 1), which is what the entry's low bits hold.  `neg` counts the used bits
-// downwards (adding ~e takes off the entry's count plus one); only its low six bits mean anything.
-template <int N>
-__device__ __forceinline__ void parse_group(const Window& w, const unsigned char* tab, uint32_t& p,
-                                            uint32_t (&win)[3], uint32_t (&e)[3])
-{
-    const uint32_t top = __brev(__builtin_amdgcn_alignbit(w.w1, w.w0, p));    // shifts use p mod 32
-    const uint32_t nxt = __brev(__builtin_amdgcn_alignbit(w.w2, w.w1, p));
-    uint32_t neg = 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        win[i] = i == 0 ? top : __builtin_amdgcn_alignbit(top, nxt, neg);     // (top:nxt) << used, upper word
-        e[i] = *reinterpret_cast<const uint16_t*>(tab + kTabLvalBytes + ((win[i] >> 18) & 0x3FFEu));
-        neg += ~e[i];
-    }
-    p -= neg | 0xFFFFFFC0u;                                                   // minus (minus the bits used)
-}
-
-// The same chain for the kernel of the full positions, which stages its chunks back to front
-// (commit_chunk_reversed): the cursor r is a bit position in the buffer and moves DOWN, the three words
-// from it give the 64 bits with the first stream bit on top by two funnel shifts and nothing else.
+// The dependent chain: window i needs the lengths of the symbols before it.  The cursor r is a bit position
+// in the buffer and moves DOWN, the three words from it give the 64 bits with the first stream bit on top by
+// two funnel shifts and nothing else.
 // The windows are taken one bit early: r + 63 is the buffer bit of the stream bit BEFORE the next symbol,
 // so bit 31 of a symbol's window is the last bit of the symbol before it, which is that symbol's sign
 // if it has one.  The sign of a symbol is thus read off the window of the next one with a single
@@ -160,8 +191,8 @@ __device__ __forceinline__ void parse_group(const Window& w, const unsigned char
 // 15..31, valid entries never do, so no per-symbol flag is kept.
 // WIDE: the 8-byte table's entries are the negative counts themselves and only need adding up.
 template <int N, bool WIDE, bool LAST>
-__device__ __forceinline__ void parse_group_early(const Window& w, const unsigned char* tab, uint32_t& r,
-                                                  uint32_t (&W)[4], uint32_t (&e)[3], float (&lv)[3], uint32_t& seen)
+__device__ __forceinline__ void parse_group(const Window& w, const unsigned char* tab, uint32_t& r,
+                                            uint32_t (&W)[4], uint32_t (&e)[3], float (&lv)[3], uint32_t& seen)
 {
     static_assert(!LAST || N == 2, "a run of 32 symbols ends with a group of two");
     const uint32_t top = __builtin_amdgcn_alignbit(w.w2, w.w1, r);            // shifts use r mod 32
@@ -195,7 +226,7 @@ __device__ __forceinline__ float signed_norm(uint32_t w_next, float n)
 // EXACT_ZERO: +0 for the zero symbol, whose sign bit is not in the stream (the level 0 is the only one
 // that is zero)
 template <bool EXACT_ZERO>
-__device__ __forceinline__ float value_early(uint32_t w_next, float lv, float n)
+__device__ __forceinline__ float symbol_value(uint32_t w_next, float lv, float n)
 {
     const float val = __uint_as_float((w_next & 0x80000000u) | __float_as_uint(n * lv));
     if (EXACT_ZERO) return lv == 0.0f ? 0.0f : val;
@@ -207,48 +238,24 @@ __device__ __forceinline__ float level_of(const unsigned char* tab, uint32_t e)
     return *reinterpret_cast<const float*>(tab + (e >> 4));                  // the entry holds 4 * idx
 }
 
-// Signed value norm * l_idx of one parsed symbol, lv = level_of(entry).
-// EXACT_ZERO: give +0 for the zero symbol (whose sign bit is not in the stream); the accumulating
-// modes leave the stray sign on the zero, which adds nothing.
-template <bool EXACT_ZERO>
-__device__ __forceinline__ float symbol_value(float lv, uint32_t win, uint32_t e, float n)
-{
-    const uint32_t sg = win << (e & 31u);                                      // last bit of the symbol -> bit 31
-    // norm and level are not negative: the sign goes in with one OR
-    const float val = __uint_as_float((sg & 0x80000000u) | __float_as_uint(n * lv));
-    if (EXACT_ZERO) return (e >> 4) == 0u ? 0.0f : val;
-    return val;
-}
-
-struct SubMeta {             // what a lane needs to parse its run of one worker's chunk
-    uint32_t p0, p_end;      // bit cursor at the start and expected at the end
-    uint32_t p_mid;          // where the lane's second sub-chunk starts
-    float n;                 // norm of the bucket
-};
-
-__device__ __forceinline__ SubMeta load_meta(const uint16_t* sub_end, const float* norms, uint32_t k, uint32_t c,
-                                             uint32_t bkt, const Layout& lay, int lane)
-{
-    const uint16_t* se = sub_end + ((size_t)k * lay.NC + c) * kSubs;
-    SubMeta m;
-    m.p_end = se[2 * lane + 1];
-    m.p_mid = se[2 * lane];
-    m.p0 = lane ? (uint32_t)se[2 * lane - 1] : 0u;
-    // the lane's 64 coordinates lie in one bucket: the chunk's own, or with shared chunks one further on
-    // (a lane past the end of a short chunk has nothing to decode: its index is kept inside the table)
-    m.n = norms[(size_t)k * lay.NB + min(bkt + (((uint32_t)lane * (uint32_t)kLaneCoords) >> lay.bucket_shift), lay.NB - 1u)];
-    return m;
-}
+// Bits of a symbol (sign included) and the reject flag, from its table entry.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t symbol_bits(uint32_t e) { return WIDE ? 0u - e : (e & 15u) + 1u; }
+template <bool WIDE>
+__device__ __forceinline__ bool is_reject(uint32_t e) { return WIDE ? e == kWideReject : (e & kDlutReject) != 0u; }
 
 // Level values and decode table of one Tables object into the decoder's LDS array (WIDE: the table of
-// 8-byte entries, which has the same size).
-template <bool WIDE = false>
+// 8-byte entries, which has the same size and holds the level values itself).
+template <bool WIDE>
 __device__ __forceinline__ void load_tables(unsigned char* s_tab, const Tables* __restrict__ tab, int tid, int nthreads)
 {
     static_assert(kWide * sizeof(uint2) == kDlut * sizeof(uint16_t), "the two decode tables share one LDS area");
-    for (int i = tid; i < kSymMax; i += nthreads) reinterpret_cast<float*>(s_tab)[i] = tab->lval[i];
-    const uint32_t* src = WIDE ? reinterpret_cast<const uint32_t*>(tab->dlutw) : reinterpret_cast<const uint32_t*>(tab->dlut);
-    for (int i = tid; i < kDlut / 2; i += nthreads) reinterpret_cast<uint32_t*>(s_tab + kTabLvalBytes)[i] = src[i];
+    static_assert(offsetof(Tables, dlut) % 16 == 0 && offsetof(Tables, dlutw) % 16 == 0 && sizeof(Tables) % 16 == 0, "16-byte copies");
+    if constexpr (!WIDE) {
+        for (int i = tid; i < kSymMax; i += nthreads) reinterpret_cast<float*>(s_tab)[i] = tab->lval[i];
+    }
+    const uint4* src = WIDE ? reinterpret_cast<const uint4*>(tab->dlutw) : reinterpret_cast<const uint4*>(tab->dlut);
+    for (int i = tid; i < kDlut / 8; i += nthreads) reinterpret_cast<uint4*>(s_tab + kTabLvalBytes)[i] = src[i];
 }
 
 // First coordinate, length and bucket of chunk position c.
@@ -266,35 +273,43 @@ __device__ __forceinline__ void chunk_geometry(const Layout& lay, uint32_t c, ui
     }
 }
 
-// Covers the chunk positions that hold 4096 coordinates (straight-line parse, output turned through
-// LDS); the others are k_decode_ragged's.
+template <bool B> struct BoolTag { static constexpr bool value = B; };
+
+// Four consecutive floats; a decoded vector of an odd length puts them at any multiple of 4 bytes.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // PREV (Half1): the previous half-step's streams are there; without them the vectors count as zero.
 // TWO: those were coded with another level table and code (a.tab_p) than the current ones.
 // WIDE: the first kWideBits bits of a code word always tell which one it is, so the 8-byte decode table
 // is there (of both codes, with TWO).
-// KSPLIT = 2 or 4: that many neighbouring waves share a position, each takes a run of the workers (as
+// KSPLIT = 2 or 4: that many neighbouring waves share a task, each takes a run of the workers (as
 // equal as K allows, the longer runs first), and they add their sums through LDS before the update
-// (for layouts with too few positions to fill the GPU's wave slots).
-// The kernel's body, for workgroup `block` of the full positions' grid; the LDS arrays are the caller's:
-// s_dyn [waves][1 or 2][stage_stride], s_tab and (TWO) s_tab2 of kTabBytes, s_sd [kDecWaves] (KSPLIT > 1).
+// (for layouts with too few tasks to fill the GPU's wave slots).
+// What bounds it: the parse, whose chains wait for their look-ups (vector ALUs busy for about 55 % of the time, LDS
+// for about half), and at the largest sizes of one stream the memory path (the update moves 6 TB/s).
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-__device__ __forceinline__ void decode_full_body(const Layout& lay, const Tables* __restrict__ tab, Scalars* sc,
-                                                 const DecodeArgs& a, uint32_t block, uint32_t* s_dyn,
-                                                 unsigned char* s_tab, unsigned char* s_tab2, double* s_sd)
+__global__ __launch_bounds__((most_waves<MODE, PREV>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>()) ? 4 : 8)))
+void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
 {
     static_assert(!PREV || MODE == DecMode::Half1, "only the second half-step reads two streams");
     static_assert(!TWO || PREV, "a second table only comes with a second stream");
     static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "the waves of a workgroup in groups of 1, 2 or 4");
     static_assert(KSPLIT == 1 || MODE != DecMode::Decode, "plain decoding has nothing to add up");
-    const unsigned char* s_tab_p = TWO ? s_tab2 : s_tab;
+    extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][2][stage_stride]
+    __shared__ double s_sd[KSPLIT > 1 ? most_waves<MODE, PREV>() : 1];
+    constexpr bool kTwo = two_chains<MODE, PREV>();       // chains per lane
+    constexpr uint32_t kBufs = kTwo ? 2u : 1u;
+    __shared__ __align__(16) unsigned char s_tab[kTabBytes];
+    __shared__ __align__(16) unsigned char s_tab2[TWO ? kTabBytes : 16];
+    const unsigned char* s_tab_b = TWO ? s_tab2 : s_tab;
 
-    const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    const uint32_t nwaves = blockDim.x >> 6;
     const int part = w & (KSPLIT - 1);                   // this wave's place in its group
-    constexpr int kBufs = PREV ? 2 : 1;
-    const uint32_t stage_words = a.stage_words;          // words a chunk of this code can take
+    const uint32_t stage_words = a.stage_words;          // words half a chunk of this code can touch
     const uint32_t stage_stride = a.stage_stride;        // padded size of one staging buffer, words
     uint32_t* stage = s_dyn + (size_t)w * kBufs * stage_stride;
-    uint32_t* stage_p = stage + stage_stride;
+    uint32_t* stage_b = stage + stage_stride;
 
     if constexpr (WIDE) {
         bool ok = tab->wide_ok != 0u;
@@ -304,233 +319,298 @@ __device__ __forceinline__ void decode_full_body(const Layout& lay, const Tables
             return;
         }
     }
-    load_tables<WIDE>(s_tab, tab, tid, kDecWaves * kWave);
-    if constexpr (TWO) load_tables<WIDE>(s_tab2, a.tab_p, tid, kDecWaves * kWave);
-    // words past a chunk's end are read by the window of its last symbols: keep them defined
+
+    // ---- the task ---------------------------------------------------------------------------------
+    // The chains of a lane: worker k; and its previous stream (PREV), or worker k + 1 (Decode).
+    constexpr uint32_t kStep = MODE == DecMode::Decode ? 2u : 1u;
+    const uint32_t g = blockIdx.x * nwaves + (uint32_t)w;                        // global wave number
+    uint32_t task, k_first, k_count;
+    bool mine;                                           // wave-uniform: there is such a task
+    if (MODE == DecMode::Decode) {                       // a task of two workers
+        const uint32_t pair = g / lay.n_tasks;
+        task = g - pair * lay.n_tasks;
+        mine = 2u * pair < lay.K;
+        k_first = mine ? 2u * pair : 0u;
+        k_count = min(2u, lay.K - k_first);
+    } else {
+        const uint32_t each = lay.K / KSPLIT, more = lay.K % KSPLIT;   // `more` runs of each + 1, then runs of each
+        task = g / KSPLIT;
+        mine = task < lay.n_tasks;
+        k_first = (uint32_t)part * each + min((uint32_t)part, more);
+        k_count = each + ((uint32_t)part < more ? 1u : 0u);            // (the host: KSPLIT <= K)
+    }
+    if (!mine) task = 0u;                                // does task 0's work for nobody (workgroup barriers below)
+    const uint32_t ch = lay.task ? scalar_load(lay.task + task) : task;
+    const uint32_t c = ch >> 1, half = ch & 1u;
+    uint32_t clo, clen, bkt;
+    chunk_geometry(lay, c, clo, clen, bkt);
+    const uint32_t cend = clo + clen;
+    const uint32_t base = clo + (uint32_t)kHalfCoords * half;                    // first coordinate of the task
+    const bool full = base + (uint32_t)kHalfCoords <= cend;                      // (wave-uniform)
+
+    StreamAt sa = stream_at(a.chunk_off, a.sub_end, a.norms, a.payload, a.cap_words, k_first, c, lay), sb = sa;
+    if constexpr (PREV) sb = stream_at(a.chunk_off_p, a.sub_end_p, a.norms_p, a.payload_p, a.cap_words_p, k_first, c, lay);
+    else if (kTwo && k_count > 1u) step_workers(sb, a.cap_words, 1u, lay);              // (an odd worker out: itself again, for nothing)
+    const uint64_t cap_b = PREV ? a.cap_words_p : a.cap_words;
+    auto meta_of = [&](const StreamAt& s, uint32_t ln) {
+        // the lane's 32 coordinates lie in one bucket: the chunk's own, or with shared chunks one further on
+        // (a lane past the end of a short chunk has nothing to decode: its index is kept inside the table)
+        const uint32_t run = (uint32_t)kWave * half + ln;
+        const uint32_t bucket = min(bkt + ((run * (uint32_t)kSub) >> lay.bucket_shift), lay.NB - 1u);
+        return RunMeta{s.ends[run], s.norms[bucket]};
+    };
+    // Ahead of the parse travel, in registers, the next half chunks with their runs' ends and norms, and (scalar)
+    // the extents of the ones after them, which have to be known before their words can be asked for.
+    RunMeta ma{}, mb{};
+    HalfRef ra{}, rb{};
+    Extent xa{}, xb{};
+    uint4 pre_a[kPre], pre_b[kPre];
+    auto fetch = [&](uint32_t i, uint32_t ln) {
+        ra = half_ref(sa.payload, a.cap_words, xa, stage_words, sc);
+        prefetch_half(ra, pre_a, ln);
+        ma = meta_of(sa, ln);
+        if constexpr (kTwo) {
+            rb = half_ref(sb.payload, cap_b, xb, stage_words, sc);
+            prefetch_half(rb, pre_b, ln);
+            mb = meta_of(sb, ln);
+        }
+        if (i + kStep < k_count) {
+            step_workers(sa, a.cap_words, kStep, lay);
+            xa = load_extent(sa, half);
+            if constexpr (kTwo) {
+                if (PREV || i + kStep + 1u < k_count) step_workers(sb, cap_b, kStep, lay);
+                xb = load_extent(sb, half);
+            }
+        }
+    };
+    uint32_t fresh = (uint32_t)lane;
+    xa = load_extent(sa, half);
+    if constexpr (kTwo) xb = load_extent(sb, half);
+    if (kTwo && full) fetch(0u, fresh);
+    load_tables<WIDE>(s_tab, tab, tid, (int)blockDim.x);
+    if constexpr (TWO) load_tables<WIDE>(s_tab2, a.tab_p, tid, (int)blockDim.x);
+    // words past a half chunk's end are read by the window of its last symbols: keep them defined
     for (uint32_t q = (uint32_t)lane; q < kBufs * stage_stride; q += kWave) stage[q] = 0;
     __syncthreads();
-
-    const uint32_t g = block * (uint32_t)kDecWaves + (uint32_t)w;                // global wave number
-    const uint32_t n_pos = lay.NC;
-    uint32_t c, k_first, k_count;
-    bool mine;                                           // wave-uniform: a full position that this launch covers
-    if (MODE == DecMode::Decode) {
-        mine = g < lay.K * n_pos;
-        k_first = g / n_pos; c = g - k_first * n_pos; k_count = 1;
-    } else if (KSPLIT > 1) {
-        const uint32_t each = lay.K / KSPLIT, more = lay.K % KSPLIT;   // `more` runs of each + 1, then runs of each
-        c = g / KSPLIT;
-        mine = c < n_pos;
-        k_first = (uint32_t)part * each + min((uint32_t)part, more);
-        k_count = each + ((uint32_t)part < more ? 1u : 0u);
-    } else {
-        mine = g < n_pos;
-        c = g; k_first = 0; k_count = lay.K;
-    }
-    uint32_t clo = 0, clen = 0, bkt = 0;
-    if (mine) chunk_geometry(lay, c, clo, clen, bkt);
-    mine = mine && clen == (uint32_t)kChunk;             // the ragged launch takes the other positions
     if constexpr (KSPLIT == 1) {
         if (!mine) return;
-    } else {
-        // the waves of a group meet at workgroup barriers below, so every wave of the workgroup
-        // goes there, the ones without a position with nothing to do on the way
-        if (!mine) k_count = 0;
-    }
-    // A cursor from a corrupt table is pulled back so that a chain of 32 symbols from it stays inside
-    // the buffer.  No valid cursor is beyond that: the last chain of a chunk starts after 4064 symbols
-    // of at most sym_bits each, and the buffer holds 4096 of them.
-    const uint32_t p_limit = stage_words * 32u - 32u * a.sym_bits;
+    }                                                    // (else: the waves of a group meet at workgroup barriers below)
 
-    float acc[kLaneCoords];
+    // From bit t of the staged words to the buffer bit r with the bit before t on top of the 64 bits
+    // from r: r = r_base - t (they lie back to front).
+    const uint32_t r_base = 32u * ((uint32_t)kTail + stage_words) - 63u;
+    // A cursor from a corrupt table is pulled back so that a chain of 32 symbols from it stays inside
+    // the buffer.  No valid cursor is beyond that: the last run of a half starts after 2016 symbols of
+    // at most sym_bits each and up to 127 bits of the run before, and the buffer holds 2048 and 256 bits.
+    const uint32_t p_limit = stage_words * 32u - (uint32_t)kSub * a.sym_bits;
+    auto symbols_of = [&](uint32_t ln) {                  // symbols of lane ln's run
+        const uint32_t at0 = base + (uint32_t)kSub * ln;
+        return full ? kSub : (int)min((uint32_t)kSub, cend > at0 ? cend - at0 : 0u);
+    };
+
+    float acc[kSub], acc_b[MODE == DecMode::Decode ? kSub : 1];
 #pragma unroll
-    for (int s = 0; s < kLaneCoords; ++s) acc[s] = 0.0f;
+    for (int s = 0; s < kSub; ++s) acc[s] = 0.0f;
     double sdiff = 0.0;
     uint32_t seen = 0xFFFFFFFFu;
-    bool malformed = false;
+    uint32_t bad = 0;                                    // not 0: malformed
 
-    // Two streams: the next worker's chunks are already in flight in registers while these are parsed.
-    // One stream: the registers go to the second parse chain instead; the load of a chunk is covered
-    // by the other waves of the SIMD.  The lane's cursors and the norm travel ahead either way.
-    constexpr bool kAhead = PREV;
-    uint4 pre[kPre];
-    uint4 pre_p[PREV ? kPre : 1];
-    ChunkRef cr{nullptr, 0u}, cp{nullptr, 0u};
-    SubMeta nxt{0u, 0u, 0u, 0.0f}, nxt_p{0u, 0u, 0u, 0.0f};
-    if (k_count != 0u) {                                  // (always, unless KSPLIT left this wave without work)
-        cr = chunk_ref(a.payload, a.cap_words, a.chunk_off, a.sub_end, k_first, c, lay.NC, stage_words, sc);
-        if constexpr (kAhead) prefetch_chunk(cr, pre);
-        nxt = load_meta(a.sub_end, a.norms, k_first, c, bkt, lay, lane);
-        if constexpr (PREV) {
-            cp = chunk_ref(a.payload_p, a.cap_words_p, a.chunk_off_p, a.sub_end_p, k_first, c, lay.NC, stage_words, sc);
-            prefetch_chunk(cp, pre_p);
-            nxt_p = load_meta(a.sub_end_p, a.norms_p, k_first, c, bkt, lay, lane);
-        }
-    }
-
-    for (uint32_t kk = 0; kk < k_count; ++kk) {
-        const uint32_t k = k_first + kk;
-        const SubMeta cur = nxt, prv = nxt_p;
-        if constexpr (!kAhead) prefetch_chunk(cr, pre);
-        wave_lds_fence();                                     // the last worker's windows have been read
-        commit_chunk_reversed(stage, pre, stage_words, (uint32_t)__builtin_amdgcn_readfirstlane((int)cr.words));
-        if constexpr (PREV)
-            commit_chunk_reversed(stage_p, pre_p, stage_words, (uint32_t)__builtin_amdgcn_readfirstlane((int)cp.words));
+    // RAG: a short half.  The symbols past a lane's count are parsed like the others (from a cursor below p_limit
+    // 32 of them stay inside the buffer, and any window finds a table entry) and count for nothing.  It has a loop
+    // of its own, without a look-ahead, so that what it holds on top costs the full halves no registers.
+    auto all_workers = [&](auto rag_tag) __attribute__((always_inline)) {
+    constexpr bool RAG = decltype(rag_tag)::value;
+    uint32_t i = 0;
+    do {
+        // (the lane number anew, so that the addresses made from it are worked out here and not held in two dozen
+        // registers around the loop)
+        asm volatile("" : "+v"(fresh));
+        if (RAG || !kTwo) fetch(i, fresh);
+        wave_lds_fence();                                     // the windows of the workers before have been read
+        commit_half(stage, pre_a, ra, stage_words, fresh);
+        if constexpr (kTwo) commit_half(stage_b, pre_b, rb, stage_words, fresh);
         wave_lds_fence();                                     // a lane parses words that other lanes stored
-        if (kk + 1 < k_count) {
-            cr = chunk_ref(a.payload, a.cap_words, a.chunk_off, a.sub_end, k + 1, c, lay.NC, stage_words, sc);
-            nxt = load_meta(a.sub_end, a.norms, k + 1, c, bkt, lay, lane);
-            if constexpr (kAhead) prefetch_chunk(cr, pre);
-            if constexpr (PREV) {
-                cp = chunk_ref(a.payload_p, a.cap_words_p, a.chunk_off_p, a.sub_end_p, k + 1, c, lay.NC, stage_words, sc);
-                nxt_p = load_meta(a.sub_end_p, a.norms_p, k + 1, c, bkt, lay, lane);
-                prefetch_chunk(cp, pre_p);
-            }
+        const bool have_b = PREV || (kTwo && i + 1u < k_count);         // wave-uniform
+        const float n = ma.n, nB = have_b ? mb.n : 0.0f;
+        // first and last bit of the lane's runs, from the staged words' start (they wrap past p_limit if before it)
+        const uint32_t t_end = ma.hi - 32u * ra.w0, tb_end = mb.hi - 32u * rb.w0;
+        uint32_t t = wave_shift_in(ma.hi, ra.start) - 32u * ra.w0, tb = wave_shift_in(mb.hi, rb.start) - 32u * rb.w0;
+        {
+            const bool any = !RAG || symbols_of(fresh) > 0;
+            bad |= (t > p_limit) & any;
+            bad |= (tb > p_limit) & any & have_b;
         }
-        uint32_t p = cur.p0, pp = prv.p0;
-        if (p > p_limit) { p = p_limit; malformed = true; }
-        if (pp > p_limit) { pp = p_limit; malformed = true; }
-        const float n = cur.n, np = prv.n;
-        float* vout = nullptr;
-        if constexpr (MODE == DecMode::Decode) vout = a.out + (size_t)k * lay.d + clo + 64u * (uint32_t)lane;
-        // From stream bit p to the buffer bit r with the bit before p on top of the 64 bits from r:
-        // r = r_base - p (the chunk lies back to front).
-        const uint32_t r_base = 32u * ((uint32_t)kTail + stage_words) - 63u;
-        constexpr int kHalf = kLaneCoords / 2;
-        if constexpr (!PREV) {
-            // the lane's two sub-chunks side by side: ten groups of three symbols and one of two each;
-            // a group's last symbol is finished when the next group's first window (its sign on top) is there
-            uint32_t pb = cur.p_mid;
-            if (pb > p_limit) { pb = p_limit; malformed = true; }
-            uint32_t q = r_base - p, qb = r_base - pb;
+        t = min(t, p_limit);
+        tb = min(tb, p_limit);
+        if (!RAG && kTwo && i + kStep < k_count) fetch(i + kStep, fresh);
+        // Squared differences: six at a time in binary32 (at most six roundings on a sum of
+        // non-negative terms), the groups in binary64.  The differences are scaled by a power of two
+        // taken from the larger of the lane's two norms, so that no square leaves the range of
+        // binary32 whatever the scale of the vectors; the sum is scaled back in binary64.
+        const uint32_t ex = min((__float_as_uint(fmaxf(n, nB)) >> 23) & 0xFFu, 253u);        // (254 - ex = 0 would be no power of two)
+        const float down = __uint_as_float((254u - ex) << 23);                       // 2^(127 - ex)
+        const double up2 = __longlong_as_double((long long)(2 * (int)ex - 254 + 1023) << 52);   // 2^(2 ex - 254)
+        float sd32 = 0.0f;
+        double sw = 0.0;
+
+        auto parse = [&](auto pair_tag) __attribute__((always_inline)) {
+            constexpr bool PAIR = decltype(pair_tag)::value;                    // both chains
+            uint32_t q = r_base - t, qb = r_base - tb;
             uint32_t W[4], e[3], W_b[4], e_b[3];
-            float lv_held = 0.0f, lv_held_b = 0.0f;
-            Window wn = read_window(stage, q), wn_b = read_window(stage, qb);
-            auto emit = [&](int at, uint32_t w_next, float lv) {
+            float held = 0.0f, held_b = 0.0f;
+            uint32_t used = 0, used_b = 0, ignored = 0;
+            const int cnt = RAG ? symbols_of(fresh) : kSub;
+            Window wn = read_window(stage, q), wn_b{};
+            if constexpr (PAIR) wn_b = read_window(stage_b, qb);
+            auto emit = [&](int at, uint32_t w_next, float lv, uint32_t w_next_b, float lv_b) __attribute__((always_inline)) {
                 if constexpr (MODE == DecMode::Decode) {
-                    vout[at] = value_early<true>(w_next, lv, n);
+                    acc[at] = symbol_value<true>(w_next, lv, n);
+                    if constexpr (PAIR) acc_b[at] = symbol_value<true>(w_next_b, lv_b, nB);
+                } else if constexpr (PREV) {
+                    const float val = symbol_value<false>(w_next, lv, n);
+                    acc[at] += val;
+                    const float df = (symbol_value<false>(w_next_b, lv_b, nB) - val) * down;   // (a stray sign on a zero does not show in a difference)
+                    sd32 = fmaf(df, df, sd32);
                 } else if constexpr (MODE == DecMode::Half1) {           // no previous streams: the vectors of t count as zero
-                    const float val = value_early<false>(w_next, lv, n);
+                    const float val = symbol_value<false>(w_next, lv, n);
                     acc[at] += val;
                     sdiff = fma((double)val, (double)val, sdiff);
+                    if constexpr (PAIR) {
+                        const float val_b = symbol_value<false>(w_next_b, lv_b, nB);
+                        acc[at] += val_b;
+                        sdiff = fma((double)val_b, (double)val_b, sdiff);
+                    }
                 } else {
                     acc[at] = fmaf(signed_norm(w_next, n), lv, acc[at]);    // (a stray sign on a zero adds nothing)
+                    if constexpr (PAIR) acc[at] = fmaf(signed_norm(w_next_b, nB), lv_b, acc[at]);
                 }
             };
 #pragma unroll
-            for (int s = 0; s < kHalf; s += 3) {
-                float lv[3], lv_b[3];
-                if (s + 3 <= kHalf) {
-                    parse_group_early<3, WIDE, false>(wn, s_tab, q, W, e, lv, seen);
+            for (int s = 0; s < kSub; s += 3) {
+                // a group's last symbol is finished when the next group's first window (its sign on top) is there
+                float lv[3] = {0.f, 0.f, 0.f}, lv_b[3] = {0.f, 0.f, 0.f};
+                const bool last = s + 3 > kSub;
+                const int num = last ? 2 : 3;
+                if (!last) {
+                    parse_group<3, WIDE, false>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
                     wn = read_window(stage, q);
-                    parse_group_early<3, WIDE, false>(wn_b, s_tab, qb, W_b, e_b, lv_b, seen);
-                    wn_b = read_window(stage, qb);
-                } else {
-                    parse_group_early<2, WIDE, true>(wn, s_tab, q, W, e, lv, seen);
-                    parse_group_early<2, WIDE, true>(wn_b, s_tab, qb, W_b, e_b, lv_b, seen);
-                }
-                const int cnt = s + 3 <= kHalf ? 3 : 2;
-                if constexpr (!WIDE) {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        if (i < cnt) { lv[i] = level_of(s_tab, e[i]); lv_b[i] = level_of(s_tab, e_b[i]); }
+                    if constexpr (PAIR) {
+                        parse_group<3, WIDE, false>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
+                        wn_b = read_window(stage_b, qb);
                     }
-                }
-                if (s > 0) { emit(s - 1, W[0], lv_held); emit(kHalf + s - 1, W_b[0], lv_held_b); }
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    if (i + 1 < cnt || cnt == 2) { emit(s + i, W[i + 1], lv[i]); emit(kHalf + s + i, W_b[i + 1], lv_b[i]); }
-                }
-                if (cnt == 3) { lv_held = lv[2]; lv_held_b = lv_b[2]; }
-            }
-            if (r_base - q != cur.p_mid) malformed = true;
-            p = r_base - qb;
-        } else {
-            // two streams, two sub-chunks each: four chains, ten groups of three symbols and one of two
-            uint32_t pb = cur.p_mid, ppb = prv.p_mid;
-            if (pb > p_limit) { pb = p_limit; malformed = true; }
-            if (ppb > p_limit) { ppb = p_limit; malformed = true; }
-            uint32_t q = r_base - p, qb = r_base - pb, qp = r_base - pp, qpb = r_base - ppb;
-            uint32_t W[4], e[3], W_b[4], e_b[3], W_p[4], e_p[3], W_pb[4], e_pb[3];
-            float lv_held = 0.0f, lv_held_b = 0.0f, lv_held_p = 0.0f, lv_held_pb = 0.0f;
-            Window wn = read_window(stage, q), wn_b = read_window(stage, qb);
-            Window wn_p = read_window(stage_p, qp), wn_pb = read_window(stage_p, qpb);
-            // Squared differences: six at a time in binary32 (at most six roundings on a sum of
-            // non-negative terms), the groups in binary64.  The differences are scaled by a power of two
-            // taken from the larger of the lane's two norms, so that no square leaves the range of
-            // binary32 whatever the scale of the vectors; the sum is scaled back in binary64.
-            const uint32_t ex = min((__float_as_uint(fmaxf(n, np)) >> 23) & 0xFFu, 253u);   // (254 - ex = 0 would be no power of two)
-            const float down = __uint_as_float((254u - ex) << 23);                       // 2^(127 - ex)
-            const double up2 = __longlong_as_double((long long)(2 * (int)ex - 254 + 1023) << 52);   // 2^(2 ex - 254)
-            float sd32 = 0.0f;
-            double sw = 0.0;
-            auto emit2 = [&](int at, uint32_t w_next, float lv, uint32_t w_next_p, float lv_p) {
-                const float val = value_early<false>(w_next, lv, n);
-                acc[at] += val;
-                const float df = (value_early<false>(w_next_p, lv_p, np) - val) * down;   // (a stray sign on a zero does not show in a difference)
-                sd32 = fmaf(df, df, sd32);
-            };
-#pragma unroll
-            for (int s = 0; s < kHalf; s += 3) {
-                float lv[3], lv_p[3], lv_b[3], lv_pb[3];
-                if (s + 3 <= kHalf) {
-                    parse_group_early<3, WIDE, false>(wn, s_tab, q, W, e, lv, seen);
-                    wn = read_window(stage, q);
-                    parse_group_early<3, WIDE, false>(wn_p, s_tab_p, qp, W_p, e_p, lv_p, seen);
-                    wn_p = read_window(stage_p, qp);
-                    parse_group_early<3, WIDE, false>(wn_b, s_tab, qb, W_b, e_b, lv_b, seen);
-                    wn_b = read_window(stage, qb);
-                    parse_group_early<3, WIDE, false>(wn_pb, s_tab_p, qpb, W_pb, e_pb, lv_pb, seen);
-                    wn_pb = read_window(stage_p, qpb);
                 } else {
-                    parse_group_early<2, WIDE, true>(wn, s_tab, q, W, e, lv, seen);
-                    parse_group_early<2, WIDE, true>(wn_p, s_tab_p, qp, W_p, e_p, lv_p, seen);
-                    parse_group_early<2, WIDE, true>(wn_b, s_tab, qb, W_b, e_b, lv_b, seen);
-                    parse_group_early<2, WIDE, true>(wn_pb, s_tab_p, qpb, W_pb, e_pb, lv_pb, seen);
+                    parse_group<2, WIDE, true>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
+                    if constexpr (PAIR) parse_group<2, WIDE, true>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
                 }
-                const int cnt = s + 3 <= kHalf ? 3 : 2;
-                if constexpr (!WIDE) {
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        if (i < cnt) {
-                            lv[i] = level_of(s_tab, e[i]);
-                            lv_p[i] = level_of(s_tab_p, e_p[i]);
-                            lv_b[i] = level_of(s_tab, e_b[i]);
-                            lv_pb[i] = level_of(s_tab_p, e_pb[i]);
+                for (int j = 0; j < 3; ++j) {
+                    if (j >= num) continue;
+                    if constexpr (!WIDE) {
+                        lv[j] = level_of(s_tab, e[j]);
+                        if constexpr (PAIR) lv_b[j] = level_of(s_tab_b, e_b[j]);
+                    }
+                    if constexpr (RAG) {
+                        const bool in = s + j < cnt;
+                        used += in ? symbol_bits<WIDE>(e[j]) : 0u;
+                        bad |= in & is_reject<WIDE>(e[j]);
+                        lv[j] = in ? lv[j] : 0.0f;
+                        if constexpr (PAIR) {
+                            used_b += in ? symbol_bits<WIDE>(e_b[j]) : 0u;
+                            bad |= in & have_b & is_reject<WIDE>(e_b[j]);
+                            lv_b[j] = in ? lv_b[j] : 0.0f;
                         }
                     }
                 }
-                if (s > 0) {
-                    emit2(s - 1, W[0], lv_held, W_p[0], lv_held_p);
-                    emit2(kHalf + s - 1, W_b[0], lv_held_b, W_pb[0], lv_held_pb);
-                }
+                if (s > 0) emit(s - 1, W[0], held, W_b[0], held_b);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    if (i + 1 < cnt || cnt == 2) {
-                        emit2(s + i, W[i + 1], lv[i], W_p[i + 1], lv_p[i]);
-                        emit2(kHalf + s + i, W_b[i + 1], lv_b[i], W_pb[i + 1], lv_pb[i]);
-                    }
+                for (int j = 0; j < 2; ++j) emit(s + j, W[j + 1], lv[j], W_b[j + 1], lv_b[j]);
+                held = lv[2]; held_b = lv_b[2];
+                if constexpr (PREV) {
+                    if ((s / 3) % 2 == 1 || last) { sw += (double)sd32; sd32 = 0.0f; }
                 }
-                if (cnt == 3) { lv_held = lv[2]; lv_held_b = lv_b[2]; lv_held_p = lv_p[2]; lv_held_pb = lv_pb[2]; }
-                sw += (double)sd32;
-                sd32 = 0.0f;
+                // A group's values are done before the next group's look-ups.  The compiler would move them behind
+                // the whole chain of look-ups (into the block after the parse, and the scheduler again inside it)
+                // and keep every entry and window until then, hundreds of registers.
+#pragma unroll
+                for (int at = s > 0 ? s - 1 : 0; at < s + 2; ++at) {
+                    asm volatile("" : "+v"(acc[at]));
+                    if constexpr (MODE == DecMode::Decode && PAIR) asm volatile("" : "+v"(acc_b[at]));
+                }
+                asm volatile("" : "+v"(seen), "+v"(bad));
+                if constexpr (PREV) asm volatile("" : "+v"(sd32), "+v"(sw));
+                else if constexpr (MODE == DecMode::Half1) asm volatile("" : "+v"(sdiff));
+                if constexpr (RAG) asm volatile("" : "+v"(used));
+                if constexpr (RAG && PAIR) asm volatile("" : "+v"(used_b));
+                __builtin_amdgcn_sched_barrier(0);
             }
-            sdiff = fma(sw, up2, sdiff);
-            if (r_base - q != cur.p_mid || r_base - qp != prv.p_mid) malformed = true;
-            p = r_base - qb;
-            pp = r_base - qpb;
-        }
-        if (p != cur.p_end) malformed = true;
-        if constexpr (PREV) {
-            if (pp != prv.p_end) malformed = true;
-        }
-    }
+            if constexpr (RAG) {
+                bad |= ((cnt > 0) & (t + used != t_end)) | ((cnt > 0) & have_b & (tb + used_b != tb_end));
+            } else {
+                bad |= (r_base - q) ^ t_end;
+                if constexpr (PAIR) bad |= (r_base - qb) ^ tb_end;
+            }
+        };
+        if constexpr (!kTwo) parse(BoolTag<false>{});
+        else if (RAG || have_b) parse(BoolTag<true>{});       // (Decode of a short half, an odd worker out: a second chain for nothing)
+        else parse(BoolTag<false>{});
+        if constexpr (PREV) sdiff = fma(sw, up2, sdiff);
+        i += kStep;
+    } while (i < k_count);
+    };
+    if (full) all_workers(BoolTag<false>{});
+    else all_workers(BoolTag<true>{});
     // a reject entry leaves a zero among bits 15..31 of its group's negative bit count
-    malformed = malformed || (seen >> 15) != 0x1FFFFu;
-    if (__any(malformed) && lane == 0) raise_error(sc, QGX_EBIT_STREAM);
-    if (MODE == DecMode::Decode) return;
+    bad |= (seen >> 15) ^ 0x1FFFFu;
+    if (__any(bad != 0u) && lane == 0) raise_error(sc, QGX_EBIT_STREAM);
 
     // ---- aggregate and update ---------------------------------------------------------------------
+    // Lane L holds coordinates 32 L .. 32 L + 31 of the task.  Through LDS the wave turns them, kTurn lanes
+    // at a time, so that eight lanes own a row of 32 consecutive floats and global accesses touch whole
+    // 128-byte lines.
+    constexpr int kPitch = kSub + 4;                            // rows of 36 floats
+    constexpr int kTurn = kTwo ? 32 : 16;                       // 1152 floats in two staging buffers, or 576 in one
+    constexpr int kPasses = kWave / kTurn, kReads = kTurn / 8;
+    float* tr = reinterpret_cast<float*>(stage);
+    auto put_rows = [&](const float (&v)[kSub], int q, float scale) __attribute__((always_inline)) {
+        if (mine && lane / kTurn == q) {
+#pragma unroll
+            for (int j = 0; j < kSub / 4; ++j)
+                *reinterpret_cast<float4*>(tr + (lane % kTurn) * kPitch + 4 * j) =
+                    make_float4(v[4 * j] * scale, v[4 * j + 1] * scale, v[4 * j + 2] * scale, v[4 * j + 3] * scale);
+        }
+    };
+    const int row0 = lane >> 3, col = lane & 7;
+    auto place = [&](int q, int i) -> uint32_t {                // this lane's i-th float4 of pass q
+        return base + (uint32_t)(kSub * (kTurn * q + row0 + 8 * i) + 4 * col);
+    };
+    if constexpr (MODE == DecMode::Decode) {
+        auto write_out = [&](const float (&v)[kSub], uint32_t k) __attribute__((always_inline)) {
+            float* __restrict__ out = a.out + (size_t)k * lay.d;
+#pragma unroll
+            for (int q = 0; q < kPasses; ++q) {
+                wave_lds_fence();
+                put_rows(v, q, 1.0f);
+                wave_lds_fence();
+                if (full) {
+#pragma unroll
+                    for (int i = 0; i < kReads; ++i) {
+                        const float4 m = *reinterpret_cast<const float4*>(tr + (row0 + 8 * i) * kPitch + 4 * col);
+                        const f32x4_any o = {m.x, m.y, m.z, m.w};
+                        *reinterpret_cast<f32x4_any*>(out + place(q, i)) = o;
+                    }
+                } else {
+#pragma unroll 1
+                    for (uint32_t f = (uint32_t)lane; f < (uint32_t)(kTurn * kSub); f += kWave) {
+                        const uint32_t at = base + (uint32_t)(kTurn * kSub * q) + f;
+                        if (at < cend) out[at] = tr[(f >> 5) * kPitch + (f & 31u)];
+                    }
+                }
+            }
+        };
+        write_out(acc, k_first);
+        if (k_count > 1u) write_out(acc_b, k_first + 1u);
+        return;
+    } else {
     const float invK = 1.0f / (float)lay.K;
     const float gam = sc->gamma_f;
     if constexpr (MODE == DecMode::Half1) {
@@ -538,426 +618,150 @@ __device__ __forceinline__ void decode_full_body(const Layout& lay, const Tables
         if constexpr (KSPLIT > 1) {
             if (lane == 0) s_sd[w] = sdiff;               // joined below, after the first barrier
         } else {
-            if (lane == 0) a.s_partial[c] = sdiff;
+            if (lane == 0) a.s_partial[task] = sdiff;
         }
     }
-    // Lane L holds coordinates 64L..64L+63 of the chunk.  Through LDS the wave turns them, a quarter of them
-    // at a time, so that neighbouring lanes own consecutive floats and global accesses touch whole pieces
-    // of kPiece floats instead of 16 bytes per 256.  Where the output is another array than the one read
-    // (the first half-step, the plain average) a piece is a whole 128-byte line, from the 32 lanes of one
-    // half of the wave and 32 of their symbols: with pieces of 64 bytes the cache fetched the other half of
-    // every output line that it did not hold, a sixth more traffic for the launch.  The second half-step
-    // updates Y in place, the line is there when it is written, and pieces of 64 bytes from all 64 lanes
-    // and 16 of their symbols are the quicker turn.
     // KSPLIT: all waves of the group put their sums there, and after a barrier each of them adds them
     // up (in the order of the workers' runs) for its share of the rows and does the update for those.
-    constexpr int kPiece = MODE == DecMode::Half1 ? 16 : 32;   // floats of a row per pass
-    constexpr int kPitch = kPiece + 4;                          // 64 rows of 20 floats or 32 rows of 36: at most 5120 bytes
-    constexpr int kRowLanes = kPiece / 4;                       // lanes that read a row, a float4 each
-    constexpr int kRowsPerRead = kWave / kRowLanes;
-    float* tr = reinterpret_cast<float*>(stage);
     const float* tr0 = KSPLIT > 1 ? reinterpret_cast<const float*>(s_dyn + (size_t)(w - part) * kBufs * stage_stride) : tr;
-    const size_t tr_step = (size_t)kBufs * stage_stride;  // from one wave's buffer to the next, in words
+    const size_t tr_step = kBufs * (size_t)stage_stride;     // from one wave's buffer to the next, in words
     const float scale = KSPLIT > 1 ? 1.0f : invK;         // KSPLIT: the division comes after the group's sum
-    // Where this lane's i-th float4 of pass q lies in the vectors.
-    auto place = [&](int q, int i) -> uint32_t {
-        const int first_lane = kPiece == 32 ? 32 * (q >> 1) : 0, first_sym = kPiece == 32 ? 32 * (q & 1) : 16 * q;
-        const int row = lane / kRowLanes + kRowsPerRead * i, col = lane % kRowLanes;
-        return clo + 64u * (uint32_t)(first_lane + row) + (uint32_t)first_sym + 4u * (uint32_t)col;
-    };
     // A piece of Y is asked for as soon as the piece before it in the same registers has been used, a pass
-    // ahead of its own use: every wave of the launch reaches this stage at about the same time, and a load
-    // issued where it is used would be waited for in full, four times over.
-    constexpr bool kReadsY = MODE == DecMode::Half0 || MODE == DecMode::Half1;
-    float4 y_ahead[4];
+    // ahead of its own use: a load issued where it is used would be waited for in full.
+    constexpr bool kYAhead = kTwo;                        // (with eight waves per SIMD the others cover it)
+    float4 y_ahead[kReads];
     auto load_y = [&](int q, int i) {
         y_ahead[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (KSPLIT > 1 && i * KSPLIT / 4 != part) return;
-        if (mine) y_ahead[i] = *reinterpret_cast<const float4*>(a.Y + place(q, i));
+        if (KSPLIT > 1 && ((q * kReads + i) & (KSPLIT - 1)) != part) return;
+        if (mine && full) y_ahead[i] = *reinterpret_cast<const float4*>(a.Y + place(q, i));
     };
-    if constexpr (kReadsY) {
+    if constexpr (kYAhead) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_y(0, i);
+        for (int i = 0; i < kReads; ++i) load_y(0, i);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int first_lane = kPiece == 32 ? 32 * (q >> 1) : 0;    // the lanes whose symbols this pass turns
-        const int first_sym = kPiece == 32 ? 32 * (q & 1) : 16 * q;  // ... and which of their symbols
-        if (mine && (kPiece == 16 || (lane >> 5) == (q >> 1))) {
-#pragma unroll
-            for (int j = 0; j < kRowLanes; ++j)
-                *reinterpret_cast<float4*>(tr + (lane - first_lane) * kPitch + 4 * j) =
-                    make_float4(acc[first_sym + 4 * j] * scale, acc[first_sym + 4 * j + 1] * scale,
-                                acc[first_sym + 4 * j + 2] * scale, acc[first_sym + 4 * j + 3] * scale);
-        }
+    for (int q = 0; q < kPasses; ++q) {
+        wave_lds_fence();                                     // (the windows, the rows of the pass before: read)
+        put_rows(acc, q, scale);
         wave_lds_fence();                                     // the rows are read by other lanes than wrote them
         if constexpr (KSPLIT > 1) {
             __syncthreads();
             if (MODE == DecMode::Half1 && q == 0 && mine && part == 0 && lane == 0) {
                 double sd = s_sd[w];
                 for (int j = 1; j < KSPLIT; ++j) sd += s_sd[w + j];
-                a.s_partial[c] = sd;
+                a.s_partial[task] = sd;
             }
         }
+        if (mine && full) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (KSPLIT > 1 && i * KSPLIT / 4 != part) continue;   // a share of the rows for each wave of the group
-            if (!mine) continue;
-            const int row = lane / kRowLanes + kRowsPerRead * i, col = lane % kRowLanes;
-            float4 m = *reinterpret_cast<const float4*>(tr0 + row * kPitch + 4 * col);
-            if constexpr (KSPLIT > 1) {
+            for (int i = 0; i < kReads; ++i) {
+                if (kYAhead && q + 1 < kPasses && KSPLIT > 1 && ((q * kReads + i) & (KSPLIT - 1)) != part) { load_y(q + 1, i); continue; }
+                if (KSPLIT > 1 && ((q * kReads + i) & (KSPLIT - 1)) != part) continue;   // a share of the rows for each wave of the group
+                const int at_lds = (row0 + 8 * i) * kPitch + 4 * col;
+                float4 m = *reinterpret_cast<const float4*>(tr0 + at_lds);
+                if constexpr (KSPLIT > 1) {
 #pragma unroll
-                for (int j = 1; j < KSPLIT; ++j) {
-                    const float4 h4 = *reinterpret_cast<const float4*>(tr0 + j * tr_step + row * kPitch + 4 * col);
-                    m.x += h4.x; m.y += h4.y; m.z += h4.z; m.w += h4.w;
-                }
-                m.x *= invK; m.y *= invK; m.z *= invK; m.w *= invK;
-            }
-            const uint32_t at = place(q, i);
-            if (MODE == DecMode::Average) {
-                *reinterpret_cast<float4*>(a.out + at) = m;
-            } else if (MODE == DecMode::Half0) {
-                const float4 y = y_ahead[i];
-                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (a.anchor) x = *reinterpret_cast<const float4*>(a.anchor + at);
-                x.x = (x.x + gam * y.x) - gam * m.x;
-                x.y = (x.y + gam * y.y) - gam * m.y;
-                x.z = (x.z + gam * y.z) - gam * m.z;
-                x.w = (x.w + gam * y.w) - gam * m.w;
-                *reinterpret_cast<float4*>(a.out + at) = x;
-                if (q < 3) load_y(q + 1, i);
-                if (a.x_sum) {                                   // ergodic average: sum of the half-step iterates
-                    double2* xs = reinterpret_cast<double2*>(a.x_sum + at);
-                    double2 s0 = xs[0], s1 = xs[1];
-                    s0.x += (double)x.x; s0.y += (double)x.y; s1.x += (double)x.z; s1.y += (double)x.w;
-                    xs[0] = s0; xs[1] = s1;
-                }
-            } else {
-                float4 y = y_ahead[i];
-                y.x -= m.x; y.y -= m.y; y.z -= m.z; y.w -= m.w;
-                *reinterpret_cast<float4*>(a.Y + at) = y;
-                if (q < 3) load_y(q + 1, i);
-            }
-        }
-        wave_lds_fence();                                     // ... and written again in the next pass
-        if constexpr (KSPLIT > 1) {
-            if (q < 3) __syncthreads();                       // the partners have read this quarter
-        }
-    }
-}
-
-template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT = 1>
-__global__ __launch_bounds__(kDecWaves * kWave) __attribute__((amdgpu_waves_per_eu(MODE == DecMode::Half1 ? 2 : 4)))
-void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
-{
-    __shared__ double s_sd[KSPLIT > 1 ? kDecWaves : 1];
-    extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][1 or 2][stage_stride]
-    __shared__ __align__(16) unsigned char s_tab[kTabBytes];
-    __shared__ __align__(16) unsigned char s_tab2[TWO ? kTabBytes : 16];
-    decode_full_body<MODE, PREV, TWO, WIDE, KSPLIT>(lay, tab, sc, a, blockIdx.x, s_dyn, s_tab, s_tab2, s_sd);
-}
-
-// ---- chunk positions with fewer than 4096 coordinates --------------------------------------------
-// They are the tails of buckets and tensors: few, but a wave that walked all K workers of one, symbol
-// by symbol, would take as long as the whole launch of the full positions.  So a position gets a
-// workgroup of its own and its workers are spread over the waves: wave w stages and parses the chunk
-// of worker k0 + w (every lane its two sub-chunks side by side, as far as they go), then the waves
-// add their values to accumulators in LDS one after the other, so that a coordinate's K values are
-// summed in worker order like everywhere else.  The update itself is done by all threads, coalesced.
-constexpr int kAccPitch = 65;                         // s_acc[s][lane], padded: both access patterns spread over the banks
-
-template <bool PREV>
-constexpr int ragged_waves() { return PREV ? 4 : 8; } // two staging buffers per wave with two streams
-
-// The body, for ragged position `index` (of lay.ragged_chunk) and the first ragged_waves() waves of the workgroup
-// (further waves leave at once, before any barrier); the LDS arrays are the caller's: s_dyn [waves][1 or 2]
-// [rag_stride], s_tab and (TWO) s_tab2 of kTabBytes, s_acc [kLaneCoords * kAccPitch], s_sd [ragged_waves()].
-template <DecMode MODE, bool PREV, bool TWO>
-__device__ __forceinline__ void decode_ragged_body(const Layout& lay, const Tables* __restrict__ tab, Scalars* sc,
-                                                   const DecodeArgs& a, uint32_t index, uint32_t* s_dyn,
-                                                   unsigned char* s_tab, unsigned char* s_tab2, float* s_acc, double* s_sd)
-{
-    static_assert(!PREV || MODE == DecMode::Half1, "only the second half-step reads two streams");
-    static_assert(!TWO || PREV, "a second table only comes with a second stream");
-    constexpr int W = ragged_waves<PREV>();
-    constexpr int kBufs = PREV ? 2 : 1;
-    constexpr bool kExact = MODE == DecMode::Decode;
-    constexpr int kHalf = kLaneCoords / 2;
-    const unsigned char* s_tab_p = TWO ? s_tab2 : s_tab;
-
-    const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
-    if (w >= W) return;
-    const uint32_t stage_words = a.rag_words, stage_stride = a.rag_stride;
-    uint32_t* stage = s_dyn + (size_t)w * kBufs * stage_stride;
-    uint32_t* stage_p = stage + stage_stride;
-
-    load_tables(s_tab, tab, tid, W * kWave);
-    if constexpr (TWO) load_tables(s_tab2, a.tab_p, tid, W * kWave);
-    for (int i = tid; i < kLaneCoords * kAccPitch; i += W * kWave) s_acc[i] = 0.0f;
-    for (uint32_t q = (uint32_t)lane; q < kBufs * stage_stride; q += kWave) stage[q] = 0;
-    __syncthreads();
-
-    const uint32_t c = lay.ragged_chunk[index];
-    uint32_t clo, clen, bkt;
-    chunk_geometry(lay, c, clo, clen, bkt);
-    const int cnt = (int)min(64u, clen > 64u * (uint32_t)lane ? clen - 64u * (uint32_t)lane : 0u);
-    const int cnt_a = min(cnt, kHalf), cnt_b = cnt - cnt_a;       // symbols of the lane's two sub-chunks
-    // Every chain parses 32 symbols whatever its count, so the buffer has room for that beyond the
-    // longest chunk (rag_words); a cursor from a corrupt table is pulled back to where that room starts.
-    const uint32_t p_limit = stage_words * 32u - (uint32_t)kHalf * a.sym_bits - 64u;
-
-    double sdiff = 0.0;
-    uint32_t flags = 0;
-    bool malformed = false;
-
-    for (uint32_t k0 = 0; k0 < lay.K; k0 += W) {
-        const uint32_t k = k0 + (uint32_t)w;
-        const bool active = k < lay.K;                    // wave-uniform
-        float val[kLaneCoords];
-#pragma unroll
-        for (int s = 0; s < kLaneCoords; ++s) val[s] = 0.0f;
-        if (active) {
-            uint4 pre[kPre];
-            const ChunkRef cr = chunk_ref(a.payload, a.cap_words, a.chunk_off, a.sub_end, k, c, lay.NC, stage_words, sc);
-            prefetch_chunk(cr, pre);
-            const SubMeta cur = load_meta(a.sub_end, a.norms, k, c, bkt, lay, lane);
-            SubMeta prv{0u, 0u, 0u, 0.0f};
-            commit_chunk(stage, pre, stage_words);
-            if constexpr (PREV) {
-                const ChunkRef cp = chunk_ref(a.payload_p, a.cap_words_p, a.chunk_off_p, a.sub_end_p, k, c, lay.NC, stage_words, sc);
-                prefetch_chunk(cp, pre);
-                prv = load_meta(a.sub_end_p, a.norms_p, k, c, bkt, lay, lane);
-                commit_chunk(stage_p, pre, stage_words);
-            }
-            wave_lds_fence();                                 // a lane parses words that other lanes stored
-            uint32_t p = cur.p0, pb = cur.p_mid, pp = prv.p0, ppb = prv.p_mid;
-            if (p > p_limit) { p = p_limit; malformed = true; }
-            if (pb > p_limit) { pb = p_limit; malformed = true; }
-            if (pp > p_limit) { pp = p_limit; malformed = true; }
-            if (ppb > p_limit) { ppb = p_limit; malformed = true; }
-            const float n = cur.n, np = prv.n;
-            // Every lane parses 32 symbols per chain whatever its count (from a cursor below p_limit they
-            // stay inside the buffer, and any window finds a table entry), and what lies past its count
-            // is masked out: without branches the chains of a lane advance side by side, in groups of
-            // three symbols per window as in the kernel for the full positions.
-            float* vout = nullptr;
-            if constexpr (MODE == DecMode::Decode) vout = a.out + (size_t)k * lay.d + clo + 64u * (uint32_t)lane;
-            const uint32_t start_a = p, start_b = pb, start_pa = pp, start_pb = ppb;
-            uint32_t used_a = 0, used_b = 0, used_pa = 0, used_pb = 0;     // bits of the symbols that count
-            uint32_t win[3], e[3], win_b[3], e_b[3];
-            uint32_t win_p[3] = {0u, 0u, 0u}, e_p[3] = {0u, 0u, 0u}, win_pb[3] = {0u, 0u, 0u}, e_pb[3] = {0u, 0u, 0u};
-            Window wn = read_window(stage, p), wn_b = read_window(stage, pb);
-            Window wn_p{0u, 0u, 0u}, wn_pb{0u, 0u, 0u};
-            if constexpr (PREV) { wn_p = read_window(stage_p, pp); wn_pb = read_window(stage_p, ppb); }
-#pragma unroll
-            for (int s = 0; s < kHalf; s += 3) {
-                if (s + 3 <= kHalf) { parse_group<3>(wn, s_tab, p, win, e); parse_group<3>(wn_b, s_tab, pb, win_b, e_b); }
-                else { parse_group<2>(wn, s_tab, p, win, e); parse_group<2>(wn_b, s_tab, pb, win_b, e_b); }
-                if (s + 3 < kHalf) { wn = read_window(stage, p); wn_b = read_window(stage, pb); }
-                if constexpr (PREV) {
-                    if (s + 3 <= kHalf) { parse_group<3>(wn_p, s_tab_p, pp, win_p, e_p); parse_group<3>(wn_pb, s_tab_p, ppb, win_pb, e_pb); }
-                    else { parse_group<2>(wn_p, s_tab_p, pp, win_p, e_p); parse_group<2>(wn_pb, s_tab_p, ppb, win_pb, e_pb); }
-                    if (s + 3 < kHalf) { wn_p = read_window(stage_p, pp); wn_pb = read_window(stage_p, ppb); }
-                }
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    if (s + i < kHalf) {
-                        const bool ok_a = s + i < cnt_a, ok_b = s + i < cnt_b;
-                        const float v = symbol_value<kExact>(level_of(s_tab, e[i]), win[i], e[i], n);
-                        const float v_b = symbol_value<kExact>(level_of(s_tab, e_b[i]), win_b[i], e_b[i], n);
-                        if constexpr (MODE == DecMode::Decode) {
-                            if (ok_a) vout[s + i] = v;
-                            if (ok_b) vout[kHalf + s + i] = v_b;
-                        } else {
-                            val[s + i] = ok_a ? v : 0.0f;
-                            val[kHalf + s + i] = ok_b ? v_b : 0.0f;
-                        }
-                        flags |= (ok_a ? e[i] : 0u) | (ok_b ? e_b[i] : 0u);
-                        used_a += ok_a ? (e[i] & 15u) + 1u : 0u;
-                        used_b += ok_b ? (e_b[i] & 15u) + 1u : 0u;
-                        if constexpr (MODE == DecMode::Half1) {
-                            float pv = 0.0f, pv_b = 0.0f;
-                            if constexpr (PREV) {
-                                pv = symbol_value<true>(level_of(s_tab_p, e_p[i]), win_p[i], e_p[i], np);
-                                pv_b = symbol_value<true>(level_of(s_tab_p, e_pb[i]), win_pb[i], e_pb[i], np);
-                                flags |= (ok_a ? e_p[i] : 0u) | (ok_b ? e_pb[i] : 0u);
-                                used_pa += ok_a ? (e_p[i] & 15u) + 1u : 0u;
-                                used_pb += ok_b ? (e_pb[i] & 15u) + 1u : 0u;
-                            }
-                            const double df = ok_a ? (double)pv - (double)v : 0.0;
-                            const double df_b = ok_b ? (double)pv_b - (double)v_b : 0.0;
-                            sdiff = fma(df, df, sdiff);
-                            sdiff = fma(df_b, df_b, sdiff);
-                        }
+                    for (int j = 1; j < KSPLIT; ++j) {
+                        const float4 h4 = *reinterpret_cast<const float4*>(tr0 + j * tr_step + at_lds);
+                        m.x += h4.x; m.y += h4.y; m.z += h4.z; m.w += h4.w;
                     }
+                    m.x *= invK; m.y *= invK; m.z *= invK; m.w *= invK;
+                }
+                const uint32_t at = place(q, i);
+                if (MODE == DecMode::Average) {
+                    *reinterpret_cast<float4*>(a.out + at) = m;
+                } else if (MODE == DecMode::Half0) {
+                    const float4 y = kYAhead ? y_ahead[i] : *reinterpret_cast<const float4*>(a.Y + at);
+                    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (a.anchor) x = *reinterpret_cast<const float4*>(a.anchor + at);
+                    x.x = (x.x + gam * y.x) - gam * m.x;
+                    x.y = (x.y + gam * y.y) - gam * m.y;
+                    x.z = (x.z + gam * y.z) - gam * m.z;
+                    x.w = (x.w + gam * y.w) - gam * m.w;
+                    *reinterpret_cast<float4*>(a.out + at) = x;
+                    if (kYAhead && q + 1 < kPasses) load_y(q + 1, i);
+                    if (a.x_sum) {                               // ergodic average: sum of the half-step iterates
+                        double2* xs = reinterpret_cast<double2*>(a.x_sum + at);
+                        double2 s0 = xs[0], s1 = xs[1];
+                        s0.x += (double)x.x; s0.y += (double)x.y; s1.x += (double)x.z; s1.y += (double)x.w;
+                        xs[0] = s0; xs[1] = s1;
+                    }
+                } else {
+                    float4 y = kYAhead ? y_ahead[i] : *reinterpret_cast<const float4*>(a.Y + at);
+                    y.x -= m.x; y.y -= m.y; y.z -= m.z; y.w -= m.w;
+                    *reinterpret_cast<float4*>(a.Y + at) = y;
+                    if (kYAhead && q + 1 < kPasses) load_y(q + 1, i);
                 }
             }
-            if (cnt > 0 && (start_a + used_a != cur.p_mid || start_b + used_b != cur.p_end)) malformed = true;
-            if constexpr (PREV) {
-                if (cnt > 0 && (start_pa + used_pa != prv.p_mid || start_pb + used_pb != prv.p_end)) malformed = true;
-            }
-        }
-        if constexpr (MODE != DecMode::Decode) {
-            for (int turn = 0; turn < W; ++turn) {        // worker order: k0, k0 + 1, ...
-                if (turn == w && active) {
-#pragma unroll
-                    for (int s = 0; s < kLaneCoords; ++s)
-                        if (s < cnt) s_acc[s * kAccPitch + lane] += val[s];
+        } else if (mine) {
+            // a short half: coordinate by coordinate, each wave of a group its share of the rows
+#pragma unroll 1
+            for (uint32_t f = (uint32_t)(kTurn * kSub / KSPLIT * part + lane); f < (uint32_t)(kTurn * kSub / KSPLIT * (part + 1)); f += kWave) {
+                const uint32_t at = base + (uint32_t)(kTurn * kSub * q) + f;
+                if (at >= cend) break;
+                const uint32_t at_lds = (f >> 5) * (uint32_t)kPitch + (f & 31u);
+                float m = tr0[at_lds];
+                if constexpr (KSPLIT > 1) {
+                    for (int j = 1; j < KSPLIT; ++j) m += tr0[j * tr_step + at_lds];
+                    m *= invK;
                 }
-                __syncthreads();
+                if (MODE == DecMode::Average) {
+                    a.out[at] = m;
+                } else if (MODE == DecMode::Half0) {
+                    const float x = ((a.anchor ? a.anchor[at] : 0.0f) + gam * a.Y[at]) - gam * m;
+                    a.out[at] = x;
+                    if (a.x_sum) a.x_sum[at] += (double)x;
+                } else {
+                    a.Y[at] -= m;
+                }
             }
         }
-    }
-    malformed = malformed || (flags & 0x8000u) != 0u;
-    if (__any(malformed) && lane == 0) raise_error(sc, QGX_EBIT_STREAM);
-    if (MODE == DecMode::Decode) return;
-
-    if constexpr (MODE == DecMode::Half1) {
-        sdiff = wave_sum(sdiff);
-        if (lane == 0) s_sd[w] = sdiff;
-        __syncthreads();
-        if (tid == 0) {
-            double t = 0.0;
-            for (int i = 0; i < W; ++i) t += s_sd[i];
-            a.s_partial[c] = t;
+        if constexpr (KSPLIT > 1) {
+            if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
-    const float invK = 1.0f / (float)lay.K;
-    const float gam = sc->gamma_f;
-    for (uint32_t i = (uint32_t)tid; i < clen; i += W * kWave) {
-        const float m = s_acc[(i & 63u) * kAccPitch + (i >> 6)] * invK;
-        const uint32_t at = clo + i;
-        if (MODE == DecMode::Average) a.out[at] = m;
-        else if (MODE == DecMode::Half0) {
-            const float x = a.anchor ? a.anchor[at] : 0.0f;
-            const float xh = (x + gam * a.Y[at]) - gam * m;
-            a.out[at] = xh;
-            if (a.x_sum) a.x_sum[at] += (double)xh;
-        } else a.Y[at] -= m;
-    }
-}
-
-template <DecMode MODE, bool PREV, bool TWO>
-__global__ __launch_bounds__(ragged_waves<PREV>() * kWave)
-void k_decode_ragged(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
-{
-    extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][1 or 2][rag_stride]
-    __shared__ __align__(16) unsigned char s_tab[kTabBytes];
-    __shared__ __align__(16) unsigned char s_tab2[TWO ? kTabBytes : 16];
-    __shared__ float s_acc[kLaneCoords * kAccPitch];
-    __shared__ double s_sd[ragged_waves<PREV>()];
-    decode_ragged_body<MODE, PREV, TWO>(lay, tab, sc, a, blockIdx.x, s_dyn, s_tab, s_tab2, s_acc, s_sd);
-}
-
-// Layouts with both kinds of positions: one launch, a workgroup per ragged position first and the workgroups
-// of the full positions after them, so that the few, slow ragged ones (a cold instruction cache and the
-// tables' load for a single position each) start at once and run beside the full ones, not before or after
-// them.  The ragged workgroups take their sums' array from the dynamic LDS, behind their staging buffers.
-template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-__global__ __launch_bounds__(kDecWaves * kWave) __attribute__((amdgpu_waves_per_eu(MODE == DecMode::Half1 ? 2 : 4)))
-void k_decode_both(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
-{
-    __shared__ double s_sd[kDecWaves];
-    extern __shared__ __align__(16) uint32_t s_dyn[];
-    __shared__ __align__(16) unsigned char s_tab[kTabBytes];
-    __shared__ __align__(16) unsigned char s_tab2[TWO ? kTabBytes : 16];
-    if (blockIdx.x >= lay.n_ragged) {
-        decode_full_body<MODE, PREV, TWO, WIDE, KSPLIT>(lay, tab, sc, a, blockIdx.x - lay.n_ragged, s_dyn, s_tab, s_tab2, s_sd);
-    } else {
-        float* s_acc = reinterpret_cast<float*>(s_dyn + (size_t)ragged_waves<PREV>() * (PREV ? 2 : 1) * a.rag_stride);
-        decode_ragged_body<MODE, PREV, TWO>(lay, tab, sc, a, blockIdx.x, s_dyn, s_tab, s_tab2, s_acc, s_sd);
     }
 }
 
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-static hipError_t launch_full_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
+static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
 {
-    if (lay.n_ragged == lay.NC) return hipSuccess;
-    const size_t lds = (size_t)kDecWaves * (PREV ? 2 : 1) * a.stage_stride * sizeof(uint32_t);
+    const uint64_t nwaves = MODE == DecMode::Decode ? (uint64_t)lay.n_tasks * ((lay.K + 1u) / 2u) : (uint64_t)lay.n_tasks * (uint32_t)KSPLIT;
+    // Workgroups of four waves spread over the compute units and are replaced as soon as four waves are done, but
+    // each has tables of its own: the smallest with which the launch's waves all fit the LDS at once, and
+    // where they do not fit anyway the largest, of which LDS holds the most waves (decode of 2^22 coordinates of
+    // eight workers, 4096 waves: 26.5 us in workgroups of four, 28 to 30 in workgroups of sixteen).
+    const size_t wave_lds = (size_t)(two_chains<MODE, PREV>() ? 2 : 1) * a.stage_stride * sizeof(uint32_t);
+    const size_t tables_lds = (size_t)(TWO ? 2 : 1) * kTabBytes + 256;
+    uint32_t per = (uint32_t)most_waves<MODE, PREV>();
+    for (uint32_t small = 4; small < (uint32_t)most_waves<MODE, PREV>(); small *= 2) {
+        const uint64_t held = min((uint64_t)(160u * 1024u / (small * wave_lds + tables_lds)) * small, (uint64_t)(two_chains<MODE, PREV>() ? 16 : 32));
+        if (nwaves <= held * a.n_cu) { per = small; break; }
+    }
+    const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
     if (e != hipSuccess) return e;
-    const uint64_t nwork = (MODE == DecMode::Decode) ? (uint64_t)lay.K * lay.NC : (uint64_t)lay.NC * (uint32_t)KSPLIT;
-    const uint32_t grid = (uint32_t)((nwork + kDecWaves - 1) / kDecWaves);
-    hipLaunchKernelGGL((k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), dim3(grid), dim3(kDecWaves * kWave), lds, st, lay, tab, sc, a);
+    hipLaunchKernelGGL((k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), dim3((uint32_t)((nwaves + per - 1u) / per)), dim3(per * kWave), lds, st,
+                       lay, tab, sc, a);
     return hipGetLastError();
 }
 
-template <DecMode MODE, bool PREV, bool TWO>
-static hipError_t launch_full(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
-{
-    if constexpr (MODE != DecMode::Decode) {
-        if (a.ksplit == 2u) {
-            if (a.wide) return launch_full_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st);
-            return launch_full_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st);
-        }
-        if (a.ksplit == 4u) {
-            if (a.wide) return launch_full_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st);
-            return launch_full_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st);
-        }
-    }
-    if (a.wide) return launch_full_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st);
-    return launch_full_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st);
-}
-
-template <DecMode MODE, bool PREV, bool TWO>
-static hipError_t launch_ragged(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
-{
-    if (lay.n_ragged == 0) return hipSuccess;
-    constexpr int W = ragged_waves<PREV>();
-    const size_t lds = (size_t)W * (PREV ? 2 : 1) * a.rag_stride * sizeof(uint32_t);
-    static LdsLimit limit;
-    hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode_ragged<MODE, PREV, TWO>), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_decode_ragged<MODE, PREV, TWO>), dim3(lay.n_ragged), dim3(W * kWave), lds, st, lay, tab, sc, a);
-    return hipGetLastError();
-}
-
-// Both kinds of positions in one launch (k_decode_both).
-template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-static hipError_t launch_both_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
-{
-    constexpr int W = ragged_waves<PREV>();
-    constexpr size_t bufs = PREV ? 2 : 1;
-    const size_t lds_full = (size_t)kDecWaves * bufs * a.stage_stride * sizeof(uint32_t);
-    const size_t lds_ragged = (size_t)W * bufs * a.rag_stride * sizeof(uint32_t) + (size_t)kLaneCoords * kAccPitch * sizeof(float);
-    const size_t lds = lds_full > lds_ragged ? lds_full : lds_ragged;
-    static LdsLimit limit;
-    hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode_both<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
-    if (e != hipSuccess) return e;
-    const uint64_t nwork = (MODE == DecMode::Decode) ? (uint64_t)lay.K * lay.NC : (uint64_t)lay.NC * (uint32_t)KSPLIT;
-    const uint32_t full_blocks = (uint32_t)((nwork + kDecWaves - 1) / kDecWaves);
-    hipLaunchKernelGGL((k_decode_both<MODE, PREV, TWO, WIDE, KSPLIT>), dim3(lay.n_ragged + full_blocks), dim3(kDecWaves * kWave),
-                       lds, st, lay, tab, sc, a);
-    return hipGetLastError();
-}
-
-template <DecMode MODE, bool PREV, bool TWO>
-static hipError_t launch_both(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
-{
-    if constexpr (MODE != DecMode::Decode) {
-        if (a.ksplit == 2u) {
-            if (a.wide) return launch_both_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st);
-            return launch_both_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st);
-        }
-        if (a.ksplit == 4u) {
-            if (a.wide) return launch_both_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st);
-            return launch_both_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st);
-        }
-    }
-    if (a.wide) return launch_both_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st);
-    return launch_both_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st);
-}
-
-// A layout's full positions go to k_decode, its ragged ones to k_decode_ragged; a layout that has both
-// takes one launch of the kernel that holds both bodies.
 template <DecMode MODE, bool PREV, bool TWO = false>
 static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
 {
-    if (lay.n_ragged != 0 && lay.n_ragged != lay.NC) return launch_both<MODE, PREV, TWO>(lay, tab, sc, a, st);
-    hipError_t e = launch_ragged<MODE, PREV, TWO>(lay, tab, sc, a, st);
-    if (e != hipSuccess) return e;
-    return launch_full<MODE, PREV, TWO>(lay, tab, sc, a, st);
+    if constexpr (MODE != DecMode::Decode) {
+        if (a.ksplit == 2u) {
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st);
+            return launch_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st);
+        }
+        if (a.ksplit == 4u) {
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st);
+            return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st);
+        }
+    }
+    if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st);
+    return launch_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st);
 }
 
 hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a,
@@ -975,11 +779,11 @@ hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Sca
 }
 
 // ---- the scalar end of the second half-step: S, gamma_{t+1}, t; then X_{t+1} on request -----------
-__global__ __launch_bounds__(256) void k_finish_half1(uint32_t NC, uint32_t K, Scalars* sc, const double* s_partial)
+__global__ __launch_bounds__(256) void k_finish_half1(uint32_t n_tasks, uint32_t K, Scalars* sc, const double* s_partial)
 {
     __shared__ double s_red[256];
     double acc = 0.0;
-    for (uint32_t i = threadIdx.x; i < NC; i += 256) acc += s_partial[i];     // fixed order: reproducible
+    for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) acc += s_partial[i];     // fixed order: reproducible
     s_red[threadIdx.x] = acc;
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {
@@ -1007,7 +811,7 @@ __global__ __launch_bounds__(256) void k_x_from_y(uint32_t d, const Scalars* sc,
 hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_partial, const float* Y,
                                const float* anchor, float* X_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(256), 0, st, lay.NC, lay.K, sc, s_partial);
+    hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(256), 0, st, lay.n_tasks, lay.K, sc, s_partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || X_out == nullptr) return e;
     const uint32_t grid = min((lay.d + 255u) / 256u, 4096u);
@@ -1143,6 +947,8 @@ __global__ __launch_bounds__(1024) void k_compact_offsets(uint32_t NC, const uin
     }
 }
 
+constexpr int kChunkPieces = kChunkWordsMax / (kWave * 4);   // 7 x uint4 per lane cover a worst-case chunk
+
 __global__ __launch_bounds__(256) void k_compact_copy(uint32_t NC, uint32_t K, const uint16_t* __restrict__ sub_end,
                                                       const uint32_t* __restrict__ in_off, const uint32_t* __restrict__ in_payload,
                                                       uint64_t in_cap, const uint32_t* __restrict__ out_off,
@@ -1159,17 +965,17 @@ __global__ __launch_bounds__(256) void k_compact_copy(uint32_t NC, uint32_t K, c
     }
     const uint4* s = reinterpret_cast<const uint4*>(in_payload + (size_t)k * in_cap + src);
     uint4* d = reinterpret_cast<uint4*>(out_payload + (size_t)k * out_cap + dst);
-    // a chunk of the largest size is kPre pieces per lane: all of a lane's loads are on their way before
+    // a chunk of the largest size is kChunkPieces pieces per lane: all of a lane's loads are on their way before
     // its first store (a chunk of some other origin may be longer: the loop goes on)
-    for (uint32_t q0 = 0; q0 < (words >> 2); q0 += (uint32_t)(kPre * kWave)) {
-        uint4 held[kPre];
+    for (uint32_t q0 = 0; q0 < (words >> 2); q0 += (uint32_t)(kChunkPieces * kWave)) {
+        uint4 held[kChunkPieces];
 #pragma unroll
-        for (int j = 0; j < kPre; ++j) {
+        for (int j = 0; j < kChunkPieces; ++j) {
             const uint32_t q = q0 + lane + (uint32_t)j * kWave;
             held[j] = q < (words >> 2) ? nt_load4u(s + q) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
-        for (int j = 0; j < kPre; ++j) {
+        for (int j = 0; j < kChunkPieces; ++j) {
             const uint32_t q = q0 + lane + (uint32_t)j * kWave;
             if (q < (words >> 2)) d[q] = held[j];
         }

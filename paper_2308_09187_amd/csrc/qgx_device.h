@@ -97,6 +97,12 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
+// The value of the lane before; lane 0 gets `first`.
+__device__ __forceinline__ uint32_t wave_shift_in(uint32_t x, uint32_t first)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xf, 0xf, false);   // wave_shr:1
+}
+
 __device__ __forceinline__ double wave_sum(double x)
 {
 #pragma unroll
@@ -172,6 +178,11 @@ __device__ __forceinline__ uint32_t lds_address(const void* p)
 
 typedef uint32_t lds_u32x2 __attribute__((ext_vector_type(2)));
 typedef float lds_f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t lds_load_u32(uint32_t addr)
+{
+    return *(const __attribute__((address_space(3))) uint32_t*)(uintptr_t)addr;
+}
 
 __device__ __forceinline__ uint2 lds_load_u2(uint32_t addr)
 {

@@ -17,7 +17,6 @@ constexpr int kChunk = QGX_CHUNK;         // coordinates per chunk = one wave's 
 constexpr int kRows = 16;                 // rows of 256 coordinates per chunk (4 per lane and row)
 constexpr int kSub = QGX_SUB;
 constexpr int kSubs = QGX_SUBS;           // sub-chunk table entries per chunk
-constexpr int kLaneCoords = 64;           // coordinates one decoder lane parses: two sub-chunks
 constexpr int kMaxCode = QGX_MAX_CODE_BITS;             // longest code word
 constexpr int kMaxSymBits = kMaxCode + 1;               // plus the sign bit
 constexpr int kChunkWordsMax = kChunk * kMaxSymBits / 32;  // 1792
@@ -104,10 +103,11 @@ struct Layout {                 // device pointers into one allocation
     const uint32_t* bucket_chunk0;  // [NB+1] first chunk of each bucket
     const uint32_t* chunk_start;    // [NC+1]
     const uint32_t* chunk_bucket;   // [NC] bucket of the chunk's first coordinate
-    const uint32_t* ragged_chunk;   // [n_ragged] chunk positions with fewer than kChunk coordinates, ascending
+    // The decoder's tasks, half a chunk position each: 2 * chunk + half.  Null when every position is full: task
+    // t is then entry t.  Otherwise the full halves come first, then the others (a half without coordinates is none).
+    const uint32_t* task;           // [n_tasks]
     uint32_t NB, NC, K, d;
-    uint32_t n_ragged;
-    uint32_t max_ragged;            // coordinates of the longest of them
+    uint32_t n_tasks;
     uint32_t waves_per_bucket;      // ceil(bucket / kChunk)
     uint32_t uniform_bucket;        // bucket size if there is one segment (offsets are then arithmetic), else 0
     // Buckets of 256, 512, 1024 or 2048 coordinates share chunks: a segment is cut into runs of kChunk
@@ -172,16 +172,14 @@ struct DecodeArgs {
     float* out;                 // Decode: Vhat [K][d]; Average: mean [d]; Half0: X_{t+1/2} [d]
     float* Y;                   // [d] dual state (Half0 reads, Half1 updates)
     const float* anchor;        // [d] or null
-    double* s_partial;          // [NC] per-chunk partial of S (Half1)
+    double* s_partial;          // [n_tasks] per-task partial of S (Half1)
     double* x_sum;              // [d] running sum of the X_{t+1/2} or null (Half0 adds its output)
-    uint32_t stage_words;       // most words a chunk can take with the code in use (multiple of 4)
+    uint32_t stage_words;       // most words half a chunk of the code in use touches (multiple of 4)
     uint32_t stage_stride;      // words of one LDS staging buffer (padded layout plus slack)
     uint32_t sym_bits;          // most bits a symbol can take with the codes in use (longest word + sign)
-    uint32_t rag_words;         // the same two for the layout's longest chunk of fewer than 4096 coordinates,
-                                // plus room for 32 symbols and a window past its end
-    uint32_t rag_stride;
     uint32_t wide;              // the 8-byte decode table of the current streams' code is valid (Tables::wide_ok)
-    uint32_t ksplit;            // fused modes: 1, 2 or 4 waves per full position, a run of the workers each
+    uint32_t ksplit;            // fused modes: 1, 2 or 4 waves per task, a run of the workers each
+    uint32_t n_cu;              // compute units of the device
 };
 
 // The dynamic LDS a kernel may be launched with is an attribute of the kernel on a device, raised with

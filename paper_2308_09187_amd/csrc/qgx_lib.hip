@@ -14,11 +14,11 @@
 using namespace qgx;
 
 // Scratch of qgx_eg_step_static, the variant of qgx_eg_step for callers that may not allocate: the
-// per-chunk partial sums of the step-size accumulator S, which qgx_eg_step keeps in memory that
+// partial sums (two per chunk) of the step-size accumulator S, which qgx_eg_step keeps in memory that
 // qgx_create allocated.  Every GPU the library runs on holds its own copy of the array, at its own
 // address, until the process ends.  The name below is a host-side stand-in for it, not a device
 // address: host code uses the address hipGetSymbolAddress gave for the device (static_scratch_of).
-static __device__ __align__(256) double scratch[QGX_STATIC_MAX_CHUNKS];
+static __device__ __align__(256) double scratch[2 * QGX_STATIC_MAX_CHUNKS];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -220,15 +220,13 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     if (sum != cfg->d) { delete c; return QGX_ERR_ARG; }
 
     // buckets and chunks of one worker
-    std::vector<uint32_t> bstart, bchunk0, cstart, cbucket, ragged;
+    std::vector<uint32_t> bstart, bchunk0, cstart, cbucket, tasks, ragged;
     uint64_t pos = 0, worst = 0;
-    uint32_t max_ragged = 0;
     const bool shared = shares_chunks(cfg->bucket);
     auto add_chunk = [&](uint64_t start, uint64_t cl, uint32_t first_bucket) {
-        if (cl < (uint64_t)kChunk) {
-            ragged.push_back((uint32_t)cstart.size());
-            if (cl > max_ragged) max_ragged = (uint32_t)cl;
-        }
+        const uint32_t first_half = 2u * (uint32_t)cstart.size();
+        (cl >= (uint64_t)kChunk / 2 ? tasks : ragged).push_back(first_half);
+        if (cl > (uint64_t)kChunk / 2) (cl == (uint64_t)kChunk ? tasks : ragged).push_back(first_half + 1u);
         cstart.push_back((uint32_t)start);
         cbucket.push_back(first_bucket);
         const uint64_t wds = (cl * kMaxSymBits + 31) / 32;
@@ -268,19 +266,20 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess && cus > 0)
             c->n_simd = 4u * (uint32_t)cus;
     }
-    const size_t n_lay = (size_t)(NB + 1) * 2 + (NC + 1) + NC + ragged.size() + 1;
+    const bool all_full = tasks.size() == 2 * (size_t)NC;      // then task t is half t & 1 of chunk t >> 1
+    tasks.insert(tasks.end(), ragged.begin(), ragged.end());
+    const size_t n_lay = (size_t)(NB + 1) * 2 + (NC + 1) + NC + (all_full ? 0 : tasks.size()) + 1;
     std::vector<uint32_t> flat;
     flat.reserve(n_lay);
     flat.insert(flat.end(), bstart.begin(), bstart.end());
     flat.insert(flat.end(), bchunk0.begin(), bchunk0.end());
     flat.insert(flat.end(), cstart.begin(), cstart.end());
     flat.insert(flat.end(), cbucket.begin(), cbucket.end());
-    flat.insert(flat.end(), ragged.begin(), ragged.end());
+    if (!all_full) flat.insert(flat.end(), tasks.begin(), tasks.end());
     flat.push_back(0u);
 
     c->lay.NB = NB; c->lay.NC = NC; c->lay.K = cfg->K; c->lay.d = (uint32_t)cfg->d;
-    c->lay.n_ragged = (uint32_t)ragged.size();
-    c->lay.max_ragged = max_ragged;
+    c->lay.n_tasks = (uint32_t)tasks.size();
     uint32_t max_len = 0;
     for (uint32_t b = 0; b < NB; ++b) max_len = bstart[b + 1] - bstart[b] > max_len ? bstart[b + 1] - bstart[b] : max_len;
     c->lay.waves_per_bucket = (max_len + kChunk - 1) / kChunk;
@@ -308,7 +307,7 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
         ok = ok && hipMemset(c->d_xch, 0, n_units * 4 * sizeof(unsigned long long)) == hipSuccess;
     }
     ok = ok && hipMalloc(&c->d_tickets, (size_t)cfg->K * kTicketStride * sizeof(unsigned long long)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_spartial, (size_t)NC * sizeof(double)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_spartial, (size_t)c->lay.n_tasks * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hpartial, (size_t)c->h_groups * QGX_MAX_BINS * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hist, QGX_MAX_BINS * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_prob, kSymMax * sizeof(double)) == hipSuccess;
@@ -330,7 +329,7 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     c->lay.bucket_chunk0 = c->d_layout + (NB + 1);
     c->lay.chunk_start = c->d_layout + 2 * (size_t)(NB + 1);
     c->lay.chunk_bucket = c->lay.chunk_start + (NC + 1);
-    c->lay.ragged_chunk = c->lay.chunk_bucket + NC;
+    c->lay.task = all_full ? nullptr : c->lay.chunk_bucket + NC;
     *out = c;
     return QGX_OK;
 }
@@ -634,27 +633,33 @@ qgx_status qgx_quantization_metrics(qgx_ctx* ctx, const float* V, const float* V
 
 static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream* cur, const qgx_stream* prev)
 {
-    a.stage_words = chunk_slot_words(ctx);
-    a.stage_stride = (a.stage_words + a.stage_words / 16 + 20 + 3) / 4 * 4;   // padded layout, four zero words below the chunk's end, zero words above its first
-    if (a.stage_stride < 1280u) a.stage_stride = 1280u;   // the buffer also turns the output (32 rows of 36 floats)
     a.sym_bits = longest_code(ctx) + 1;
-    a.rag_words = ((ctx->lay.max_ragged * a.sym_bits + 31) / 32 + a.sym_bits + 2 + 3) / 4 * 4;
-    a.rag_stride = (a.rag_words + a.rag_words / 16 + 12 + 3) / 4 * 4;
+    a.stage_words = (uint32_t)(kChunk / 2) * a.sym_bits / 32u + 8u;      // half a chunk, from a multiple of 4 words to one
+    a.stage_stride = (a.stage_words + a.stage_words / 16 + 20 + 3) / 4 * 4;   // padded layout, four zero words below the end, zero words above the first
+    if (a.stage_stride < 576u) a.stage_stride = 576u;     // a buffer also turns the output (16 rows of 36 floats)
     a.wide = (T(ctx).wide && (!prev || ctx->ts[ctx->sel_prev].wide)) ? 1u : 0u;   // one kernel variant reads both streams
-    // Full positions against the wave slots the kernel can hold (4 per SIMD with one stream, 2 with two):
-    // a launch takes about as long as its rounds of waves, counted whole; with a position given to f
-    // waves, a run of the workers each, the rounds are 1/f as long and the last one is rounded up to
-    // 1/f of one.  Taken (f = 2 or 4) when that saves more than the joining costs.
+    // Waves per task.  Tasks against the wave slots (8 per SIMD with one stream, 4 with two), in rounds of waves: a
+    // launch takes about as long as its whole rounds and, for a last one that fills a part x of the slots,
+    // max(0.36, 0.15 + 0.85 x) of a round (few waves wait for their look-ups, many for each other).  A round is
+    // as long as the workers a wave takes.  With f waves to a task, a run of the workers each, the rounds are
+    // 1/f as long, and the joining costs about 0.3 (f = 2) or 0.62 (f = 4) of a worker's time.  Measured, first
+    // half-step with 1 / 2 / 4 waves: 512 tasks of 8 workers 28.7 / 19.6 / 16.5 us, 2048 of 8 31.7 / 26.9 / 30.8,
+    // 4816 of 8 57 / 70 / 71; second: 2048 of 8 55.5 / 52 / 59, 4816 of 8 140 / 130 / 136, 1500 of 5 52.5 / 45 / 50.
     a.ksplit = 1u;
     {
-        const double r = (double)(ctx->lay.NC - ctx->lay.n_ragged) / ((double)ctx->n_simd * (prev ? 2.0 : 4.0));
-        double best = std::ceil(r);
+        const double K = (double)ctx->lay.K, r = (double)ctx->lay.n_tasks / ((double)ctx->n_simd * (prev ? 4.0 : 8.0));
+        auto rounds = [](double x) {
+            const double whole = std::floor(x), part = x - whole;
+            return whole + (part > 0.0 ? std::fmax(0.36, 0.15 + 0.85 * part) : 0.0);
+        };
+        double best = rounds(r) * K;
         for (uint32_t f = 2; f <= 4u && f <= ctx->lay.K; f *= 2) {
-            const double cost = std::ceil(f * r) / f * (f == 2 ? 1.05 : 1.10);
+            const double cost = rounds(f * r) * K / f + (f == 2 ? 0.30 : 0.62);
             if (cost < best) { best = cost; a.ksplit = f; }
         }
         if (ctx->ksplit_forced >= 0 && (uint32_t)ctx->ksplit_forced <= ctx->lay.K) a.ksplit = (uint32_t)ctx->ksplit_forced;
     }
+    a.n_cu = ctx->n_simd / 4u;
     a.norms = cur->norms; a.chunk_off = cur->chunk_off; a.sub_end = cur->sub_end; a.payload = cur->payload;
     a.cap_words = cur->payload_words_per_worker;
     if (prev) {

@@ -1,0 +1,50 @@
+"""The decoder's tasks at their edges: half chunk positions of 1 .. 2047 coordinates beside full ones, halves whose
+words do not fit the pieces that travel ahead, odd numbers of workers, vectors at odd addresses.  Decoded vectors bit
+for bit against the oracle (one binary32 product each); mean, iterates and S within the bounds the parity tests derive."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2308_09187_amd import synth
+from test_gpu_parity import REL, WAVES_PER_POSITION, _vectors_of_very_different_density, assert_elementwise, dev, make_ctx, mean_abs, oracle_stream, qgx, rel_err  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+ENDS = [1, 31, 32, 33, 2016, 2047, 2048, 2049, 2081, 4095]     # coordinates of the last position
+
+
+@pytest.mark.parametrize("waves", [1, 4])
+@pytest.mark.parametrize("n_levels", [16, 64])                  # with 64, half a chunk of dense vectors takes 830 words
+@pytest.mark.parametrize("end", ENDS)
+def test_short_halves(qgx, monkeypatch, end, n_levels, waves):
+    monkeypatch.setitem(WAVES_PER_POSITION, "waves", waves)
+    K = 5 if waves == 4 else 3
+    d = 4096 + end
+    levels = synth.levels_uniform(n_levels)
+    ctx, lay = make_ctx(qgx, d, K, 4096, oracle.NORM_LINF, levels, seed=11)
+    kinds = ["dense", "t3", "sparse", "dense", "zero"][:K]
+    V = [_vectors_of_very_different_density(d, kinds), _vectors_of_very_different_density(d, kinds[::-1])]
+    ctx.state_init(None)
+    st = oracle.EGState(d, K)
+    A, B = ctx.new_stream(slotted=True), ctx.new_stream(slotted=True)
+    X = torch.empty(d, device="cuda")
+    Vhat = []
+    for call, s in ((0, A), (1, B)):
+        ctx.quantize_encode(dev(V[call]), call, s)
+        norms = s.norms.cpu().numpy()
+        so = oracle_stream(V[call], lay, oracle.NORM_LINF, levels, 11, call, norms, ctx.worst_words)[3]
+        Vhat.append(oracle.decode(so, norms, lay, levels)[0])
+        flat = torch.full((K * d + 2,), -7.0, device="cuda")    # at an address that is a multiple of 4 bytes and no more
+        ctx.decode(s, flat[1:-1].view(K, d))
+        flat = flat.cpu().numpy()
+        np.testing.assert_array_equal(flat[1:-1].reshape(K, d), Vhat[call])
+        assert flat[0] == -7.0 and flat[-1] == -7.0
+        assert_elementwise(ctx.decode_average(s).cpu().numpy(), oracle.mean(Vhat[call]), mean_abs(Vhat[call]), "mean")
+    ctx.eg_step(0, A, None, X)
+    assert rel_err(X.cpu().numpy(), st.half0(Vhat[0])) <= REL
+    ctx.eg_step(1, B, A, X)
+    assert rel_err(X.cpu().numpy(), st.half1(Vhat[1], Vhat[0])) <= REL
+    assert abs(ctx.scalars()["S"] - st.S) <= REL * st.S
+    assert ctx.poll_error() == 0
+    ctx.close()
