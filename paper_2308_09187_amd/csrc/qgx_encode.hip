@@ -10,15 +10,19 @@
 // between the norm reduction and the rounding pass, (c) one Philox4x32 block (four words) serves
 // exactly the four coordinates of a lane and row.
 //
-// The kernel runs close to what the memory system gives (about 93 % of a plain copy of its input) and
-// at about two thirds of what the vector ALUs could issue, so the per-coordinate path is kept to a straight
-// line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, address of the lower candidate table row) -> one
+// The vector ALUs' issue bounds it (busy for about 80 % of the time; 145 instructions per row of four
+// coordinates a lane, a third of them the generator), the memory system is next (4.6 TB/s of the 6.2 that the best
+// streaming kernel reaches), so the per-coordinate path is kept to a straight line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, address of the lower candidate table row) -> one
 // 16-byte LDS row holding the level, the scaled gap and the two candidate code words with the sign
-// already appended -> compare against the Philox draw -> select.  Chunks that are not full, buckets
-// with a zero norm and level tables too fine for the cell table take a general path.
+// already appended -> compare against the Philox draw -> select.  A chunk's short last row, buckets
+// with a zero norm and level tables too fine for the cell table take a general path, row by row from memory.
+// (Whole rows of a chunk that is not full, and of workers whose vectors start at odd addresses, took that path as
+// well: 5 x 3000001 coordinates in buckets of 6000, 59 us; now 36.)
 //
-// The stream keeps coordinate order: per row the lanes' code lengths are prefix-summed across the wave
-// (DPP) and every lane ORs its (at most 56) bits into the wave's LDS staging buffer.
+// The stream keeps coordinate order: the lanes' code lengths are prefix-summed across the wave (DPP, two rows in
+// one scan) and every lane ORs its (at most 56) bits into the wave's LDS staging buffer.  No branch lies between
+// the rows of a full chunk.  (A scan per row and a branch around the store of the sub-chunk ends: 160
+// instructions a row, 8 x 2^24 coordinates 173 us; 163 now.)
 // Placement of the chunks in the payload.  Slotted: chunk c goes to c * slot_words; no workgroup waits
 // for another.  Compact: chunks in chunk order without gaps, so a workgroup needs the total length of
 // all earlier buckets of its worker: a decoupled look-back over per-bucket (flag, length) words gives
@@ -200,19 +204,34 @@ __device__ __forceinline__ uint32_t quantize_one(float x, float rinv, uint32_t r
     return up ? __float_as_uint(t.w) : __float_as_uint(t.z);
 }
 
-// Appends one row (four entries per lane) to the wave's staging buffer; returns the row's bit count.
-// sub_mine: where the lane's run of this row ends in the sub-chunk table, written by the run's last
-// lane (ends_run); both are the caller's so that they are worked out once per chunk, not per row.
-__device__ __forceinline__ uint32_t pack_row(uint32_t* stage, uint16_t* sub_mine, bool ends_run, uint32_t row_base,
-                                             const uint32_t (&e)[4])
+// Where a chunk's sub-chunk ends go, eight lanes of a row one 16-byte piece: the row of the table as a buffer
+// of 256 bytes.  A run's last lane writes; the others' offset lies outside the buffer, and such stores are dropped:
+// no branch, so that the rows of a chunk are one straight line for the scheduler.
+struct SubEnds {
+    __amdgpu_buffer_rsrc_t row;
+    uint32_t at;                 // 2 * (the lane's run in a row), or outside
+    __device__ __forceinline__ SubEnds(uint16_t* table_row, int lane)
+        : row(__builtin_amdgcn_make_buffer_rsrc(table_row, 0, kSubs * (int)sizeof(uint16_t), 0x00027000)),
+          at((lane & 7) == 7 ? 2u * (uint32_t)(lane >> 3) : 0x40000000u) {}
+    __device__ __forceinline__ void put(int r, uint32_t end) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)end, row, (int)(at + 16u * (uint32_t)r), 0, 0);
+    }
+};
+
+struct RowCode { uint32_t len; uint64_t bits; };       // a lane's four entries of a row, one after the other (<= 56 bits)
+
+__device__ __forceinline__ RowCode join_row(const uint32_t (&e)[4])
 {
     const uint32_t l0 = e[0] >> 16, l1 = e[1] >> 16, l2 = e[2] >> 16, l3 = e[3] >> 16;
     const uint32_t c01 = (e[0] & 0xFFFFu) | ((e[1] & 0xFFFFu) << l0);     // <= 28 bits
     const uint32_t c23 = (e[2] & 0xFFFFu) | ((e[3] & 0xFFFFu) << l2);
-    const uint32_t l01 = l0 + l1, len = l01 + l2 + l3;
-    const uint64_t bits = (uint64_t)c01 | ((uint64_t)c23 << l01);         // <= 56 bits
-    const uint32_t incl = wave_incl_scan(len);
-    const uint32_t pos = row_base + incl - len;
+    const uint32_t l01 = l0 + l1;
+    return RowCode{l01 + l2 + l3, (uint64_t)c01 | ((uint64_t)c23 << l01)};
+}
+
+__device__ __forceinline__ void place_row(uint32_t* stage, uint32_t pos, uint64_t bits)
+{
     const uint32_t wi = pos >> 5, sh = pos & 31u;
     const uint64_t lo64 = (uint64_t)(uint32_t)bits << sh;
     const uint64_t hi64 = (uint64_t)(uint32_t)(bits >> 32) << sh;
@@ -220,8 +239,34 @@ __device__ __forceinline__ uint32_t pack_row(uint32_t* stage, uint16_t* sub_mine
     __hip_atomic_fetch_or(&stage[wi + 1], (uint32_t)(lo64 >> 32) | (uint32_t)hi64, __ATOMIC_RELAXED,
                           __HIP_MEMORY_SCOPE_WORKGROUP);
     __hip_atomic_fetch_or(&stage[wi + 2], (uint32_t)(hi64 >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (ends_run) *sub_mine = (uint16_t)(row_base + incl);                      // a sub-chunk is eight lanes of a row
+}
+
+// Appends row r (four entries per lane) to the wave's staging buffer; returns the row's bit count.
+__device__ __forceinline__ uint32_t pack_row(uint32_t* stage, const SubEnds& ends, int r, uint32_t row_base, const uint32_t (&e)[4])
+{
+    const RowCode c = join_row(e);
+    const uint32_t incl = wave_incl_scan(c.len);
+    place_row(stage, row_base + incl - c.len, c.bits);
+    ends.put(r, row_base + incl);
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+}
+
+// The same for rows r and r + 1: a row's bit count (at most 64 * 56) fits 16 bits, so one scan across the wave
+// does both.
+__device__ __forceinline__ uint32_t pack_two_rows(uint32_t* stage, const SubEnds& ends, int r, uint32_t row_base,
+                                                  const uint32_t (&ea)[4], const uint32_t (&eb)[4])
+{
+    const RowCode a = join_row(ea), b = join_row(eb);
+    const uint32_t both = a.len | (b.len << 16);
+    const uint32_t incl = wave_incl_scan(both), excl = incl - both;
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    const uint32_t second = row_base + (total & 0xFFFFu);
+    const uint32_t pa = row_base + (excl & 0xFFFFu), pb = second + (excl >> 16);
+    place_row(stage, pa, a.bits);
+    ends.put(r, pa + a.len);
+    place_row(stage, pb, b.bits);
+    ends.put(r + 1, pb + b.len);
+    return (total & 0xFFFFu) + (total >> 16);
 }
 
 struct ChunkGeom {            // one wave's share of a bucket
@@ -253,24 +298,26 @@ __device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, i
     return g;
 }
 
-// Issues the loads of one chunk into registers (16 rows x 4 coordinates per lane).
-__device__ __forceinline__ void load_chunk(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g,
-                                           bool vec_ok, int lane)
+// Issues the loads of one chunk into registers (16 rows x 4 coordinates per lane).  Vectors of an odd length put
+// a worker's rows at any multiple of 4 bytes, which 16-byte loads from global memory take.
+__device__ __forceinline__ void load_chunk(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g, int lane)
 {
-    if (g.full && vec_ok) {
+    if (g.full) {
 #pragma unroll
         for (int r = 0; r < kRows; ++r)
-            v[r] = nt_load4(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
+            v[r] = nt_load4_any(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
     } else {
+const int whole = (int)(g.clen >> 8);                    // rows before a short last one (all wave-uniform)
+        const uint32_t i0 = g.clo + (uint32_t)whole * 256u + (uint32_t)lane * 4u;
+        float4 tail = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i0 < g.cend) tail.x = Vk[i0];
+        if (i0 + 1 < g.cend) tail.y = Vk[i0 + 1];
+        if (i0 + 2 < g.cend) tail.z = Vk[i0 + 2];
+        if (i0 + 3 < g.cend) tail.w = Vk[i0 + 3];
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 < g.cend) x.x = Vk[i0];
-            if (i0 + 1 < g.cend) x.y = Vk[i0 + 1];
-            if (i0 + 2 < g.cend) x.z = Vk[i0 + 2];
-            if (i0 + 3 < g.cend) x.w = Vk[i0 + 3];
-            v[r] = x;
+            if (r < whole) v[r] = nt_load4_any(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
+            else v[r] = r == whole ? tail : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
 }
@@ -361,15 +408,32 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
 // GROUPED: the layout has shared chunks; a workgroup is four waves with a chunk each, and every wave
 // finds the norms of its chunk's buckets by itself.
 // CM: cell_mant of the level table, so that the rounding pass has the cell size as a constant.
+// Waves per SIMD: five where V is read (four: 177 us instead of 163 at 8 x 2^24); four where it is formed, whose
+// second generator and transcendentals spill at five (16 x 2^26 coordinates: 2.07 ms instead of 2.30).
 template <EncMode MODE, bool GROUPED, int CM>
-__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(5)))
+__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(MODE == EncMode::Generate ? 4 : 5)))
 void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
 {
     extern __shared__ __align__(16) unsigned char s_all[];
     const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
     const int nwaves = (int)(blockDim.x >> 6);
     const uint32_t n_sym = tab->n_sym;
-    const uint32_t k = (uint32_t)blockIdx.x % lay.K;    // worker fixed by the block, buckets by ticket
+    // The worker and, without tickets, the unit of work are fixed by the block.  Workgroups go round the eight XCDs, each
+    // with a second-level cache of its own: where the workers read the same operands (Generate), the K workgroups of
+    // a unit are put on one XCD, one after the other, so that the operands come from memory once and not from
+    // every XCD.
+    uint32_t k, own_unit;
+    if constexpr (MODE == EncMode::Generate) {
+        constexpr uint32_t kXcds = 8u;
+        const uint32_t even = (gridDim.x / lay.K) / kXcds * kXcds;            // units in whole rounds of the XCDs
+        const uint32_t i = blockIdx.x, j = i / kXcds;
+        const bool round = i < even * lay.K;
+        k = round ? j % lay.K : (i - even * lay.K) % lay.K;
+        own_unit = round ? j / lay.K * kXcds + i % kXcds : even + (i - even * lay.K) / lay.K;
+    } else {
+        k = (uint32_t)blockIdx.x % lay.K;
+        own_unit = (uint32_t)blockIdx.x / lay.K;
+    }
 
     // LDS plan: [cell][lev + / lev -][reduction scratch][one staging buffer per wave]
     float2* s_cell = reinterpret_cast<float2*>(s_all);
@@ -444,7 +508,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             return Vk[i];
         }
     };
-    const uint32_t unit = ticketed ? s_misc[2] : (uint32_t)blockIdx.x / lay.K;
+    const uint32_t unit = ticketed ? s_misc[2] : own_unit;
     const uint32_t epoch = ticketed ? s_misc[3] : 0u;
     uint32_t b = a.parts > 1u ? unit / a.parts : unit;  // the bucket; with shared chunks the first of the wave's chunk
     const uint32_t part = GROUPED ? 0u : unit - b * a.parts;
@@ -474,12 +538,11 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     }
     const bool split = a.parts > 1u && g.bparts > 1u;
     unsigned long long* xch = a.xch + ((size_t)k * lay.NB + b) * a.parts * 4u;
-    // The sub-chunk ends go straight to the table in global memory (eight lanes of a row write one
-    // 16-byte piece): staging them in LDS would cost the fifth workgroup of a compute unit.
+    // The sub-chunk ends go straight to the table in global memory: staging them in LDS would cost the fifth
+    // workgroup of a compute unit.
     uint16_t* __restrict__ sub_g =
         MODE != EncMode::QuantOnly ? a.sub_end + ((size_t)k * lay.NC + g.c) * kSubs : nullptr;
-    uint16_t* __restrict__ sub_mine = sub_g + (lane >> 3);
-    const bool ends_run = (lane & 7) == 7;
+    const SubEnds ends(reinterpret_cast<uint16_t*>(uniform_address(sub_g)), lane);
     float4 v[kRows];
     if constexpr (MODE == EncMode::Generate) {
         // the dual vector is formed here instead of read: operator and noise for four coordinates per lane and row
@@ -495,7 +558,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             v[r] = x;
         }
     } else if (MODE != EncMode::EncodeOnly) {
-        load_chunk(v, Vk, g, vec_ok, lane);
+        load_chunk(v, Vk, g, lane);
     }
     {
 
@@ -613,35 +676,56 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         }
         const float rinv = GROUPED ? 0.0f : 1.0f / n;  // one IEEE division per bucket
         const bool live = GROUPED ? plain : n > 0.0f;
-        const bool fast = g.full && live && vec_ok && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
+        // (a chunk's last row, if short, always takes the general path)
+        const bool fast = live && (vec_ok || MODE != EncMode::QuantOnly) && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
         const uint32_t rshift = GROUPED ? lay.bucket_shift - 8u : 0u;         // rows per bucket, as a shift
 
         // ---- per row: quantise, code, pack -------------------------------------------------------
         uint32_t row_base = 0;                         // bits of this chunk written so far (wave-uniform)
-        if (fast) {
+        int rows_done = 0;
+        const uint32_t block0 = (g.clo >> 2) + (uint32_t)lane;                // Philox block of row 0 (chunks start at multiples of 4)
+        auto quantize_row = [&](int r, uint32_t (&e)[4]) __attribute__((always_inline)) {
+            uint32_t rnd[4], idx[4];
+            philox4x32_10(block0 + 64u * (uint32_t)r, 0u, k, call_id, a.seed_lo, a.seed_hi, rnd);
+            const float rinv_r = GROUPED ? s_rinv[w * 16 + (int)((uint32_t)r >> rshift)] : rinv;
+            e[0] = quantize_one<true, CM>(v[r].x, rinv_r, rnd[0], L, n_sym, idx[0]);
+            e[1] = quantize_one<true, CM>(v[r].y, rinv_r, rnd[1], L, n_sym, idx[1]);
+            e[2] = quantize_one<true, CM>(v[r].z, rinv_r, rnd[2], L, n_sym, idx[2]);
+            e[3] = quantize_one<true, CM>(v[r].w, rinv_r, rnd[3], L, n_sym, idx[3]);
+            if (MODE == EncMode::QuantOnly) {
+                uint32_t pk = 0;
+                const float xs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) pk |= (idx[q] | ((__float_as_uint(xs[q]) >> 31) << 7)) << (8 * q);
+                *reinterpret_cast<uint32_t*>(a.sym_out + kbase + 4u * (size_t)(block0 + 64u * (uint32_t)r)) = pk;
+            }
+        };
+        if (fast && g.full) {
+#pragma unroll
+            for (int r = 0; r < kRows; r += 2) {
+                uint32_t ea[4], eb[4];
+                quantize_row(r, ea);
+                quantize_row(r + 1, eb);
+                if (MODE != EncMode::QuantOnly) row_base += pack_two_rows(stage, ends, r, row_base, ea, eb);
+                __builtin_amdgcn_sched_barrier(0);     // (two rows at a time: more of them in flight spill)
+            }
+            rows_done = kRows;
+        } else if (fast) {
+            const int whole = (int)(g.clen >> 8);
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
-                const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
-                uint32_t rnd[4], e[4], idx[4];
-                philox4x32_10(i0 >> 2, 0u, k, call_id, a.seed_lo, a.seed_hi, rnd);
-                const float rinv_r = GROUPED ? s_rinv[w * 16 + (int)((uint32_t)r >> rshift)] : rinv;
-                e[0] = quantize_one<true, CM>(v[r].x, rinv_r, rnd[0], L, n_sym, idx[0]);
-                e[1] = quantize_one<true, CM>(v[r].y, rinv_r, rnd[1], L, n_sym, idx[1]);
-                e[2] = quantize_one<true, CM>(v[r].z, rinv_r, rnd[2], L, n_sym, idx[2]);
-                e[3] = quantize_one<true, CM>(v[r].w, rinv_r, rnd[3], L, n_sym, idx[3]);
-                if (MODE == EncMode::QuantOnly) {
-                    uint32_t pk = 0;
-                    const float xs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) pk |= (idx[q] | ((__float_as_uint(xs[q]) >> 31) << 7)) << (8 * q);
-                    *reinterpret_cast<uint32_t*>(a.sym_out + kbase + i0) = pk;
-                } else {
-                    row_base += pack_row(stage, sub_mine + 8 * r, ends_run, row_base, e);
+                if (r < whole) {                       // (wave-uniform)
+                    uint32_t e[4];
+                    quantize_row(r, e);
+                    if (MODE != EncMode::QuantOnly) row_base += pack_row(stage, ends, r, row_base, e);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
-        } else {
+            rows_done = whole;
+        }
+        {
 #pragma unroll 1
-            for (int r = 0; r < g.nrows; ++r) {
+            for (int r = rows_done; r < g.nrows; ++r) {
                 const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
                 uint32_t e[4], idx[4], neg[4];
                 if (MODE == EncMode::EncodeOnly) {
@@ -689,7 +773,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                         const float4 t = *reinterpret_cast<const float4*>(s_lev + idx[q] * 16u + neg[q] * a.lev_stride);
                         e[q] = (i0 + (uint32_t)q < g.cend) ? __float_as_uint(t.z) : 0u;
                     }
-                    row_base += pack_row(stage, sub_mine + 8 * r, ends_run, row_base, e);
+                    row_base += pack_row(stage, ends, r, row_base, e);
                 }
             }
         }
