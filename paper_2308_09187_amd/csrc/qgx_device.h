@@ -64,18 +64,22 @@ __device__ __forceinline__ float4 game_operator_row(const GameArgs& G, uint32_t 
 }
 
 // The same four coordinates of worker k's dual vector in call `call_id`: F(z) + sigma N, the noise from the
-// Philox block with key (seed_lo, seed_hi) and counter (i0 / 4, 1, k, call_id).
-__device__ __forceinline__ float4 game_dual_row(const GameArgs& G, uint32_t i0, uint32_t k, uint32_t call_id)
+// Philox block with key (seed_lo, seed_hi) and counter (i0 / 4, 1, k, call_id).  F: game_operator_row(G, i0).
+__device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, uint32_t i0, uint32_t k, uint32_t call_id)
 {
     uint32_t w[4];
     philox4x32_10(i0 >> 2, 1u, k, call_id, G.seed_lo, G.seed_hi, w);
     const float2 n01 = box_muller(w[0], w[1]), n23 = box_muller(w[2], w[3]);
-    float4 v = game_operator_row(G, i0);
-    v.x += G.sigma * n01.x;
-    v.y += G.sigma * n01.y;
-    v.z += G.sigma * n23.x;
-    v.w += G.sigma * n23.y;
-    return v;
+    F.x += G.sigma * n01.x;
+    F.y += G.sigma * n01.y;
+    F.z += G.sigma * n23.x;
+    F.w += G.sigma * n23.y;
+    return F;
+}
+
+__device__ __forceinline__ float4 game_dual_row(const GameArgs& G, uint32_t i0, uint32_t k, uint32_t call_id)
+{
+    return game_noisy_row(G, game_operator_row(G, i0), i0, k, call_id);
 }
 
 // Between two phases in which the lanes of a wave exchange data through LDS without a workgroup barrier.

@@ -20,25 +20,33 @@ hipError_t launch_game_operator(const GameArgs& g, uint32_t d, float* F_out, hip
     return hipGetLastError();
 }
 
-// The worker is the fast index of the grid, so that the K blocks that need the same piece of z, a and b run
-// together and share it through the cache (the pieces would otherwise be streamed from memory K times).  The
-// call number may come from the iteration counter on the device, as in the coding kernel, so that a replayed
-// graph draws fresh noise.
-__global__ __launch_bounds__(256) void k_game_dual_vectors(GameArgs G, uint32_t d, uint32_t K, uint32_t call_id,
+// A workgroup forms a piece of 1024 coordinates of F once and adds every worker's noise to it: z, a and b come
+// from memory once, and what is left is the generator (issue) beside a pure stream of writes.  (A workgroup per
+// worker and piece, the worker as the fast index, shared the operands through the cache only between workgroups on
+// one XCD and read them from memory eight times over: 16 x 2^26 coordinates 1.64 ms, 0.92 now.)  Pieces are few for
+// short vectors: there the workers are cut into runs, a workgroup per piece and run.  The call number may come from
+// the iteration counter on the device, as in the coding kernel, so that a replayed graph draws fresh noise.
+__global__ __launch_bounds__(256) void k_game_dual_vectors(GameArgs G, uint32_t d, uint32_t K, uint32_t runs, uint32_t call_id,
                                                            uint32_t call_mode, const Scalars* sc, float* __restrict__ V)
 {
-    const uint32_t k = blockIdx.x % K, piece = blockIdx.x / K, pieces = gridDim.x / K;
+    const uint32_t run = blockIdx.x % runs, piece = blockIdx.x / runs;
+    const uint32_t each = (K + runs - 1u) / runs, k0 = min(run * each, K), k1 = min(k0 + each, K);
     const uint32_t call = call_mode ? 2u * (uint32_t)(sc->t - 1ull) + (call_mode - 1u) : call_id;
-    float* __restrict__ Vk = V + (size_t)k * d;
-    for (uint32_t i0 = (piece * 256u + threadIdx.x) * 4u; i0 < d; i0 += pieces * 1024u)
-        *reinterpret_cast<float4*>(Vk + i0) = game_dual_row(G, i0, k, call);
+    const uint32_t i0 = (piece * 256u + threadIdx.x) * 4u;
+    if (i0 >= d) return;
+    const float4 F = game_operator_row(G, i0);
+    float* __restrict__ out = V + (size_t)k0 * d + i0;
+    for (uint32_t k = k0; k < k1; ++k, out += d)
+        *reinterpret_cast<float4*>(out) = game_noisy_row(G, F, i0, k, call);
 }
 
 hipError_t launch_game_dual_vectors(const GameArgs& g, uint32_t d, uint32_t K, uint32_t call_id, uint32_t call_mode,
                                     const Scalars* sc, float* V_out, hipStream_t st)
 {
-    const uint32_t pieces = min((d / 4u + 255u) / 256u, 16384u);
-    hipLaunchKernelGGL(k_game_dual_vectors, dim3(pieces * K), dim3(256), 0, st, g, d, K, call_id, call_mode, sc, V_out);
+    const uint32_t pieces = (d / 4u + 255u) / 256u;
+    // enough workgroups to fill the GPU (eight per compute unit) twice over
+    const uint32_t runs = min(K, max(1u, 4096u / pieces));
+    hipLaunchKernelGGL(k_game_dual_vectors, dim3(pieces * runs), dim3(256), 0, st, g, d, K, runs, call_id, call_mode, sc, V_out);
     return hipGetLastError();
 }
 
