@@ -469,8 +469,14 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                 } else if constexpr (PREV) {
                     const float val = symbol_value<false>(w_next, lv, n);
                     acc[at] += val;
-                    const float df = (symbol_value<false>(w_next_b, lv_b, nB) - val) * down;   // (a stray sign on a zero does not show in a difference)
-                    sd32 = fmaf(df, df, sd32);
+                    const float val_p = symbol_value<false>(w_next_b, lv_b, nB);   // (a stray sign on a zero does not show in a difference)
+                    if constexpr (RAG) {                                  // (short halves are few: every term in binary64)
+                        const double df = (double)val_p - (double)val;
+                        sdiff = fma(df, df, sdiff);
+                    } else {
+                        const float df = (val_p - val) * down;
+                        sd32 = fmaf(df, df, sd32);
+                    }
                 } else if constexpr (MODE == DecMode::Half1) {           // no previous streams: the vectors of t count as zero
                     const float val = symbol_value<false>(w_next, lv, n);
                     acc[at] += val;
@@ -525,7 +531,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
 #pragma unroll
                 for (int j = 0; j < 2; ++j) emit(s + j, W[j + 1], lv[j], W_b[j + 1], lv_b[j]);
                 held = lv[2]; held_b = lv_b[2];
-                if constexpr (PREV) {
+                if constexpr (PREV && !RAG) {
                     if ((s / 3) % 2 == 1 || last) { sw += (double)sd32; sd32 = 0.0f; }
                 }
                 // A group's values are done before the next group's look-ups.  The compiler would move them behind
@@ -537,7 +543,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                     if constexpr (MODE == DecMode::Decode && PAIR) asm volatile("" : "+v"(acc_b[at]));
                 }
                 asm volatile("" : "+v"(seen), "+v"(bad));
-                if constexpr (PREV) asm volatile("" : "+v"(sd32), "+v"(sw));
+                if constexpr (PREV && !RAG) asm volatile("" : "+v"(sd32), "+v"(sw));
                 else if constexpr (MODE == DecMode::Half1) asm volatile("" : "+v"(sdiff));
                 if constexpr (RAG) asm volatile("" : "+v"(used));
                 if constexpr (RAG && PAIR) asm volatile("" : "+v"(used_b));
@@ -553,7 +559,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         if constexpr (!kTwo) parse(BoolTag<false>{});
         else if (RAG || have_b) parse(BoolTag<true>{});       // (Decode of a short half, an odd worker out: a second chain for nothing)
         else parse(BoolTag<false>{});
-        if constexpr (PREV) sdiff = fma(sw, up2, sdiff);
+        if constexpr (PREV && !RAG) sdiff = fma(sw, up2, sdiff);
         i += kStep;
     } while (i < k_count);
     };
