@@ -483,18 +483,24 @@ __device__ double stationary_point(const Tree& T, double a, double c)
     const uint32_t q2 = dn1 > p2 ? dn1 : p2;
     const uint32_t lo[5] = {P, p1, p2 >> 4, q2, Q1}, hi[5] = {P1, p2, p2 < q2 ? q2 >> 4 : p2 >> 4, q1, Q};
     const uint32_t lvl[5] = {0u, 1u, 2u, 1u, 0u};
-    double m[5], rho = 0.0;
+    // A lane past its run's end reads the run's first place (inside the tree, whatever the run) and counts as 0: no
+    // branch, so that the loads of all five runs are on their way at once.
+    double m[5], rho = 0.0, term[5];
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-        const uint32_t idx = lo[s] + li;
-        m[s] = 0.0;
-        if (idx < hi[s]) {
-            m[s] = item_mass(T, lvl[s], idx);
-            if (lvl[s] == 0u) rho += m[s] * (c - 0.5 * (bin_edge(idx, nb) + bin_edge(idx + 1u, nb)));
-            else if (lvl[s] == 1u) rho += (c - bin_edge(16u * idx + 16u, nb)) * m[s] + T.r1[idx];
-            else rho += (c - bin_edge(256u * idx + 256u, nb)) * m[s] + T.r2[idx];
-        }
+        const uint32_t last = lvl[s] == 0u ? nb - 1u : lvl[s] == 1u ? nb / 16u - 1u : (nb + 255u) / 256u - 1u;
+        const bool in = lo[s] + li < hi[s];
+        const uint32_t idx = in ? lo[s] + li : min(lo[s], last);
+        const double mass = item_mass(T, lvl[s], idx);
+        double t;
+        if (lvl[s] == 0u) t = mass * (c - 0.5 * (bin_edge(idx, nb) + bin_edge(idx + 1u, nb)));
+        else if (lvl[s] == 1u) t = (c - bin_edge(16u * idx + 16u, nb)) * mass + T.r1[idx];
+        else t = (c - bin_edge(256u * idx + 256u, nb)) * mass + T.r2[idx];
+        m[s] = in ? mass : 0.0;
+        term[s] = in ? t : 0.0;
     }
+#pragma unroll
+    for (int s = 0; s < 5; ++s) rho += term[s];
     // int_a^c (c - u) dF~
     const double right_all = m_a * (c - 0.5 * (a + a_hi)) + row_sum(rho) + m_c * (c - 0.5 * (c_e0 + c));
     if (!(right_all > 0.0)) return a;                                  // no mass between the neighbours
@@ -511,20 +517,23 @@ __device__ double stationary_point(const Tree& T, double a, double c)
         cum[s] += base[s];
         base[s + 1] = base[s] + tot[s];
     }
-    double acc = base[5], prev = 0.0;
-    uint32_t at_lvl = 0u, at_idx = 0u;
-    bool found = false;
+    double acc = base[5];
+    // the first run in which the mass reaches t (looked for from the last one down), then the place in it
+    uint32_t at_lvl = 0u, at_idx = 0u, at_first = kRow;
+    double at_cum = 0.0, at_base = 0.0;
 #pragma unroll
-    for (int s = 0; s < 5; ++s) {
+    for (int s = 4; s >= 0; --s) {
         const uint32_t first = row_first(lo[s] + li < hi[s] && cum[s] >= t);
-        if (!found && first < kRow) {
-            found = true;
-            at_lvl = lvl[s];
-            at_idx = lo[s] + first;
-            const double before = __shfl(cum[s], (int)(first > 0u ? first - 1u : 0u), (int)kRow);
-            prev = first > 0u ? before : base[s];
-        }
+        const bool here = first < kRow;
+        at_first = here ? first : at_first;
+        at_lvl = here ? lvl[s] : at_lvl;
+        at_idx = here ? lo[s] + first : at_idx;
+        at_cum = here ? cum[s] : at_cum;
+        at_base = here ? base[s] : at_base;
     }
+    const bool found = at_first < kRow;
+    const double at_before = __shfl(at_cum, (int)((at_first - 1u) & (kRow - 1u)), (int)kRow);
+    double prev = at_first > 0u ? at_before : at_base;
     double x;
     if (!found) {
         // the mass reaches t in the piece of c's bin, or t is a rounding above all the mass: then the answer
@@ -633,20 +642,30 @@ __global__ __launch_bounds__(256) void k_fit(Tables* tab, const double* __restri
         }
     }
     // strictly increasing with gaps of at least 2^-24: up from l_0 = 0, then down from l_s = 1; one
-    // lane, the table is short
+    // lane, in LDS (in the table itself each step waits for global memory: 0.25 us a level)
+    __shared__ float s_out[kSymMax];
+    __syncthreads();
     if (tid == 0) {
-        float* lv = tab->levels;
-        lv[0] = 0.0f; lv[top] = 1.0f;
+        float below = 0.0f;
+#pragma unroll 4
         for (uint32_t j = 1; j < top; ++j) {
             const float x = (float)s_lev[j];
-            const float floor_ = lv[j - 1] + 0x1p-24f;
-            lv[j] = x < floor_ ? floor_ : x;
+            const float floor_ = below + 0x1p-24f;
+            below = x < floor_ ? floor_ : x;
+            s_out[j] = below;
         }
+        float above = 1.0f;
+#pragma unroll 4
         for (uint32_t j = top - 1u; j >= 1u; --j) {
-            const float ceil_ = lv[j + 1] - 0x1p-24f;
-            if (lv[j] > ceil_) lv[j] = ceil_;
+            const float ceil_ = above - 0x1p-24f, x = s_out[j];
+            above = x > ceil_ ? ceil_ : x;
+            s_out[j] = above;
         }
+        s_out[0] = 0.0f;
+        s_out[top] = 1.0f;
     }
+    __syncthreads();
+    if (tid < n_sym) tab->levels[tid] = s_out[tid];
 }
 
 hipError_t launch_fit(Tables* tab, const double* hist, uint32_t n_bins, uint32_t sweeps, hipStream_t st)
@@ -659,10 +678,9 @@ hipError_t launch_fit(Tables* tab, const double* hist, uint32_t n_bins, uint32_t
 }
 
 // ---- Psi from estimated symbol probabilities (Proposition 1; Appendix J, Huffman coding) ---------------
-// p_j: the mass F~ sends to level j through the random rounding.  Thread j walks the bins under the
-// gap below its level (rising part of its hat function) and then the gap above (falling part); a
-// piece of a bin contributes its mass times the rounding probability at its midpoint, which is exact
-// for the piecewise-uniform density.
+// p_j: the mass F~ sends to level j through the random rounding: the gap below it sends it the rising part of its
+// hat function, the gap above the falling part.  A piece of a bin contributes its mass times the rounding
+// probability at its midpoint, which is exact for the piecewise-uniform density.
 //
 // The code: optimal prefix code for the weights round(p 2^32) (at least 1) with no word longer than
 // max_len, by package-merge (Larmore and Hirschberg 1990); with a slack limit that is Huffman's code.
@@ -671,12 +689,15 @@ hipError_t launch_fit(Tables* tab, const double* hist, uint32_t n_bins, uint32_t
 // cheapest 2 (n - 1) entries of the top list are bought, a package standing for its two entries one
 // level down.  A symbol's length is the number of its coins bought.  Equal weights: coin before
 // package, lower index first.  Words are numbered canonically by (length, index), first bit first.
-__global__ __launch_bounds__(256) void k_fit_code(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
+constexpr uint32_t kFitCodeThreads = 512;
+// pieces of 64 bins: 64 for all the bins, and one more for every gap (its first piece starts anywhere, its last ends anywhere)
+constexpr uint32_t kFitPieces = QGX_MAX_BINS / 64 + 2 * kSymMax;
+__global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
                                                   uint32_t max_len, double* __restrict__ p_out)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
     double* H = reinterpret_cast<double*>(s_raw);                      // [n_bins]
-    __shared__ double s_part[256];
+    __shared__ double s_part[kFitCodeThreads];
     __shared__ double s_lev[kSymMax];
     __shared__ unsigned long long s_w[kSymMax], s_sw[kSymMax], s_cur[2 * kSymMax], s_nxt[2 * kSymMax];
     __shared__ uint8_t s_pkg[kMaxCode][2 * kSymMax];
@@ -685,44 +706,70 @@ __global__ __launch_bounds__(256) void k_fit_code(Tables* tab, const double* __r
 
     const uint32_t tid = threadIdx.x, n = tab->n_sym;
     double part = 0.0;
-    for (uint32_t b = tid; b < n_bins; b += 256u) { const double h = hist[b]; H[b] = h; part += h; }
+    for (uint32_t b = tid; b < n_bins; b += kFitCodeThreads) { const double h = hist[b]; H[b] = h; part += h; }
     s_part[tid] = part;
     if (tid < n) s_lev[tid] = (double)tab->levels[tid];
     __syncthreads();
-    for (uint32_t off = 128; off > 0; off >>= 1) {
+    for (uint32_t off = kFitCodeThreads / 2; off > 0; off >>= 1) {
         if (tid < off) s_part[tid] += s_part[tid + off];
         __syncthreads();
     }
     const double total = s_part[0];
 
-    // p_j: a row of 16 lanes per level, every lane each 16th bin under the two gaps next to the level
-    for (uint32_t j = tid >> 4; j < ((n + 15u) & ~15u); j += 16u) {        // whole rows walk together
-        const uint32_t li = tid & 15u;
-        double acc = 0.0;
-        if (j < n && total > 0.0) {
-            for (int side = 0; side < 2; ++side) {                         // 0: gap below (rising), 1: gap above (falling)
-                if ((side == 0 && j == 0) || (side == 1 && j + 1 >= n)) continue;
-                const double a = side == 0 ? s_lev[j - 1] : s_lev[j], c = side == 0 ? s_lev[j] : s_lev[j + 1];
-                uint32_t b = bin_of((float)a, n_bins);
-                while (b > 0 && bin_edge(b, n_bins) > a) --b;
-                for (b += li; b < n_bins; b += 16u) {
-                    const double e0 = bin_edge(b, n_bins), e1 = bin_edge(b + 1, n_bins);
-                    if (e0 >= c) break;
-                    const double lo = a > e0 ? a : e0, hi = c < e1 ? c : e1;
-                    if (!(hi > lo) || H[b] == 0.0) continue;
-                    const double mass = H[b] * (hi - lo) / (e1 - e0);
-                    const double up = (0.5 * (lo + hi) - a) / (c - a);
-                    acc += side == 0 ? mass * up : mass * (1.0 - up);
-                }
+    // p_j.  The bins under a gap [l_j, l_{j+1}], a piece of 64 of them per wave and turn, a bin per lane: what the
+    // piece sends up to l_{j+1} and down to l_j, summed across the wave; then every level adds up the pieces of the
+    // gap below it and of the gap above, in order.  (A row of lanes per level left the gap above l_0 = 0, which
+    // spans most of the bins, to sixteen lanes: the kernel took 91 us for 33 symbols, now 36.)
+    __shared__ uint32_t s_b0[kSymMax], s_first[kSymMax + 1];
+    __shared__ double s_up[kFitPieces], s_down[kFitPieces];
+    if (tid + 1u < n) {
+        uint32_t b = bin_of((float)s_lev[tid], n_bins);
+        while (b > 0 && bin_edge(b, n_bins) > s_lev[tid]) --b;
+        const uint32_t b_end = bin_of((float)s_lev[tid + 1u], n_bins) + 1u;      // one past the last bin the gap may reach
+        s_b0[tid] = b;
+        s_first[tid] = b_end > b ? (b_end - b + (kWave - 1u)) / kWave : 0u;      // pieces, for now
+    }
+    __syncthreads();
+    uint32_t before = 0;
+    if (tid < n) for (uint32_t k = 0; k < tid; ++k) before += s_first[k];
+    __syncthreads();
+    if (tid < n) s_first[tid] = before;                                          // first piece of gap tid; [n - 1]: all of them
+    __syncthreads();
+    const uint32_t pieces = s_first[n - 1u], lane = tid % kWave;
+    for (uint32_t q = tid / kWave; q < pieces; q += kFitCodeThreads / kWave) {
+        uint32_t lo_j = 0, hi_j = n - 2u;                                        // the last gap that starts at or before piece q
+        while (lo_j < hi_j) {
+            const uint32_t mid = (lo_j + hi_j + 1u) >> 1;
+            if (s_first[mid] <= q) lo_j = mid; else hi_j = mid - 1u;
+        }
+        const double a = s_lev[lo_j], c = s_lev[lo_j + 1u];
+        const uint32_t b = s_b0[lo_j] + (q - s_first[lo_j]) * kWave + lane;
+        double rise = 0.0, fall = 0.0;
+        if (b < n_bins) {
+            const double e0 = bin_edge(b, n_bins), e1 = bin_edge(b + 1, n_bins);
+            const double lo = a > e0 ? a : e0, hi = c < e1 ? c : e1;
+            if (hi > lo) {
+                const double mass = H[b] * (hi - lo) / (e1 - e0);
+                const double up = (0.5 * (lo + hi) - a) / (c - a);
+                rise = mass * up;
+                fall = mass * (1.0 - up);
             }
         }
-        acc = row_sum(acc);
-        if (j < n && li == 0u) {
-            if (total > 0.0) acc /= total;
-            p_out[j] = acc;
-            const double x = floor(acc * 4294967296.0 + 0.5);
-            s_w[j] = x >= 1.0 ? (unsigned long long)x : 1ull;
+        rise = wave_sum(rise);
+        fall = wave_sum(fall);
+        if (lane == 0u) { s_up[q] = rise; s_down[q] = fall; }
+    }
+    __syncthreads();
+    if (tid < n) {
+        double acc = 0.0;
+        if (total > 0.0) {
+            if (tid > 0u) for (uint32_t q = s_first[tid - 1u]; q < s_first[tid]; ++q) acc += s_up[q];
+            if (tid + 1u < n) for (uint32_t q = s_first[tid]; q < s_first[tid + 1u]; ++q) acc += s_down[q];
+            acc /= total;
         }
+        p_out[tid] = acc;
+        const double x = floor(acc * 4294967296.0 + 0.5);
+        s_w[tid] = x >= 1.0 ? (unsigned long long)x : 1ull;
     }
     __syncthreads();
 
@@ -806,7 +853,7 @@ __global__ __launch_bounds__(256) void k_fit_code(Tables* tab, const double* __r
 hipError_t launch_fit_code(Tables* tab, const double* hist, uint32_t n_bins, uint32_t max_len, double* p_out,
                            hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fit_code, dim3(1), dim3(256), (size_t)n_bins * sizeof(double), st, tab, hist, n_bins, max_len, p_out);
+    hipLaunchKernelGGL(k_fit_code, dim3(1), dim3(kFitCodeThreads), (size_t)n_bins * sizeof(double), st, tab, hist, n_bins, max_len, p_out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_build_tables(tab, st);
