@@ -216,7 +216,6 @@ hipError_t launch_state_init(const Layout& lay, Scalars* sc, float* Y, float* an
                              hipStream_t st);
 hipError_t launch_average(uint32_t d, const double* x_sum, const Scalars* sc, float* out, hipStream_t st);
 hipError_t launch_average_reset(uint32_t d, double* x_sum, Scalars* sc, hipStream_t st);
-hipError_t launch_average_count(Scalars* sc, hipStream_t st);
 hipError_t launch_state_set(Scalars* sc, double S, unsigned long long t, uint32_t K, hipStream_t st);
 hipError_t launch_sum_bits(const Layout& lay, const uint16_t* sub_end, Scalars* sc, hipStream_t st);
 hipError_t launch_histogram(const Layout& lay, const float* V, int norm_kind, uint32_t n_bins, double* partial,

@@ -771,7 +771,6 @@ static qgx_status eg_step_with(qgx_ctx* ctx, int half, const qgx_stream* cur, co
         a.out = X_out;
         a.x_sum = ctx->xsum_on ? ctx->d_xsum : nullptr;
         QGX_HIP(ctx, launch_decode(DecMode::Half0, ctx->lay, tab_of(ctx), ctx->d_sc, a, st));
-        if (ctx->xsum_on) QGX_HIP(ctx, launch_average_count(ctx->d_sc, st));
         return QGX_OK;
     }
     fill_decode_args(ctx, a, cur, prev);
