@@ -693,7 +693,7 @@ constexpr uint32_t kFitCodeThreads = 512;
 // pieces of 64 bins: 64 for all the bins, and one more for every gap (its first piece starts anywhere, its last ends anywhere)
 constexpr uint32_t kFitPieces = QGX_MAX_BINS / 64 + 2 * kSymMax;
 __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
-                                                  uint32_t max_len, double* __restrict__ p_out)
+                                                  uint32_t max_len, FitCodeResult* __restrict__ result)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
     double* H = reinterpret_cast<double*>(s_raw);                      // [n_bins]
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
             if (tid + 1u < n) for (uint32_t q = s_first[tid]; q < s_first[tid + 1u]; ++q) acc += s_down[q];
             acc /= total;
         }
-        p_out[tid] = acc;
+        result->p[tid] = acc;
         const double x = floor(acc * 4294967296.0 + 0.5);
         s_w[tid] = x >= 1.0 ? (unsigned long long)x : 1ull;
     }
@@ -846,14 +846,16 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
             const uint32_t lk = s_len[k];
             if (lk < L || (lk == L && k < tid)) code += 1u << (L - lk);
         }
-        tab->code[tid] = (__brev(code) >> (32u - L)) | (L << 16);
+        const uint32_t word = (__brev(code) >> (32u - L)) | (L << 16);
+        tab->code[tid] = word;
+        result->code[tid] = word;
     }
 }
 
-hipError_t launch_fit_code(Tables* tab, const double* hist, uint32_t n_bins, uint32_t max_len, double* p_out,
+hipError_t launch_fit_code(Tables* tab, const double* hist, uint32_t n_bins, uint32_t max_len, FitCodeResult* result,
                            hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fit_code, dim3(1), dim3(kFitCodeThreads), (size_t)n_bins * sizeof(double), st, tab, hist, n_bins, max_len, p_out);
+    hipLaunchKernelGGL(k_fit_code, dim3(1), dim3(kFitCodeThreads), (size_t)n_bins * sizeof(double), st, tab, hist, n_bins, max_len, result);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_build_tables(tab, st);

@@ -72,7 +72,7 @@ struct qgx_ctx {
     double* d_static_scratch = nullptr;   // this device's copy of the file-scope scratch array (not owned)
     double* d_hpartial = nullptr;
     double* d_hist = nullptr;
-    double* d_prob = nullptr;       // [kSymMax] symbol probabilities of the last qgx_fit_code
+    FitCodeResult* d_prob = nullptr;   // what the last qgx_fit_code left for the host
     double* d_norm = nullptr;       // [2 kNormBlocks + 2] partial sums and results of qgx_norm2 and qgx_game_gap
     double* d_metrics = nullptr;    // [K][3][kMetricBlocks] partial sums, then [K][3] results of qgx_quantization_metrics
     double* d_xsum = nullptr;       // [d] sum of the X_{t+1/2} since qgx_average_reset (allocated there)
@@ -310,7 +310,7 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     ok = ok && hipMalloc(&c->d_spartial, (size_t)c->lay.n_tasks * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hpartial, (size_t)c->h_groups * QGX_MAX_BINS * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hist, QGX_MAX_BINS * sizeof(double)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_prob, kSymMax * sizeof(double)) == hipSuccess;
+    ok = ok && hipMalloc(&c->d_prob, sizeof(FitCodeResult)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_norm, (2 * kNormBlocks + 2) * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_metrics, (size_t)cfg->K * 3 * (kMetricBlocks + 1) * sizeof(double)) == hipSuccess;
     ok = ok && hipMemcpy(c->d_layout, flat.data(), n_lay * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess;
@@ -724,10 +724,11 @@ qgx_status qgx_fit_code(qgx_ctx* ctx, double* p_host, uint8_t* code_len_host, ui
     if (need > QGX_FIT_CODE_BITS) return fail(ctx, QGX_ERR_ARG, "too many symbols for the longest code word");
     hipStream_t st = (hipStream_t)stream;
     QGX_HIP(ctx, launch_fit_code(tab_of(ctx), ctx->d_hist, ctx->hist_bins, QGX_FIT_CODE_BITS, ctx->d_prob, st));
-    uint32_t packed[kSymMax];
-    QGX_HIP(ctx, hipMemcpyAsync(packed, tab_of(ctx)->code, sizeof(packed), hipMemcpyDeviceToHost, st));
-    if (p_host) QGX_HIP_DRAIN(ctx, st, hipMemcpyAsync(p_host, ctx->d_prob, T(ctx).n_sym * sizeof(double), hipMemcpyDeviceToHost, st));
+    FitCodeResult host;                                   // probabilities and code words in one copy
+    QGX_HIP(ctx, hipMemcpyAsync(&host, ctx->d_prob, sizeof(host), hipMemcpyDeviceToHost, st));
     QGX_HIP(ctx, hipStreamSynchronize(st));
+    const uint32_t* packed = host.code;
+    if (p_host) std::memcpy(p_host, host.p, T(ctx).n_sym * sizeof(double));
     T(ctx).max_code_len = 0;
     for (uint32_t j = 0; j < T(ctx).n_sym; ++j) {
         const uint32_t len = packed[j] >> 16;

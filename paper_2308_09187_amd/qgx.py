@@ -120,6 +120,7 @@ class Context:
             nseg = len(segment_len)
         cfg = _Config(self.d, self.K, self.bucket, nseg, seg, norm, code, seed)
         self._h = C.c_void_p()
+        self._table, self._n_sym = 0, {}          # the table selected; symbols of each table that was set
         with torch.cuda.device(device):
             st = self.lib.qgx_create(C.byref(self._h), C.byref(cfg))
         if st != OK:
@@ -165,6 +166,7 @@ class Context:
         lv = np.ascontiguousarray(levels, dtype=np.float32)
         self._check(self.lib.qgx_set_levels(self._h, lv.ctypes.data_as(C.c_void_p), C.c_uint32(len(lv)),
                                             _stream_handle(stream)))
+        self._n_sym[self._table] = len(lv)
 
     def get_levels(self, stream=None):
         lv = np.zeros(MAX_SYM, np.float32)
@@ -265,11 +267,11 @@ class Context:
 
     def fit_code(self, stream=None):
         """Returns (p, code_len, code_bits) of the code the context now uses."""
-        n = len(self.get_levels(stream))
-        p = np.zeros(n, np.float64); cl = np.zeros(n, np.uint8); cb = np.zeros(n, np.uint32)
+        n = self._n_sym.get(self._table) or len(self.get_levels(stream))
+        p = np.zeros(MAX_SYM, np.float64); cl = np.zeros(MAX_SYM, np.uint8); cb = np.zeros(MAX_SYM, np.uint32)
         self._check(self.lib.qgx_fit_code(self._h, p.ctypes.data_as(C.c_void_p), cl.ctypes.data_as(C.c_void_p),
                                           cb.ctypes.data_as(C.c_void_p), _stream_handle(stream)))
-        return p, cl, cb
+        return p[:n].copy(), cl[:n].copy(), cb[:n].copy()
 
     def state_init(self, X1=None, stream=None):
         self._check(self.lib.qgx_state_init(self._h, _ptr(X1), _stream_handle(stream)))
@@ -286,6 +288,7 @@ class Context:
     def select_table(self, table, prev_table=None):
         self._check(self.lib.qgx_select_table(self._h, C.c_uint32(table),
                                               C.c_uint32(table if prev_table is None else prev_table)))
+        self._table = table
 
     def average_reset(self, on=True, stream=None):
         self._check(self.lib.qgx_average_reset(self._h, C.c_int(1 if on else 0), _stream_handle(stream)))
