@@ -415,7 +415,8 @@ __global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_p
 void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
 {
     extern __shared__ __align__(16) unsigned char s_all[];
-    const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = (int)threadIdx.x, lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(wave_id());    // (scalar, and all of the chunk's geometry with it)
     const int nwaves = (int)(blockDim.x >> 6);
     const uint32_t n_sym = tab->n_sym;
     // The worker and, without tickets, the unit of work are fixed by the block.  Workgroups go round the eight XCDs, each
