@@ -26,6 +26,7 @@
 // without coordinates is no task at all.  (A workgroup per such position, its workers spread over the waves, took
 // 0.168 ms for the second half-step of 5 x 3 M coordinates in buckets of 6000, this takes 0.035.)
 #include "qgx_device.h"
+#include "qgx_plan.h"
 
 namespace qgx {
 
@@ -99,22 +100,13 @@ struct HalfRef {
 
 __device__ __forceinline__ HalfRef half_ref(const uint32_t* payload, uint64_t cap, const Extent& x, uint32_t max_words, Scalars* sc)
 {
-    HalfRef r;
-    r.start = x.start;
-    r.w0 = (x.start >> 5) & ~3u;
-    r.words = ((((x.end + 31u) >> 5) + 3u) & ~3u) - r.w0;      // (an end before the start: beyond max_words, or an empty run)
-    uint64_t at = (uint64_t)x.off + r.w0;
-    if (r.words > max_words || (x.off & 3u) || at + r.words > cap) {
-        if (lane_id() == 0) raise_error(sc, QGX_EBIT_STREAM);
-        r.words = 0;                                      // nothing is staged: what was staged before is parsed
-        at = 0;
-    }
-    r.src = reinterpret_cast<const uint4*>(payload + at);
-    return r;
+    const HalfWords h = half_words(x.off, x.start, x.end, max_words, cap);
+    if (!h.ok && lane_id() == 0) raise_error(sc, QGX_EBIT_STREAM);     // (nothing is staged: what was staged before is parsed)
+    return HalfRef{reinterpret_cast<const uint4*>(payload + h.at), h.w0, h.words, x.start};
 }
 
 // Lanes past the half's words read its last piece once more (no branch per load); nobody stages it.  With no words
-// at all that is the first piece of the worker's payload, which holds at least one.
+// (half_words refused the extent) that is the first piece of the worker's payload, which holds at least one.
 __device__ __forceinline__ void prefetch_half(const HalfRef& hr, uint4 (&pre)[kPre], uint32_t lane)
 {
     const uint32_t last = max(hr.words >> 2, 1u) - 1u;

@@ -48,3 +48,31 @@ def test_short_halves(qgx, monkeypatch, end, n_levels, waves):
     assert abs(ctx.scalars()["S"] - st.S) <= REL * st.S
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+def test_tables_that_point_at_the_payloads_end(qgx):
+    """Extents without words at the very end of the payload, and ends before their starts: refused by every decoder, for
+    both streams of the second half-step, and the context goes on."""
+    d, K = 4096 + 700, 2
+    levels = synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, K, 4096, oracle.NORM_L2, levels, seed=3)
+    ctx.state_init(None)
+    good, bad = ctx.new_stream(), ctx.new_stream()
+    X = torch.empty(d, device="cuda")
+    for s in (good, bad):
+        ctx.quantize_encode(dev(synth.student_t3(K, d, seed=8)), 0, s)
+    Vhat = ctx.decode(good).cpu().numpy()
+    cap = bad.payload.shape[1]
+    ends, offs = bad.sub_end.clone(), bad.chunk_off.clone()
+    for at, end in ((cap, 0), (cap - 4, 128), (cap - 4, 100)):
+        bad.sub_end.fill_(end)                               # every run ends where it starts
+        bad.chunk_off.fill_(at)
+        for call in (lambda: ctx.decode(bad), lambda: ctx.decode_average(bad), lambda: ctx.eg_step(0, bad, None, X),
+                     lambda: ctx.eg_step(1, bad, good, X), lambda: ctx.eg_step(1, good, bad, X), lambda: ctx.eg_step(1, bad, None, X)):
+            call()
+            assert ctx.poll_error() & qgx.EBIT_STREAM, (at, end)
+    bad.sub_end.copy_(ends)
+    bad.chunk_off.copy_(offs)
+    np.testing.assert_array_equal(ctx.decode(bad).cpu().numpy(), Vhat)
+    assert ctx.poll_error() == 0
+    ctx.close()
