@@ -339,6 +339,9 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     const uint32_t cend = clo + clen;
     const uint32_t base = clo + (uint32_t)kHalfCoords * half;                    // first coordinate of the task
     const bool full = base + (uint32_t)kHalfCoords <= cend;                      // (wave-uniform)
+    // The loop with a look-ahead and, with two streams, squared differences in binary32 groups; the first half of a
+    // short position has all its coordinates, but the sum of a short position is formed in binary64 throughout.
+    const bool straight = PREV ? clen == (uint32_t)kChunk : full;
 
     StreamAt sa = stream_at(a.chunk_off, a.sub_end, a.norms, a.payload, a.cap_words, k_first, c, lay), sb = sa;
     if constexpr (PREV) sb = stream_at(a.chunk_off_p, a.sub_end_p, a.norms_p, a.payload_p, a.cap_words_p, k_first, c, lay);
@@ -378,7 +381,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     uint32_t fresh = (uint32_t)lane;
     xa = load_extent(sa, half);
     if constexpr (kTwo) xb = load_extent(sb, half);
-    if (kTwo && full) fetch(0u, fresh);
+    if (kTwo && straight) fetch(0u, fresh);
     load_tables<WIDE>(s_tab, tab, tid, (int)blockDim.x);
     if constexpr (TWO) load_tables<WIDE>(s_tab2, a.tab_p, tid, (int)blockDim.x);
     // words past a half chunk's end are read by the window of its last symbols: keep them defined
@@ -407,9 +410,10 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     uint32_t seen = 0xFFFFFFFFu;
     uint32_t bad = 0;                                    // not 0: malformed
 
-    // RAG: a short half.  The symbols past a lane's count are parsed like the others (from a cursor below p_limit
-    // 32 of them stay inside the buffer, and any window finds a table entry) and count for nothing.  It has a loop
-    // of its own, without a look-ahead, so that what it holds on top costs the full halves no registers.
+    // RAG: a short half, or with two streams a half of a short position.  The symbols past a lane's count are parsed
+    // like the others (from a cursor below p_limit 32 of them stay inside the buffer, and any window finds a table
+    // entry) and count for nothing.  It has a loop of its own, without a look-ahead, so that what it holds on top costs
+    // the full halves no registers.
     auto all_workers = [&](auto rag_tag) __attribute__((always_inline)) {
     constexpr bool RAG = decltype(rag_tag)::value;
     uint32_t i = 0;
@@ -462,7 +466,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                     const float val = symbol_value<false>(w_next, lv, n);
                     acc[at] += val;
                     const float val_p = symbol_value<false>(w_next_b, lv_b, nB);   // (a stray sign on a zero does not show in a difference)
-                    if constexpr (RAG) {                                  // (short halves are few: every term in binary64)
+                    if constexpr (RAG) {                                  // (short positions are few: every term in binary64)
                         const double df = (double)val_p - (double)val;
                         sdiff = fma(df, df, sdiff);
                     } else {
@@ -555,7 +559,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         i += kStep;
     } while (i < k_count);
     };
-    if (full) all_workers(BoolTag<false>{});
+    if (straight) all_workers(BoolTag<false>{});
     else all_workers(BoolTag<true>{});
     // a reject entry leaves a zero among bits 15..31 of its group's negative bit count
     bad |= (seen >> 15) ^ 0x1FFFFu;

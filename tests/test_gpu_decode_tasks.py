@@ -1,6 +1,8 @@
 """The decoder's tasks at their edges: half chunk positions of 1 .. 2047 coordinates beside full ones, halves whose
 words do not fit the pieces that travel ahead, odd numbers of workers, vectors at odd addresses.  Decoded vectors bit
 for bit against the oracle (one binary32 product each); mean, iterates and S within the bounds the parity tests derive."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -74,5 +76,24 @@ def test_tables_that_point_at_the_payloads_end(qgx):
     bad.sub_end.copy_(ends)
     bad.chunk_off.copy_(offs)
     np.testing.assert_array_equal(ctx.decode(bad).cpu().numpy(), Vhat)
+    assert ctx.poll_error() == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("d,bucket", [(9000, 3000), (2 * 4095, 4092), (2048, 4096), (3072, 1024), (2500 + 700, 2500)])
+def test_step_size_sum_of_short_positions(qgx, d, bucket):
+    """S of layouts without a whole position: every squared difference formed and added in binary64, the first half of a
+    position that is more than half full included.  A lane adds 32 K terms one after the other, what follows is fewer
+    than 128 additions, none of a negative number: a relative error of at most (32 K + 128) 2^-53."""
+    K, levels = 3, synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, K, bucket, oracle.NORM_L2, levels, seed=21)
+    ctx.state_init(None)
+    A, B = ctx.new_stream(slotted=True), ctx.new_stream(slotted=True)
+    ctx.quantize_encode(dev(synth.student_t3(K, d, seed=5)), 0, A)
+    ctx.quantize_encode(dev(synth.student_t3(K, d, seed=6)), 1, B)
+    diff = ctx.decode(A).double() - ctx.decode(B).double()
+    S = math.fsum((diff * diff).flatten().cpu().tolist())
+    ctx.eg_step(1, B, A, None)
+    assert abs(ctx.scalars()["S"] - S) <= (32 * K + 128) * 2.0 ** -53 * S
     assert ctx.poll_error() == 0
     ctx.close()
