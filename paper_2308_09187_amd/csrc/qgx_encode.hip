@@ -30,6 +30,7 @@
 // buckets come from that worker's atomic ticket, so every bucket a waiting workgroup depends on is
 // held by a running workgroup that needs nothing from later tickets; the wait is bounded all the same.
 #include "qgx_device.h"
+#include "qgx_plan.h"
 
 namespace qgx {
 
@@ -103,7 +104,8 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
 // the launch's epoch, so a reader knows a word is this launch's without any ordering between
 // stores.  The wait cannot deadlock: parts take their (bucket, part) from the worker's ticket
 // counter, so at most the bucket of the newest tickets is incomplete, and every other waiting
-// workgroup has all its partners running; the wait is bounded all the same.
+// workgroup has all its partners running; for the partners of the newest there is always a place on the
+// XCD whose queue they are in (block_by_worker).  The wait is bounded all the same.
 // Called by one whole wave; returns the parts' values combined in part order in every lane.
 __device__ double exchange_parts(unsigned long long* words /* [parts][2 phases][2] of this bucket */, uint32_t parts,
                                  uint32_t part, uint32_t phase, double mine, bool take_max, uint32_t epoch, Scalars* sc)
@@ -307,7 +309,7 @@ __device__ __forceinline__ void load_chunk(float4 (&v)[kRows], const float* __re
         for (int r = 0; r < kRows; ++r)
             v[r] = nt_load4_any(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
     } else {
-const int whole = (int)(g.clen >> 8);                    // rows before a short last one (all wave-uniform)
+        const int whole = (int)(g.clen >> 8);                    // rows before a short last one (all wave-uniform)
         const uint32_t i0 = g.clo + (uint32_t)whole * 256u + (uint32_t)lane * 4u;
         float4 tail = make_float4(0.f, 0.f, 0.f, 0.f);
         if (i0 < g.cend) tail.x = Vk[i0];
@@ -410,8 +412,10 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
 // CM: cell_mant of the level table, so that the rounding pass has the cell size as a constant.
 // Waves per SIMD: five where V is read (four: 177 us instead of 163 at 8 x 2^24); four where it is formed, whose
 // second generator and transcendentals spill at five (16 x 2^26 coordinates: 2.07 ms instead of 2.30).
+template <EncMode MODE> constexpr bool kWaits = MODE != EncMode::EncodeOnly;     // for partners: it needs the bucket's norm
+template <EncMode MODE> constexpr int kSimdWaves = MODE == EncMode::Generate ? 4 : 5;
 template <EncMode MODE, bool GROUPED, int CM>
-__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(MODE == EncMode::Generate ? 4 : 5)))
+__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(kSimdWaves<MODE>)))
 void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
 {
     extern __shared__ __align__(16) unsigned char s_all[];
@@ -419,21 +423,15 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const int w = __builtin_amdgcn_readfirstlane(wave_id());    // (scalar, and all of the chunk's geometry with it)
     const int nwaves = (int)(blockDim.x >> 6);
     const uint32_t n_sym = tab->n_sym;
-    // The worker and, without tickets, the unit of work are fixed by the block.  Workgroups go round the eight XCDs, each
-    // with a second-level cache of its own: where the workers read the same operands (Generate), the K workgroups of
-    // a unit are put on one XCD, one after the other, so that the operands come from memory once and not from
-    // every XCD.
-    uint32_t k, own_unit;
-    if constexpr (MODE == EncMode::Generate) {
-        constexpr uint32_t kXcds = 8u;
-        const uint32_t even = (gridDim.x / lay.K) / kXcds * kXcds;            // units in whole rounds of the XCDs
-        const uint32_t i = blockIdx.x, j = i / kXcds;
-        const bool round = i < even * lay.K;
-        k = round ? j % lay.K : (i - even * lay.K) % lay.K;
-        own_unit = round ? j / lay.K * kXcds + i % kXcds : even + (i - even * lay.K) / lay.K;
-    } else {
-        k = (uint32_t)blockIdx.x % lay.K;
-        own_unit = (uint32_t)blockIdx.x / lay.K;
+    // The worker and, without tickets, the unit of work are fixed by the block.
+    uint32_t k = blockIdx.x % lay.K, own_unit = blockIdx.x / lay.K;
+    if (MODE == EncMode::Generate && a.by_unit) {
+        const BlockWork own = block_by_unit(blockIdx.x, lay.K, a.units);
+        k = own.k; own_unit = own.unit;
+    } else if (kWaits<MODE> && a.group_bits != 0u) {
+        const BlockWork own = block_by_worker(blockIdx.x, lay.K, a.units, a.group_bits);
+        if (!own.there) return;
+        k = own.k; own_unit = own.unit;
     }
 
     // LDS plan: [cell][lev + / lev -][reduction scratch][one staging buffer per wave]
@@ -844,8 +842,16 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     if (e != hipSuccess) return e;
     // one workgroup per bucket, per part of a bucket, or (shared chunks) per four chunks; in compact
     // placement and with split buckets each takes one ticket of its worker (the kernel's per_launch)
-    const uint32_t units = GROUPED ? (lay.NC + 3u) / 4u : lay.NB * a.parts;
-    hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM>), dim3(lay.K * units), dim3(waves * kWave), lds, st, lay, tab, sc, a);
+    EncodeArgs b = a;
+    b.units = GROUPED ? (lay.NC + 3u) / 4u : lay.NB * a.parts;
+    // Where the workgroups of a bucket wait for each other, no XCD may have more workers than leave it a place to
+    // start one in (see block_by_worker).  The game's form puts the K workgroups of a unit on one XCD, which all K workers
+    // then share, as long as that holds for K (42 workers with four workgroups to a compute unit, 31 with three).
+    const uint32_t held = held_per_xcd(kSimdWaves<MODE>, lds, a.n_cu);
+    b.group_bits = kWaits<MODE> && a.parts > 1u ? worker_groups_log2(lay.K, a.parts, held) : 0u;
+    b.by_unit = MODE == EncMode::Generate && b.group_bits == 0u ? 1u : 0u;
+    const uint32_t grid = grid_by_worker(lay.K, b.units, b.group_bits);
+    hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM>), dim3(grid), dim3(waves * kWave), lds, st, lay, tab, sc, b);
     return hipGetLastError();
 }
 

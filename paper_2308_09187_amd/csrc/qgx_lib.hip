@@ -297,8 +297,8 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     ok = ok && hipMalloc(&c->d_Y, cfg->d * sizeof(float)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_anchor, cfg->d * sizeof(float)) == hipSuccess;
     // A bucket of more than four chunks is shared by workgroups of four waves.  Per worker, the parts
-    // of one bucket (the newest tickets) can be waiting for partners that have not started yet: up
-    // to 3 K workgroups, which must stay below what the GPU holds at once, so only for K <= 64.
+    // of one bucket (the newest tickets) can be waiting for partners that have not started yet: up to
+    // three, which must leave a place free on every XCD (see block_by_worker), so only for K <= 64.
     c->parts = (c->lay.waves_per_bucket > 4u && cfg->K <= 64u) ? (c->lay.waves_per_bucket + 3u) / 4u : 1u;
     const size_t n_units = (size_t)cfg->K * NB * c->parts;
     ok = ok && hipMalloc(&c->d_scan, n_units * sizeof(unsigned long long)) == hipSuccess;
@@ -495,6 +495,7 @@ static qgx_status run_encode(qgx_ctx* ctx, EncMode mode, const float* V, uint32_
     if (game) a.game = *game;
     a.parts = ctx->parts;
     a.xch = ctx->d_xch;
+    a.n_cu = ctx->n_simd / 4u;
     a.tickets = ctx->d_tickets;
     hipError_t le = launch_encode(mode, ctx->lay, tab_of(ctx), ctx->d_sc, a, (hipStream_t)stream);
     if (le != hipSuccess) return fail(ctx, QGX_ERR_HIP, "encode launch: %s", hipGetErrorString(le));

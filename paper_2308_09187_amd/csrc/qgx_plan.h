@@ -1,6 +1,7 @@
 // Index arithmetic that memory safety rests on, free of HIP so that a host compiler can build it and
 // the tests can go through it exhaustively.
 #pragma once
+#include <cstddef>
 #include <cstdint>
 
 #ifdef __HIPCC__
@@ -29,6 +30,60 @@ QGX_PLAN HalfWords half_words(uint32_t off, uint32_t start, uint32_t end, uint32
     h.ok = h.words - 1u < max_words && (off & 3u) == 0u && h.at + h.words <= cap;
     if (!h.ok) { h.at = 0; h.words = 0; }
     return h;
+}
+
+// ---- which worker's which unit of work a workgroup of the coding kernel takes ----------------------
+// Workgroups are dealt to the eight XCDs by their number, each XCD starts its own in order, and no other XCD takes over
+// what is queued behind a busy one.  Where workgroups share a bucket (`parts` of them) one that has started waits for its
+// partners.  They take (bucket, part) from their worker's ticket counter, so of each worker only the newest bucket is
+// incomplete and at most parts - 1 workgroups wait.  An XCD that is behind (the others have run out of work) can thus
+// hold (parts - 1) x the workers that have workgroups on it, all waiting for partners in its own queue: a free place
+// must always be left, so the workers on an XCD are kept below what `held`, the workgroups an XCD holds at once, allows.
+constexpr uint32_t kXcds = 8;
+
+struct BlockWork { uint32_t k, unit; bool there; };
+
+// The K workgroups of a unit on one XCD, one after the other: for operands that the workers share.  All workers have
+// workgroups on every XCD.  Grid: K * units.
+QGX_PLAN BlockWork block_by_unit(uint32_t i, uint32_t K, uint32_t units)
+{
+    const uint32_t even = units / kXcds * kXcds;              // units in whole rounds of the XCDs
+    const uint32_t j = i / kXcds, rest = i - even * K;
+    if (i < even * K) return BlockWork{j % K, j / K * kXcds + i % kXcds, true};
+    return BlockWork{rest % K, even + rest / K, true};
+}
+
+// The workers in 2^lg groups (lg: 0 .. 3), group g with the XCDs x of x mod 2^lg = g to itself, units in order.  lg = 0
+// deals the workers round; for a K that is a multiple of 8 every lg gives that same map.  Not there: a workgroup beyond the
+// work of its group.  Grid: grid_by_worker.
+QGX_PLAN BlockWork block_by_worker(uint32_t i, uint32_t K, uint32_t units, uint32_t lg)
+{
+    const uint32_t mask = (1u << lg) - 1u, x = i % kXcds, n = (K + mask) >> lg;      // n: places of workers in a group
+    const uint32_t s = i / kXcds * (kXcds >> lg) + (x >> lg), unit = s / n;           // s: the block's place in its group's order
+    const uint32_t k = (x & mask) + ((s - unit * n) << lg);
+    return BlockWork{k, unit, k < K && unit < units};
+}
+
+inline uint32_t grid_by_worker(uint32_t K, uint32_t units, uint32_t lg)
+{
+    if (lg == 0u) return K * units;
+    const uint32_t mask = (1u << lg) - 1u, per_round = kXcds >> lg;
+    return (((K + mask) >> lg) * units + per_round - 1u) / per_round * kXcds;
+}
+
+// Workgroups of four waves that an XCD holds at once: a wave of each on every SIMD, and their LDS (in steps of 2 KiB).
+inline uint32_t held_per_xcd(uint32_t waves_per_simd, size_t lds_bytes, uint32_t n_cu)
+{
+    const size_t fit = 160u * 1024u / ((lds_bytes + 2047u) / 2048u * 2048u);
+    return (uint32_t)(fit < waves_per_simd ? fit : waves_per_simd) * (n_cu / kXcds);
+}
+
+// The fewest groups (as lg) that leave an XCD a free place; 3 if none do.
+inline uint32_t worker_groups_log2(uint32_t K, uint32_t parts, uint32_t held)
+{
+    uint32_t lg = 0;
+    while (lg < 3u && (parts - 1u) * ((K + (1u << lg) - 1u) >> lg) >= held) ++lg;
+    return lg;
 }
 
 }  // namespace qgx
