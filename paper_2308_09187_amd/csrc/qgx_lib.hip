@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "qgx_internal.h"
+#include "qgx_plan.h"
 
 using namespace qgx;
 
@@ -639,27 +640,8 @@ static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream
     a.stage_stride = (a.stage_words + a.stage_words / 16 + 20 + 3) / 4 * 4;   // padded layout, four zero words below the end, zero words above the first
     if (a.stage_stride < 576u) a.stage_stride = 576u;     // a buffer also turns the output (16 rows of 36 floats)
     a.wide = (T(ctx).wide && (!prev || ctx->ts[ctx->sel_prev].wide)) ? 1u : 0u;   // one kernel variant reads both streams
-    // Waves per task.  Tasks against the wave slots (8 per SIMD with one stream, 4 with two), in rounds of waves: a
-    // launch takes about as long as its whole rounds and, for a last one that fills a part x of the slots,
-    // max(0.36, 0.15 + 0.85 x) of a round (few waves wait for their look-ups, many for each other).  A round is
-    // as long as the workers a wave takes.  With f waves to a task, a run of the workers each, the rounds are
-    // 1/f as long, and the joining costs about 0.3 (f = 2) or 0.62 (f = 4) of a worker's time.  Measured, first
-    // half-step with 1 / 2 / 4 waves: 512 tasks of 8 workers 28.7 / 19.6 / 16.5 us, 2048 of 8 31.7 / 26.9 / 30.8,
-    // 4816 of 8 57 / 70 / 71; second: 2048 of 8 55.5 / 52 / 59, 4816 of 8 140 / 130 / 136, 1500 of 5 52.5 / 45 / 50.
-    a.ksplit = 1u;
-    {
-        const double K = (double)ctx->lay.K, r = (double)ctx->lay.n_tasks / ((double)ctx->n_simd * (prev ? 4.0 : 8.0));
-        auto rounds = [](double x) {
-            const double whole = std::floor(x), part = x - whole;
-            return whole + (part > 0.0 ? std::fmax(0.36, 0.15 + 0.85 * part) : 0.0);
-        };
-        double best = rounds(r) * K;
-        for (uint32_t f = 2; f <= 4u && f <= ctx->lay.K; f *= 2) {
-            const double cost = rounds(f * r) * K / f + (f == 2 ? 0.30 : 0.62);
-            if (cost < best) { best = cost; a.ksplit = f; }
-        }
-        if (ctx->ksplit_forced >= 0 && (uint32_t)ctx->ksplit_forced <= ctx->lay.K) a.ksplit = (uint32_t)ctx->ksplit_forced;
-    }
+    a.ksplit = waves_per_task(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u);
+    if (ctx->ksplit_forced >= 0 && (uint32_t)ctx->ksplit_forced <= ctx->lay.K) a.ksplit = (uint32_t)ctx->ksplit_forced;
     a.n_cu = ctx->n_simd / 4u;
     a.norms = cur->norms; a.chunk_off = cur->chunk_off; a.sub_end = cur->sub_end; a.payload = cur->payload;
     a.cap_words = cur->payload_words_per_worker;

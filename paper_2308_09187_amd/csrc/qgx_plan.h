@@ -1,6 +1,7 @@
 // Index arithmetic that memory safety rests on, free of HIP so that a host compiler can build it and
 // the tests can go through it exhaustively.
 #pragma once
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -84,6 +85,31 @@ inline uint32_t worker_groups_log2(uint32_t K, uint32_t parts, uint32_t held)
     uint32_t lg = 0;
     while (lg < 3u && (parts - 1u) * ((K + (1u << lg) - 1u) >> lg) >= held) ++lg;
     return lg;
+}
+
+// ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
+// x = f * tasks against the wave slots (8 per SIMD with one stream, 4 with two).  A launch is bound by latency,
+// ceil(K / f) workers one after the other (a worker's chain of look-ups takes 2.2 us with one stream, 3.3 with two, however
+// few waves there are), or by throughput, x K / f of the time that full slots take for a worker (7.7 and 7.1 us, the unit
+// below); where a last round fills a part of the slots, that part counts max(0.36, 0.15 + 0.85 x).  Joining costs more the
+// more waves do it.  Measured with 1 / 2 / 4 waves, us: first half-step, 512 tasks of 8 workers 23.3 / 15.1 / 12.6, 1024 of 5
+// 17.8 / 14.8 / 16.3, 2048 of 8 30.2 / 26.2 / 30.7, of 12 39.7 / 33.1 / 37.6, 4096 of 8 40.8 / 45.7 / 53.2; second, 512 of 8
+// 37.3 / 26.0 / 22.0, 2048 of 8 51.6 / 51.0 / 57.3, 4096 of 8 81.8 / 87.9 / 97.1, 4816 of 8 113 / 105 / 112.
+inline uint32_t waves_per_task(uint32_t n_tasks, uint32_t workers, uint32_t n_simd, uint32_t streams)
+{
+    const bool two = streams == 2u;
+    const double K = workers, tasks = n_tasks / (n_simd * (two ? 4.0 : 8.0));
+    auto cost = [&](uint32_t f) {
+        const double x = f * tasks, whole = std::floor(x), part = x - whole;
+        const double rounds = whole > 0.0 && part > 0.0 ? whole + std::fmax(0.36, 0.15 + 0.85 * part) : x;
+        const double latency = (two ? 0.47 : 0.28) * std::ceil(K / f), throughput = rounds * K / f;
+        const double join = f == 1u ? 0.0 : f == 2u ? (two ? 0.28 : 0.10) + 0.28 * x : two ? 0.28 + 0.42 * x : 0.22 + 0.58 * x;
+        return std::sqrt(std::hypot(latency * latency, throughput * throughput)) + join;      // (the larger of the two, rounded off)
+    };
+    uint32_t best = 1;
+    for (uint32_t f = 2; f <= 4u && f <= workers; f *= 2)
+        if (cost(f) < cost(best)) best = f;
+    return best;
 }
 
 }  // namespace qgx

@@ -27,6 +27,7 @@ extern "C" void blocks(uint32_t grid, uint32_t K, uint32_t units, int lg, int64_
 }
 extern "C" uint32_t grid_by_worker(uint32_t K, uint32_t units, uint32_t lg) { return qgx::grid_by_worker(K, units, lg); }
 extern "C" uint32_t worker_groups_log2(uint32_t K, uint32_t parts, uint32_t held) { return qgx::worker_groups_log2(K, parts, held); }
+extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::waves_per_task(n, K, simds, streams); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
 
@@ -108,3 +109,29 @@ def test_no_xcd_fills_up_with_workgroups_that_wait(plan):
             assert not _stalls(_blocks(plan, K, units, m), K, units, parts, held, late), (K, held, late, m)
         seen += _stalls(_blocks(plan, K, units, -1), K, units, parts, held, late)
     assert seen                                              # the model knows a stall: many workers, all on every XCD
+
+
+# tasks, workers, {waves: us} of the first and of the second half-step on 1024 SIMDs, where one choice is clearly better
+MEASURED = [
+    (512, 3, {1: 12.7, 2: 10.6}, {1: 21.5, 2: 19.2}), (1024, 3, {1: 13.4, 2: 12.3}, None), (3072, 3, {1: 21.1, 2: 22.9}, {1: 40.2, 2: 49.6}),
+    (256, 4, {1: 14.6, 2: 10.3, 4: 8.7}, {1: 23.8, 2: 17.9, 4: 14.6}), (512, 4, None, {1: 24.6, 2: 19.1, 4: 17.1}),
+    (1024, 4, {1: 15.5, 2: 12.6, 4: 14.1}, {1: 28.5, 2: 25.5, 4: 26.0}), (4096, 4, {1: 27.8, 2: 31.3, 4: 41.4}, {1: 54.8, 2: 62.3, 4: 69.1}),
+    (512, 5, {1: 17.0, 2: 12.7, 4: 12.2}, {1: 27.8, 2: 22.4, 4: 20.2}), (1024, 5, {1: 17.8, 2: 14.8, 4: 16.3}, {1: 31.8, 2: 28.4, 4: 29.2}),
+    (3072, 5, {1: 26.4, 2: 28.1, 4: 38.9}, {1: 50.7, 2: 59.6, 4: 66.2}), (4096, 5, {1: 31.0, 2: 35.5, 4: 48.3}, {1: 62.0, 2: 72.4, 4: 86.3}),
+    (512, 8, {1: 23.3, 2: 15.1, 4: 12.6}, {1: 37.3, 2: 26.0, 4: 22.0}), (2048, 8, {1: 30.2, 2: 26.2, 4: 30.7}, None),
+    (4096, 8, {1: 40.8, 2: 45.7, 4: 53.2}, {1: 81.8, 2: 87.9, 4: 97.1}), (4816, 8, {1: 48.2, 2: 61.1, 4: 64.7}, {1: 113.3, 2: 105.1, 4: 111.8}),
+    (1024, 12, {1: 34.2, 2: 22.6, 4: 21.5}, {1: 54.8, 2: 41.7, 4: 40.5}), (2048, 12, {1: 39.7, 2: 33.1, 4: 37.6}, {1: 67.1, 2: 64.2, 4: 70.8}),
+    (2048, 16, {1: 49.3, 2: 39.9, 4: 44.8}, {1: 82.3, 2: 77.3, 4: 83.5}),
+    (9216, 16, {1: 175.5, 2: 158.6, 4: 161.8}, None), (2048, 32, {1: 87.8, 2: 67.8, 4: 72.3}, {1: 143.8, 2: 131.8, 4: 135.8}),
+    (4096, 32, {1: 123.7, 2: 128.0, 4: 129.8}, None), (3072, 32, {1: 100.2, 2: 94.5, 4: 96.8}, None),
+]
+
+
+def test_waves_per_task_follow_the_measurements(plan):
+    for tasks, K, first, second in MEASURED:
+        for streams, us in ((1, first), (2, second)):
+            if us:
+                got = plan.waves_per_task(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(streams))
+                assert us[got] <= 1.025 * min(us.values()), (tasks, K, streams, got)
+    for tasks, K in itertools.product([1, 2, 100000, (1 << 32) - 1], [1, 2, 3, 4, 65535]):
+        assert 1 <= plan.waves_per_task(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(1)) <= min(K, 4)
