@@ -295,7 +295,8 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     __shared__ __align__(16) unsigned char s_tab2[TWO ? kTabBytes : 16];
     const unsigned char* s_tab_b = TWO ? s_tab2 : s_tab;
 
-    const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    const int tid = (int)threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
+    int lane = lane_id();
     const uint32_t nwaves = blockDim.x >> 6;
     const int part = w & (KSPLIT - 1);                   // this wave's place in its group
     const uint32_t stage_words = a.stage_words;          // words half a chunk of this code can touch
@@ -569,6 +570,10 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     // Lane L holds coordinates 32 L .. 32 L + 31 of the task.  Through LDS the wave turns them, kTurn lanes
     // at a time, so that eight lanes own a row of 32 consecutive floats and global accesses touch whole
     // 128-byte lines.
+    // At 64 registers the loop has none to hold the lane's number in.  (Spilled, it and what is made from it cost the first
+    // half-step of 8 x 2^24 coordinates 1.5 us, 8 bytes a lane written and read; the second half-step without a
+    // previous stream then spills its sum's registers instead and is no faster.)
+    if constexpr (!kTwo && MODE != DecMode::Half1) lane = late_lane_id();
     constexpr int kPitch = kSub + 4;                            // rows of 36 floats
     constexpr int kTurn = kTwo ? 32 : 16;                       // 1152 floats in two staging buffers, or 576 in one
     constexpr int kPasses = kWave / kTurn, kReads = kTurn / 8;
@@ -616,7 +621,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     const float invK = 1.0f / (float)lay.K;
     const float gam = sc->gamma_f;
     if constexpr (MODE == DecMode::Half0) {               // one more term of the ergodic average
-        if (a.x_sum && blockIdx.x == 0 && tid == 0) sc->avg_count += 1ull;
+        if (a.x_sum && blockIdx.x == 0 && w == 0 && lane == 0) sc->avg_count += 1ull;
     }
     if constexpr (MODE == DecMode::Half1) {
         sdiff = wave_sum(sdiff);

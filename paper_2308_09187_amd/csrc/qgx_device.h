@@ -7,6 +7,13 @@
 namespace qgx {
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
+// The same, worked out where it stands: no register holds it from the kernel's start until then.
+__device__ __forceinline__ int late_lane_id()
+{
+    uint32_t all = 0xFFFFFFFFu;
+    asm volatile("" : "+s"(all));
+    return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
 __device__ __forceinline__ int wave_id() { return (int)(threadIdx.x >> 6); }
 
 // Philox4x32 with 10 rounds (Salmon, Moraes, Dror, Shaw, SC'11).  The key schedule is uniform
