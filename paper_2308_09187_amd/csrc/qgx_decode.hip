@@ -34,7 +34,9 @@ constexpr int kHalfCoords = kChunk / 2;               // coordinates of a task, 
 constexpr int kPre = 3;                               // uint4 per lane that travel ahead: 768 words, 12 bits per coordinate
 static_assert(kHalfCoords * kMaxSymBits / 32 + 8 <= (kPre + 1) * kWave * 4, "one more covers any half chunk");
 template <DecMode MODE, bool PREV> constexpr bool two_chains() { return PREV || MODE == DecMode::Decode; }
-template <DecMode MODE, bool PREV> constexpr int most_waves() { return two_chains<MODE, PREV>() ? 8 : 16; }   // per workgroup: they share the decode table
+// Most waves per workgroup; they share the decode table.  Two tables leave LDS for one workgroup of eight waves with two chains
+// to a compute unit, and for one of sixteen: second half-step of 8 x 2^24 coordinates, two tables, 191 -> 164 us (180 with a wave per whole position).
+template <DecMode MODE, bool PREV, bool TWO> constexpr int most_waves() { return two_chains<MODE, PREV>() && !TWO ? 8 : 16; }
 static_assert(kSub * kWave == kHalfCoords && kSubs == 2 * kWave, "a sub-chunk per lane, two tasks per chunk");
 
 // Staged words in LDS.  Lane j parses the j-th run of the half, whose bits start roughly bits-per-coordinate
@@ -280,7 +282,7 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // What bounds it: the parse, whose chains wait for their look-ups (vector ALUs busy for about 55 % of the time, LDS
 // for about half), and at the largest sizes of one stream the memory path (the update moves 6 TB/s).
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-__global__ __launch_bounds__((most_waves<MODE, PREV>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>()) ? 4 : 8)))
+__global__ __launch_bounds__((most_waves<MODE, PREV, TWO>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>()) ? 4 : 8)))
 void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
 {
     static_assert(!PREV || MODE == DecMode::Half1, "only the second half-step reads two streams");
@@ -288,7 +290,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "the waves of a workgroup in groups of 1, 2 or 4");
     static_assert(KSPLIT == 1 || MODE != DecMode::Decode, "plain decoding has nothing to add up");
     extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][2][stage_stride]
-    __shared__ double s_sd[KSPLIT > 1 ? most_waves<MODE, PREV>() : 1];
+    __shared__ double s_sd[KSPLIT > 1 ? most_waves<MODE, PREV, TWO>() : 1];
     constexpr bool kTwo = two_chains<MODE, PREV>();       // chains per lane
     constexpr uint32_t kBufs = kTwo ? 2u : 1u;
     __shared__ __align__(16) unsigned char s_tab[kTabBytes];
@@ -743,11 +745,13 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     // eight workers, 4096 waves: 26.5 us in workgroups of four, 28 to 30 in workgroups of sixteen).
     const size_t wave_lds = (size_t)(two_chains<MODE, PREV>() ? 2 : 1) * a.stage_stride * sizeof(uint32_t);
     const size_t tables_lds = (size_t)(TWO ? 2 : 1) * kTabBytes + 256;
-    uint32_t per = (uint32_t)most_waves<MODE, PREV>();
-    for (uint32_t small = 4; small < (uint32_t)most_waves<MODE, PREV>(); small *= 2) {
-        const uint64_t held = min((uint64_t)(160u * 1024u / (small * wave_lds + tables_lds)) * small, (uint64_t)(two_chains<MODE, PREV>() ? 16 : 32));
-        if (nwaves <= held * a.n_cu) { per = small; break; }
-    }
+    auto held = [&](uint32_t n) {                            // waves on a compute unit in workgroups of n
+        return min((uint64_t)(160u * 1024u / (n * wave_lds + tables_lds)) * n, (uint64_t)(two_chains<MODE, PREV>() ? 16 : 32));
+    };
+    uint32_t per = (uint32_t)most_waves<MODE, PREV, TWO>();
+    if (TWO && held(8) >= held(16)) per = 8;                 // (short codes: two of eight beside each other, 160 us to 164)
+    for (uint32_t small = 4; small < per; small *= 2)
+        if (nwaves <= held(small) * a.n_cu) { per = small; break; }
     const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);

@@ -97,3 +97,28 @@ def test_step_size_sum_of_short_positions(qgx, d, bucket):
     assert abs(ctx.scalars()["S"] - S) <= (32 * K + 128) * 2.0 ** -53 * S
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("waves", [1, 4])
+def test_two_tables_in_workgroups_of_sixteen_waves(qgx, monkeypatch, waves):
+    """The second half-step with a table for either stream and more waves than workgroups of eight can hold at once."""
+    monkeypatch.setitem(WAVES_PER_POSITION, "waves", waves)
+    K, d = 4, 2300 * 2048 + 700
+    ctx, lay = make_ctx(qgx, d, K, 8192, oracle.NORM_L2, synth.levels_exponential(16), seed=9)
+    ctx.select_table(1)
+    ctx.set_levels(synth.levels_uniform(40))
+    A, B = ctx.new_stream(slotted=True), ctx.new_stream(slotted=True)
+    ctx.quantize_encode(dev(synth.student_t3(K, d, seed=1)), 0, A)
+    Va = ctx.decode(A).cpu().numpy()
+    ctx.select_table(0, 1)
+    ctx.quantize_encode(dev(synth.student_t3(K, d, seed=2)), 1, B)
+    Vb = ctx.decode(B).cpu().numpy()
+    ctx.state_init(None)
+    st = oracle.EGState(d, K)
+    st.half0(Va)
+    X = torch.empty(d, device="cuda")
+    ctx.eg_step(1, B, A, X)
+    assert rel_err(X.cpu().numpy(), st.half1(Vb, Va)) <= REL
+    assert abs(ctx.scalars()["S"] - st.S) <= REL * st.S
+    assert ctx.poll_error() == 0
+    ctx.close()
