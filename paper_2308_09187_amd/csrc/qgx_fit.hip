@@ -483,24 +483,18 @@ __device__ double stationary_point(const Tree& T, double a, double c)
     const uint32_t q2 = dn1 > p2 ? dn1 : p2;
     const uint32_t lo[5] = {P, p1, p2 >> 4, q2, Q1}, hi[5] = {P1, p2, p2 < q2 ? q2 >> 4 : p2 >> 4, q1, Q};
     const uint32_t lvl[5] = {0u, 1u, 2u, 1u, 0u};
-    // A lane past its run's end reads the run's first place (inside the tree, whatever the run) and counts as 0: no
-    // branch, so that the loads of all five runs are on their way at once.
-    double m[5], rho = 0.0, term[5];
+    double m[5], rho = 0.0;
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-        const uint32_t last = lvl[s] == 0u ? nb - 1u : lvl[s] == 1u ? nb / 16u - 1u : (nb + 255u) / 256u - 1u;
-        const bool in = lo[s] + li < hi[s];
-        const uint32_t idx = in ? lo[s] + li : min(lo[s], last);
-        const double mass = item_mass(T, lvl[s], idx);
-        double t;
-        if (lvl[s] == 0u) t = mass * (c - 0.5 * (bin_edge(idx, nb) + bin_edge(idx + 1u, nb)));
-        else if (lvl[s] == 1u) t = (c - bin_edge(16u * idx + 16u, nb)) * mass + T.r1[idx];
-        else t = (c - bin_edge(256u * idx + 256u, nb)) * mass + T.r2[idx];
-        m[s] = in ? mass : 0.0;
-        term[s] = in ? t : 0.0;
+        const uint32_t idx = lo[s] + li;
+        m[s] = 0.0;
+        if (idx < hi[s]) {
+            m[s] = item_mass(T, lvl[s], idx);
+            if (lvl[s] == 0u) rho += m[s] * (c - 0.5 * (bin_edge(idx, nb) + bin_edge(idx + 1u, nb)));
+            else if (lvl[s] == 1u) rho += (c - bin_edge(16u * idx + 16u, nb)) * m[s] + T.r1[idx];
+            else rho += (c - bin_edge(256u * idx + 256u, nb)) * m[s] + T.r2[idx];
+        }
     }
-#pragma unroll
-    for (int s = 0; s < 5; ++s) rho += term[s];
     // int_a^c (c - u) dF~
     const double right_all = m_a * (c - 0.5 * (a + a_hi)) + row_sum(rho) + m_c * (c - 0.5 * (c_e0 + c));
     if (!(right_all > 0.0)) return a;                                  // no mass between the neighbours
