@@ -244,12 +244,15 @@ __device__ __forceinline__ void place_row(uint32_t* stage, uint32_t pos, uint64_
 }
 
 // Appends row r (four entries per lane) to the wave's staging buffer; returns the row's bit count.
+// BRANCH: the sub-chunk ends' store behind a branch after all, for the rolled loop, whose rows no scheduler mixes: dropped
+// stores are not free (symbols of 8 x 2^22 coordinates in words of three bits coded in 28 us instead of 31).
+template <bool BRANCH>
 __device__ __forceinline__ uint32_t pack_row(uint32_t* stage, const SubEnds& ends, int r, uint32_t row_base, const uint32_t (&e)[4])
 {
     const RowCode c = join_row(e);
     const uint32_t incl = wave_incl_scan(c.len);
     place_row(stage, row_base + incl - c.len, c.bits);
-    ends.put(r, row_base + incl);
+    if (!BRANCH || ends.at < (uint32_t)kSubs) ends.put(r, row_base + incl);
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
 }
 
@@ -716,7 +719,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 if (r < whole) {                       // (wave-uniform)
                     uint32_t e[4];
                     quantize_row(r, e);
-                    if (MODE != EncMode::QuantOnly) row_base += pack_row(stage, ends, r, row_base, e);
+                    if (MODE != EncMode::QuantOnly) row_base += pack_row<false>(stage, ends, r, row_base, e);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -769,10 +772,11 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         // E(idx, sign) from the table row of idx (its third word), nothing for a padded slot
-                        const float4 t = *reinterpret_cast<const float4*>(s_lev + idx[q] * 16u + neg[q] * a.lev_stride);
-                        e[q] = (i0 + (uint32_t)q < g.cend) ? __float_as_uint(t.z) : 0u;
+                        uint32_t code = reinterpret_cast<const uint32_t*>(s_lev + idx[q] * 16u + neg[q] * a.lev_stride)[2];
+                        asm("" : "+v"(code));                  // (read by all lanes: four branches a row cost more)
+                        e[q] = (i0 + (uint32_t)q < g.cend) ? code : 0u;
                     }
-                    row_base += pack_row(stage, ends, r, row_base, e);
+                    row_base += pack_row<true>(stage, ends, r, row_base, e);
                 }
             }
         }
