@@ -105,7 +105,7 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
 // stores.  The wait cannot deadlock: parts take their (bucket, part) from the worker's ticket
 // counter, so at most the bucket of the newest tickets is incomplete, and every other waiting
 // workgroup has all its partners running; for the partners of the newest there is always a place on the
-// XCD whose queue they are in (block_by_worker).  The wait is bounded all the same.
+// XCD whose queue they are in (worker_span).  The wait is bounded all the same.
 // Called by one whole wave; returns the parts' values combined in part order in every lane.
 __device__ double exchange_parts(unsigned long long* words /* [parts][2 phases][2] of this bucket */, uint32_t parts,
                                  uint32_t part, uint32_t phase, double mine, bool take_max, uint32_t epoch, Scalars* sc)
@@ -427,13 +427,9 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const int nwaves = (int)(blockDim.x >> 6);
     const uint32_t n_sym = tab->n_sym;
     // The worker and, without tickets, the unit of work are fixed by the block.
-    uint32_t k = blockIdx.x % lay.K, own_unit = blockIdx.x / lay.K;
+    uint32_t k = blockIdx.x % a.span, own_unit = blockIdx.x / a.span;
     if (MODE == EncMode::Generate && a.by_unit) {
         const BlockWork own = block_by_unit(blockIdx.x, lay.K, a.units);
-        k = own.k; own_unit = own.unit;
-    } else if (kWaits<MODE> && a.group_bits != 0u) {
-        const BlockWork own = block_by_worker(blockIdx.x, lay.K, a.units, a.group_bits);
-        if (!own.there) return;
         k = own.k; own_unit = own.unit;
     }
 
@@ -470,7 +466,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     // launch, which tags what the workgroups publish to each other (30 bits, never 0: untouched
     // words hold 0).  Nothing about it comes from the host: a captured graph can be replayed.
     if (ticketed) {
-        if (tid == 0) {
+        if (tid == 0 && (!kWaits<MODE> || k < lay.K)) {
             const unsigned long long per_launch = GROUPED ? (lay.NC + 3u) / 4u : (unsigned long long)lay.NB * a.parts;
             const unsigned long long raw = atomicAdd(a.tickets + k * kTicketStride, 1ull);
             const unsigned long long launch = raw / per_launch;
@@ -495,6 +491,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const uint32_t cell_exact = (tab->cell_exact != 0u && (uint32_t)cell_mant(n_sym) == a.cell_mant) ? 1u : 0u;
     __syncthreads();
 
+    if (kWaits<MODE> && k >= lay.K) return;             // a row's end (asked before the ticket it costs compact placement 1 %)
     const size_t kbase = (size_t)k * lay.d;
     const bool vec_ok = MODE == EncMode::Generate || (kbase & 3u) == 0;    // 16-byte aligned rows for this worker
     // the number of this quantisation call: given, or taken from the iteration counter (replayed graphs)
@@ -849,12 +846,12 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     EncodeArgs b = a;
     b.units = GROUPED ? (lay.NC + 3u) / 4u : lay.NB * a.parts;
     // Where the workgroups of a bucket wait for each other, no XCD may have more workers than leave it a place to
-    // start one in (see block_by_worker).  The game's form puts the K workgroups of a unit on one XCD, which all K workers
+    // start one in (see worker_span).  The game's form puts the K workgroups of a unit on one XCD, which all K workers
     // then share, as long as that holds for K (42 workers with four workgroups to a compute unit, 31 with three).
     const uint32_t held = held_per_xcd(kSimdWaves<MODE>, lds, a.n_cu);
-    b.group_bits = kWaits<MODE> && a.parts > 1u ? worker_groups_log2(lay.K, a.parts, held) : 0u;
-    b.by_unit = MODE == EncMode::Generate && b.group_bits == 0u ? 1u : 0u;
-    const uint32_t grid = grid_by_worker(lay.K, b.units, b.group_bits);
+    b.span = kWaits<MODE> && a.parts > 1u ? worker_span(lay.K, a.parts, held) : lay.K;
+    b.by_unit = MODE == EncMode::Generate && (a.parts == 1u || (a.parts - 1u) * lay.K < held) ? 1u : 0u;
+    const uint32_t grid = b.span * b.units;
     hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM>), dim3(grid), dim3(waves * kWave), lds, st, lay, tab, sc, b);
     return hipGetLastError();
 }

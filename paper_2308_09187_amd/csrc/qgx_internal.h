@@ -152,8 +152,8 @@ struct EncodeArgs {
     uint32_t n_cu;              // compute units of the device
     // filled in by the launch: which worker's which unit a block takes
     uint32_t units;             // workgroups per worker
-    uint32_t by_unit;           // block_by_unit (Generate); else block_by_worker with
-    uint32_t group_bits;        // log2 of its number of groups
+    uint32_t span;              // worker = block % span (past K: none), unit = block / span (worker_span)
+    uint32_t by_unit;           // or block_by_unit (Generate)
     uint32_t seed_lo, seed_hi, call_id;
     uint32_t call_mode;         // 0: call_id as given; 1, 2: 2(t-1), 2(t-1)+1 from the iteration counter on the device
     int norm_kind;

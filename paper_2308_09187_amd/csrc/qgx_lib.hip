@@ -299,7 +299,7 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     ok = ok && hipMalloc(&c->d_anchor, cfg->d * sizeof(float)) == hipSuccess;
     // A bucket of more than four chunks is shared by workgroups of four waves.  Per worker, the parts
     // of one bucket (the newest tickets) can be waiting for partners that have not started yet: up to
-    // three, which must leave a place free on every XCD (see block_by_worker), so only for K <= 64.
+    // three, which must leave a place free on every XCD (see worker_span), so only for K <= 64.
     c->parts = (c->lay.waves_per_bucket > 4u && cfg->K <= 64u) ? (c->lay.waves_per_bucket + 3u) / 4u : 1u;
     const size_t n_units = (size_t)cfg->K * NB * c->parts;
     ok = ok && hipMalloc(&c->d_scan, n_units * sizeof(unsigned long long)) == hipSuccess;

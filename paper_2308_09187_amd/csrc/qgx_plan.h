@@ -42,34 +42,20 @@ QGX_PLAN HalfWords half_words(uint32_t off, uint32_t start, uint32_t end, uint32
 // must always be left, so the workers on an XCD are kept below what `held`, the workgroups an XCD holds at once, allows.
 constexpr uint32_t kXcds = 8;
 
-struct BlockWork { uint32_t k, unit; bool there; };
+// Blocks deal the workers round, in rows of `span` of which the first K are workers: block i is worker i % span's unit
+// i / span.  With a span of K all workers can have workgroups on every XCD; with one that is a multiple of 2, 4 or 8 the
+// workers k of one k mod 2 (4, 8) have the XCDs of that number mod 2 (4, 8) to themselves.
 
-// The K workgroups of a unit on one XCD, one after the other: for operands that the workers share.  All workers have
-// workgroups on every XCD.  Grid: K * units.
+// The K workgroups of a unit on one XCD instead, one after the other: for operands that the workers share.  All workers
+// have workgroups on every XCD.  Grid: K * units.
+struct BlockWork { uint32_t k, unit; };
+
 QGX_PLAN BlockWork block_by_unit(uint32_t i, uint32_t K, uint32_t units)
 {
     const uint32_t even = units / kXcds * kXcds;              // units in whole rounds of the XCDs
     const uint32_t j = i / kXcds, rest = i - even * K;
-    if (i < even * K) return BlockWork{j % K, j / K * kXcds + i % kXcds, true};
-    return BlockWork{rest % K, even + rest / K, true};
-}
-
-// The workers in 2^lg groups (lg: 0 .. 3), group g with the XCDs x of x mod 2^lg = g to itself, units in order.  lg = 0
-// deals the workers round; for a K that is a multiple of 8 every lg gives that same map.  Not there: a workgroup beyond the
-// work of its group.  Grid: grid_by_worker.
-QGX_PLAN BlockWork block_by_worker(uint32_t i, uint32_t K, uint32_t units, uint32_t lg)
-{
-    const uint32_t mask = (1u << lg) - 1u, x = i % kXcds, n = (K + mask) >> lg;      // n: places of workers in a group
-    const uint32_t s = i / kXcds * (kXcds >> lg) + (x >> lg), unit = s / n;           // s: the block's place in its group's order
-    const uint32_t k = (x & mask) + ((s - unit * n) << lg);
-    return BlockWork{k, unit, k < K && unit < units};
-}
-
-inline uint32_t grid_by_worker(uint32_t K, uint32_t units, uint32_t lg)
-{
-    if (lg == 0u) return K * units;
-    const uint32_t mask = (1u << lg) - 1u, per_round = kXcds >> lg;
-    return (((K + mask) >> lg) * units + per_round - 1u) / per_round * kXcds;
+    if (i < even * K) return BlockWork{j % K, j / K * kXcds + i % kXcds};
+    return BlockWork{rest % K, even + rest / K};
 }
 
 // Workgroups of four waves that an XCD holds at once: a wave of each on every SIMD, and their LDS (in steps of 2 KiB).
@@ -79,12 +65,12 @@ inline uint32_t held_per_xcd(uint32_t waves_per_simd, size_t lds_bytes, uint32_t
     return (uint32_t)(fit < waves_per_simd ? fit : waves_per_simd) * (n_cu / kXcds);
 }
 
-// The fewest groups (as lg) that leave an XCD a free place; 3 if none do.
-inline uint32_t worker_groups_log2(uint32_t K, uint32_t parts, uint32_t held)
+// The shortest row that leaves an XCD a free place; a multiple of 8 if none does.
+inline uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held)
 {
-    uint32_t lg = 0;
-    while (lg < 3u && (parts - 1u) * ((K + (1u << lg) - 1u) >> lg) >= held) ++lg;
-    return lg;
+    uint32_t groups = 1;
+    while (groups < kXcds && (parts - 1u) * ((K + groups - 1u) / groups) >= held) groups *= 2;
+    return (K + groups - 1u) / groups * groups;
 }
 
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --

@@ -17,16 +17,14 @@ extern "C" int half_words(uint32_t off, uint32_t start, uint32_t end, uint32_t m
     out[0] = h.at; out[1] = h.w0; out[2] = h.words;
     return h.ok;
 }
-// out[i] = k * units + unit, or -1; lg < 0: block_by_unit
-extern "C" void blocks(uint32_t grid, uint32_t K, uint32_t units, int lg, int64_t* out)
+extern "C" void blocks_by_unit(uint32_t K, uint32_t units, int64_t* out)
 {
-    for (uint32_t i = 0; i < grid; ++i) {
-        const qgx::BlockWork b = lg < 0 ? qgx::block_by_unit(i, K, units) : qgx::block_by_worker(i, K, units, (uint32_t)lg);
-        out[i] = b.there ? (int64_t)b.k * units + b.unit : -1;
+    for (uint32_t i = 0; i < K * units; ++i) {
+        const qgx::BlockWork b = qgx::block_by_unit(i, K, units);
+        out[i] = (int64_t)b.k * units + b.unit;
     }
 }
-extern "C" uint32_t grid_by_worker(uint32_t K, uint32_t units, uint32_t lg) { return qgx::grid_by_worker(K, units, lg); }
-extern "C" uint32_t worker_groups_log2(uint32_t K, uint32_t parts, uint32_t held) { return qgx::worker_groups_log2(K, parts, held); }
+extern "C" uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held) { return qgx::worker_span(K, parts, held); }
 extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::waves_per_task(n, K, simds, streams); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
@@ -59,27 +57,22 @@ def test_half_words_stay_inside_the_payload(plan):
             assert not valid or (ok and at == off + w0 and w0 == start // 128 * 4 and words == last - w0), (cap, off, start, end)
 
 
-def _blocks(plan, K, units, lg):
-    grid = K * units if lg < 0 else plan.grid_by_worker(K, units, lg)
-    out = np.empty(grid, np.int64)
-    plan.blocks(C.c_uint32(grid), C.c_uint32(K), C.c_uint32(units), C.c_int(lg), out.ctypes.data_as(C.c_void_p))
+def _blocks(plan, K, units, span):
+    """worker * units + unit of every block, -1 where there is none; span 0: block_by_unit"""
+    if span:
+        i = np.arange(span * units)
+        return np.where(i % span < K, i % span * units + i // span, -1)
+    out = np.empty(K * units, np.int64)
+    plan.blocks_by_unit(C.c_uint32(K), C.c_uint32(units), out.ctypes.data_as(C.c_void_p))
     return out
 
 
-@pytest.mark.parametrize("lg", [-1, 0, 1, 2, 3])
-def test_every_worker_has_every_unit_once(plan, lg):
+def test_a_units_workgroups_on_one_xcd(plan):
     for K, units in itertools.product([1, 2, 3, 5, 7, 8, 9, 16, 31, 33, 63, 64], [1, 2, 7, 8, 9, 15, 16, 17, 40, 67]):
-        got = _blocks(plan, K, units, lg)
-        np.testing.assert_array_equal(np.sort(got[got >= 0]), np.arange(K * units), err_msg="K %d units %d" % (K, units))
-        if lg < 0:                                           # a unit's workgroups in whole rounds: one XCD, one after the other
-            for unit in range(units // 8 * 8):
-                np.testing.assert_array_equal(got[unit // 8 * 8 * K + unit % 8 + 8 * np.arange(K)], np.arange(K) * units + unit)
-        if lg == 0 or K % 8 == 0 and lg > 0:
-            i = np.arange(K * units)
-            np.testing.assert_array_equal(got, i % K * units + i // K)
-        if lg > 0:
-            there = np.flatnonzero(got >= 0)
-            np.testing.assert_array_equal(there % (1 << lg), got[there] // units % (1 << lg))
+        got = _blocks(plan, K, units, 0)
+        np.testing.assert_array_equal(np.sort(got), np.arange(K * units), err_msg="K %d units %d" % (K, units))
+        for unit in range(units // 8 * 8):                   # in whole rounds: one XCD, one after the other
+            np.testing.assert_array_equal(got[unit // 8 * 8 * K + unit % 8 + 8 * np.arange(K)], np.arange(K) * units + unit)
 
 
 def _stalls(work, K, units, parts, held, late):
@@ -99,15 +92,16 @@ def _stalls(work, K, units, parts, held, late):
 
 def test_no_xcd_fills_up_with_workgroups_that_wait(plan):
     """Buckets of four parts, an XCD that is behind: the map that a launch takes always leaves it a place (with 160, 128
-    or 96 workgroups to an XCD; the game's form takes block_by_unit when one group is enough)."""
+    or 96 workgroups to an XCD; the game's form takes block_by_unit while 3 K is below that)."""
     assert [plan.held_per_xcd(C.c_uint32(5), C.c_size_t(n), C.c_uint32(256)) for n in (30000, 40000, 53000)] == [160, 128, 96]
     parts, units, seen = 4, 64, 0
     for K, held, late in itertools.product([1, 8, 31, 32, 33, 42, 43, 47, 48, 53, 54, 57, 63, 64], [96, 128, 160], [0, 3, 7]):
-        lg = plan.worker_groups_log2(K, parts, held)
-        assert not (lg == 0 and 3 * K >= held) and 3 * -(-K // (1 << lg)) < held
-        for m in (lg,) if lg else (-1, 0):
-            assert not _stalls(_blocks(plan, K, units, m), K, units, parts, held, late), (K, held, late, m)
-        seen += _stalls(_blocks(plan, K, units, -1), K, units, parts, held, late)
+        span = plan.worker_span(K, parts, held)
+        assert K <= span < K + 8 and (span == K or 3 * K >= held)
+        assert not _stalls(_blocks(plan, K, units, span), K, units, parts, held, late), (K, held, late, span)
+        by_unit = _stalls(_blocks(plan, K, units, 0), K, units, parts, held, late)
+        assert not (by_unit and 3 * K < held), (K, held, late)
+        seen += by_unit
     assert seen                                              # the model knows a stall: many workers, all on every XCD
 
 
