@@ -194,8 +194,8 @@ qgx_status qgx_quantize_encode(qgx_ctx* ctx, const float* V, uint32_t call_id, c
 qgx_status qgx_decode(qgx_ctx* ctx, const qgx_stream* in, float* Vhat, void* stream);
 
 /* Aggregate of Algorithm 1: mean DEVICE [d] = (1/K) sum_k DEQ(CODE_k), decoded on the fly.
- * The K values of a coordinate are added in binary32, in worker order; on layouts with too few
- * chunks to fill the GPU the workers are split in two or four runs (as equal as K allows, the
+ * The K values of a coordinate are added in binary32, in worker order; on layouts whose chunks fill
+ * the GPU badly the workers are split in two or four runs (as equal as K allows, the
  * longer ones first), each added in order, and the runs' sums added in order (the same in
  * qgx_eg_step).  The number of runs follows from the layout, K and the device, so results repeat bit
  * for bit (qgx_debug_set_waves_per_position overrides the choice, for tests and timing). */
@@ -294,14 +294,15 @@ qgx_status qgx_eg_step(qgx_ctx* ctx, int half, const qgx_stream* cur, const qgx_
 /* qgx_eg_step for callers that may not allocate device memory and want the guarantee in the interface:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
  * same kernels, same results bit for bit as qgx_eg_step; the one difference is where the second
- * half-step keeps its scratch, the per-chunk partial sums of S: not in memory that qgx_create allocated
+ * half-step keeps its scratch, the partial sums of S, two per chunk (one per half of a chunk position that
+ * holds coordinates): not in memory that qgx_create allocated
  * but in a fixed array inside the library's device image (16 * QGX_STATIC_MAX_CHUNKS = 1 MiB per GPU,
  * held until the process ends; its address on a device is looked up once, in the first qgx_create on
  * that device).  The call itself allocates and frees nothing.
  *   - QGX_ERR_CAPACITY if the layout has more than QGX_STATIC_MAX_CHUNKS chunks per worker (qgx_eg_step
  *     has no such limit); QGX_ERR_STATE if the context's device is not the current one.
- *   - All contexts on one GPU share the array: every call overwrites the entries 0 .. n_chunks - 1 it
- *     then reads and relies on nothing a previous call left, but two such calls that overlap on one
+ *   - All contexts on one GPU share the array: every call overwrites entries from 0 on, at most
+ *     2 * n_chunks of them, then reads those and relies on nothing a previous call left, but two such calls that overlap on one
  *     GPU (different streams or threads) race on it.  Calls on one stream, or ordered by events, do not. */
 qgx_status qgx_eg_step_static(qgx_ctx* ctx, int half, const qgx_stream* cur, const qgx_stream* prev,
                               float* X_out, void* stream);
@@ -313,8 +314,9 @@ qgx_status qgx_get_scalars(qgx_ctx* ctx, double* S, double* gamma, uint64_t* t, 
  * 32 bits per bucket for the norm (the quantity Theorem 2 bounds, less C_b per bucket).  Synchronises. */
 qgx_status qgx_stream_bits(qgx_ctx* ctx, const qgx_stream* coded, uint64_t* total_bits, void* stream);
 
-/* Test and timing hook: the number of waves that share a full chunk position in the decoding calls
- * (1, 2 or 4; ignored when above K), or 0 to go back to the library's own rule.  Host-side only. */
+/* Test and timing hook: the number of waves that share a task, half a chunk position, short ones
+ * included, in qgx_decode_average and the half-steps (1, 2 or 4; ignored when above K), or 0 to go back to
+ * the library's own rule.  Host-side only. */
 qgx_status qgx_debug_set_waves_per_position(qgx_ctx* ctx, int waves);
 
 /* Copies the dual state out (checkpoint) or in (resume).  Y, anchor DEVICE [d]; NULL skips. */

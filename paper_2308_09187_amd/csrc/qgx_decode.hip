@@ -21,7 +21,9 @@
 // Why half a position: a wave per whole position held 64 sums per lane, which left four (one stream) or two
 // (two streams) waves per SIMD, and a launch of a round or two of equal waves in step.  Measured, whole position
 // -> half: second half-step of 16 x 2^26 coordinates 1.246 -> 1.02 ms, of 8 x 9.86 M 0.150 -> 0.115 ms; first
-// half-step 0.593 -> 0.535 and 0.085 -> 0.057 ms.
+// half-step 0.593 -> 0.497 and 0.085 -> 0.057 ms, of 8 x 2^24 73 us as before in a loop of coding and half-step, but
+// 69 -> 74 us inside a whole iteration: it reads 10 MB more (a chunk's extents and the line that its halves share are asked for
+// by two waves).
 // Positions of fewer than 4096 coordinates are the same tasks with some lanes' symbols masked out; a half
 // without coordinates is no task at all.  (A workgroup per such position, its workers spread over the waves, took
 // 0.168 ms for the second half-step of 5 x 3 M coordinates in buckets of 6000, this takes 0.035.)

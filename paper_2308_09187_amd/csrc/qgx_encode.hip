@@ -10,7 +10,7 @@
 // between the norm reduction and the rounding pass, (c) one Philox4x32 block (four words) serves
 // exactly the four coordinates of a lane and row.
 //
-// The vector ALUs' issue bounds it (busy for about 80 % of the time; 145 instructions per row of four
+// The vector ALUs' issue bounds it (busy for about 80 % of the time; 138 instructions per row of four
 // coordinates a lane, a third of them the generator), the memory system is next (4.6 TB/s of the 6.2 that the best
 // streaming kernel reaches), so the per-coordinate path is kept to a straight line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, address of the lower candidate table row) -> one
 // 16-byte LDS row holding the level, the scaled gap and the two candidate code words with the sign
@@ -97,7 +97,7 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
 }
 
 // Buckets longer than four chunks are shared by several workgroups of four waves (parts), which a
-// compute unit holds five of at different points of their life, where one workgroup of sixteen waves
+// compute unit holds five of (four in the game's form) at different points of their life, where one workgroup of sixteen waves
 // would have the unit to itself and leave the memory system idle while it computes and the ALUs idle
 // while it loads.  What the parts must agree on is the bucket's norm: every part publishes its
 // partial sum (or maximum) and reads the others'.  A published value is two words, each tagged with
@@ -407,8 +407,8 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
     return plain;
 }
 
-// One workgroup per (worker, bucket).  Workgroups are short-lived on purpose: with five of them per
-// compute unit at different points of their life, the load, ticket and look-back latencies of one
+// One workgroup per (worker, bucket).  Workgroups are short-lived on purpose: with five of them (four in
+// the game's form) per compute unit at different points of their life, the load, ticket and look-back latencies of one
 // overlap the arithmetic of the others (a persistent, lock-stepped variant measured slower).
 // GROUPED: the layout has shared chunks; a workgroup is four waves with a chunk each, and every wave
 // finds the norms of its chunk's buckets by itself.
