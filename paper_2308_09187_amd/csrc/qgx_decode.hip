@@ -48,13 +48,6 @@ static_assert(kSub * kWave == kHalfCoords && kSubs == 2 * kWave, "a sub-chunk pe
 // each other.
 __device__ __forceinline__ uint32_t staged(uint32_t i) { return i + ((i >> 5) << 1); }
 
-// A load through the scalar cache, of what an earlier launch wrote and this one only reads: a wave's tables of
-// extents cost no vector registers and no wait on the vector loads in flight.
-__device__ __forceinline__ uint32_t scalar_load(const void* p)
-{
-    return *reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uintptr_t>(p));
-}
-
 // One worker's stream as this wave reads it (wave-uniform): its chunk's entry in the offset table, its row of
 // sub-chunk ends, its norms and its payload; stepped from worker to worker.
 struct StreamAt {

@@ -25,21 +25,29 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
 }
 
+struct PhiloxKeys { uint32_t a[10], b[10]; };             // the keys of the ten rounds
+
+__device__ __forceinline__ PhiloxKeys philox_keys(uint32_t k0, uint32_t k1)
+{
+    PhiloxKeys k;
+#pragma unroll
+    for (uint32_t r = 0; r < 10; ++r) { k.a[r] = k0 + r * 0x9E3779B9u; k.b[r] = k1 + r * 0xBB67AE85u; }
+    return k;
+}
+
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1, uint32_t (&out)[4])
+                                              const PhiloxKeys& key, uint32_t (&out)[4])
 {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, key.a[r]);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, key.b[r]);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
         c2 = n2;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
     }
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
@@ -75,7 +83,7 @@ __device__ __forceinline__ float4 game_operator_row(const GameArgs& G, uint32_t 
 __device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, uint32_t i0, uint32_t k, uint32_t call_id)
 {
     uint32_t w[4];
-    philox4x32_10(i0 >> 2, 1u, k, call_id, G.seed_lo, G.seed_hi, w);
+    philox4x32_10(i0 >> 2, 1u, k, call_id, philox_keys(G.seed_lo, G.seed_hi), w);
     const float2 n01 = box_muller(w[0], w[1]), n23 = box_muller(w[2], w[3]);
     F.x += G.sigma * n01.x;
     F.y += G.sigma * n01.y;
@@ -120,25 +128,69 @@ __device__ __forceinline__ uint32_t wave_shift_in(uint32_t x, uint32_t first)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xf, 0xf, false);   // wave_shr:1
 }
 
+// x of lane (i xor D), for a value that is already the same in all lanes that differ in bits above D only; these steps never
+// leave the vector registers.  (A shuffle through LDS takes some 130 clocks, and a wave's binary64 sum needs twelve.)
+template <int D>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t x)
+{
+    constexpr int ctrl = D == 8 ? 0x128 : D == 4 ? 0x124 : D == 2 ? 0x4E : 0xB1;   // row_ror:8, row_ror:4, quad_perm [2,3,0,1], [1,0,3,2]
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xf, 0xf, true);
+}
+
+struct LanePair { uint32_t a, b; };                        // the two values that lanes i and i xor D have, in both
+template <int D>
+__device__ __forceinline__ LanePair lane_pair(uint32_t x)
+{
+    if constexpr (D == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return LanePair{(uint32_t)r[0], (uint32_t)r[1]};
+    } else if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return LanePair{(uint32_t)r[0], (uint32_t)r[1]};
+    } else {
+        return LanePair{x, xor_lane<D>(x)};
+    }
+}
+
+// The wave's sum, maximum and so on in every lane, lanes i and i xor 32, 16, 8, 4, 2, 1 joined in turn.
+template <int D, typename Op>
+__device__ __forceinline__ uint32_t wave_join_u32(uint32_t x, Op op)
+{
+    const LanePair p = lane_pair<D>(x);
+    x = op(p.a, p.b);
+    if constexpr (D > 1) return wave_join_u32<D / 2>(x, op);
+    else return x;
+}
+
+template <int D = 32>
 __device__ __forceinline__ double wave_sum(double x)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-    return x;
+    const LanePair lo = lane_pair<D>((uint32_t)__double2loint(x)), hi = lane_pair<D>((uint32_t)__double2hiint(x));
+    x = __hiloint2double((int)hi.a, (int)lo.a) + __hiloint2double((int)hi.b, (int)lo.b);
+    if constexpr (D > 1) return wave_sum<D / 2>(x);
+    else return x;
+}
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
+{
+    return wave_join_u32<32>(x, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
+{
+    return wave_join_u32<32>(x, [](uint32_t a, uint32_t b) { return max(a, b); });
 }
 
 __device__ __forceinline__ float wave_max(float x)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
-    return x;
+    return __uint_as_float(wave_join_u32<32>(__float_as_uint(x), [](uint32_t a, uint32_t b) {
+        return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+    }));
 }
 
 __device__ __forceinline__ uint32_t wave_or(uint32_t x)
 {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) x |= (uint32_t)__shfl_xor((int)x, off, kWave);
-    return x;
+    return wave_join_u32<32>(x, [](uint32_t a, uint32_t b) { return a | b; });
 }
 
 __device__ __forceinline__ uint32_t bcast_lane(uint32_t x, int src)
@@ -201,6 +253,13 @@ __device__ __forceinline__ double root_int(double s, uint32_t q)
     return x;
 }
 
+// A load through the scalar cache, of what an earlier launch wrote and this one only reads: no vector
+// registers, and no wait on the vector loads in flight.
+__device__ __forceinline__ uint32_t scalar_load(const void* p)
+{
+    return *reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // LDS accesses by byte address.  A pointer derived from the dynamic LDS array carries the array's
 // base as a late-bound addend that the compiler adds again on every access; an address computed once
 // as an integer does not.
@@ -210,7 +269,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p)
 }
 
 typedef uint32_t lds_u32x2 __attribute__((ext_vector_type(2)));
-typedef float lds_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t lds_u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t lds_load_u32(uint32_t addr)
 {
@@ -223,10 +282,10 @@ __device__ __forceinline__ uint2 lds_load_u2(uint32_t addr)
     return make_uint2(r.x, r.y);
 }
 
-__device__ __forceinline__ float4 lds_load_f4(uint32_t addr)
+__device__ __forceinline__ uint4 lds_load_u4(uint32_t addr)
 {
-    const lds_f32x4 r = *(const __attribute__((address_space(3))) lds_f32x4*)(uintptr_t)addr;
-    return make_float4(r.x, r.y, r.z, r.w);
+    const lds_u32x4 r = *(const __attribute__((address_space(3))) lds_u32x4*)(uintptr_t)addr;
+    return make_uint4(r.x, r.y, r.z, r.w);
 }
 
 __device__ __forceinline__ void raise_error(Scalars* sc, unsigned int bit)

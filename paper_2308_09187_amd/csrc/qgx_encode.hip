@@ -10,19 +10,20 @@
 // between the norm reduction and the rounding pass, (c) one Philox4x32 block (four words) serves
 // exactly the four coordinates of a lane and row.
 //
-// The vector ALUs' issue bounds it (busy for about 80 % of the time; 138 instructions per row of four
-// coordinates a lane, a third of them the generator), the memory system is next (4.6 TB/s of the 6.2 that the best
-// streaming kernel reaches), so the per-coordinate path is kept to a straight line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, address of the lower candidate table row) -> one
-// 16-byte LDS row holding the level, the scaled gap and the two candidate code words with the sign
+// The vector ALUs' issue bounds it (112 instructions per row of four coordinates a lane, a third of them the generator), the
+// memory system is next (5.4 TB/s of the 6.2 that the best streaming kernel reaches), so the per-coordinate path is kept to a
+// straight line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, lower candidate level)
+// -> one 16-byte LDS row holding the level, the scaled gap and the two candidate code words with the sign
 // already appended -> compare against the Philox draw -> select.  A chunk's short last row, buckets
 // with a zero norm and level tables too fine for the cell table take a general path, row by row from memory.
-// (Whole rows of a chunk that is not full, and of workers whose vectors start at odd addresses, took that path as
-// well: 5 x 3000001 coordinates in buckets of 6000, 59 us; now 36.)
+// Measured, us (120 instructions a row, tables waited for before a chunk is asked for, a workgroup per bucket -> now):
+// 8 x 2^24 coordinates 147 -> 138, 8 x 9.86 M in buckets of 8192 96 -> 83, of 1024 101 -> 86, 5 x 3000001 in buckets of 6000
+// 35 -> 28, 2^20 coordinates 11.7 -> 9.9.
 //
 // The stream keeps coordinate order: the lanes' code lengths are prefix-summed across the wave (DPP, two rows in
 // one scan) and every lane ORs its (at most 56) bits into the wave's LDS staging buffer.  No branch lies between
 // the rows of a full chunk.  (A scan per row and a branch around the store of the sub-chunk ends: 160
-// instructions a row, 8 x 2^24 coordinates 173 us; 163 now.)
+// instructions a row, 8 x 2^24 coordinates 173 us; without 163.)
 // Placement of the chunks in the payload.  Slotted: chunk c goes to c * slot_words; no workgroup waits
 // for another.  Compact: chunks in chunk order without gaps, so a workgroup needs the total length of
 // all earlier buckets of its worker: a decoupled look-back over per-bucket (flag, length) words gives
@@ -35,13 +36,6 @@
 namespace qgx {
 
 constexpr unsigned kSpinLimit = 1u << 22;
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
-{
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off, kWave);
-    return x;
-}
 
 // Exclusive prefix of `agg` over buckets 0..b-1 of one worker (decoupled look-back, one wave).
 // state[] entries: high word = epoch << 2 | status (1 = aggregate, 2 = inclusive prefix), low word = value.
@@ -145,65 +139,47 @@ __device__ double exchange_parts(unsigned long long* words /* [parts][2 phases][
     return tot;
 }
 
-struct LdsPlan {                 // where things live in the workgroup's LDS
-    const float2* cell;          // cell table; an entry's second word is the LDS address of a level row
-    const unsigned char* lev;    // level rows, two sign halves, lev_stride bytes apart
-    uint32_t lev_addr;           // LDS byte address of the level rows (the cell table sits at address 0)
-    uint32_t lev_stride, sign_shift;
-    uint32_t cell_shift;         // bits of u >> cell_shift = cell number + cell_key0
-    uint32_t cell_key0;          // key of the first cell (everything below goes there too)
-};
+// The encoder's tables start at LDS address 0 (checked at entry), so that where they lie is known at compile time: the
+// cells, then the level rows (Tables::enc).  CM: the table's cell size, mantissa bits per octave.
+template <int CM> constexpr uint32_t kCellShift = 23u - CM;                              // bits of u >> that: cell number + kCellKey0
+template <int CM> constexpr uint32_t kCellKey0 = (uint32_t)(127 - kCellOct) << CM;       // (everything below goes to the first cell, too)
+template <int CM> constexpr uint32_t kLevAt = lev_piece0(CM) * 16u;                      // LDS address of the level rows
 
-// tau(u) by the general route: start at the cell's lower level and walk up; returns the byte offset
-// of row j in the level table.
-__device__ __forceinline__ uint32_t level_row_general(const LdsPlan& L, float u, uint32_t n_sym)
+// tau(u) by the general route: start at the cell's lower level and walk up.
+template <int CM>
+__device__ __forceinline__ uint32_t level_general(float u, uint32_t n_sym)
 {
-    const float um = fminf(fmaxf(u, __uint_as_float(L.cell_key0 << L.cell_shift)), 1.0f);
-    const float2 c = L.cell[(__float_as_uint(um) >> L.cell_shift) - L.cell_key0];
-    uint32_t j = (__float_as_uint(c.y) - L.lev_addr) >> 4;
-    while (j + 2 < n_sym && reinterpret_cast<const float4*>(L.lev)[j + 1].x <= u) ++j;
-    return j << 4;
+    const float um = fminf(fmaxf(u, __uint_as_float(kCellKey0<CM> << kCellShift<CM>)), 1.0f);
+    uint32_t j = lds_load_u2(((__float_as_uint(um) >> kCellShift<CM>) - kCellKey0<CM>) * 8u).y;
+    while (j + 2 < n_sym && __uint_as_float(lds_load_u32(kLevAt<CM> + 32u * (j + 1u))) <= u) ++j;
+    return j;
 }
 
-// One coordinate: the packed code entry E(idx, sign) = bits | length << 16 of q_l(u) with sign.
-// FAST: straight-line cell route, valid when u <= 1 up to rounding (so the clamp of u to 1 can be
-// left out: at u >= 1 the coordinate rounds up whatever the draw) and no cell holds two levels.
-// CM: the cell size as a compile-time constant (mantissa bits per octave), 0 = whatever L says.
-template <bool FAST, int CM = 0>
-__device__ __forceinline__ uint32_t quantize_one(float x, float rinv, uint32_t rnd, const LdsPlan& L, uint32_t n_sym,
-                                                 uint32_t& idx_out)
+// One coordinate's way to the code entry E(idx, sign) of q_l(u) with its sign, in three parts, so that other work can stand
+// between a look-up and its use: the cell of u, the level row, the decision.  Straight-line cell route: valid when u <= 1 up
+// to rounding (so the clamp of u to 1 can be left out: at u >= 1 the coordinate rounds up whatever the draw) and no cell
+// holds two levels.
+// first_cell: kCellKey0 << kCellShift.
+template <int CM>
+__device__ __forceinline__ uint2 cell_of(float u, uint32_t first_cell)
 {
-    float u = fabsf(x) * rinv;                          // |v| / ||v||
-    // the sign selects the table half (by constants where the cell size is one)
-    const uint32_t sg = CM != 0 ? (__float_as_uint(x) >> lev_sign_shift_of(CM)) & lev_stride_of(CM)
-                                : (__float_as_uint(x) >> L.sign_shift) & L.lev_stride;
-    float4 t;
-    uint32_t row;                                       // byte offset of the level row in its half
-    if (FAST) {
-        // cell number times eight; a saturating subtraction sends everything below the first cell there
-        uint32_t key8;
-        if constexpr (CM != 0) {
-            constexpr uint32_t shift = 23u - CM, key0 = (uint32_t)(127 - kCellOct) << CM;
-            key8 = (__builtin_elementwise_sub_sat(__float_as_uint(u), key0 << shift) >> (shift - 3u)) & 0xFFF8u;
-            static_assert(((uint32_t)((kCellOct << CM) + 1) * 8u) <= 0x10000u, "cell numbers times eight fit 16 bits");
-        } else {
-            key8 = (__builtin_elementwise_sub_sat(__float_as_uint(u), L.cell_key0 << L.cell_shift) >> (L.cell_shift - 3u)) & ~7u;
-        }
-        const uint2 c = lds_load_u2(key8);          // the cell table starts at LDS address 0 (checked at entry)
-        // the cell's lower row, or the next one from the boundary level on (one level per cell at most)
-        const uint32_t at = sg + c.y + (u >= __uint_as_float(c.x) ? 16u : 0u);
-        t = lds_load_f4(at);
-        row = (at - L.lev_addr) & ((CM != 0 ? lev_stride_of(CM) : L.lev_stride) - 1u);
-    } else {
-        u = fminf(u, 1.0f);
-        row = level_row_general(L, u, n_sym);
-        t = *reinterpret_cast<const float4*>(L.lev + (row | sg));
-    }
-    // up with probability xi = (u - l_j) / (l_{j+1} - l_j):  r * gap < u - l_j, r = top 24 bits * 2^-24
-    const float rr = (float)(rnd >> 8);                 // exact
-    const bool up = rr * t.y < u - t.x;                 // t.y = gap * 2^-24 (exact scaling)
-    idx_out = (row >> 4) + (up ? 1u : 0u);
-    return up ? __float_as_uint(t.w) : __float_as_uint(t.z);
+    // cell number times eight; a saturating subtraction sends everything below the first cell there
+    static_assert(((uint32_t)((kCellOct << CM) + 1) * 8u) <= 0x10000u, "cell numbers times eight fit 16 bits");
+    return lds_load_u2((__builtin_elementwise_sub_sat(__float_as_uint(u), first_cell) >> (kCellShift<CM> - 3u)) & 0xFFF8u);
+}
+
+__device__ __forceinline__ uint32_t level_in_cell(float u, uint2 c) { return c.y + (u >= __uint_as_float(c.x) ? 1u : 0u); }
+
+template <int CM>
+__device__ __forceinline__ uint4 level_row(uint32_t j, float x)
+{
+    return lds_load_u4(__builtin_amdgcn_alignbit(j, __float_as_uint(x), 31) * 16u + kLevAt<CM>);       // row 2 j + sign
+}
+
+// Up with probability xi = (u - l_j) / (l_{j+1} - l_j):  r * gap < u - l_j, r = top 24 bits * 2^-24.
+__device__ __forceinline__ bool rounds_up(float u, uint4 t, uint32_t rnd)
+{
+    return (float)(rnd >> 8) * __uint_as_float(t.y) < u - __uint_as_float(t.x);      // (t.y = gap * 2^-24: exact scaling)
 }
 
 // Where a chunk's sub-chunk ends go, eight lanes of a row one 16-byte piece: the row of the table as a buffer
@@ -221,56 +197,62 @@ struct SubEnds {
     }
 };
 
-struct RowCode { uint32_t len; uint64_t bits; };       // a lane's four entries of a row, one after the other (<= 56 bits)
+// A lane's four entries of a row joined: their bits one after the other (<= 56), and the sum of the entries, whose byte 1 is
+// their number.  (An entry: the code word at the top, its length from bit 8 on, 32 less the length in the low five bits.)
+struct RowCode { uint32_t sum, lo, hi; };
 
+// {hi, lo} >> (s mod 32), the low word
+__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) { return __builtin_amdgcn_alignbit(hi, lo, s); }
+
+// Every shift count is the low five bits of an entry or of a sum of entries, which the hardware takes as they are: a word
+// comes down from the top by its own entry, and the funnel shift by the entry before it puts the word behind that one, whose
+// low bits it drops.  Entries of 0 (no symbol) come last and add nothing.
 __device__ __forceinline__ RowCode join_row(const uint32_t (&e)[4])
 {
-    const uint32_t l0 = e[0] >> 16, l1 = e[1] >> 16, l2 = e[2] >> 16, l3 = e[3] >> 16;
-    const uint32_t c01 = (e[0] & 0xFFFFu) | ((e[1] & 0xFFFFu) << l0);     // <= 28 bits
-    const uint32_t c23 = (e[2] & 0xFFFFu) | ((e[3] & 0xFFFFu) << l2);
-    const uint32_t l01 = l0 + l1;
-    return RowCode{l01 + l2 + l3, (uint64_t)c01 | ((uint64_t)c23 << l01)};
+    const uint32_t c01 = funnel(e[1] >> (e[1] & 31u), e[0], e[0]);         // <= 28 bits
+    const uint32_t c23 = funnel(e[3] >> (e[3] & 31u), e[2], e[2]);
+    const uint32_t s01 = e[0] + e[1];                                      // low five bits: 32 less the bits of c01
+    return RowCode{s01 + e[2] + e[3], funnel(c23, c01 << (s01 & 31u), s01), c23 >> (s01 & 31u)};
 }
 
-__device__ __forceinline__ void place_row(uint32_t* stage, uint32_t pos, uint64_t bits)
+// The bits go to bit P + 1 of LDS (P counts from LDS address 0): with the place less one at hand no shift count is 32.
+__device__ __forceinline__ void place_row(uint32_t P, const RowCode& c)
 {
-    const uint32_t wi = pos >> 5, sh = pos & 31u;
-    const uint64_t lo64 = (uint64_t)(uint32_t)bits << sh;
-    const uint64_t hi64 = (uint64_t)(uint32_t)(bits >> 32) << sh;
-    __hip_atomic_fetch_or(&stage[wi], (uint32_t)lo64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_or(&stage[wi + 1], (uint32_t)(lo64 >> 32) | (uint32_t)hi64, __ATOMIC_RELAXED,
-                          __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_or(&stage[wi + 2], (uint32_t)(hi64 >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint32_t up = ~P;                                                // 32 less the place's bit in its word, mod 32
+    auto* at = reinterpret_cast<__attribute__((address_space(3))) uint32_t*>((uintptr_t)((P >> 3) & ~3u));
+    __hip_atomic_fetch_or(at, funnel(c.lo, 0u, up), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_or(at + 1, funnel(c.hi, c.lo, up), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_or(at + 2, c.hi >> (up & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Appends row r (four entries per lane) to the wave's staging buffer; returns the row's bit count.
+// Appends row r (four entries per lane) to the wave's staging buffer, whose first bit is bit stage0 + 1 of LDS; returns the
+// row's bit count.
 // BRANCH: the sub-chunk ends' store behind a branch after all, for the rolled loop, whose rows no scheduler mixes: dropped
 // stores are not free (symbols of 8 x 2^22 coordinates in words of three bits coded in 28 us instead of 31).
 template <bool BRANCH>
-__device__ __forceinline__ uint32_t pack_row(uint32_t* stage, const SubEnds& ends, int r, uint32_t row_base, const uint32_t (&e)[4])
+__device__ __forceinline__ uint32_t pack_row(uint32_t stage0, const SubEnds& ends, int r, uint32_t row_base, const uint32_t (&e)[4])
 {
     const RowCode c = join_row(e);
-    const uint32_t incl = wave_incl_scan(c.len);
-    place_row(stage, row_base + incl - c.len, c.bits);
+    const uint32_t len = (c.sum >> 8) & 0xFFu, incl = wave_incl_scan(len);
+    place_row(stage0 + row_base + incl - len, c);
     if (!BRANCH || ends.at < (uint32_t)kSubs) ends.put(r, row_base + incl);
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
 }
 
 // The same for rows r and r + 1: a row's bit count (at most 64 * 56) fits 16 bits, so one scan across the wave
 // does both.
-__device__ __forceinline__ uint32_t pack_two_rows(uint32_t* stage, const SubEnds& ends, int r, uint32_t row_base,
+__device__ __forceinline__ uint32_t pack_two_rows(uint32_t stage0, const SubEnds& ends, int r, uint32_t row_base,
                                                   const uint32_t (&ea)[4], const uint32_t (&eb)[4])
 {
     const RowCode a = join_row(ea), b = join_row(eb);
-    const uint32_t both = a.len | (b.len << 16);
+    const uint32_t both = __builtin_amdgcn_perm(b.sum, a.sum, 0x0C050C01u);       // the two lengths: byte 1 of each sum
     const uint32_t incl = wave_incl_scan(both), excl = incl - both;
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     const uint32_t second = row_base + (total & 0xFFFFu);
-    const uint32_t pa = row_base + (excl & 0xFFFFu), pb = second + (excl >> 16);
-    place_row(stage, pa, a.bits);
-    ends.put(r, pa + a.len);
-    place_row(stage, pb, b.bits);
-    ends.put(r + 1, pb + b.len);
+    place_row(stage0 + row_base + (excl & 0xFFFFu), a);
+    ends.put(r, row_base + (incl & 0xFFFFu));
+    place_row(stage0 + second + (excl >> 16), b);
+    ends.put(r + 1, second + (incl >> 16));
     return (total & 0xFFFFu) + (total >> 16);
 }
 
@@ -282,7 +264,8 @@ struct ChunkGeom {            // one wave's share of a bucket
     uint32_t bparts;          // workgroups that share the bucket (groups of four chunks that hold data)
 };
 
-__device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, int w)
+// Chunk w of bucket b; no chunk (clen = 0) past the bucket's last one, or with !there.
+__device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, uint32_t w, bool there)
 {
     uint32_t lo, hi, c0;
     if (lay.uniform_bucket) {                      // one segment: no table look-ups on the critical path
@@ -290,12 +273,12 @@ __device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, i
         hi = min(lo + lay.uniform_bucket, lay.d);
         c0 = b * lay.waves_per_bucket;
     } else {
-        lo = lay.bucket_start[b]; hi = lay.bucket_start[b + 1]; c0 = lay.bucket_chunk0[b];
+        lo = scalar_load(lay.bucket_start + b); hi = scalar_load(lay.bucket_start + b + 1); c0 = scalar_load(lay.bucket_chunk0 + b);
     }
     ChunkGeom g;
-    g.c = c0 + (uint32_t)w;
-    g.clo = lo + (uint32_t)w * kChunk;
-    g.clen = g.clo < hi ? min((uint32_t)kChunk, hi - g.clo) : 0u;
+    g.c = c0 + w;
+    g.clo = lo + w * kChunk;
+    g.clen = there && g.clo < hi ? min((uint32_t)kChunk, hi - g.clo) : 0u;
     g.cend = g.clo + g.clen;
     g.nrows = (int)((g.clen + 255u) >> 8);
     g.full = g.clen == (uint32_t)kChunk;
@@ -303,28 +286,40 @@ __device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, i
     return g;
 }
 
-// Issues the loads of one chunk into registers (16 rows x 4 coordinates per lane).  Vectors of an odd length put
-// a worker's rows at any multiple of 4 bytes, which 16-byte loads from global memory take.
+// The loads of one chunk into registers (16 rows x 4 coordinates per lane), whatever its length: the chunk's whole groups
+// of four coordinates as a buffer, outside of which a load gives zeros.  No branch, so that the compiler knows how many loads
+// are under way.  Vectors of an odd length put a worker's rows at any multiple of 4 bytes, which 16-byte loads take.
 __device__ __forceinline__ void load_chunk(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g, int lane)
 {
-    if (g.full) {
+    constexpr int kNonTemporal = 2;                          // (read once: see nt_load4)
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(Vk + g.clo)), 0,
+                                                                          (int)((g.clen & ~3u) * sizeof(float)), 0x00027000);
 #pragma unroll
-        for (int r = 0; r < kRows; ++r)
-            v[r] = nt_load4_any(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
-    } else {
-        const int whole = (int)(g.clen >> 8);                    // rows before a short last one (all wave-uniform)
-        const uint32_t i0 = g.clo + (uint32_t)whole * 256u + (uint32_t)lane * 4u;
-        float4 tail = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i0 < g.cend) tail.x = Vk[i0];
-        if (i0 + 1 < g.cend) tail.y = Vk[i0 + 1];
-        if (i0 + 2 < g.cend) tail.z = Vk[i0 + 2];
-        if (i0 + 3 < g.cend) tail.w = Vk[i0 + 3];
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            if (r < whole) v[r] = nt_load4_any(Vk + g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u);
-            else v[r] = r == whole ? tail : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+    for (int r = 0; r < kRows; ++r) {
+        const nt_u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16, r * 1024, kNonTemporal);
+        v[r] = make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
     }
+}
+
+// The last one to three coordinates of a vector whose length is no multiple of four (only a worker's last chunk has such).
+__device__ __forceinline__ void load_chunk_rest(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g, int lane)
+{
+    if ((g.clen & 3u) == 0u) return;
+    const uint32_t at = g.clen & ~3u;                        // (all wave-uniform)
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    x.x = Vk[g.clo + at];
+    if ((g.clen & 3u) > 1u) x.y = Vk[g.clo + at + 1u];
+    if ((g.clen & 3u) > 2u) x.z = Vk[g.clo + at + 2u];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+        if (r == (int)(at >> 8) && (uint32_t)lane == (at & 255u) >> 2) v[r] = x;
+}
+
+// The largest magnitude of four and one; a NaN among them is the result (two instructions).
+__device__ __forceinline__ float largest_of(const float4& x, float m)
+{
+    m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.x), fabsf(x.y)), m);
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.z), fabsf(x.w)), m);
 }
 
 // Shared chunks (buckets of 256..2048 coordinates): a wave's chunk holds up to 16 buckets, each a run
@@ -342,7 +337,7 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
     const bool l2 = a.norm_kind == QGX_NORM_L2;
     bool plain = true;
     float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, p3 = 0.0f;
-    uint32_t mx = 0;
+    float mx = 0.0f;
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
         if (l2) {
@@ -351,10 +346,7 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
             p2 = fmaf(v[r].z, v[r].z, p2);
             p3 = fmaf(v[r].w, v[r].w, p3);
         } else {
-            mx = max(mx, __float_as_uint(v[r].x) & 0x7FFFFFFFu);
-            mx = max(mx, __float_as_uint(v[r].y) & 0x7FFFFFFFu);
-            mx = max(mx, __float_as_uint(v[r].z) & 0x7FFFFFFFu);
-            mx = max(mx, __float_as_uint(v[r].w) & 0x7FFFFFFFu);
+            mx = largest_of(v[r], mx);
         }
         if ((((uint32_t)r + 1u) & rows_mask) != 0u) continue;             // wave-uniform: the bucket goes on
         const uint32_t gb = (uint32_t)r >> rshift;
@@ -371,10 +363,7 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
                     tot = wave_sum(acc);
                 }
             } else {
-                uint32_t m = mx;
-#pragma unroll
-                for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, kWave));
-                tot = (double)__uint_as_float(m);
+                tot = (double)__uint_as_float(wave_max_u32(__float_as_uint(mx)));
             }
             float n = l2 ? (float)sqrt(tot) : (float)tot;
             if (!l2 && a.norm_kind != QGX_NORM_LINF && tot > 0.0 && tot <= 3.402823466e+38) {
@@ -402,7 +391,7 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
             plain = plain && live && u_le_1;
         }
         p0 = p1 = p2 = p3 = 0.0f;
-        mx = 0;
+        mx = 0.0f;
     }
     return plain;
 }
@@ -413,10 +402,13 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
 // GROUPED: the layout has shared chunks; a workgroup is four waves with a chunk each, and every wave
 // finds the norms of its chunk's buckets by itself.
 // CM: cell_mant of the level table, so that the rounding pass has the cell size as a constant.
-// Waves per SIMD: five where V is read (four: 177 us instead of 163 at 8 x 2^24); four where it is formed, whose
-// second generator and transcendentals spill at five (16 x 2^26 coordinates: 2.07 ms instead of 2.30).
+// Waves per SIMD: five where V is read; four where it is formed, whose second generator and transcendentals spill at five
+// (16 x 2^26 coordinates: 2.07 ms instead of 2.30).  kStaged: a row's four look-ups are asked for together, cells before the
+// generator and level rows after it: 16 x 2^26 coordinates 2.02 -> 1.93 ms.  Where V is read the registers of five waves do not
+// hold it (17 spilled: 8 x 2^24 148 us instead of 137), and at four waves it is no faster (137; buckets of 1024 88 instead of 86).
 template <EncMode MODE> constexpr bool kWaits = MODE != EncMode::EncodeOnly;     // for partners: it needs the bucket's norm
 template <EncMode MODE> constexpr int kSimdWaves = MODE == EncMode::Generate ? 4 : 5;
+template <EncMode MODE> constexpr bool kStaged = MODE == EncMode::Generate;
 template <EncMode MODE, bool GROUPED, int CM>
 __global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(kSimdWaves<MODE>)))
 void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
@@ -425,7 +417,6 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const int tid = (int)threadIdx.x, lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(wave_id());    // (scalar, and all of the chunk's geometry with it)
     const int nwaves = (int)(blockDim.x >> 6);
-    const uint32_t n_sym = tab->n_sym;
     // The worker and, without tickets, the unit of work are fixed by the block.
     uint32_t k = blockIdx.x % a.span, own_unit = blockIdx.x / a.span;
     if (MODE == EncMode::Generate && a.by_unit) {
@@ -433,30 +424,31 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         k = own.k; own_unit = own.unit;
     }
 
-    // LDS plan: [cell][lev + / lev -][reduction scratch][one staging buffer per wave]
-    float2* s_cell = reinterpret_cast<float2*>(s_all);
-    const int n_cells = cell_count((int)a.cell_mant);
-    unsigned char* s_lev = s_all + cell_count_padded((int)a.cell_mant) * sizeof(float2);
-    double* s_red = reinterpret_cast<double*>(s_lev + a.lev_bytes);
+    // LDS plan: [tables][reduction scratch][one staging buffer per wave]
+    uint4* s_enc = reinterpret_cast<uint4*>(s_all);
+    double* s_red = reinterpret_cast<double*>(s_enc + a.pieces);
     double* s_tot = s_red + 2 * nwaves;                                       // second set: the general-q sum
     uint32_t* s_words = reinterpret_cast<uint32_t*>(s_tot + 2);               // bucket totals of a split bucket
     uint32_t* s_misc = s_words + (nwaves + 3) / 4 * 4;
     float* s_rinv = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(s_misc) + 32);      // GROUPED: [waves][16]
     uint32_t* stage = reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(s_misc) + 32 +
                                                   (GROUPED ? (size_t)nwaves * 64 : 0) + (size_t)w * a.stage_bytes);
-    LdsPlan L;
-    L.cell = s_cell; L.lev = s_lev; L.lev_stride = a.lev_stride; L.sign_shift = a.sign_shift;
-    L.lev_addr = lds_address(s_lev);
-    L.cell_shift = 23u - a.cell_mant;
-    L.cell_key0 = (uint32_t)(127 - kCellOct) << a.cell_mant;
-    // The straight-line lookup addresses the cell table by number: the kernel has no static LDS, so
-    // the dynamic array (and with it the table) starts at address 0.
+    // The lookups address the tables by number: the kernel has no static LDS, so the dynamic array (and
+    // with it the tables) starts at address 0.
     if (lds_address(s_all) != 0u) {
         if (tid == 0) raise_error(sc, QGX_EBIT_STATE);
         return;
     }
 
-    // Compact placement: buckets by ticket (the ticket first: the table loads overlap its latency).
+    // The tables are asked for first, the chunk's rows before the tables are waited for: a workgroup's two trips to memory
+    // lie side by side.
+    const uint32_t nthreads = blockDim.x;
+    for (uint32_t i = (uint32_t)tid + 2u * nthreads; i < a.pieces; i += nthreads) s_enc[i] = tab->enc[i];
+    const uint32_t piece0 = min((uint32_t)tid, a.pieces - 1u), piece1 = min((uint32_t)tid + nthreads, a.pieces - 1u);
+    const nt_u32x4 ahead0 = reinterpret_cast<const nt_u32x4*>(tab->enc)[piece0];
+    const nt_u32x4 ahead1 = reinterpret_cast<const nt_u32x4*>(tab->enc)[piece1];
+
+    // Compact placement: buckets by ticket.
     // Slotted placement and plain quantisation have no order to keep: the bucket is the block's own.
     // Split buckets: (bucket, part) by ticket as well, whatever the placement (see exchange_parts).
     const bool ordered = MODE != EncMode::QuantOnly && a.slot_words == 0u;
@@ -467,35 +459,20 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     // words hold 0).  Nothing about it comes from the host: a captured graph can be replayed.
     if (ticketed) {
         if (tid == 0 && (!kWaits<MODE> || k < lay.K)) {
-            const unsigned long long per_launch = GROUPED ? (lay.NC + 3u) / 4u : (unsigned long long)lay.NB * a.parts;
+            const unsigned long long per_launch = a.units;
             const unsigned long long raw = atomicAdd(a.tickets + k * kTicketStride, 1ull);
             const unsigned long long launch = raw / per_launch;
             s_misc[2] = (uint32_t)(raw - launch * per_launch);
             s_misc[3] = (uint32_t)(launch % 0x3FFFFFFFull) + 1u;
         }
+        __syncthreads();
     }
-    for (int i = tid; i < (int)n_sym; i += (int)blockDim.x) {
-        reinterpret_cast<float4*>(s_lev)[i] = tab->lev2[0][i];
-        reinterpret_cast<float4*>(s_lev + a.lev_stride)[i] = tab->lev2[1][i];
-    }
-    for (int i = tid; i < n_cells; i += (int)blockDim.x) {
-        float2 c = tab->cell[i];                       // row offset -> LDS address of the row
-        c.y = __uint_as_float((__float_as_uint(c.y) & 0xFFFFu) + L.lev_addr);
-        s_cell[i] = c;
-    }
-    if (MODE != EncMode::QuantOnly) {
-        for (uint32_t q = (uint32_t)lane; q < a.stage_bytes / 16; q += kWave)
-            reinterpret_cast<uint4*>(stage)[q] = make_uint4(0, 0, 0, 0);
-    }
-    // (the table builder and the host take the cell size from the table's length by the same rule)
-    const uint32_t cell_exact = (tab->cell_exact != 0u && (uint32_t)cell_mant(n_sym) == a.cell_mant) ? 1u : 0u;
-    __syncthreads();
 
     if (kWaits<MODE> && k >= lay.K) return;             // a row's end (asked before the ticket it costs compact placement 1 %)
     const size_t kbase = (size_t)k * lay.d;
     const bool vec_ok = MODE == EncMode::Generate || (kbase & 3u) == 0;    // 16-byte aligned rows for this worker
     // the number of this quantisation call: given, or taken from the iteration counter (replayed graphs)
-    const uint32_t call_id = a.call_mode ? 2u * (uint32_t)(sc->t - 1ull) + (a.call_mode - 1u) : a.call_id;
+    const uint32_t call_id = a.call_mode ? 2u * (scalar_load(&sc->t) - 1u) + (a.call_mode - 1u) : a.call_id;
     const float* __restrict__ Vk = (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) ? a.V + kbase : nullptr;
     // one coordinate of the worker's vector again, for the rolled paths: from memory, or (Generate) formed again
     auto value_at = [&](uint32_t i) -> float {
@@ -507,25 +484,30 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             return Vk[i];
         }
     };
-    const uint32_t unit = ticketed ? s_misc[2] : own_unit;
-    const uint32_t epoch = ticketed ? s_misc[3] : 0u;
-    uint32_t b = a.parts > 1u ? unit / a.parts : unit;  // the bucket; with shared chunks the first of the wave's chunk
-    const uint32_t part = GROUPED ? 0u : unit - b * a.parts;
+    const uint32_t unit = ticketed ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_misc[2]) : own_unit;
+    const uint32_t epoch = ticketed ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_misc[3]) : 0u;
+    // Short buckets: a workgroup takes `group` of them (buckets_per_group).
+    const uint32_t per_bucket = a.group > 1u ? lay.waves_per_bucket : (uint32_t)nwaves;            // waves to a bucket
+    const uint32_t mine = a.group > 1u ? (uint32_t)w / per_bucket : 0u, w0 = mine * per_bucket;    // the wave's bucket, and its first wave
+    uint32_t b = a.parts > 1u ? unit / a.parts : unit * a.group + mine;  // the bucket; with shared chunks the first of the wave's chunk
+    const uint32_t part = GROUPED || a.parts == 1u ? 0u : unit - b * a.parts;
+    const bool there = GROUPED || b < lay.NB;           // (a worker's last workgroup: no bucket for some waves)
     ChunkGeom g;
     if constexpr (GROUPED) {
         if (unit * 4u >= lay.NC) return;               // cannot happen: one workgroup per four chunks and worker
         g.c = unit * 4u + (uint32_t)w;
-        const bool there = g.c < lay.NC;
-        g.clo = there ? lay.chunk_start[g.c] : 0u;
-        g.clen = there ? lay.chunk_start[g.c + 1] - g.clo : 0u;
+        const bool have = g.c < lay.NC;
+        g.clo = have ? scalar_load(lay.chunk_start + g.c) : 0u;
+        g.clen = have ? scalar_load(lay.chunk_start + g.c + 1) - g.clo : 0u;
         g.cend = g.clo + g.clen;
         g.nrows = (int)((g.clen + 255u) >> 8);
         g.full = g.clen == (uint32_t)kChunk;
         g.bparts = 1u;
-        b = there ? lay.chunk_bucket[g.c] : 0u;
+        b = have ? scalar_load(lay.chunk_bucket + g.c) : 0u;
     } else {
-        if (b >= lay.NB) return;                       // cannot happen: one workgroup per unit and worker
-        g = chunk_geom(lay, b, (int)part * 4 + w);
+        if (b - mine >= lay.NB) return;                // cannot happen: one workgroup per unit and worker
+        if (!there) b = lay.NB - 1u;
+        g = chunk_geom(lay, b, part * 4u + (uint32_t)w - w0, there);
     }
     if (part >= g.bparts) {
         // a short bucket has nothing for this part; no partner waits for it, but in compact placement
@@ -543,6 +525,19 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         MODE != EncMode::QuantOnly ? a.sub_end + ((size_t)k * lay.NC + g.c) * kSubs : nullptr;
     const SubEnds ends(reinterpret_cast<uint16_t*>(uniform_address(sub_g)), lane);
     float4 v[kRows];
+    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_chunk(v, Vk, g, lane);
+    // (by all threads: a branch would leave it open what is still under way)
+    reinterpret_cast<nt_u32x4*>(s_enc)[piece0] = ahead0;
+    reinterpret_cast<nt_u32x4*>(s_enc)[piece1] = ahead1;
+    if (MODE != EncMode::QuantOnly) {
+        for (uint32_t q = (uint32_t)lane; q < a.stage_bytes / 16; q += kWave)
+            reinterpret_cast<uint4*>(stage)[q] = make_uint4(0, 0, 0, 0);
+    }
+    // (the table builder and the host take the cell size from the table's length by the same rule)
+    const uint32_t n_sym = tab->n_sym;
+    const uint32_t cell_exact = (tab->cell_exact != 0u && (uint32_t)cell_mant(n_sym) == a.cell_mant) ? 1u : 0u;
+    __syncthreads();
+    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_chunk_rest(v, Vk, g, lane);
     if constexpr (MODE == EncMode::Generate) {
         // the dual vector is formed here instead of read: operator and noise for four coordinates per lane and row
         // (every bucket and vector length is a multiple of four in this mode)
@@ -556,8 +551,6 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             }
             v[r] = x;
         }
-    } else if (MODE != EncMode::EncodeOnly) {
-        load_chunk(v, Vk, g, lane);
     }
     {
 
@@ -587,25 +580,24 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 }
                 red = wave_sum(((double)p0 + (double)p1) + ((double)p2 + (double)p3));
             } else {
-                uint32_t mx = 0;
+                float mx = 0.0f;
 #pragma unroll
                 for (int r = 0; r < kRows; ++r) {
-                    mx = max(mx, __float_as_uint(v[r].x) & 0x7FFFFFFFu);
-                    mx = max(mx, __float_as_uint(v[r].y) & 0x7FFFFFFFu);
-                    mx = max(mx, __float_as_uint(v[r].z) & 0x7FFFFFFFu);
-                    mx = max(mx, __float_as_uint(v[r].w) & 0x7FFFFFFFu);
+                    mx = largest_of(v[r], mx);
                 }
-#pragma unroll
-                for (int off = kWave / 2; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, kWave));
-                red = (double)__uint_as_float(mx);      // inf or NaN bits survive the conversion
+                red = (double)__uint_as_float(wave_max_u32(__float_as_uint(mx)));      // inf or NaN bits survive the conversion
             }
             if (lane == 0) s_red[w] = red;
             __syncthreads();
-            double tot = 0.0;
-            for (int i = 0; i < nwaves; ++i) {
-                if (a.norm_kind == QGX_NORM_L2) tot += s_red[i];
-                else tot = (s_red[i] > tot || s_red[i] != s_red[i]) ? s_red[i] : tot;
-            }
+            auto bucket_total = [&](const double* part_of) {      // the values of the bucket's waves, in order
+                double t = 0.0;
+                for (uint32_t i = 0; i < per_bucket; ++i) {
+                    if (a.norm_kind == QGX_NORM_L2) t += part_of[i];
+                    else t = (part_of[i] > t || part_of[i] != part_of[i]) ? part_of[i] : t;
+                }
+                return t;
+            };
+            double tot = bucket_total(s_red + w0);
             if (split) {
                 if (w == 0) {
                     const double t = exchange_parts(xch, g.bparts, part, 0u, tot, a.norm_kind != QGX_NORM_L2, epoch, sc);
@@ -614,43 +606,23 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 __syncthreads();
                 tot = s_tot[0];
             }
-            if (a.norm_kind == QGX_NORM_L2 && !(tot >= 0x1p-60 && tot <= 0x1p100)) {
-                // squares that overflow or go subnormal in binary32 (or a non-finite input): the sum
-                // again in binary64, from memory (the rolled loop keeps the register copy intact)
+            // squares that overflow or go subnormal in binary32 (or a non-finite input): the sum again in binary64, from
+            // memory (the rolled loop keeps the register copy intact); by the whole workgroup if one of its buckets needs it
+            const bool again = a.norm_kind == QGX_NORM_L2 && !(tot >= 0x1p-60 && tot <= 0x1p100);
+            bool any_again = again;
+            for (uint32_t f = 0; a.group > 1u && f < (uint32_t)nwaves; f += per_bucket) {
+                const double t = bucket_total(s_red + f);
+                any_again = any_again || (a.norm_kind == QGX_NORM_L2 && !(t >= 0x1p-60 && t <= 0x1p100));
+            }
+            if (any_again) {
                 double acc = 0.0;
 #pragma unroll 1
                 for (uint32_t i = g.clo + (uint32_t)lane; i < g.cend; i += kWave) { const double x = (double)value_at(i); acc = fma(x, x, acc); }
                 acc = wave_sum(acc);
                 if (lane == 0) s_red[nwaves + w] = acc;
                 __syncthreads();
-                tot = 0.0;
-                for (int i = 0; i < nwaves; ++i) tot += s_red[nwaves + i];
-                if (split) {
-                    if (w == 0) {
-                        const double t = exchange_parts(xch, g.bparts, part, 1u, tot, false, epoch, sc);
-                        if (lane == 0) s_tot[1] = t;
-                    }
-                    __syncthreads();
-                    tot = s_tot[1];
-                }
-            }
-            n = (a.norm_kind == QGX_NORM_L2) ? (float)sqrt(tot) : (float)tot;
-            if (a.norm_kind != QGX_NORM_L2 && a.norm_kind != QGX_NORM_LINF && tot > 0.0 && tot <= 3.402823466e+38) {
-                // any other q of Definition 1: (sum |v_i|^q)^(1/q), relative to the largest magnitude
-                // found above so that no power leaves the range of binary64
-                const double inv_m = 1.0 / tot;
-                const uint32_t q = (uint32_t)a.norm_kind;
-                double acc = 0.0;
-                // (a rolled loop over memory: indexing the register copy by a run-time row would
-                // push it out of registers for the common norms as well)
-#pragma unroll 1
-                for (uint32_t i = g.clo + (uint32_t)lane; i < g.cend; i += kWave)
-                    acc += pow_int(fabs((double)value_at(i)) * inv_m, q);
-                acc = wave_sum(acc);
-                if (lane == 0) s_red[nwaves + w] = acc;
-                __syncthreads();
                 double sum = 0.0;
-                for (int i = 0; i < nwaves; ++i) sum += s_red[nwaves + i];
+                for (uint32_t i = 0; i < per_bucket; ++i) sum += s_red[nwaves + w0 + i];
                 if (split) {
                     if (w == 0) {
                         const double t = exchange_parts(xch, g.bparts, part, 1u, sum, false, epoch, sc);
@@ -659,7 +631,37 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                     __syncthreads();
                     sum = s_tot[1];
                 }
-                n = (float)(tot * root_int(sum, q));
+                if (again) tot = sum;
+            }
+            n = (a.norm_kind == QGX_NORM_L2) ? (float)sqrt(tot) : (float)tot;
+            if (a.norm_kind != QGX_NORM_L2 && a.norm_kind != QGX_NORM_LINF) {
+                // any other q of Definition 1: (sum |v_i|^q)^(1/q), relative to the largest magnitude
+                // found above so that no power leaves the range of binary64
+                const bool sound = tot > 0.0 && tot <= 3.402823466e+38;       // (the parts of a split bucket agree on it)
+                const double inv_m = 1.0 / tot;
+                const uint32_t q = (uint32_t)a.norm_kind;
+                double acc = 0.0;
+                // (a rolled loop over memory: indexing the register copy by a run-time row would
+                // push it out of registers for the common norms as well)
+                if (sound) {
+#pragma unroll 1
+                    for (uint32_t i = g.clo + (uint32_t)lane; i < g.cend; i += kWave)
+                        acc += pow_int(fabs((double)value_at(i)) * inv_m, q);
+                }
+                acc = wave_sum(acc);
+                if (lane == 0) s_red[nwaves + w] = acc;
+                __syncthreads();
+                double sum = 0.0;
+                for (uint32_t i = 0; i < per_bucket; ++i) sum += s_red[nwaves + w0 + i];
+                if (split && sound) {
+                    if (w == 0) {
+                        const double t = exchange_parts(xch, g.bparts, part, 1u, sum, false, epoch, sc);
+                        if (lane == 0) s_tot[1] = t;
+                    }
+                    __syncthreads();
+                    sum = s_tot[1];
+                }
+                if (sound) n = (float)(tot * root_int(sum, q));
             }
             if (a.norms_in) {
                 const float forced = a.norms_in[(size_t)k * lay.NB + b];
@@ -668,7 +670,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             }
             const bool bucket_bad = !(fabsf(n) <= 3.402823466e+38f);
             if (bucket_bad) n = 0.0f;
-            if (tid == 0) {
+            if (there && (uint32_t)w == w0 && lane == 0) {
                 if (bucket_bad) raise_error(sc, QGX_EBIT_NONFINITE);
                 if (a.norms_out && part == 0u) a.norms_out[(size_t)k * lay.NB + b] = n;
             }
@@ -680,24 +682,47 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         const uint32_t rshift = GROUPED ? lay.bucket_shift - 8u : 0u;         // rows per bucket, as a shift
 
         // ---- per row: quantise, code, pack -------------------------------------------------------
+        uint32_t first_cell = kCellKey0<CM> << kCellShift<CM>;
+        asm("" : "+v"(first_cell));
+        const uint32_t stage0 = 8u * (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_address(stage)) - 1u;     // (see place_row)
         uint32_t row_base = 0;                         // bits of this chunk written so far (wave-uniform)
         int rows_done = 0;
         const uint32_t block0 = (g.clo >> 2) + (uint32_t)lane;                // Philox block of row 0 (chunks start at multiples of 4)
+        const PhiloxKeys keys = philox_keys(a.seed_lo, a.seed_hi);
         auto quantize_row = [&](int r, uint32_t (&e)[4]) __attribute__((always_inline)) {
-            uint32_t rnd[4], idx[4];
-            philox4x32_10(block0 + 64u * (uint32_t)r, 0u, k, call_id, a.seed_lo, a.seed_hi, rnd);
+            const float xs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
             const float rinv_r = GROUPED ? s_rinv[w * 16 + (int)((uint32_t)r >> rshift)] : rinv;
-            e[0] = quantize_one<true, CM>(v[r].x, rinv_r, rnd[0], L, n_sym, idx[0]);
-            e[1] = quantize_one<true, CM>(v[r].y, rinv_r, rnd[1], L, n_sym, idx[1]);
-            e[2] = quantize_one<true, CM>(v[r].z, rinv_r, rnd[2], L, n_sym, idx[2]);
-            e[3] = quantize_one<true, CM>(v[r].w, rinv_r, rnd[3], L, n_sym, idx[3]);
-            if (MODE == EncMode::QuantOnly) {
-                uint32_t pk = 0;
-                const float xs[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+            uint32_t rnd[4], pk = 0;
+            auto decide = [&](int q, float u, uint32_t j, uint4 t) __attribute__((always_inline)) {
+                const bool up = rounds_up(u, t, rnd[q]);
+                e[q] = up ? t.w : t.z;
+                if (MODE == EncMode::QuantOnly) pk |= (j + (up ? 1u : 0u) + ((__float_as_uint(xs[q]) >> 31) << 7)) << (8 * q);
+            };
+            if constexpr (kStaged<MODE>) {
+                float u[4];
+                uint2 c[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) pk |= (idx[q] | ((__float_as_uint(xs[q]) >> 31) << 7)) << (8 * q);
-                *reinterpret_cast<uint32_t*>(a.sym_out + kbase + 4u * (size_t)(block0 + 64u * (uint32_t)r)) = pk;
+                for (int q = 0; q < 4; ++q) { u[q] = fabsf(xs[q]) * rinv_r; c[q] = cell_of<CM>(u[q], first_cell); }      // |v| / ||v||
+                __builtin_amdgcn_sched_barrier(0);
+                philox4x32_10(block0 + 64u * (uint32_t)r, 0u, k, call_id, keys, rnd);
+                __builtin_amdgcn_sched_barrier(0);
+                uint32_t j[4];
+                uint4 t[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { j[q] = level_in_cell(u[q], c[q]); t[q] = level_row<CM>(j[q], xs[q]); }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) decide(q, u[q], j[q], t[q]);
+            } else {
+                philox4x32_10(block0 + 64u * (uint32_t)r, 0u, k, call_id, keys, rnd);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float u = fabsf(xs[q]) * rinv_r;                                                           // |v| / ||v||
+                    const uint32_t j = level_in_cell(u, cell_of<CM>(u, first_cell));
+                    decide(q, u, j, level_row<CM>(j, xs[q]));
+                }
             }
+            if (MODE == EncMode::QuantOnly) *reinterpret_cast<uint32_t*>(a.sym_out + kbase + 4u * (size_t)(block0 + 64u * (uint32_t)r)) = pk;
         };
         if (fast && g.full) {
 #pragma unroll
@@ -705,7 +730,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 uint32_t ea[4], eb[4];
                 quantize_row(r, ea);
                 quantize_row(r + 1, eb);
-                if (MODE != EncMode::QuantOnly) row_base += pack_two_rows(stage, ends, r, row_base, ea, eb);
+                if (MODE != EncMode::QuantOnly) row_base += pack_two_rows(stage0, ends, r, row_base, ea, eb);
                 __builtin_amdgcn_sched_barrier(0);     // (two rows at a time: more of them in flight spill)
             }
             rows_done = kRows;
@@ -716,7 +741,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 if (r < whole) {                       // (wave-uniform)
                     uint32_t e[4];
                     quantize_row(r, e);
-                    if (MODE != EncMode::QuantOnly) row_base += pack_row<false>(stage, ends, r, row_base, e);
+                    if (MODE != EncMode::QuantOnly) row_base += pack_row<false>(stage0, ends, r, row_base, e);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -740,7 +765,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                     if (__any(unknown) && lane == 0) raise_error(sc, QGX_EBIT_STREAM);
                 } else {
                     uint32_t rnd[4];
-                    philox4x32_10(i0 >> 2, 0u, k, call_id, a.seed_lo, a.seed_hi, rnd);
+                    philox4x32_10(i0 >> 2, 0u, k, call_id, philox_keys(a.seed_lo, a.seed_hi), rnd);
                     // the register copy is indexed by compile-time row numbers only: this path reads the row again
                     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
                     if constexpr (MODE == EncMode::Generate) {
@@ -758,7 +783,11 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                     for (int q = 0; q < 4; ++q) {
                         idx[q] = 0;
                         neg[q] = __float_as_uint(xs[q]) >> 31;
-                        if (live_r) (void)quantize_one<false>(xs[q], rinv_r, rnd[q], L, n_sym, idx[q]);
+                        if (live_r) {
+                            const float u = fminf(fabsf(xs[q]) * rinv_r, 1.0f);
+                            const uint32_t j = level_general<CM>(u, n_sym);
+                            idx[q] = j + (rounds_up(u, level_row<CM>(j, xs[q]), rnd[q]) ? 1u : 0u);
+                        }
                     }
                 }
                 if (MODE == EncMode::QuantOnly) {
@@ -769,11 +798,11 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         // E(idx, sign) from the table row of idx (its third word), nothing for a padded slot
-                        uint32_t code = reinterpret_cast<const uint32_t*>(s_lev + idx[q] * 16u + neg[q] * a.lev_stride)[2];
+                        uint32_t code = lds_load_u32(kLevAt<CM> + 8u + (2u * idx[q] + neg[q]) * 16u);
                         asm("" : "+v"(code));                  // (read by all lanes: four branches a row cost more)
                         e[q] = (i0 + (uint32_t)q < g.cend) ? code : 0u;
                     }
-                    row_base += pack_row<true>(stage, ends, r, row_base, e);
+                    row_base += pack_row<true>(stage0, ends, r, row_base, e);
                 }
             }
         }
@@ -827,7 +856,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
 
 static size_t encode_lds_bytes(int waves, const EncodeArgs& a, bool with_stage, bool grouped)
 {
-    size_t n = cell_count_padded((int)a.cell_mant) * sizeof(float2) + (size_t)a.lev_bytes + (grouped ? (size_t)waves * 64 : 0) +
+    size_t n = (size_t)a.pieces * sizeof(uint4) + (grouped ? (size_t)waves * 64 : 0) +
                (2 * (size_t)waves + 2) * sizeof(double) + (size_t)(waves + 3) / 4 * 4 * sizeof(uint32_t) + 32;
     if (with_stage) n += (size_t)waves * a.stage_bytes;
     return n;
@@ -836,15 +865,17 @@ static size_t encode_lds_bytes(int waves, const EncodeArgs& a, bool with_stage, 
 template <EncMode MODE, bool GROUPED, int CM>
 static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
 {
-    const int waves = (GROUPED || a.parts > 1u) ? 4 : (int)lay.waves_per_bucket;
+    EncodeArgs b = a;
+    const bool ordered = MODE != EncMode::QuantOnly && a.slot_words == 0u;
+    b.group = GROUPED || a.parts > 1u ? 1u : buckets_per_group(lay.waves_per_bucket, (uint64_t)lay.K * lay.NC, ordered);
+    const int waves = (GROUPED || a.parts > 1u) ? 4 : (int)(b.group * lay.waves_per_bucket);
     const size_t lds = encode_lds_bytes(waves, a, MODE != EncMode::QuantOnly, GROUPED);
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_encode<MODE, GROUPED, CM>), 160 * 1024);
     if (e != hipSuccess) return e;
-    // one workgroup per bucket, per part of a bucket, or (shared chunks) per four chunks; in compact
-    // placement and with split buckets each takes one ticket of its worker (the kernel's per_launch)
-    EncodeArgs b = a;
-    b.units = GROUPED ? (lay.NC + 3u) / 4u : lay.NB * a.parts;
+    // one workgroup per bucket or group of buckets, per part of a bucket, or (shared chunks) per four chunks; in compact
+    // placement and with split buckets each takes one ticket of its worker
+    b.units = GROUPED ? (lay.NC + 3u) / 4u : a.parts > 1u ? lay.NB * a.parts : (lay.NB + b.group - 1u) / b.group;
     // Where the workgroups of a bucket wait for each other, no XCD may have more workers than leave it a place to
     // start one in (see worker_span).  The game's form puts the K workgroups of a unit on one XCD, which all K workers
     // then share, as long as that holds for K (42 workers with four workgroups to a compute unit, 31 with three).

@@ -32,14 +32,13 @@ constexpr int kCellMantMax = 6;
 constexpr int kCellsMax = (kCellOct << kCellMantMax) + 1;    // 1537
 constexpr int kCellsPadMax = 1540;
 inline __host__ __device__ int cell_mant(uint32_t n_sym) { return n_sym <= 33u ? 4 : n_sym <= 65u ? 5 : 6; }
-// Bytes between the two sign halves of the encoder's level rows in LDS, by cell size (that is, by the
-// largest table of the class): a power of two that the kernel knows at compile time, so that the sign of
-// a coordinate picks its half with a shift and a mask by constants.
-inline __host__ __device__ constexpr uint32_t lev_stride_of(int mant) { return mant == 4 ? 1024u : 2048u; }
-inline __host__ __device__ constexpr uint32_t lev_sign_shift_of(int mant) { return mant == 4 ? 21u : 20u; }
-inline __host__ __device__ int cell_count(int mant) { return (kCellOct << mant) + 1; }
-inline __host__ __device__ int cell_count_padded(int mant) { return (cell_count(mant) + 3) / 4 * 4; }
-constexpr int kLevRegion = kSymMax * 16;                // bytes between the two sign halves of lev2
+inline __host__ __device__ constexpr int cell_count(int mant) { return (kCellOct << mant) + 1; }
+inline __host__ __device__ constexpr int cell_count_padded(int mant) { return (cell_count(mant) + 3) / 4 * 4; }
+// The encoder's tables as one run of 16-byte pieces, the same in memory and in LDS: the cells (two to a piece), then
+// the level rows, row 2 j + sign for a coordinate of that sign between levels j and j + 1.
+inline __host__ __device__ constexpr uint32_t lev_piece0(int mant) { return (uint32_t)cell_count_padded(mant) / 2u; }
+inline __host__ __device__ constexpr uint32_t enc_pieces(int mant, uint32_t n_sym) { return lev_piece0(mant) + 2u * n_sym; }
+constexpr uint32_t kEncPiecesMax = kCellsPadMax / 2 + 2 * kSymMax;
 
 constexpr int kDlutBits = kMaxCode;       // decode window
 constexpr int kDlut = 1 << kDlutBits;     // 8192 entries
@@ -61,14 +60,14 @@ constexpr uint32_t kWideReject = 0xFFFF7FFFu;
 
 // Device-resident tables: rebuilt on the device whenever the level table or the code changes.
 struct Tables {
-    // lev2[sg][j] = {l_j, (l_{j+1}-l_j)*2^-24, E(j, sg), E(j+1, sg)}: everything the rounding of a
-    // coordinate with sign sg between levels j and j+1 needs.  E(idx, sg) = code word of idx with the
-    // sign bit appended (idx != 0), first-written bit in bit 0, total length << 16.
-    float4 lev2[2][kSymMax];
-    // cell[c] = {B, a0 | a1 << 16} for the c-th cell of u (cell_mant(n_sym) mantissa bits per octave): a0 = byte offset in lev2 of the row of
-    // the last level <= the cell's lower edge; B = the level inside the cell (+inf if none), a1 = the
-    // row to use when u >= B.  Exact only if no cell holds two levels (cell_exact).
-    float2 cell[kCellsPadMax];
+    // enc: enc_pieces(cell_mant(n_sym), n_sym) pieces.
+    // Cell c of u (cell_mant(n_sym) mantissa bits per octave) = {B, j}: j = the last level <= the cell's lower edge, B =
+    // the level inside the cell (+inf if none), from which on it is level j + 1.  Exact only if no cell holds two levels
+    // (cell_exact).
+    // Level row 2 j + sg = {l_j, (l_{j+1}-l_j)*2^-24, E(j, sg), E(j+1, sg)}: everything the rounding of a
+    // coordinate with sign sg between levels j and j+1 needs.  E(idx, sg) = coded_entry of the code word of idx with the
+    // sign bit appended (idx != 0).
+    uint4 enc[kEncPiecesMax];
     float lval[kSymMax];        // l_j
     float levels[kSymMax];      // the table as set or fitted (source of the ones above)
     uint32_t code[kSymMax];     // code word (first-written bit in bit 0) | length << 16, no sign
@@ -152,16 +151,15 @@ struct EncodeArgs {
     uint32_t n_cu;              // compute units of the device
     // filled in by the launch: which worker's which unit a block takes
     uint32_t units;             // workgroups per worker
+    uint32_t group;             // whole buckets per workgroup
     uint32_t span;              // worker = block % span (past K: none), unit = block / span (worker_span)
     uint32_t by_unit;           // or block_by_unit (Generate)
     uint32_t seed_lo, seed_hi, call_id;
     uint32_t call_mode;         // 0: call_id as given; 1, 2: 2(t-1), 2(t-1)+1 from the iteration counter on the device
     int norm_kind;
-    // LDS plan of the launch (bytes): [cell][lev: two sign halves lev_stride apart][misc][stage x waves]
+    // LDS plan of the launch (bytes): [enc][misc][stage x waves]
     uint32_t cell_mant;         // cell_mant(n_sym) of the table in use
-    uint32_t lev_stride;        // lev_stride_of(cell_mant): a power of two >= 16 * n_sym
-    uint32_t lev_bytes;         // lev_stride + 16 * n_sym: the second half ends with its last row
-    uint32_t sign_shift;        // (bits of v) >> sign_shift puts the sign bit on lev_stride
+    uint32_t pieces;            // enc_pieces(cell_mant, n_sym)
     uint32_t stage_bytes;       // per wave, multiple of 16, covers 4096 symbols of the longest code + sign
     uint32_t slot_words;        // 0: compact placement (ordered scan); else chunk c goes to c * slot_words
     GameArgs game;              // EncMode::Generate

@@ -73,6 +73,18 @@ inline uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held)
     return (K + groups - 1u) / groups * groups;
 }
 
+// Whole buckets to a workgroup of the coding kernel, where buckets have few chunks (a wave each): four waves then share the
+// tables in LDS, and a compute unit holds twenty waves whatever the bucket.  A small launch is over sooner with more and
+// smaller workgroups, unless they have to keep an order, which has the fewer members.  Measured, one bucket to a workgroup /
+// four waves, us, in slots: 256 chunks 9.9 / 10.6, 2048 15.8 / 16.3, 3665 24.2 / 24.5, 5005 (half of them short) 26.3 / 25.1,
+// 8192 47.1 / 45.6; in order: 256 chunks 13.7 / 13.8 and (a chunk to a bucket) 15.3 / 13.9, 2048 20.8 / 21.1 and 30.2 / 20.5,
+// 8192 81.6 / 68.3 and 88.4 / 69.1.
+inline uint32_t buckets_per_group(uint32_t waves_per_bucket, uint64_t chunks_of_all, bool ordered)
+{
+    if (waves_per_bucket > 2u || chunks_of_all < (ordered ? 256u : 4096u)) return 1u;
+    return 4u / waves_per_bucket;
+}
+
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
 // x = f * tasks against the wave slots (8 per SIMD with one stream, 4 with two).  A launch is bound by latency,
 // ceil(K / f) workers one after the other (a worker's chain of look-ups takes 2.2 us with one stream, 3.3 with two, however

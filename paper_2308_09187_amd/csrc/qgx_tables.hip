@@ -22,12 +22,16 @@ __device__ inline uint32_t elias_omega(uint32_t N, uint32_t* len_out)
     return bits;
 }
 
-// E(idx, sg): code word of idx with the sign bit appended when idx != 0, total length << 16.
+// E(idx, sg): code word of idx with the sign bit appended when idx != 0, as the encoder joins them (join_row): the word
+// at the top (its first-written bit lowest, its last one bit 31), its length from bit 8 on, and 32 less the length in the
+// low five bits.
 __device__ inline uint32_t coded_entry(uint32_t cw, uint32_t idx, uint32_t sg)
 {
+    static_assert(kMaxSymBits <= 16 && 4 * kMaxSymBits < 64, "words in bits 16 and up, four lengths' sum below bit 14");
     uint32_t bits = cw & 0xFFFFu, len = cw >> 16;
     if (idx != 0) { bits |= sg << len; len += 1; }
-    return bits | (len << 16);
+    if (len == 0) return 0u;                               // (no code set yet)
+    return (bits << (32u - len)) | (len << 8) | (32u - len);
 }
 
 static __device__ void build_tables_block(Tables* tab)
@@ -55,27 +59,28 @@ static __device__ void build_tables_block(Tables* tab)
     for (int i = tid; i < kWide; i += nt) tab->dlutw[i] = make_uint2(kWideReject, 0u);
     __syncthreads();
 
+    const int mant = cell_mant(n_sym), cells = cell_count(mant), cell_shift = 23 - mant;
+    const int key0 = (127 - kCellOct) << mant;
+    float2* cell = reinterpret_cast<float2*>(tab->enc);
+    uint4* rows = tab->enc + lev_piece0(mant);
     for (int j = tid; j < kSymMax; j += nt) {
         float l = 1.0f, g = 0.0f;
         if ((uint32_t)j < n_sym) l = lv[j];
         if ((uint32_t)j + 1 < n_sym) g = (lv[j + 1] - lv[j]) * 0x1p-24f;
         for (uint32_t sg = 0; sg < 2; ++sg) {
-            float4 e = make_float4(l, g, 0.0f, 0.0f);
-            if ((uint32_t)j < n_sym) e.z = __uint_as_float(coded_entry(code[j], (uint32_t)j, sg));
-            if ((uint32_t)j + 1 < n_sym) e.w = __uint_as_float(coded_entry(code[j + 1], (uint32_t)j + 1, sg));
-            tab->lev2[sg][j] = e;
+            uint4 e = make_uint4(__float_as_uint(l), __float_as_uint(g), 0u, 0u);
+            if ((uint32_t)j < n_sym) e.z = coded_entry(code[j], (uint32_t)j, sg);
+            if ((uint32_t)j + 1 < n_sym) e.w = coded_entry(code[j + 1], (uint32_t)j + 1, sg);
+            rows[2 * j + (int)sg] = e;
         }
         tab->lval[j] = l;
     }
     // cells: lower level, the level inside (if any), and whether a second one makes the cell inexact
     if (tid == 0) { tab->cell_exact = 1u; tab->wide_ok = 1u; }
     __syncthreads();
-    const int mant = cell_mant(n_sym), cells = cell_count(mant), cell_shift = 23 - mant;
-    const int key0 = (127 - kCellOct) << mant;
     for (int c = tid; c < cell_count_padded(mant); c += nt) {
         uint32_t j = 0;
         float B = inf;
-        uint32_t a1 = 0;
         bool crowded = false;
         if (c < cells) {
             const float edge = c == 0 ? 0.0f : __uint_as_float((uint32_t)(c + key0) << cell_shift);
@@ -86,14 +91,12 @@ static __device__ void build_tables_block(Tables* tab)
                 const uint32_t mid = (j + hi + 1u) >> 1;
                 if (lv[mid] <= edge) j = mid; else hi = mid - 1u;
             }
-            a1 = j;
             if (j + 2 < n_sym && lv[j + 1] < next) {      // a level strictly inside the cell
                 B = lv[j + 1];
-                a1 = j + 1;
                 if (j + 3 < n_sym && lv[j + 2] < next) crowded = true;
             }
         }
-        tab->cell[c] = make_float2(B, __uint_as_float((j << 4) | (a1 << 20)));
+        cell[c] = make_float2(B, __uint_as_float(j));
         if (crowded) tab->cell_exact = 0u;
     }
     // every 13-bit window that starts with code word j decodes to j: with the first stream bit on

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2308_09187_amd import synth
-from test_gpu_parity import assert_stream_equal, dev, make_ctx, oracle_stream, qgx  # noqa: F401
+from test_gpu_parity import assert_slotted_equal, assert_stream_equal, dev, make_ctx, oracle_stream, qgx  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -31,4 +31,42 @@ def test_rows(qgx, d, bucket):
     ctx.encode(norms, sym, again)
     assert_stream_equal(again.to_host(), so, lay)
     assert ctx.poll_error() == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("norm", [oracle.NORM_L2, oracle.NORM_LINF, 3])
+@pytest.mark.parametrize("bucket,d", [(4096, 32 * 4096 + 1), (4096, 34 * 4096), (8192, 65 * 4096 + 77), (3000, 400001), (6000, 400004)])
+def test_buckets_side_by_side(qgx, bucket, d, norm):
+    """Several buckets to a workgroup (256 chunks in order, 4096 in slots): neighbours whose squares overflow or vanish in
+    binary32, zeros, a non-finite coordinate, and a worker's last workgroup without buckets for all its waves."""
+    K, seed = 128 if d < 200000 else 32, 23
+    levels = synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, K, bucket, norm, levels, seed=seed)
+    rng = np.random.default_rng(d + bucket)
+    V = rng.standard_normal((K, d), dtype=np.float32)
+    V[1, :bucket] *= np.float32(1e25)
+    V[1, 3 * bucket: 4 * bucket] *= np.float32(1e-30)
+    V[2, 2 * bucket: 3 * bucket] = 0.0
+    V[3, -1] *= np.float32(1e24)
+    V[4, bucket + 5] = np.inf
+    V[5, 0] = np.nan
+    V[6, -1] = np.nan
+    for slotted in (False, True):
+        s = ctx.new_stream(slotted=slotted)
+        ctx.quantize_encode(dev(V), 9, s)
+        assert ctx.poll_error() == qgx.EBIT_NONFINITE
+        h = s.to_host()
+        assert h["norms"][4, 1] == 0 and h["norms"][5, 0] == 0 and h["norms"][6, -1] == 0 and np.isfinite(h["norms"]).all()
+        assert (h["norms"][1, [0, 3]] > 0).all() and h["norms"][2, 2] == 0 and h["norms"][2, 1] > 0
+        clean = np.nan_to_num(V, nan=0.0, posinf=0.0)
+        clean[4, bucket: 2 * bucket] = 0.0
+        clean[5, :bucket] = 0.0
+        clean[6, (lay.NB - 1) * bucket:] = 0.0
+        norms_o = oracle.quantize(clean, lay, norm, levels, seed, 9)[0]
+        np.testing.assert_allclose(h["norms"], norms_o, rtol=1e-6, atol=0)
+        _, idx, neg, so = oracle_stream(clean, lay, norm, levels, seed, 9, h["norms"], ctx.worst_words)
+        if slotted:
+            assert_slotted_equal(h, so, lay, s.slot_words)
+        else:
+            assert_stream_equal(h, so, lay)
     ctx.close()

@@ -26,6 +26,7 @@ extern "C" void blocks_by_unit(uint32_t K, uint32_t units, int64_t* out)
 }
 extern "C" uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held) { return qgx::worker_span(K, parts, held); }
 extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::waves_per_task(n, K, simds, streams); }
+extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int ordered) { return qgx::buckets_per_group(waves, chunks, ordered != 0); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
 
@@ -129,3 +130,10 @@ def test_waves_per_task_follow_the_measurements(plan):
                 assert us[got] <= 1.025 * min(us.values()), (tasks, K, streams, got)
     for tasks, K in itertools.product([1, 2, 100000, (1 << 32) - 1], [1, 2, 3, 4, 65535]):
         assert 1 <= plan.waves_per_task(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(1)) <= min(K, 4)
+
+
+def test_buckets_per_group_fills_four_waves(plan):
+    plan.buckets_per_group.argtypes = [C.c_uint32, C.c_uint64, C.c_int]
+    for waves, chunks, ordered in itertools.product(range(1, 17), (1, 255, 256, 4095, 4096, 1 << 40), (0, 1)):
+        n = plan.buckets_per_group(waves, chunks, ordered)
+        assert n == (4 // waves if waves <= 2 and chunks >= (256 if ordered else 4096) else 1), (waves, chunks, ordered)
