@@ -56,14 +56,18 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
     for (;;) {
         const int i = pos - lane;
         unsigned long long s = 0;
-        bool ready = true;
+        bool ready = i < 0;
+        unsigned long long done, pre;
         for (;;) {
-            if (i >= 0) {
+            if (!ready) {                         // (what has been seen is not asked for again)
                 s = __hip_atomic_load(&state[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const uint32_t flag = (uint32_t)(s >> 32);
                 ready = ((flag >> 2) == epoch) && ((flag & 3u) != 0u);
             }
-            if (__all(ready)) break;
+            done = __ballot(ready);
+            pre = __ballot(ready && i >= 0 && ((uint32_t)(s >> 32) & 3u) == 2u);
+            // the nearest full prefix and everything since, or the whole window
+            if (pre != 0ull ? (~done & (pre & (0ull - pre)) - 1ull) == 0ull : done == ~0ull) break;
             if (++spins > kSpinLimit) {           // never expected: every predecessor is already running
                 if (lane == 0) raise_error(sc, QGX_EBIT_STATE);
                 if (!ready) s = 0;
@@ -71,12 +75,9 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
             }
             __builtin_amdgcn_s_sleep(8);
         }
-        const bool have = (i >= 0) && ready;
-        const uint32_t val = have ? (uint32_t)s : 0u;
-        const bool is_pre = have && (((uint32_t)(s >> 32) & 3u) == 2u);
-        const unsigned long long m = __ballot(is_pre);
-        if (m != 0ull) {
-            const int first = __ffsll((long long)m) - 1;      // nearest predecessor with a full prefix
+        const uint32_t val = i >= 0 ? (uint32_t)s : 0u;
+        if (pre != 0ull) {
+            const int first = __ffsll((long long)pre) - 1;    // nearest predecessor with a full prefix
             excl += wave_sum_u32(lane <= first ? val : 0u);
             break;
         }
@@ -419,6 +420,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const int nwaves = (int)(blockDim.x >> 6);
     // The worker and, without tickets, the unit of work are fixed by the block.
     uint32_t k = blockIdx.x % a.span, own_unit = blockIdx.x / a.span;
+    if (a.spread) k = worker_spread(k, own_unit, a.span);
     if (MODE == EncMode::Generate && a.by_unit) {
         const BlockWork own = block_by_unit(blockIdx.x, lay.K, a.units);
         k = own.k; own_unit = own.unit;
@@ -881,6 +883,7 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     // then share, as long as that holds for K (42 workers with four workgroups to a compute unit, 31 with three).
     const uint32_t held = held_per_xcd(kSimdWaves<MODE>, lds, a.n_cu);
     b.span = kWaits<MODE> && a.parts > 1u ? worker_span(lay.K, a.parts, held) : lay.K;
+    b.spread = ordered && a.parts == 1u && spread_workers(lay.K, b.units) ? 1u : 0u;
     b.by_unit = MODE == EncMode::Generate && (a.parts == 1u || (a.parts - 1u) * lay.K < held) ? 1u : 0u;
     const uint32_t grid = b.span * b.units;
     hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM>), dim3(grid), dim3(waves * kWave), lds, st, lay, tab, sc, b);

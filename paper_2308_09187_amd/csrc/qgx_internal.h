@@ -153,6 +153,7 @@ struct EncodeArgs {
     uint32_t units;             // workgroups per worker
     uint32_t group;             // whole buckets per workgroup
     uint32_t span;              // worker = block % span (past K: none), unit = block / span (worker_span)
+    uint32_t spread;            // rows of blocks turned against each other (worker_spread)
     uint32_t by_unit;           // or block_by_unit (Generate)
     uint32_t seed_lo, seed_hi, call_id;
     uint32_t call_mode;         // 0: call_id as given; 1, 2: 2(t-1), 2(t-1)+1 from the iteration counter on the device

@@ -58,6 +58,16 @@ QGX_PLAN BlockWork block_by_unit(uint32_t i, uint32_t K, uint32_t units)
     return BlockWork{rest % K, even + rest / K};
 }
 
+// Where a worker's workgroups keep an order (compact placement, whole buckets) and K is a multiple of 8, the plain rows put each
+// worker on one XCD, whose workgroups then all wait for the same straggler, go on together and are in step from there on. Rows
+// turned against each other by 0, 2, 4 and 6 workers give a worker four XCDs.  8 workers in buckets of 16384, us, plain / turned:
+// 2^20 coordinates 20.1 / 20.7, 2^21 34.5 / 31.1, 2^22 64.9 / 56.7, 9.86 M 141 / 108, 2^24 224 / 166 (without an order 145);
+// 16 workers, 2^22 103 / 95, 2^23 201 / 162.  With more workers to an XCD each has fewer workgroups there and the wait is a
+// part of it: 24 workers of 2^21 70 / 80, 32 of 2^20 50 / 60, of 2^22 157 / 161.
+QGX_PLAN uint32_t worker_spread(uint32_t k, uint32_t unit, uint32_t span) { return (k + 2u * (unit & 3u)) % span; }
+
+inline bool spread_workers(uint32_t K, uint32_t units) { return K % kXcds == 0u && units >= 16u * K; }
+
 // Workgroups of four waves that an XCD holds at once: a wave of each on every SIMD, and their LDS (in steps of 2 KiB).
 inline uint32_t held_per_xcd(uint32_t waves_per_simd, size_t lds_bytes, uint32_t n_cu)
 {

@@ -26,6 +26,8 @@ extern "C" void blocks_by_unit(uint32_t K, uint32_t units, int64_t* out)
 }
 extern "C" uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held) { return qgx::worker_span(K, parts, held); }
 extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::waves_per_task(n, K, simds, streams); }
+extern "C" uint32_t worker_spread(uint32_t k, uint32_t unit, uint32_t span) { return qgx::worker_spread(k, unit, span); }
+extern "C" int spread_workers(uint32_t K, uint32_t units) { return qgx::spread_workers(K, units); }
 extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int ordered) { return qgx::buckets_per_group(waves, chunks, ordered != 0); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
@@ -130,6 +132,18 @@ def test_waves_per_task_follow_the_measurements(plan):
                 assert us[got] <= 1.025 * min(us.values()), (tasks, K, streams, got)
     for tasks, K in itertools.product([1, 2, 100000, (1 << 32) - 1], [1, 2, 3, 4, 65535]):
         assert 1 <= plan.waves_per_task(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(1)) <= min(K, 4)
+
+
+def test_turned_rows_give_every_worker_every_unit_on_four_xcds(plan):
+    for K in (8, 16, 24, 64):
+        assert plan.spread_workers(K, 16 * K) and not plan.spread_workers(K, 16 * K - 1) and not plan.spread_workers(K + 1, 1 << 20)
+        xcds = [set() for _ in range(K)]
+        for unit in range(33):
+            row = [plan.worker_spread(k, unit, K) for k in range(K)]
+            assert sorted(row) == list(range(K))
+            for k, worker in enumerate(row):
+                xcds[worker].add((unit * K + k) % 8)
+        assert all(len(x) == 4 for x in xcds)
 
 
 def test_buckets_per_group_fills_four_waves(plan):
