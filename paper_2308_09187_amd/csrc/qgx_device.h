@@ -230,6 +230,48 @@ __device__ __forceinline__ uint4 nt_load4u(const uint4* p)
     return make_uint4(r.x, r.y, r.z, r.w);
 }
 
+// A chunk's coordinates in registers: 16 rows of 256, four to a lane.  Its whole groups of four coordinates are a buffer, outside of
+// which a load gives zeros: no branch whatever the chunk's length, so that the compiler knows how many loads are under way.
+// Vectors of an odd length put a worker's rows at any multiple of 4 bytes, which 16-byte loads take.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rows(const float* first, uint32_t len)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(first)), 0, (int)((len & ~3u) * sizeof(float)), 0x00027000);
+}
+
+__device__ __forceinline__ float4 load_row(__amdgpu_buffer_rsrc_t rows, int r, int lane)
+{
+    constexpr int kNonTemporal = 2;                          // (read once: see nt_load4)
+    const nt_u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16, r * 1024, kNonTemporal);
+    return make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
+}
+
+__device__ __forceinline__ void load_rows(float4 (&v)[kRows], __amdgpu_buffer_rsrc_t rows, int lane)
+{
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) v[r] = load_row(rows, r, lane);
+}
+
+// The last one to three coordinates of a vector whose length is no multiple of four (only a worker's last chunk has such).
+__device__ __forceinline__ void load_rest(float4 (&v)[kRows], const float* __restrict__ first, uint32_t len, int lane)
+{
+    if ((len & 3u) == 0u) return;
+    const uint32_t at = len & ~3u;                           // (all wave-uniform)
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    x.x = first[at];
+    if ((len & 3u) > 1u) x.y = first[at + 1u];
+    if ((len & 3u) > 2u) x.z = first[at + 2u];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+        if (r == (int)(at >> 8) && (uint32_t)lane == (at & 255u) >> 2) v[r] = x;
+}
+
+// The largest magnitude of four and one; a NaN among them is the result (two instructions).
+__device__ __forceinline__ float largest_of(const float4& x, float m)
+{
+    m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.x), fabsf(x.y)), m);
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.z), fabsf(x.w)), m);
+}
+
 // t^q for a small positive integer q (the same q in every lane).
 __device__ __forceinline__ double pow_int(double t, uint32_t q)
 {

@@ -287,42 +287,6 @@ __device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, u
     return g;
 }
 
-// The loads of one chunk into registers (16 rows x 4 coordinates per lane), whatever its length: the chunk's whole groups
-// of four coordinates as a buffer, outside of which a load gives zeros.  No branch, so that the compiler knows how many loads
-// are under way.  Vectors of an odd length put a worker's rows at any multiple of 4 bytes, which 16-byte loads take.
-__device__ __forceinline__ void load_chunk(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g, int lane)
-{
-    constexpr int kNonTemporal = 2;                          // (read once: see nt_load4)
-    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(Vk + g.clo)), 0,
-                                                                          (int)((g.clen & ~3u) * sizeof(float)), 0x00027000);
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const nt_u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16, r * 1024, kNonTemporal);
-        v[r] = make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
-    }
-}
-
-// The last one to three coordinates of a vector whose length is no multiple of four (only a worker's last chunk has such).
-__device__ __forceinline__ void load_chunk_rest(float4 (&v)[kRows], const float* __restrict__ Vk, const ChunkGeom& g, int lane)
-{
-    if ((g.clen & 3u) == 0u) return;
-    const uint32_t at = g.clen & ~3u;                        // (all wave-uniform)
-    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    x.x = Vk[g.clo + at];
-    if ((g.clen & 3u) > 1u) x.y = Vk[g.clo + at + 1u];
-    if ((g.clen & 3u) > 2u) x.z = Vk[g.clo + at + 2u];
-#pragma unroll
-    for (int r = 0; r < kRows; ++r)
-        if (r == (int)(at >> 8) && (uint32_t)lane == (at & 255u) >> 2) v[r] = x;
-}
-
-// The largest magnitude of four and one; a NaN among them is the result (two instructions).
-__device__ __forceinline__ float largest_of(const float4& x, float m)
-{
-    m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.x), fabsf(x.y)), m);
-    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.z), fabsf(x.w)), m);
-}
-
 // Shared chunks (buckets of 256..2048 coordinates): a wave's chunk holds up to 16 buckets, each a run
 // of whole rows, so the wave works out their norms by itself, one wave reduction at the last row of
 // every bucket, and leaves 1 / norm (0 for a bucket that is all zero or rejected) in LDS for the
@@ -527,7 +491,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         MODE != EncMode::QuantOnly ? a.sub_end + ((size_t)k * lay.NC + g.c) * kSubs : nullptr;
     const SubEnds ends(reinterpret_cast<uint16_t*>(uniform_address(sub_g)), lane);
     float4 v[kRows];
-    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_chunk(v, Vk, g, lane);
+    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_rows(v, chunk_rows(Vk + g.clo, g.clen), lane);
     // (by all threads: a branch would leave it open what is still under way)
     reinterpret_cast<nt_u32x4*>(s_enc)[piece0] = ahead0;
     reinterpret_cast<nt_u32x4*>(s_enc)[piece1] = ahead1;
@@ -539,7 +503,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     const uint32_t n_sym = tab->n_sym;
     const uint32_t cell_exact = (tab->cell_exact != 0u && (uint32_t)cell_mant(n_sym) == a.cell_mant) ? 1u : 0u;
     __syncthreads();
-    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_chunk_rest(v, Vk, g, lane);
+    if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_rest(v, Vk + g.clo, g.clen, lane);
     if constexpr (MODE == EncMode::Generate) {
         // the dual vector is formed here instead of read: operator and noise for four coordinates per lane and row
         // (every bucket and vector length is a multiple of four in this mode)

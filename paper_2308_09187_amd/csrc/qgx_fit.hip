@@ -27,103 +27,80 @@ __device__ __forceinline__ double bin_edge(uint32_t b, uint32_t n_bins)
     return (double)__uint_as_float((uint32_t)((int)b + (127 * 64 - (int)n_bins)) << 17);
 }
 
-// A workgroup walks its buckets one after the other, each in three phases divided by barriers (norm, count,
-// fold), and a compute unit holds only two or three such workgroups (LDS): nothing hides a phase's
-// latency but the next bucket's rows, so with buckets of at most four chunks those are loaded into a
-// second set of registers before the current bucket is worked on.
+// A workgroup walks its buckets one after the other, each in two phases divided by barriers: norm, then count and fold (a
+// wave that has folded a bucket's counters meets the others again before anyone counts the next).  A compute unit holds one
+// workgroup of sixteen waves (registers) or three of four (LDS), so nothing but the workgroup itself hides a phase's latency:
+// a row's registers are free once it is counted, and the next bucket's row is asked for there and then.
+// 16 x 2^26 coordinates in buckets of 65536 take 0.64 ms (6.7 TB/s; 0.85 with the loads at a bucket's start), 8 x 2^24 in
+// buckets of 16384 0.123 (0.151 with a second set of registers for the next bucket's rows, two workgroups to a unit).
+// The barriers between the rows are for the scheduler, which else forms all rows' bins first and spills.
 template <int MAXW>
 __global__ __launch_bounds__(MAXW * kWave) void k_histogram(Layout lay, const float* __restrict__ V, int norm_kind,
                                                             uint32_t n_bins, double* __restrict__ partial, Scalars* sc)
 {
-    constexpr bool kAhead = MAXW <= 4;                                   // registers for a second bucket's rows
     extern __shared__ __align__(16) unsigned char s_raw[];
     double* s_acc = reinterpret_cast<double*>(s_raw);                    // [n_bins]
     uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_acc + n_bins);       // [n_bins]
     __shared__ double s_red[kMaxWaves];
-    __shared__ uint32_t s_bad[kMaxWaves];
 
-    const int tid = (int)threadIdx.x, lane = lane_id(), w = wave_id();
+    const int tid = (int)threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
     const int nwaves = (int)(blockDim.x >> 6);
     for (uint32_t i = (uint32_t)tid; i < n_bins; i += blockDim.x) { s_acc[i] = 0.0; s_cnt[i] = 0; }
-    __syncthreads();
 
     const uint32_t n_work = lay.K * lay.NB;
-    // the rows of this wave's chunk of unit t (bucket t / K of worker t % K), zeros past the bucket's end
-    auto load_rows = [&](uint32_t t, float4 (&v)[kRows]) {
+    // this wave's chunk of unit t (bucket t / K of worker t % K); none past the bucket's end or the last unit
+    struct Piece { const float* first; uint32_t len; };
+    auto piece_of = [&](uint32_t t) {
+        if (t >= n_work) return Piece{V, 0u};
         const uint32_t b = t / lay.K, k = t - b * lay.K;
-        const uint32_t lo = lay.bucket_start[b], hi = lay.bucket_start[b + 1];
+        const uint32_t lo = scalar_load(lay.bucket_start + b), hi = scalar_load(lay.bucket_start + b + 1);
         const uint32_t clo = lo + (uint32_t)w * kChunk;
-        const uint32_t cend = clo < hi ? clo + min((uint32_t)kChunk, hi - clo) : clo;
-        const size_t kbase = (size_t)k * lay.d;
-        const bool vec_ok = (kbase & 3u) == 0;
-        const float* __restrict__ Vk = V + kbase;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const uint32_t i0 = clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 + 4u <= cend) {
-                if (vec_ok) x = nt_load4(Vk + i0);                // (read once)
-                else x = make_float4(Vk[i0], Vk[i0 + 1], Vk[i0 + 2], Vk[i0 + 3]);
-            } else if (i0 < cend) {
-                x.x = Vk[i0];
-                if (i0 + 1 < cend) x.y = Vk[i0 + 1];
-                if (i0 + 2 < cend) x.z = Vk[i0 + 2];
-            }
-            v[r] = x;
-        }
+        const uint32_t left = clo < hi ? hi - clo : 0u;
+        return Piece{V + (size_t)k * lay.d + clo, left < (uint32_t)kChunk ? left : (uint32_t)kChunk};
     };
-    float4 v[kRows], v_next[kAhead ? kRows : 1];
-    if constexpr (kAhead) {
-        if (blockIdx.x < n_work) load_rows(blockIdx.x, v);
-    }
+    float4 v[kRows];
+    Piece cur = piece_of(blockIdx.x);
+    load_rows(v, chunk_rows(cur.first, cur.len), lane);
     for (uint32_t t = blockIdx.x; t < n_work; t += gridDim.x) {
-        const uint32_t b = t / lay.K, k = t - b * lay.K;
-        const uint32_t lo = lay.bucket_start[b], hi = lay.bucket_start[b + 1];
-        const uint32_t clo = lo + (uint32_t)w * kChunk;
-        const uint32_t clen = clo < hi ? min((uint32_t)kChunk, hi - clo) : 0u;
-        const uint32_t cend = clo + clen;
-        const size_t kbase = (size_t)k * lay.d;
-        const float* __restrict__ Vk = V + kbase;
-        if constexpr (kAhead) {
-            if (t + gridDim.x < n_work) load_rows(t + gridDim.x, v_next);
-        } else {
-            load_rows(t, v);
-        }
-        double acc = 0.0;
-        float mx = 0.0f;
-        uint32_t bad = 0;
+        const Piece next = piece_of(t + gridDim.x);
+        const __amdgpu_buffer_rsrc_t next_rows = chunk_rows(next.first, next.len);
+        load_rest(v, cur.first, cur.len, lane);
+        // a non-finite coordinate shows in the sum of squares (which no finite ones overflow) and in the maximum
+        double red;
+        if (norm_kind == QGX_NORM_L2) {
+            double acc = 0.0;
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float ax = fabsf(e[q]);
-                bad |= !(ax <= 3.402823466e+38f);
-                if (norm_kind == QGX_NORM_L2) acc = fma((double)e[q], (double)e[q], acc);
-                else mx = fmaxf(mx, ax);
+            for (int r = 0; r < kRows; ++r) {
+                acc = fma((double)v[r].x, (double)v[r].x, acc);
+                acc = fma((double)v[r].y, (double)v[r].y, acc);
+                acc = fma((double)v[r].z, (double)v[r].z, acc);
+                acc = fma((double)v[r].w, (double)v[r].w, acc);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            red = wave_sum(acc);
+        } else {
+            float mx = 0.0f;
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) mx = largest_of(v[r], mx);
+            red = (double)__uint_as_float(wave_max_u32(__float_as_uint(mx)));
         }
-        if (norm_kind == QGX_NORM_L2) acc = wave_sum(acc);
-        else acc = (double)wave_max(mx);
-        bad = wave_or(bad);
-        if (lane == 0) { s_red[w] = acc; s_bad[w] = bad; }
+        if (lane == 0) s_red[w] = red;
         __syncthreads();
         double tot = 0.0;
-        uint32_t anybad = 0;
+        bool finite = true;
         for (int i = 0; i < nwaves; ++i) {
             if (norm_kind == QGX_NORM_L2) tot += s_red[i];
             else tot = fmax(tot, s_red[i]);
-            anybad |= s_bad[i];
+            finite = finite && fabs(s_red[i]) <= 1.7976931348623157e308;
         }
         float n = (norm_kind == QGX_NORM_L2) ? (float)sqrt(tot) : (float)tot;
-        if (norm_kind != QGX_NORM_L2 && norm_kind != QGX_NORM_LINF && anybad == 0 && tot > 0.0) {
+        if (norm_kind != QGX_NORM_L2 && norm_kind != QGX_NORM_LINF && finite && tot > 0.0) {
             // general q: (sum |v_i|^q)^(1/q) relative to the largest magnitude, as in the encoder
             const double inv_m = 1.0 / tot;
             double sum = 0.0;
 #pragma unroll 1
-            for (uint32_t i = clo + (uint32_t)lane; i < cend; i += kWave) {      // rolled, from memory
-                sum += pow_int(fabs((double)Vk[i]) * inv_m, (uint32_t)norm_kind);
-            }
+            for (uint32_t i = (uint32_t)lane; i < cur.len; i += kWave)                   // rolled, from memory
+                sum += pow_int(fabs((double)cur.first[i]) * inv_m, (uint32_t)norm_kind);
             sum = wave_sum(sum);
             __syncthreads();                         // everyone has read the first set of partial results
             if (lane == 0) s_red[w] = sum;
@@ -132,33 +109,25 @@ __global__ __launch_bounds__(MAXW * kWave) void k_histogram(Layout lay, const fl
             for (int i = 0; i < nwaves; ++i) all += s_red[i];
             n = (float)(tot * root_int(all, (uint32_t)norm_kind));
         }
-        const bool usable = (anybad == 0) && (n > 0.0f) && (n <= 3.402823466e+38f);
-        if (anybad != 0 && tid == 0) raise_error(sc, QGX_EBIT_NONFINITE);
-        if (usable) {
-            const float rinv = 1.0f / n;
-            if (clen == (uint32_t)kChunk) {
-                // a whole chunk: no coordinate to leave out, and u above 1 (by a rounding) ends in the last bin
-                // with the clamp of the bin number alone
+        const bool usable = finite && (n > 0.0f) && (n <= 3.402823466e+38f);
+        if (!finite && tid == 0) raise_error(sc, QGX_EBIT_NONFINITE);
+        const float rinv = usable ? 1.0f / n : 0.0f;
+        const uint32_t len = usable ? cur.len : 0u;
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) {
-                    const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+        for (int r = 0; r < kRows; ++r) {
+            const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+            // (u above 1, by a rounding, ends in the last bin with the clamp of the bin number alone)
+            if ((uint32_t)r * 256u + 256u <= len) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) atomicAdd(&s_cnt[bin_of(fabsf(e[q]) * rinv, n_bins)], 1u);
-                }
-            } else {
+                for (int q = 0; q < 4; ++q) atomicAdd(&s_cnt[bin_of(fabsf(e[q]) * rinv, n_bins)], 1u);
+            } else if ((uint32_t)r * 256u < len) {               // the short last row
+                const uint32_t i0 = (uint32_t)r * 256u + (uint32_t)lane * 4u;
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) {
-                    const uint32_t i0 = clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
-                    const float e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (i0 + (uint32_t)q < cend) {
-                            const float u = fminf(fabsf(e[q]) * rinv, 1.0f);
-                            atomicAdd(&s_cnt[bin_of(u, n_bins)], 1u);
-                        }
-                    }
-                }
+                for (int q = 0; q < 4; ++q)
+                    if (i0 + (uint32_t)q < len) atomicAdd(&s_cnt[bin_of(fabsf(e[q]) * rinv, n_bins)], 1u);
             }
+            v[r] = load_row(next_rows, r, lane);
+            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
         if (usable) {
@@ -168,13 +137,9 @@ __global__ __launch_bounds__(MAXW * kWave) void k_histogram(Layout lay, const fl
                 if (cnt) { s_acc[i] += (double)cnt * wgt; s_cnt[i] = 0; }
             }
         }
-        __syncthreads();
-        if constexpr (kAhead) {
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) v[r] = v_next[r];
-        }
+        cur = next;
     }
-    for (uint32_t i = (uint32_t)tid; i < n_bins; i += blockDim.x)
+    for (uint32_t i = (uint32_t)tid; i < n_bins; i += blockDim.x)        // (a thread's own bins)
         partial[(size_t)blockIdx.x * n_bins + i] = s_acc[i];
 }
 
@@ -331,9 +296,10 @@ __global__ __launch_bounds__(kRedBins * kRedSegs) void k_hist_reduce(uint32_t n_
 
 uint32_t histogram_groups(const Layout& lay)
 {
-    // two workgroups per compute unit; three (what its LDS holds with 4096 bins) where a workgroup is a single wave
+    // as many as the compute units hold at once: three each (LDS with 4096 bins) of up to four waves, two of up to eight,
+    // one of up to sixteen (registers); shared chunks: two
     const uint32_t n_work = lay.K * lay.NB;
-    const uint32_t groups = (!lay.shared_chunks && lay.waves_per_bucket == 1u) ? 768u : 512u;
+    const uint32_t groups = lay.shared_chunks ? 512u : lay.waves_per_bucket <= 4u ? 768u : lay.waves_per_bucket <= 8u ? 512u : 256u;
     return n_work < groups ? n_work : groups;
 }
 
