@@ -134,7 +134,7 @@ template <int D>
 __device__ __forceinline__ uint32_t xor_lane(uint32_t x)
 {
     constexpr int ctrl = D == 8 ? 0x128 : D == 4 ? 0x124 : D == 2 ? 0x4E : 0xB1;   // row_ror:8, row_ror:4, quad_perm [2,3,0,1], [1,0,3,2]
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xf, 0xf, true);
 }
 
 struct LanePair { uint32_t a, b; };                        // the two values that lanes i and i xor D have, in both

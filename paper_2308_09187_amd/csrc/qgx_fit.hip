@@ -341,25 +341,26 @@ hipError_t launch_histogram(const Layout& lay, const float* V, int norm_kind, ui
 // binary32 once, at the end.
 //
 // Everything is summed from a onwards, non-negative terms only (a difference of cumulative sums taken
-// from 0 would lose a sliver of mass next to a level against the total).  A two-level tree over the bins
-// keeps that short: nodes of 16 and 256 bins hold their mass and their moment about their own right
+// from 0 would lose a sliver of mass next to a level against the total).  Nodes of 64 bins keep that short: they hold
+// their mass and their moment about their own right
 // edge, rho = sum H_b (edge - mid_b), so that int (c - u) dF~ over a node is (c - edge) * mass + rho.
-// The whole bins between a and c are then at most five runs of at most 16 items: bins up to a multiple
-// of 16, nodes of 16 up to a multiple of 256, nodes of 256, and down again.  One update is the work of a
-// row of 16 lanes, a lane per item of a run: the integral is one sum across the row, and the place where
-// the mass reaches t is found with a prefix sum across the row per run, then inside the node that holds
-// it, a level of the tree at a time.
+// The whole bins between a and c are then at most 63 bins up to a multiple of 64, at most 64 nodes, and at most 63 bins.
+// One update is the work of a wave, a lane per item of each of the three runs: the integral is one sum across the wave, and
+// the place where the mass reaches t is found with a prefix sum across it per run, then inside the node that holds it.
+// Updates depend on each other, so a step's latency is all that counts: what is the same in all lanes is kept in scalar
+// registers (branches, the place found), sums and broadcasts stay in vector registers, and divisions by the width of a bin,
+// a power of two, are exact multiplications.  (A row of 16 lanes per update over a tree of nodes of 16 and 256 bins, four
+// updates to a wave whose lanes went through each other's branches: a fit of 2^17 coordinates with 33 levels and 10 sweeps 116 us, now
+// 99; 17 levels 89, now 71; 65 levels 159, now 126; 127 levels 226, now 218.  Without a form of its own for short intervals
+// 127 levels took 250.)
 
+// In LDS, one array of doubles: the bins' masses, then the nodes' masses, then their moments.
+constexpr uint32_t kNodes = QGX_MAX_BINS / kWave;
+constexpr uint32_t kTreeDoubles = 2u * kNodes;      // beside the bins
 struct Tree {
-    const double* H;      // LDS [n_bins]
-    const double* m1;     // [n_bins / 16] mass of a node of 16 bins
-    const double* r1;     // its moment about its right edge
-    const double* m2;     // [n_bins / 256] the same for the nodes of 256 bins
-    const double* r2;
+    const double* H;      // [n_bins], [kNodes], [kNodes]
     uint32_t n_bins;
 };
-
-constexpr uint32_t kRow = 16;     // lanes per update
 
 // The bin whose half-open interval [edge, next edge) holds x >= 0: the bins are 64 to an octave, so the bin
 // number is the exponent and the top six fraction bits, which a binary64 number shows as its bits 46 and up.
@@ -369,49 +370,43 @@ __device__ __forceinline__ uint32_t bin_containing(uint32_t n_bins, double x)
     return (uint32_t)min(max(key, 0), (int)n_bins - 1);
 }
 
-// x of another lane of the row, by a DPP control word; lanes without a source read 0
-template <int CTRL>
-__device__ __forceinline__ double row_dpp(double x)
+// y / (width of bin b), exactly: a power of two but for the first bin, which goes down to zero.
+__device__ __forceinline__ double by_bin_width(double y, uint32_t b, uint32_t n_bins)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
+    if (b == 0u) return y / bin_edge(1u, n_bins);
+    const int octave = (int)((b + (127u * 64u - n_bins)) >> 6) - 127;          // the bin lies in [2^octave, 2^(octave + 1))
+    return __builtin_amdgcn_ldexp(y, 6 - octave);
 }
 
-// The sum over the row, the same bits in all its lanes: mirror, mirror within eight, swap pairs, swap
-// neighbours; at every step the two lanes of a pair add the same two numbers.
-__device__ __forceinline__ double row_sum(double x)
+// inclusive prefix sum over the lanes of the wave, as wave_incl_scan
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double x)
 {
-    x += row_dpp<0x140>(x);      // row_mirror
-    x += row_dpp<0x141>(x);      // row_half_mirror
-    x += row_dpp<0x4E>(x);       // quad_perm [2,3,0,1]
-    x += row_dpp<0xB1>(x);       // quad_perm [1,0,3,2]
+    if constexpr (ROWS == 0xf)       // (lanes without a source read 0)
+        return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true),
+                                __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true));
+    else
+        return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ double wave_prefix(double x)
+{
+    x += dpp_or_zero<0x111, 0xf>(x);
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);
+    x += dpp_or_zero<0x143, 0xc>(x);
     return x;
 }
 
-// inclusive prefix sum over the lanes of the row (row_shr by 1, 2, 4, 8; nothing is shifted in from outside)
-__device__ __forceinline__ double row_scan(double x, uint32_t)
+__device__ __forceinline__ double lane_value(double x, uint32_t lane)           // (lane the same in all lanes)
 {
-    x += row_dpp<0x111>(x);
-    x += row_dpp<0x112>(x);
-    x += row_dpp<0x114>(x);
-    x += row_dpp<0x118>(x);
-    return x;
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), (int)lane), __builtin_amdgcn_readlane(__double2loint(x), (int)lane));
 }
 
-// first lane of this row with the predicate set, kRow if none
-__device__ __forceinline__ uint32_t row_first(bool pred)
-{
-    const unsigned long long b = __ballot(pred);
-    const uint32_t mine = (uint32_t)(b >> (threadIdx.x & 48u)) & 0xFFFFu;
-    return mine ? (uint32_t)__ffs((int)mine) - 1u : kRow;
-}
-
-// mass of item idx of a level of the tree (0: a bin, 1: 16 bins, 2: 256 bins)
-__device__ __forceinline__ double item_mass(const Tree& T, uint32_t lvl, uint32_t idx)
-{
-    return lvl == 2u ? T.m2[idx] : lvl == 1u ? T.m1[idx] : T.H[idx];
-}
+__device__ __forceinline__ bool same_in_all(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0ull; }
+__device__ __forceinline__ uint32_t same_in_all(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
 // Right edge of the last bin with mass in [first, last_plus_1), or `fallback` if none has any.
 __device__ double last_mass_edge(const Tree& T, uint32_t first, uint32_t last_plus_1, double fallback)
@@ -421,180 +416,153 @@ __device__ double last_mass_edge(const Tree& T, uint32_t first, uint32_t last_pl
     return fallback;
 }
 
-// All 16 lanes of a row call this with the same a and c and get the same x.
-__device__ double stationary_point(const Tree& T, double a, double c)
+// The middle of bin b > 0: a binary32 number as its edges are.
+__device__ __forceinline__ double bin_middle(uint32_t b, uint32_t n_bins)
 {
-    if (!(c > a)) return a;
-    const uint32_t nb = T.n_bins, li = threadIdx.x & (kRow - 1u);
-    const uint32_t ba = bin_containing(nb, a), bc = bin_containing(nb, c);
-    // the pieces of the bins that hold a and c, and the whole bins P .. Q - 1 between them
-    const double a_e0 = bin_edge(ba, nb), a_e1 = bin_edge(ba + 1u, nb);
+    return (double)__uint_as_float(((b + (127u * 64u - n_bins)) << 17) | 0x10000u);
+}
+
+// The level between its neighbours a < c, which lie in bins ba and bc.  SHORT: all the whole bins between them are in the first run.
+template <bool SHORT>
+__device__ __forceinline__ double stationary_between(const Tree& T, double a, double c, uint32_t ba, uint32_t bc)
+{
+    const uint32_t nb = T.n_bins, lane = (uint32_t)lane_id();
+    // the whole bins P .. Q - 1 between those that hold a and c: bins [P, P1), nodes [p1, q1), bins [Q1, Q)
+    const uint32_t P = ba + 1u, Q = bc > P ? bc : P;
+    const uint32_t up = (P + (kWave - 1u)) & ~(kWave - 1u), dn = Q & ~(kWave - 1u);
+    const uint32_t P1 = Q < up ? Q : up, Q1 = dn > P1 ? dn : P1;
+    const uint32_t p1 = P1 / kWave, q1 = Q1 / kWave;           // equal when no whole node lies between
+    const bool in1 = P + lane < P1, in2 = !SHORT && p1 + lane < q1, in3 = !SHORT && Q1 + lane < Q;
+    const uint32_t b1 = in1 ? P + lane : P, node = in2 ? p1 + lane : 0u, b3 = in3 ? Q1 + lane : P;
+    const double H_a = T.H[ba], H_c = T.H[bc];
+    // (P may be one past the last bin: the first node's mass, which is left out like every other item outside its run)
+    double m1 = T.H[b1], m2 = 0.0, rest = 0.0, m3 = 0.0;
+    if constexpr (!SHORT) { m2 = T.H[nb + node]; rest = T.H[nb + kNodes + node]; m3 = T.H[b3]; }
+    m1 = in1 ? m1 : 0.0;
+    if constexpr (!SHORT) { m2 = in2 ? m2 : 0.0; rest = in2 ? rest : 0.0; m3 = in3 ? m3 : 0.0; }
+    // the pieces of the bins that hold a and c
+    const double a_e1 = bin_edge(ba + 1u, nb);
     const double a_hi = c < a_e1 ? c : a_e1;
-    const double m_a = T.H[ba] * (a_hi - a) / (a_e1 - a_e0);
+    const double m_a = by_bin_width(H_a * (a_hi - a), ba, nb);
     double m_c = 0.0, c_e0 = c;
     if (bc > ba) {
         c_e0 = bin_edge(bc, nb);
-        m_c = T.H[bc] * (c - c_e0) / (bin_edge(bc + 1u, nb) - c_e0);
+        m_c = by_bin_width(H_c * (c - c_e0), bc, nb);
     }
-    const uint32_t P = ba + 1u, Q = bc > P ? bc : P;
-    // runs: bins [P, P1), nodes of 16 [p1, p2), nodes of 256 [p2 / 16, q2 / 16), nodes of 16 [q2, q1), bins [Q1, Q)
-    const uint32_t up = (P + 15u) & ~15u;
-    const uint32_t P1 = Q < up ? Q : up;
-    const uint32_t dn = Q & ~15u;
-    const uint32_t Q1 = dn > P1 ? dn : P1;
-    const uint32_t p1 = P1 >> 4, q1 = Q1 >> 4;                 // equal when no whole node of 16 lies between
-    const uint32_t up1 = (p1 + 15u) & ~15u;
-    const uint32_t p2 = q1 < up1 ? q1 : up1;
-    const uint32_t dn1 = q1 & ~15u;
-    const uint32_t q2 = dn1 > p2 ? dn1 : p2;
-    const uint32_t lo[5] = {P, p1, p2 >> 4, q2, Q1}, hi[5] = {P1, p2, p2 < q2 ? q2 >> 4 : p2 >> 4, q1, Q};
-    const uint32_t lvl[5] = {0u, 1u, 2u, 1u, 0u};
-    double m[5], rho = 0.0;
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-        const uint32_t idx = lo[s] + li;
-        m[s] = 0.0;
-        if (idx < hi[s]) {
-            m[s] = item_mass(T, lvl[s], idx);
-            if (lvl[s] == 0u) rho += m[s] * (c - 0.5 * (bin_edge(idx, nb) + bin_edge(idx + 1u, nb)));
-            else if (lvl[s] == 1u) rho += (c - bin_edge(16u * idx + 16u, nb)) * m[s] + T.r1[idx];
-            else rho += (c - bin_edge(256u * idx + 256u, nb)) * m[s] + T.r2[idx];
-        }
+    // the runs' prefix sums, then each run's mass on top of the runs before it (before they are known to be needed: beside the
+    // integral and the division they take no time)
+    double cum1 = wave_prefix(m1), cum2 = 0.0, cum3 = 0.0;
+    const double base2 = m_a + lane_value(cum1, kWave - 1u);
+    double base3 = base2, all = base2;
+    cum1 += m_a;
+    if constexpr (!SHORT) {
+        cum2 = wave_prefix(m2);
+        cum3 = wave_prefix(m3);
+        base3 = base2 + lane_value(cum2, kWave - 1u);
+        all = base3 + lane_value(cum3, kWave - 1u);
+        cum2 += base2;
+        cum3 += base3;
     }
-    // int_a^c (c - u) dF~
-    const double right_all = m_a * (c - 0.5 * (a + a_hi)) + row_sum(rho) + m_c * (c - 0.5 * (c_e0 + c));
-    if (!(right_all > 0.0)) return a;                                  // no mass between the neighbours
+    // int_a^c (c - u) dF~: an item's mass times the distance of its middle (a bin) or right edge (a node, and its moment about that)
+    double part = (c - bin_middle(b1, nb)) * m1;
+    if constexpr (!SHORT) part += ((c - bin_edge((node + 1u) * kWave, nb)) * m2 + rest) + (c - bin_middle(b3, nb)) * m3;
+    const double right_all = m_a * (c - 0.5 * (a + a_hi)) + wave_sum(part) + m_c * (c - 0.5 * (c_e0 + c));
+    if (!same_in_all(right_all > 0.0)) return a;                       // no mass between the neighbours
     const double t = right_all / (c - a);
-    // the smallest x with mass(a, x) >= t
-    if (m_a >= t) return fmin(fmax(a + t / m_a * (a_hi - a), a), c);
-    // the runs' prefix sums side by side, then each run's mass on top of the runs before it
-    double cum[5], base[6], tot[5];
-#pragma unroll
-    for (int s = 0; s < 5; ++s) { cum[s] = row_scan(m[s], li); tot[s] = row_sum(m[s]); }
-    base[0] = m_a;
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-        cum[s] += base[s];
-        base[s + 1] = base[s] + tot[s];
-    }
-    double acc = base[5];
-    // the first run in which the mass reaches t (looked for from the last one down), then the place in it
-    uint32_t at_lvl = 0u, at_idx = 0u, at_first = kRow;
-    double at_cum = 0.0, at_base = 0.0;
-#pragma unroll
-    for (int s = 4; s >= 0; --s) {
-        const uint32_t first = row_first(lo[s] + li < hi[s] && cum[s] >= t);
-        const bool here = first < kRow;
-        at_first = here ? first : at_first;
-        at_lvl = here ? lvl[s] : at_lvl;
-        at_idx = here ? lo[s] + first : at_idx;
-        at_cum = here ? cum[s] : at_cum;
-        at_base = here ? base[s] : at_base;
-    }
-    const bool found = at_first < kRow;
-    const double at_before = __shfl(at_cum, (int)((at_first - 1u) & (kRow - 1u)), (int)kRow);
-    double prev = at_first > 0u ? at_before : at_base;
-    double x;
-    if (!found) {
-        // the mass reaches t in the piece of c's bin, or t is a rounding above all the mass: then the answer
-        // is where the mass ends
-        x = m_c > 0.0 ? c_e0 + (t - acc) / m_c * (c - c_e0) : last_mass_edge(T, P, Q, m_a > 0.0 ? a_hi : a);
-    } else {
-        const uint32_t node_end = at_lvl == 2u ? 256u * at_idx + 256u : at_lvl == 1u ? 16u * at_idx + 16u : at_idx + 1u;
-        bool lost = false;
-        while (at_lvl > 0u && !lost) {                                 // into the node that holds it
-            const uint32_t child = 16u * at_idx + li;
-            const double cum = prev + row_scan(item_mass(T, at_lvl - 1u, child), li);
-            const uint32_t first = row_first(cum >= t);
-            if (first < kRow) {
-                const double before = __shfl(cum, (int)(first > 0u ? first - 1u : 0u), (int)kRow);
-                prev = first > 0u ? before : prev;
-                at_idx = 16u * at_idx + first;
-                at_lvl -= 1u;
-            } else {
-                lost = true;       // the node's mass reached t and the sum of its parts, rounded otherwise, did not
-            }
-        }
-        if (lost) {
-            x = last_mass_edge(T, P, node_end, m_a > 0.0 ? a_hi : a);
+    // the smallest x with mass(a, x) >= t: x = from + share / of * span in the bin or piece that holds it
+    double from = a, share = t, of = m_a, span = a_hi - a, least = a;
+    if (!same_in_all(m_a >= t)) {
+        // the first place in the first run in which the mass reaches t
+        const unsigned long long there1 = __ballot(in1 && cum1 >= t), there2 = __ballot(in2 && cum2 >= t), there3 = __ballot(in3 && cum3 >= t);
+        if ((there1 | there2 | there3) == 0ull) {
+            // the mass reaches t in the piece of c's bin, or t is a rounding above all the mass: then the answer
+            // is where the mass ends
+            if (!same_in_all(m_c > 0.0))
+                return fmin(fmax(last_mass_edge(T, P, Q, same_in_all(m_a > 0.0) ? a_hi : a), a), c);
+            from = c_e0; share = t - all; of = m_c; span = c - c_e0;
         } else {
-            const double e0 = bin_edge(at_idx, nb);
-            x = e0 + (t - prev) / T.H[at_idx] * (bin_edge(at_idx + 1u, nb) - e0);
-            x = fmax(x, e0);
+            const unsigned long long there = there1 != 0ull ? there1 : there2 != 0ull ? there2 : there3;
+            uint32_t first = (uint32_t)__ffsll((long long)there) - 1u;
+            const double cum = there1 != 0ull ? cum1 : there2 != 0ull ? cum2 : cum3;
+            const double base = there1 != 0ull ? m_a : there2 != 0ull ? base2 : base3;
+            double prev = first > 0u ? lane_value(cum, first - 1u) : base;
+            uint32_t bin = there1 != 0ull ? P + first : Q1 + first;
+            if (there1 == 0ull && there2 != 0ull) {                    // into the node that holds it
+                const uint32_t b0 = (p1 + first) * kWave;
+                const double below = prev + wave_prefix(T.H[b0 + lane]);
+                const unsigned long long reached = __ballot(below >= t);
+                if (reached == 0ull)       // the node's mass reached t and the sum of its parts, rounded otherwise, did not
+                    return fmin(fmax(last_mass_edge(T, P, b0 + kWave, same_in_all(m_a > 0.0) ? a_hi : a), a), c);
+                first = (uint32_t)__ffsll((long long)reached) - 1u;
+                prev = first > 0u ? lane_value(below, first - 1u) : prev;
+                bin = b0 + first;
+            }
+            from = bin_edge(bin, nb);
+            share = t - prev; of = T.H[bin]; span = bin_edge(bin + 1u, nb) - from; least = from;
         }
     }
+    const double x = fmax(from + share / of * span, least);
     return fmin(fmax(x, a), c);
+}
+
+// All lanes of a wave call this with the same a and c and get the same x.
+__device__ __forceinline__ double stationary_point(const Tree& T, double a, double c)
+{
+    if (!same_in_all(c > a)) return a;
+    const uint32_t ba = same_in_all(bin_containing(T.n_bins, a)), bc = same_in_all(bin_containing(T.n_bins, c));
+    return bc <= ((ba + kWave) & ~(kWave - 1u)) ? stationary_between<true>(T, a, c, ba, bc) : stationary_between<false>(T, a, c, ba, bc);
 }
 
 // The sweeps update level j from the new l_{j-1} and the old l_{j+1}, one level after the other.
 // Update (sweep s, level j) therefore only waits for (s, j-1) and (s-1, j+1), and all updates with
-// the same 2s + j can run together: row s of the workgroup's 16 rows of 16 lanes carries sweep s, two
-// levels behind row s-1, and takes its upper neighbour from what that row left in LDS one step ago.
+// the same 2s + j can run together: wave s of the workgroup carries sweep s, two
+// levels behind wave s-1, and takes its upper neighbour from what that wave left in LDS one step ago.
 // Same updates in the same order as the plain double loop, in 2 sweeps + n_sym steps instead of
 // sweeps * n_sym.
-__global__ __launch_bounds__(256) void k_fit(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
-                                             uint32_t sweeps)
+constexpr uint32_t kFitWaves = 16;
+__global__ __launch_bounds__(kFitWaves * kWave) void k_fit(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
+                                                           uint32_t sweeps)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
-    double* H = reinterpret_cast<double*>(s_raw);                // [n_bins]
-    __shared__ double s_m1[QGX_MAX_BINS / 16], s_r1[QGX_MAX_BINS / 16];
-    __shared__ double s_m2[QGX_MAX_BINS / 256], s_r2[QGX_MAX_BINS / 256];
+    double* H = reinterpret_cast<double*>(s_raw);                // [n_bins + kTreeDoubles]
     __shared__ double s_lev[kSymMax + 1];                         // the table between passes
-    __shared__ double s_moved[2][kRow];                           // what each row moved in the last two steps
+    __shared__ double s_moved[2][kFitWaves];                      // what each wave moved in the last two steps
 
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t b = tid; b < n_bins; b += 256u) H[b] = hist[b];
+    const uint32_t tid = threadIdx.x, nthreads = blockDim.x;
+    for (uint32_t b = tid; b < n_bins; b += nthreads) H[b] = hist[b];
     __syncthreads();
-    const uint32_t n1 = n_bins >> 4, n2 = n_bins >> 8;            // n_bins is a multiple of 64
-    if (tid < n1) {
-        const double edge = bin_edge(16u * tid + 16u, n_bins);
-        double m = 0.0, r = 0.0;
-        for (uint32_t b = 16u * tid; b < 16u * tid + 16u; ++b) {
-            m += H[b];
-            r += H[b] * (edge - 0.5 * (bin_edge(b, n_bins) + bin_edge(b + 1u, n_bins)));
-        }
-        s_m1[tid] = m; s_r1[tid] = r;
-    }
-    __syncthreads();
-    // the last node of 256 is short when n_bins is not a multiple of 256: nothing reads it then (a run of
-    // nodes of 256 only holds whole ones), but its slot is written all the same
-    if (tid < (n_bins + 255u) >> 8) {
-        const uint32_t last = min(16u * tid + 16u, n1);
-        const double edge = bin_edge(16u * last, n_bins);
-        double m = 0.0, r = 0.0;
-        for (uint32_t i = 16u * tid; i < last; ++i) {
-            m += s_m1[i];
-            r += (edge - bin_edge(16u * i + 16u, n_bins)) * s_m1[i] + s_r1[i];
-        }
-        s_m2[tid] = m; s_r2[tid] = r;
+    // the nodes, a wave each (n_bins is a multiple of 64)
+    const uint32_t wave = same_in_all(tid / kWave), waves = nthreads / kWave, lane = tid % kWave;
+    for (uint32_t i = wave; i < n_bins / kWave; i += waves) {
+        const uint32_t b = i * kWave + lane;
+        const double edge = bin_edge((i + 1u) * kWave, n_bins), mid = 0.5 * (bin_edge(b, n_bins) + bin_edge(b + 1u, n_bins));
+        const double m = wave_sum(H[b]), r = wave_sum(H[b] * (edge - mid));
+        if (lane == 0u) { H[n_bins + i] = m; H[n_bins + kNodes + i] = r; }
     }
     const uint32_t n_sym = tab->n_sym;
     if (tid < n_sym) s_lev[tid] = (double)tab->levels[tid];
     __syncthreads();
-    // is there any mass at all?  (terms that are not negative: the order of the sum does not matter to that)
-    double total = 0.0;
-    for (uint32_t i = 0; i < (n_bins + 255u) >> 8; ++i) total += s_m2[i];
-    (void)n2;
+    // is there any mass at all?
+    const double total = wave_sum(lane < n_bins / kWave ? H[n_bins + lane] : 0.0);
 
-    const Tree T = {H, s_m1, s_r1, s_m2, s_r2, n_bins};
-    const uint32_t row = tid >> 4, top = n_sym - 1u;
-    if (total > 0.0 && n_sym > 2u) {
-        for (uint32_t first = 0; first < sweeps; first += kRow) {
-            const uint32_t ns = min(kRow, sweeps - first);               // sweeps of this pass, one per row
-            double mine = 0.0;                      // the level this row moved in its last step
+    const Tree T = {H, n_bins};
+    const uint32_t top = n_sym - 1u;
+    if (same_in_all(total > 0.0) && n_sym > 2u) {
+        for (uint32_t first = 0; first < sweeps; first += waves) {
+            const uint32_t ns = min(waves, sweeps - first);              // sweeps of this pass, one per wave
+            double mine = 0.0;                      // the level this wave moved in its last step
             const uint32_t steps = 2u * (ns - 1u) + (top - 1u);
             for (uint32_t t = 1; t <= steps; ++t) {
-                const int j = (int)t - 2 * (int)row;
-                const bool active = row < ns && j >= 1 && j < (int)top;
-                if (active) {
-                    // the row below moved level j + 1 one step ago; the first row reads the table of the last pass
-                    double above = row == 0u ? s_lev[j + 1] : s_moved[(t - 1u) & 1u][row - 1u];
+                const int j = (int)t - 2 * (int)wave;
+                if (wave < ns && j >= 1 && j < (int)top) {
+                    // the wave before moved level j + 1 one step ago; the first wave reads the table of the last pass
+                    double above = wave == 0u ? s_lev[j + 1] : s_moved[(t - 1u) & 1u][wave - 1u];
                     if (j + 1 == (int)top) above = 1.0;
                     const double below = j == 1 ? 0.0 : mine;
                     mine = stationary_point(T, below, above);
-                    if ((tid & (kRow - 1u)) == 0u) {
-                        s_moved[t & 1u][row] = mine;
-                        if (row == ns - 1u) s_lev[j] = mine;
+                    if ((tid & (kWave - 1u)) == 0u) {
+                        s_moved[t & 1u][wave] = mine;
+                        if (wave == ns - 1u) s_lev[j] = mine;
                     }
                 }
                 __syncthreads();
@@ -630,8 +598,9 @@ __global__ __launch_bounds__(256) void k_fit(Tables* tab, const double* __restri
 
 hipError_t launch_fit(Tables* tab, const double* hist, uint32_t n_bins, uint32_t sweeps, hipStream_t st)
 {
-    const size_t lds = (size_t)n_bins * sizeof(double);
-    hipLaunchKernelGGL(k_fit, dim3(1), dim3(256), lds, st, tab, hist, n_bins, sweeps);
+    const size_t lds = ((size_t)n_bins + kTreeDoubles) * sizeof(double);
+    const uint32_t waves = min(max(sweeps, 8u), kFitWaves);        // (eight for the nodes)
+    hipLaunchKernelGGL(k_fit, dim3(1), dim3(waves * kWave), lds, st, tab, hist, n_bins, sweeps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_build_tables(tab, st);
