@@ -618,7 +618,7 @@ hipError_t launch_fit(Tables* tab, const double* hist, uint32_t n_bins, uint32_t
 // cheapest 2 (n - 1) entries of the top list are bought, a package standing for its two entries one
 // level down.  A symbol's length is the number of its coins bought.  Equal weights: coin before
 // package, lower index first.  Words are numbered canonically by (length, index), first bit first.
-constexpr uint32_t kFitCodeThreads = 512;
+constexpr uint32_t kFitCodeThreads = 1024;
 // pieces of 64 bins: 64 for all the bins, and one more for every gap (its first piece starts anywhere, its last ends anywhere)
 constexpr uint32_t kFitPieces = QGX_MAX_BINS / 64 + 2 * kSymMax;
 __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const double* __restrict__ hist, uint32_t n_bins,
@@ -626,7 +626,7 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
     double* H = reinterpret_cast<double*>(s_raw);                      // [n_bins]
-    __shared__ double s_part[kFitCodeThreads];
+    __shared__ double s_part[kFitCodeThreads / kWave];
     __shared__ double s_lev[kSymMax];
     __shared__ unsigned long long s_w[kSymMax], s_sw[kSymMax], s_cur[2 * kSymMax], s_nxt[2 * kSymMax];
     __shared__ uint8_t s_pkg[kMaxCode][2 * kSymMax];
@@ -636,43 +636,56 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
     const uint32_t tid = threadIdx.x, n = tab->n_sym;
     double part = 0.0;
     for (uint32_t b = tid; b < n_bins; b += kFitCodeThreads) { const double h = hist[b]; H[b] = h; part += h; }
-    s_part[tid] = part;
+    const uint32_t lane = tid % kWave, wave = tid / kWave;
+    part = wave_sum(part);
+    if (lane == 0u) s_part[wave] = part;
     if (tid < n) s_lev[tid] = (double)tab->levels[tid];
     __syncthreads();
-    for (uint32_t off = kFitCodeThreads / 2; off > 0; off >>= 1) {
-        if (tid < off) s_part[tid] += s_part[tid + off];
-        __syncthreads();
-    }
-    const double total = s_part[0];
+    const double total = wave_sum(lane < kFitCodeThreads / kWave ? s_part[lane] : 0.0);
 
     // p_j.  The bins under a gap [l_j, l_{j+1}], a piece of 64 of them per wave and turn, a bin per lane: what the
-    // piece sends up to l_{j+1} and down to l_j, summed across the wave; then every level adds up the pieces of the
-    // gap below it and of the gap above, in order.  (A row of lanes per level left the gap above l_0 = 0, which
-    // spans most of the bins, to sixteen lanes: the kernel took 91 us for 33 symbols, now 36.)
+    // piece sends up to l_{j+1} and down to l_j, summed across the wave; then a wave per level adds up the pieces of the
+    // gap below it and of the gap above.  Nothing here fills the chip, so what counts is the number of dependent
+    // accesses to LDS: which gap a piece belongs to is looked up for all pieces at once, counts are scanned across a wave,
+    // and loops over all symbols have their loads ahead.  (33 symbols: a row of lanes per level 91 us, pieces found and added
+    // up one after the other by half as many waves 35, now 28.)
     __shared__ uint32_t s_b0[kSymMax], s_first[kSymMax + 1];
+    __shared__ uint8_t s_gap[kFitPieces];
     __shared__ double s_up[kFitPieces], s_down[kFitPieces];
-    if (tid + 1u < n) {
-        uint32_t b = bin_of((float)s_lev[tid], n_bins);
-        while (b > 0 && bin_edge(b, n_bins) > s_lev[tid]) --b;
-        const uint32_t b_end = bin_of((float)s_lev[tid + 1u], n_bins) + 1u;      // one past the last bin the gap may reach
-        s_b0[tid] = b;
-        s_first[tid] = b_end > b ? (b_end - b + (kWave - 1u)) / kWave : 0u;      // pieces, for now
+    static_assert(kSymMax == 2 * kWave && kFitPieces <= kFitCodeThreads, "two gaps a lane, a thread per piece");
+    if (wave == 0u) {
+        uint32_t count[2];
+#pragma unroll
+        for (uint32_t h = 0; h < 2u; ++h) {                                      // gaps 2 lane and 2 lane + 1
+            const uint32_t j = 2u * lane + h;
+            count[h] = 0u;
+            if (j + 1u < n) {
+                uint32_t b = bin_of((float)s_lev[j], n_bins);
+                while (b > 0 && bin_edge(b, n_bins) > s_lev[j]) --b;
+                const uint32_t b_end = bin_of((float)s_lev[j + 1u], n_bins) + 1u;    // one past the last bin the gap may reach
+                s_b0[j] = b;
+                count[h] = b_end > b ? (b_end - b + (kWave - 1u)) / kWave : 0u;
+            }
+        }
+        const uint32_t both = count[0] + count[1], before = wave_incl_scan(both) - both;
+        s_first[2u * lane] = before;                                             // first piece of a gap; past the last gap: all of them
+        s_first[2u * lane + 1u] = before + count[0];
     }
     __syncthreads();
-    uint32_t before = 0;
-    if (tid < n) for (uint32_t k = 0; k < tid; ++k) before += s_first[k];
-    __syncthreads();
-    if (tid < n) s_first[tid] = before;                                          // first piece of gap tid; [n - 1]: all of them
-    __syncthreads();
-    const uint32_t pieces = s_first[n - 1u], lane = tid % kWave;
-    for (uint32_t q = tid / kWave; q < pieces; q += kFitCodeThreads / kWave) {
-        uint32_t lo_j = 0, hi_j = n - 2u;                                        // the last gap that starts at or before piece q
+    const uint32_t pieces = s_first[n - 1u];
+    if (tid < pieces) {
+        uint32_t lo_j = 0, hi_j = n - 2u;                                        // the last gap that starts at or before the piece
         while (lo_j < hi_j) {
             const uint32_t mid = (lo_j + hi_j + 1u) >> 1;
-            if (s_first[mid] <= q) lo_j = mid; else hi_j = mid - 1u;
+            if (s_first[mid] <= tid) lo_j = mid; else hi_j = mid - 1u;
         }
-        const double a = s_lev[lo_j], c = s_lev[lo_j + 1u];
-        const uint32_t b = s_b0[lo_j] + (q - s_first[lo_j]) * kWave + lane;
+        s_gap[tid] = (uint8_t)lo_j;
+    }
+    __syncthreads();
+    for (uint32_t q = wave; q < pieces; q += kFitCodeThreads / kWave) {
+        const uint32_t j = s_gap[q];
+        const double a = s_lev[j], c = s_lev[j + 1u];
+        const uint32_t b = s_b0[j] + (q - s_first[j]) * kWave + lane;
         double rise = 0.0, fall = 0.0;
         if (b < n_bins) {
             const double e0 = bin_edge(b, n_bins), e1 = bin_edge(b + 1, n_bins);
@@ -689,16 +702,15 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
         if (lane == 0u) { s_up[q] = rise; s_down[q] = fall; }
     }
     __syncthreads();
-    if (tid < n) {
+    for (uint32_t j = wave; j < n; j += kFitCodeThreads / kWave) {
         double acc = 0.0;
-        if (total > 0.0) {
-            if (tid > 0u) for (uint32_t q = s_first[tid - 1u]; q < s_first[tid]; ++q) acc += s_up[q];
-            if (tid + 1u < n) for (uint32_t q = s_first[tid]; q < s_first[tid + 1u]; ++q) acc += s_down[q];
-            acc /= total;
-        }
-        result->p[tid] = acc;
+        if (j > 0u) for (uint32_t q = s_first[j - 1u] + lane; q < s_first[j]; q += kWave) acc += s_up[q];
+        if (j + 1u < n) for (uint32_t q = s_first[j] + lane; q < s_first[j + 1u]; q += kWave) acc += s_down[q];
+        acc = total > 0.0 ? wave_sum(acc) / total : 0.0;
+        if (lane != 0u) continue;
+        result->p[j] = acc;
         const double x = floor(acc * 4294967296.0 + 0.5);
-        s_w[tid] = x >= 1.0 ? (unsigned long long)x : 1ull;
+        s_w[j] = x >= 1.0 ? (unsigned long long)x : 1ull;
     }
     __syncthreads();
 
@@ -706,6 +718,7 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
     if (tid < n) {
         const unsigned long long wi = s_w[tid];
         uint32_t rank = 0;
+#pragma unroll 8
         for (uint32_t k = 0; k < n; ++k) {
             const unsigned long long wk = s_w[k];
             rank += (wk < wi || (wk == wi && k < tid)) ? 1u : 0u;
@@ -771,6 +784,7 @@ __global__ __launch_bounds__(kFitCodeThreads) void k_fit_code(Tables* tab, const
     if (tid < n) {
         const uint32_t L = s_len[tid];
         uint32_t code = 0;
+#pragma unroll 8
         for (uint32_t k = 0; k < n; ++k) {
             const uint32_t lk = s_len[k];
             if (lk < L || (lk == L && k < tid)) code += 1u << (L - lk);

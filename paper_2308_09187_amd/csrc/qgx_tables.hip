@@ -55,8 +55,9 @@ static __device__ void build_tables_block(Tables* tab)
         }
         code[j] = cw;
     }
-    for (int i = tid; i < kDlut; i += nt) tab->dlut[i] = (uint16_t)kDlutReject;
-    for (int i = tid; i < kWide; i += nt) tab->dlutw[i] = make_uint2(kWideReject, 0u);
+    constexpr uint32_t kTwoRejects = kDlutReject | (kDlutReject << 16);
+    for (int i = tid; i < kDlut / 8; i += nt) reinterpret_cast<uint4*>(tab->dlut)[i] = make_uint4(kTwoRejects, kTwoRejects, kTwoRejects, kTwoRejects);
+    for (int i = tid; i < kWide / 2; i += nt) reinterpret_cast<uint4*>(tab->dlutw)[i] = make_uint4(kWideReject, 0u, kWideReject, 0u);
     __syncthreads();
 
     const int mant = cell_mant(n_sym), cells = cell_count(mant), cell_shift = 23 - mant;
@@ -128,6 +129,7 @@ static __device__ void build_tables_block(Tables* tab)
         const uint32_t len = cw >> 16;
         if (len <= (uint32_t)kWideBits || len > (uint32_t)kMaxCode) continue;
         const uint32_t head = cw & ((1u << kWideBits) - 1u);                  // (the first-written bit is bit 0)
+#pragma unroll 8
         for (uint32_t i = 0; i < n_sym; ++i) {
             const uint32_t ci = code[i];
             if (i != j && (ci >> 16) > (uint32_t)kWideBits && (ci & ((1u << kWideBits) - 1u)) == head) tab->wide_ok = 0u;
@@ -136,11 +138,13 @@ static __device__ void build_tables_block(Tables* tab)
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_build_tables(Tables* tab) { build_tables_block(tab); }
+// One workgroup, of as many threads as there are: 33 symbols 7.7 us with 256 and two bytes a store, now 5.1; 65 symbols 21, now 15.
+constexpr int kTableThreads = 1024;
+__global__ __launch_bounds__(kTableThreads) void k_build_tables(Tables* tab) { build_tables_block(tab); }
 
 hipError_t launch_build_tables(Tables* tab, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_build_tables, dim3(1), dim3(256), 0, st, tab);
+    hipLaunchKernelGGL(k_build_tables, dim3(1), dim3(kTableThreads), 0, st, tab);
     return hipGetLastError();
 }
 
