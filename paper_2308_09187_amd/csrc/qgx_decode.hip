@@ -6,7 +6,7 @@
 // A wave's task is half a chunk position: 2048 coordinates, of which every lane parses one run of 32
 // (a sub-chunk), starting at the bit offset the sub-chunk table gives.  The wave copies its half of a
 // worker's chunk from the payload into LDS with coalesced 16-byte loads, then every lane parses its
-// run: a 64-bit window from three LDS words per three symbols, one table look-up by the next 13 (or 11)
+// run: a 64-bit window from three LDS words per four symbols, one table look-up by the next 13 (or 11)
 // stream bits for each symbol's length and level, the sign bit, one multiply by the bucket norm.  A symbol's
 // length decides where the next one starts, so a parse is one long dependent chain of LDS look-ups.
 // The K decoded values of a coordinate are summed in registers in worker order, so decoded vectors
@@ -152,10 +152,14 @@ __device__ __forceinline__ void commit_half(uint32_t* stage, const uint4 (&pre)[
 constexpr int kTabLvalBytes = kSymMax * 4;
 constexpr int kTabBytes = kTabLvalBytes + kDlut * 2;
 
-// Symbols are parsed in groups of up to three from one 64-bit window (three LDS words): a symbol
-// takes at most 15 bits with its sign, so the third one still starts inside the first word.  An entry of the
-// 13-bit table is the symbol's bits incl. sign less one | 4 idx << 4 with bits 4 and 5 clear, so sums of entries
+// Symbols are parsed in groups of four from one 64-bit window (three LDS words): a symbol takes at most 14 bits with
+// its sign, so two leave the first word's last bits to shift from, and the fourth starts before bit 42 and has its 14 bits
+// in the window.  (Groups of three need a shift less and three windows more a run: first half-step of 8 x 2^24
+// coordinates 74.8 us, now 69.8; of 8 x 9.86 M 56.7, now 53.5; second 99.6, now 92.8.)  An entry of the
+// 13-bit table is the symbol's bits incl. sign less one | 4 idx << 4 with bits 4 and 5 clear, so sums of four entries
 // carry the consumed bits in their low six bits; the 8-byte table's entries are minus the symbol's bits.
+constexpr int kGroup = 4;
+static_assert(kSub % kGroup == 0 && 2 * kMaxSymBits < 32 && 3 * kMaxSymBits + kMaxSymBits <= 63 && kGroup * kMaxSymBits < 64, "a group in a window");
 struct Window { uint32_t w0, w1, w2; };
 
 __device__ __forceinline__ Window read_window(const uint32_t* stage, uint32_t p)
@@ -167,6 +171,10 @@ __device__ __forceinline__ Window read_window(const uint32_t* stage, uint32_t p)
     return Window{lds_load_u32(at), lds_load_u32(at + 4u), lds_load_u32(at + 8u)};
 }
 
+// Minus the bits of a symbol (sign included) in the low six bits of sums of four, from its table entry.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t negative_bits(uint32_t e) { return WIDE ? e : ~e; }
+
 // The dependent chain: window i needs the lengths of the symbols before it.  The cursor r is a bit position
 // in the buffer and moves DOWN, the three words from it give the 64 bits with the first stream bit on top by
 // two funnel shifts and nothing else.
@@ -174,35 +182,40 @@ __device__ __forceinline__ Window read_window(const uint32_t* stage, uint32_t p)
 // so bit 31 of a symbol's window is the last bit of the symbol before it, which is that symbol's sign
 // if it has one.  The sign of a symbol is thus read off the window of the next one with a single
 // AND-OR, no shift by its length: W[i + 1] for symbol i, the next group's W[0] for a group's last
-// symbol, and for the last group of a run (LAST, two symbols) the window after its second symbol, W[2].
+// symbol, and for the last group of a run (LAST) the window after its last symbol, W[4].
 // The table index sits one bit lower (bits 30..20 resp. 30..18).
-// `seen` gathers the AND of the groups' (negative) bit counts: a reject entry leaves a zero among bits
+// `seen` gathers the AND of the (negative) bit counts of the groups' halves: a reject entry leaves a zero among bits
 // 15..31, valid entries never do, so no per-symbol flag is kept.
 // WIDE: the 8-byte table's entries are the negative counts themselves and only need adding up.
-template <int N, bool WIDE, bool LAST>
+template <bool WIDE, bool LAST>
 __device__ __forceinline__ void parse_group(const Window& w, const unsigned char* tab, uint32_t& r,
-                                            uint32_t (&W)[4], uint32_t (&e)[3], float (&lv)[3], uint32_t& seen)
+                                            uint32_t (&W)[kGroup + 1], uint32_t (&e)[kGroup], float (&lv)[kGroup], uint32_t& seen)
 {
-    static_assert(!LAST || N == 2, "a run of 32 symbols ends with a group of two");
-    const uint32_t top = __builtin_amdgcn_alignbit(w.w2, w.w1, r);            // shifts use r mod 32
-    const uint32_t nxt = __builtin_amdgcn_alignbit(w.w1, w.w0, r);
-    uint32_t neg = 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        W[i] = i == 0 ? top : __builtin_amdgcn_alignbit(top, nxt, neg);       // (top:nxt) << used, upper word
+    uint32_t half[2];
+    auto look_up = [&](int i, uint32_t& neg) __attribute__((always_inline)) {
         if constexpr (WIDE) {
             const uint2 t = *reinterpret_cast<const uint2*>(tab + kTabLvalBytes + ((W[i] >> 17) & 0x3FF8u));
             e[i] = t.x;
             lv[i] = __uint_as_float(t.y);
-            neg = i == 0 ? t.x : neg + t.x;
+            neg = i % 2 == 0 ? t.x : neg + t.x;
         } else {
             e[i] = *reinterpret_cast<const uint16_t*>(tab + kTabLvalBytes + ((W[i] >> 17) & 0x3FFEu));
-            neg += ~e[i];
+            neg = i % 2 == 0 ? negative_bits<false>(e[i]) : neg + negative_bits<false>(e[i]);
         }
-    }
-    if constexpr (LAST) W[N] = __builtin_amdgcn_alignbit(top, nxt, neg);     // at least two bits used: never a shift by 0
-    seen &= neg;
-    r += neg | 0xFFFFFFC0u;                                                   // down by the bits used
+    };
+    const uint32_t nxt = __builtin_amdgcn_alignbit(w.w1, w.w0, r);
+    W[0] = __builtin_amdgcn_alignbit(w.w2, w.w1, r);                          // shifts use r mod 32
+    look_up(0, half[0]);
+    W[1] = __builtin_amdgcn_alignbit(W[0], nxt, half[0]);                     // (W[0]:nxt) << used, upper word
+    look_up(1, half[0]);
+    W[2] = __builtin_amdgcn_alignbit(W[0], nxt, half[0]);
+    const uint32_t after = __builtin_amdgcn_alignbit(nxt, 0u, half[0]);       // what follows W[2]
+    look_up(2, half[1]);
+    W[3] = __builtin_amdgcn_alignbit(W[2], after, half[1]);
+    look_up(3, half[1]);
+    if constexpr (LAST) W[4] = __builtin_amdgcn_alignbit(W[2], after, half[1]);      // at least two bits used: never a shift by 0
+    seen &= half[0] & half[1];
+    r += (half[0] + half[1]) | 0xFFFFFFC0u;                                   // down by the bits used
 }
 
 // norm with the sign of the symbol whose last bit is bit 31 of `w_next` (norms are not negative)
@@ -226,12 +239,6 @@ __device__ __forceinline__ float level_of(const unsigned char* tab, uint32_t e)
 {
     return *reinterpret_cast<const float*>(tab + (e >> 4));                  // the entry holds 4 * idx
 }
-
-// Bits of a symbol (sign included) and the reject flag, from its table entry.
-template <bool WIDE>
-__device__ __forceinline__ uint32_t symbol_bits(uint32_t e) { return WIDE ? 0u - e : (e & 15u) + 1u; }
-template <bool WIDE>
-__device__ __forceinline__ bool is_reject(uint32_t e) { return WIDE ? e == kWideReject : (e & kDlutReject) != 0u; }
 
 // Level values and decode table of one Tables object into the decoder's LDS array (WIDE: the table of
 // 8-byte entries, which has the same size and holds the level values itself).
@@ -450,7 +457,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         auto parse = [&](auto pair_tag) __attribute__((always_inline)) {
             constexpr bool PAIR = decltype(pair_tag)::value;                    // both chains
             uint32_t q = r_base - t, qb = r_base - tb;
-            uint32_t W[4], e[3], W_b[4], e_b[3];
+            uint32_t W[kGroup + 1], e[kGroup], W_b[kGroup + 1], e_b[kGroup];
             float held = 0.0f, held_b = 0.0f;
             uint32_t used = 0, used_b = 0, ignored = 0;
             const int cnt = RAG ? symbols_of(fresh) : kSub;
@@ -470,6 +477,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                     } else {
                         const float df = (val_p - val) * down;
                         sd32 = fmaf(df, df, sd32);
+                        if (at % 6 == 4 || at == kSub - 1) { sw += (double)sd32; sd32 = 0.0f; }
                     }
                 } else if constexpr (MODE == DecMode::Half1) {           // no previous streams: the vectors of t count as zero
                     const float val = symbol_value<false>(w_next, lv, n);
@@ -486,53 +494,54 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                 }
             };
 #pragma unroll
-            for (int s = 0; s < kSub; s += 3) {
+            for (int s = 0; s < kSub; s += kGroup) {
                 // a group's last symbol is finished when the next group's first window (its sign on top) is there
-                float lv[3] = {0.f, 0.f, 0.f}, lv_b[3] = {0.f, 0.f, 0.f};
-                const bool last = s + 3 > kSub;
-                const int num = last ? 2 : 3;
+                float lv[kGroup] = {0.f, 0.f, 0.f, 0.f}, lv_b[kGroup] = {0.f, 0.f, 0.f, 0.f};
+                const bool last = s + kGroup == kSub;
                 if (!last) {
-                    parse_group<3, WIDE, false>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
+                    parse_group<WIDE, false>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
                     wn = read_window(stage, q);
                     if constexpr (PAIR) {
-                        parse_group<3, WIDE, false>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
+                        parse_group<WIDE, false>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
                         wn_b = read_window(stage_b, qb);
                     }
                 } else {
-                    parse_group<2, WIDE, true>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
-                    if constexpr (PAIR) parse_group<2, WIDE, true>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
+                    parse_group<WIDE, true>(wn, s_tab, q, W, e, lv, RAG ? ignored : seen);
+                    if constexpr (PAIR) parse_group<WIDE, true>(wn_b, s_tab_b, qb, W_b, e_b, lv_b, RAG ? ignored : seen);
                 }
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    if (j >= num) continue;
+                for (int j = 0; j < kGroup; ++j) {
                     if constexpr (!WIDE) {
                         lv[j] = level_of(s_tab, e[j]);
                         if constexpr (PAIR) lv_b[j] = level_of(s_tab_b, e_b[j]);
                     }
-                    if constexpr (RAG) {
+                    if constexpr (RAG) {                                  // (a symbol past the count: minus one bit, no value)
                         const bool in = s + j < cnt;
-                        used += in ? symbol_bits<WIDE>(e[j]) : 0u;
-                        bad |= in & is_reject<WIDE>(e[j]);
+                        e[j] = in ? negative_bits<WIDE>(e[j]) : 0xFFFFFFFFu;
                         lv[j] = in ? lv[j] : 0.0f;
                         if constexpr (PAIR) {
-                            used_b += in ? symbol_bits<WIDE>(e_b[j]) : 0u;
-                            bad |= in & have_b & is_reject<WIDE>(e_b[j]);
+                            e_b[j] = in ? negative_bits<WIDE>(e_b[j]) : 0xFFFFFFFFu;
                             lv_b[j] = in ? lv_b[j] : 0.0f;
                         }
                     }
                 }
+                if constexpr (RAG) {
+                    used -= (e[0] + e[1] + e[2] + e[3]) | 0xFFFFFFC0u;
+                    seen &= (e[0] + e[1]) & (e[2] + e[3]);
+                    if constexpr (PAIR) {
+                        used_b -= (e_b[0] + e_b[1] + e_b[2] + e_b[3]) | 0xFFFFFFC0u;
+                        seen &= (e_b[0] + e_b[1]) & (e_b[2] + e_b[3]);
+                    }
+                }
                 if (s > 0) emit(s - 1, W[0], held, W_b[0], held_b);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) emit(s + j, W[j + 1], lv[j], W_b[j + 1], lv_b[j]);
-                held = lv[2]; held_b = lv_b[2];
-                if constexpr (PREV && !RAG) {
-                    if ((s / 3) % 2 == 1 || last) { sw += (double)sd32; sd32 = 0.0f; }
-                }
+                for (int j = 0; j < (last ? kGroup : kGroup - 1); ++j) emit(s + j, W[j + 1], lv[j], W_b[j + 1], lv_b[j]);
+                held = lv[kGroup - 1]; held_b = lv_b[kGroup - 1];
                 // A group's values are done before the next group's look-ups.  The compiler would move them behind
                 // the whole chain of look-ups (into the block after the parse, and the scheduler again inside it)
                 // and keep every entry and window until then, hundreds of registers.
 #pragma unroll
-                for (int at = s > 0 ? s - 1 : 0; at < s + 2; ++at) {
+                for (int at = s > 0 ? s - 1 : 0; at < s + (last ? kGroup : kGroup - 1); ++at) {
                     asm volatile("" : "+v"(acc[at]));
                     if constexpr (MODE == DecMode::Decode && PAIR) asm volatile("" : "+v"(acc_b[at]));
                 }
@@ -544,7 +553,8 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (RAG) {
-                bad |= ((cnt > 0) & (t + used != t_end)) | ((cnt > 0) & have_b & (tb + used_b != tb_end));
+                const uint32_t rest = (uint32_t)(kSub - cnt);
+                bad |= ((cnt > 0) & (t + used != t_end + rest)) | ((cnt > 0) & have_b & (tb + used_b != tb_end + rest));
             } else {
                 bad |= (r_base - q) ^ t_end;
                 if constexpr (PAIR) bad |= (r_base - qb) ^ tb_end;
