@@ -269,6 +269,17 @@ __device__ __forceinline__ void chunk_geometry(const Layout& lay, uint32_t c, ui
     }
 }
 
+// S, gamma_{t+1}, t at the end of the second half-step.
+__device__ __forceinline__ void finish_scalars(Scalars* sc, double sum, uint32_t K)
+{
+    const double S = sum + sc->S;
+    const double gamma = (double)K / sqrt(1.0 + S);           // Theorem 3: gamma_t = K (1 + sum ...)^(-1/2)
+    sc->S = S;
+    sc->gamma = gamma;
+    sc->gamma_f = (float)gamma;
+    sc->t += 1ull;
+}
+
 template <bool B> struct BoolTag { static constexpr bool value = B; };
 
 // Four consecutive floats; a decoded vector of an odd length puts them at any multiple of 4 bytes.
@@ -292,7 +303,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "the waves of a workgroup in groups of 1, 2 or 4");
     static_assert(KSPLIT == 1 || MODE != DecMode::Decode, "plain decoding has nothing to add up");
     extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][2][stage_stride]
-    __shared__ double s_sd[KSPLIT > 1 ? most_waves<MODE, PREV, TWO>() : 1];
+    __shared__ double s_sd[KSPLIT > 1 || MODE == DecMode::Half1 ? most_waves<MODE, PREV, TWO>() : 1];
     constexpr bool kTwo = two_chains<MODE, PREV>();       // chains per lane
     constexpr uint32_t kBufs = kTwo ? 2u : 1u;
     __shared__ __align__(16) unsigned char s_tab[kTabBytes];
@@ -392,9 +403,9 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     // words past a half chunk's end are read by the window of its last symbols: keep them defined
     for (uint32_t q = (uint32_t)lane; q < kBufs * stage_stride; q += kWave) stage[q] = 0;
     __syncthreads();
-    if constexpr (KSPLIT == 1) {
+    if constexpr (KSPLIT == 1 && MODE != DecMode::Half1) {
         if (!mine) return;
-    }                                                    // (else: the waves of a group meet at workgroup barriers below)
+    }                                                    // (else: the waves meet at workgroup barriers below)
 
     // From bit t of the staged words to the buffer bit r with the bit before t on top of the 64 bits
     // from r: r = r_base - t (they lie back to front).
@@ -632,11 +643,8 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     }
     if constexpr (MODE == DecMode::Half1) {
         sdiff = wave_sum(sdiff);
-        if constexpr (KSPLIT > 1) {
-            if (lane == 0) s_sd[w] = sdiff;               // joined below, after the first barrier
-        } else {
-            if (lane == 0) a.s_partial[task] = sdiff;
-        }
+        if (lane == 0) s_sd[w] = mine ? sdiff : 0.0;      // joined below, after a barrier
+        if (KSPLIT == 1 && mine && lane == 0 && a.arrived == nullptr) a.s_partial[task] = sdiff;
     }
     // KSPLIT: all waves of the group put their sums there, and after a barrier each of them adds them
     // up (in the order of the workers' runs) for its share of the rows and does the update for those.
@@ -663,7 +671,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         wave_lds_fence();                                     // the rows are read by other lanes than wrote them
         if constexpr (KSPLIT > 1) {
             __syncthreads();
-            if (MODE == DecMode::Half1 && q == 0 && mine && part == 0 && lane == 0) {
+            if (MODE == DecMode::Half1 && q == 0 && mine && part == 0 && lane == 0 && a.arrived == nullptr) {
                 double sd = s_sd[w];
                 for (int j = 1; j < KSPLIT; ++j) sd += s_sd[w + j];
                 a.s_partial[task] = sd;
@@ -737,11 +745,36 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
+    // The scalar end in this launch, where it has no more workgroups than a wave has lanes (a.arrived): each leaves its sum and
+    // counts itself, and the last one to arrive adds up the sums.  A sum is written past the caches (agent scope) and is
+    // there before its workgroup is counted (the wait); it is read past the caches, too.
+    if constexpr (MODE == DecMode::Half1) {
+        if (a.arrived != nullptr) {
+            __syncthreads();
+            if (w == 0) {
+                uint32_t before = 0;
+                if (lane == 0) {
+                    double own = 0.0;
+                    for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
+                    __hip_atomic_store(&a.s_partial[blockIdx.x], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u == gridDim.x) {
+                    const double sum = wave_sum((uint32_t)lane < gridDim.x ? __hip_atomic_load(&a.s_partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0);
+                    if (lane == 0) {
+                        finish_scalars(sc, sum, lay.K);
+                        __hip_atomic_store(a.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+            }
+        }
+    }
     }
 }
 
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
+static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, bool* finished)
 {
     const uint64_t nwaves = MODE == DecMode::Decode ? (uint64_t)lay.n_tasks * ((lay.K + 1u) / 2u) : (uint64_t)lay.n_tasks * (uint32_t)KSPLIT;
     // Workgroups of four waves spread over the compute units and are replaced as soon as four waves are done, but
@@ -757,43 +790,49 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     if (TWO && held(8) >= held(16)) per = 8;                 // (short codes: two of eight beside each other, 160 us to 164)
     for (uint32_t small = 4; small < per; small *= 2)
         if (nwaves <= held(small) * a.n_cu) { per = small; break; }
+    // The scalar end in the same launch: one bucket of 1024, 4 workers, an iteration 37.2 us with a launch of its own, 34.8 without.  With
+    // 751 workgroups (5 x 3000001 coordinates) their sums take the last one longer than the launch does, 116.5 us and 120.
+    const uint64_t grid = (nwaves + per - 1u) / per;
+    DecodeArgs b = a;
+    b.arrived = MODE == DecMode::Half1 && grid <= kWave ? &sc->arrived : nullptr;
+    if (finished) *finished = b.arrived != nullptr;
     const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), dim3((uint32_t)((nwaves + per - 1u) / per)), dim3(per * kWave), lds, st,
-                       lay, tab, sc, a);
+    hipLaunchKernelGGL((k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), dim3((uint32_t)grid), dim3(per * kWave), lds, st,
+                       lay, tab, sc, b);
     return hipGetLastError();
 }
 
 template <DecMode MODE, bool PREV, bool TWO = false>
-static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st)
+static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, bool* finished)
 {
     if constexpr (MODE != DecMode::Decode) {
         if (a.ksplit == 2u) {
-            if (a.wide) return launch_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st);
-            return launch_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st);
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st, finished);
+            return launch_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st, finished);
         }
         if (a.ksplit == 4u) {
-            if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st);
-            return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st);
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st, finished);
+            return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st, finished);
         }
     }
-    if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st);
-    return launch_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st);
+    if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st, finished);
+    return launch_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st, finished);
 }
 
 hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a,
-                         hipStream_t st)
+                         hipStream_t st, bool* finished)
 {
     switch (mode) {
-        case DecMode::Decode: return launch_mode<DecMode::Decode, false>(lay, tab, sc, a, st);
-        case DecMode::Average: return launch_mode<DecMode::Average, false>(lay, tab, sc, a, st);
-        case DecMode::Half0: return launch_mode<DecMode::Half0, false>(lay, tab, sc, a, st);
+        case DecMode::Decode: return launch_mode<DecMode::Decode, false>(lay, tab, sc, a, st, finished);
+        case DecMode::Average: return launch_mode<DecMode::Average, false>(lay, tab, sc, a, st, finished);
+        case DecMode::Half0: return launch_mode<DecMode::Half0, false>(lay, tab, sc, a, st, finished);
         default:
-            if (a.payload_p == nullptr) return launch_mode<DecMode::Half1, false>(lay, tab, sc, a, st);
-            return a.tab_p ? launch_mode<DecMode::Half1, true, true>(lay, tab, sc, a, st)
-                           : launch_mode<DecMode::Half1, true>(lay, tab, sc, a, st);
+            if (a.payload_p == nullptr) return launch_mode<DecMode::Half1, false>(lay, tab, sc, a, st, finished);
+            return a.tab_p ? launch_mode<DecMode::Half1, true, true>(lay, tab, sc, a, st, finished)
+                           : launch_mode<DecMode::Half1, true>(lay, tab, sc, a, st, finished);
     }
 }
 
@@ -812,12 +851,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_half1(uint32_t n_task
     if (threadIdx.x == 0) {
         double S = 0.0;
         for (uint32_t w = 0; w < kFinishThreads / kWave; ++w) S += s_red[w];
-        S += sc->S;
-        const double gamma = (double)K / sqrt(1.0 + S);       // Theorem 3: gamma_t = K (1 + sum ...)^(-1/2)
-        sc->S = S;
-        sc->gamma = gamma;
-        sc->gamma_f = (float)gamma;
-        sc->t += 1ull;
+        finish_scalars(sc, S, K);
     }
 }
 
@@ -837,13 +871,16 @@ __global__ __launch_bounds__(256) void k_x_from_y(uint32_t d, const Scalars* sc,
     if (at < (d & 3u)) X[4u * quads + at] = (anchor ? anchor[4u * quads + at] : 0.0f) + gam * Y[4u * quads + at];
 }
 
-// Two launches.  One, with the sum done by every workgroup and the scalars put down by the last to arrive, was no
+// Two launches, or the second only (`finished`: the half-step has left the scalars already).  One, with the sum done by every workgroup and the scalars put down by the last to arrive, was no
 // faster: iterations of 5 x 3 M 140.8 us (136.8 with two), of 8 x 9.86 M 389.9 (389.5).
 hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_partial, const float* Y,
-                               const float* anchor, float* X_out, hipStream_t st)
+                               const float* anchor, float* X_out, bool finished, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, lay.n_tasks, lay.K, sc, s_partial);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
+    if (!finished) {
+        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, lay.n_tasks, lay.K, sc, s_partial);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || X_out == nullptr) return e;
     const uint32_t grid = min(lay.d / 1024u + 1u, 16384u);
     hipLaunchKernelGGL(k_x_from_y, dim3(grid), dim3(256), 0, st, lay.d, sc, Y, anchor, X_out);

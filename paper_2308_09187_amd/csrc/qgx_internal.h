@@ -93,7 +93,8 @@ struct Scalars {
     unsigned long long total_bits;
     float gamma_f;              // gamma rounded to binary32, what the update kernels multiply by
     unsigned int err;           // QGX_EBIT_*
-    unsigned int pad_[2];
+    unsigned int arrived;       // workgroups of a second half-step that have left their sums; 0 between launches
+    unsigned int pad_;
     unsigned long long avg_count;   // first half-steps added to the running sum since its reset
 };
 
@@ -176,7 +177,8 @@ struct DecodeArgs {
     float* out;                 // Decode: Vhat [K][d]; Average: mean [d]; Half0: X_{t+1/2} [d]
     float* Y;                   // [d] dual state (Half0 reads, Half1 updates)
     const float* anchor;        // [d] or null
-    double* s_partial;          // [n_tasks] per-task partial of S (Half1)
+    double* s_partial;          // [n_tasks] per-task partial of S (Half1), or per workgroup with `arrived`
+    unsigned int* arrived;      // filled in by the launch: where workgroups count themselves, or null
     double* x_sum;              // [d] running sum of the X_{t+1/2} or null (Half0 adds its output)
     uint32_t stage_words;       // most words half a chunk of the code in use touches (multiple of 4)
     uint32_t stage_stride;      // words of one LDS staging buffer (padded layout plus slack)
@@ -213,9 +215,9 @@ hipError_t launch_build_tables(Tables* tab, hipStream_t st);
 hipError_t launch_encode(EncMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a,
                          hipStream_t st);
 hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a,
-                         hipStream_t st);
+                         hipStream_t st, bool* finished = nullptr);      // finished: whether Half1 has left S, gamma and t, too
 hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_partial, const float* Y,
-                               const float* anchor, float* X_out, hipStream_t st);
+                               const float* anchor, float* X_out, bool finished, hipStream_t st);
 hipError_t launch_state_init(const Layout& lay, Scalars* sc, float* Y, float* anchor, const float* X1,
                              hipStream_t st);
 hipError_t launch_average(uint32_t d, const double* x_sum, const Scalars* sc, float* out, hipStream_t st);
