@@ -64,39 +64,6 @@ __device__ __forceinline__ float2 box_muller(uint32_t w_radius, uint32_t w_angle
     return make_float2(r * __builtin_amdgcn_cosf(u2), r * __builtin_amdgcn_sinf(u2));
 }
 
-// Coordinates i0 .. i0 + 3 (i0 a multiple of 4) of F(z) = M z + b.
-__device__ __forceinline__ float4 game_operator_row(const GameArgs& G, uint32_t i0)
-{
-    const float4 z = *reinterpret_cast<const float4*>(G.z + i0);
-    const float4 b = *reinterpret_cast<const float4*>(G.b + i0);
-    const float2 a = *reinterpret_cast<const float2*>(G.a + (i0 >> 1));
-    float4 f;
-    f.x = (G.mu * z.x + a.x * z.y) + b.x;
-    f.y = (G.mu * z.y - a.x * z.x) + b.y;
-    f.z = (G.mu * z.z + a.y * z.w) + b.z;
-    f.w = (G.mu * z.w - a.y * z.z) + b.w;
-    return f;
-}
-
-// The same four coordinates of worker k's dual vector in call `call_id`: F(z) + sigma N, the noise from the
-// Philox block with key (seed_lo, seed_hi) and counter (i0 / 4, 1, k, call_id).  F: game_operator_row(G, i0).
-__device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, uint32_t i0, uint32_t k, uint32_t call_id)
-{
-    uint32_t w[4];
-    philox4x32_10(i0 >> 2, 1u, k, call_id, philox_keys(G.seed_lo, G.seed_hi), w);
-    const float2 n01 = box_muller(w[0], w[1]), n23 = box_muller(w[2], w[3]);
-    F.x += G.sigma * n01.x;
-    F.y += G.sigma * n01.y;
-    F.z += G.sigma * n23.x;
-    F.w += G.sigma * n23.y;
-    return F;
-}
-
-__device__ __forceinline__ float4 game_dual_row(const GameArgs& G, uint32_t i0, uint32_t k, uint32_t call_id)
-{
-    return game_noisy_row(G, game_operator_row(G, i0), i0, k, call_id);
-}
-
 // Between two phases in which the lanes of a wave exchange data through LDS without a workgroup barrier.
 // The hardware runs a wave's LDS instructions in the order they were issued; this keeps the compiler from
 // moving them across the boundary, or from making one side of the exchange part of a branch that only
@@ -230,12 +197,20 @@ __device__ __forceinline__ uint4 nt_load4u(const uint4* p)
     return make_uint4(r.x, r.y, r.z, r.w);
 }
 
+typedef uint32_t lds_u32x2 __attribute__((ext_vector_type(2)));
+
+// Memory as a buffer: a load from past its end gives zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* first, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(first)), 0, (int)bytes, 0x00027000);
+}
+
 // A chunk's coordinates in registers: 16 rows of 256, four to a lane.  Its whole groups of four coordinates are a buffer, outside of
 // which a load gives zeros: no branch whatever the chunk's length, so that the compiler knows how many loads are under way.
 // Vectors of an odd length put a worker's rows at any multiple of 4 bytes, which 16-byte loads take.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rows(const float* first, uint32_t len)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(first)), 0, (int)((len & ~3u) * sizeof(float)), 0x00027000);
+    return buffer_of(first, (len & ~3u) * (uint32_t)sizeof(float));
 }
 
 __device__ __forceinline__ float4 load_row(__amdgpu_buffer_rsrc_t rows, int r, int lane)
@@ -270,6 +245,62 @@ __device__ __forceinline__ float largest_of(const float4& x, float m)
 {
     m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.x), fabsf(x.y)), m);
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x.z), fabsf(x.w)), m);
+}
+
+// Coordinates i0 .. i0 + 3 (i0 a multiple of 4) of F(z) = M z + b, from what they take.
+struct GameOperands { float4 z, b; float2 a; };
+
+__device__ __forceinline__ float4 game_operator_row(const GameArgs& G, const GameOperands& o)
+{
+    float4 f;
+    f.x = (G.mu * o.z.x + o.a.x * o.z.y) + o.b.x;
+    f.y = (G.mu * o.z.y - o.a.x * o.z.x) + o.b.y;
+    f.z = (G.mu * o.z.z + o.a.y * o.z.w) + o.b.z;
+    f.w = (G.mu * o.z.w - o.a.y * o.z.z) + o.b.w;
+    return f;
+}
+
+__device__ __forceinline__ float4 game_operator_row(const GameArgs& G, uint32_t i0)
+{
+    return game_operator_row(G, GameOperands{*reinterpret_cast<const float4*>(G.z + i0), *reinterpret_cast<const float4*>(G.b + i0),
+                                             *reinterpret_cast<const float2*>(G.a + (i0 >> 1))});
+}
+
+// A chunk's operands as buffers, zeros past its end (its length is a multiple of four).
+struct GameRows { __amdgpu_buffer_rsrc_t z, b, a; };
+
+__device__ __forceinline__ GameRows game_rows(const GameArgs& G, uint32_t first, uint32_t len)
+{
+    return GameRows{buffer_of(G.z + first, len * sizeof(float)), buffer_of(G.b + first, len * sizeof(float)),
+                    buffer_of(G.a + (first >> 1), len / 2u * sizeof(float))};
+}
+
+__device__ __forceinline__ GameOperands load_game_operands(const GameRows& rows, int r, int lane)
+{
+    const nt_u32x4 z = __builtin_amdgcn_raw_buffer_load_b128(rows.z, lane * 16, r * 1024, 0);
+    const nt_u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rows.b, lane * 16, r * 1024, 0);
+    const lds_u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rows.a, lane * 8, r * 512, 0);
+    auto f = [](uint32_t x) { return __uint_as_float(x); };
+    return GameOperands{make_float4(f(z.x), f(z.y), f(z.z), f(z.w)), make_float4(f(b.x), f(b.y), f(b.z), f(b.w)), make_float2(f(a.x), f(a.y))};
+}
+
+// The same four coordinates of worker k's dual vector in call `call_id`: F(z) + sigma N, the noise from the
+// Philox block with key (seed_lo, seed_hi) and counter (i0 / 4, 1, k, call_id).  F: game_operator_row.
+__device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, float sigma, uint32_t i0, uint32_t k, uint32_t call_id)
+{
+    uint32_t w[4];
+    philox4x32_10(i0 >> 2, 1u, k, call_id, philox_keys(G.seed_lo, G.seed_hi), w);
+    const float2 n01 = box_muller(w[0], w[1]), n23 = box_muller(w[2], w[3]);
+    F.x += sigma * n01.x;
+    F.y += sigma * n01.y;
+    F.z += sigma * n23.x;
+    F.w += sigma * n23.y;
+    return F;
+}
+
+__device__ __forceinline__ float4 game_dual_row(const GameArgs& G, uint32_t i0, uint32_t k, uint32_t call_id)
+{
+    return game_noisy_row(G, game_operator_row(G, i0), G.sigma, i0, k, call_id);
 }
 
 // t^q for a small positive integer q (the same q in every lane).
@@ -310,7 +341,6 @@ __device__ __forceinline__ uint32_t lds_address(const void* p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-typedef uint32_t lds_u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t lds_u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t lds_load_u32(uint32_t addr)

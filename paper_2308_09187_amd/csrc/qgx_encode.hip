@@ -369,7 +369,7 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
 // CM: cell_mant of the level table, so that the rounding pass has the cell size as a constant.
 // Waves per SIMD: five where V is read; four where it is formed, whose second generator and transcendentals spill at five
 // (16 x 2^26 coordinates: 2.07 ms instead of 2.30).  kStaged: a row's four look-ups are asked for together, cells before the
-// generator and level rows after it: 16 x 2^26 coordinates 2.02 -> 1.93 ms.  Where V is read the registers of five waves do not
+// generator and level rows after it: 16 x 2^26 coordinates 2.02 -> 1.93 ms (before its operands were asked for ahead).  Where V is read the registers of five waves do not
 // hold it (17 spilled: 8 x 2^24 148 us instead of 137), and at four waves it is no faster (137; buckets of 1024 88 instead of 86).
 template <EncMode MODE> constexpr bool kWaits = MODE != EncMode::EncodeOnly;     // for partners: it needs the bucket's norm
 template <EncMode MODE> constexpr int kSimdWaves = MODE == EncMode::Generate ? 4 : 5;
@@ -506,16 +506,25 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     if constexpr (MODE == EncMode::Fused || MODE == EncMode::QuantOnly) load_rest(v, Vk + g.clo, g.clen, lane);
     if constexpr (MODE == EncMode::Generate) {
         // the dual vector is formed here instead of read: operator and noise for four coordinates per lane and row
-        // (every bucket and vector length is a multiple of four in this mode)
+        // (every bucket and vector length is a multiple of four in this mode).  The operands are buffers, zeros past the chunk's
+        // end, so that no branch divides the rows and a row's operands are asked for while the row before it is worked out
+        // (16 x 2^26 coordinates 1.96 ms with a branch and a wait in every row, 1.66 without).
+        const GameRows rows = game_rows(a.game, g.clo, g.clen);
+        GameOperands next = load_game_operands(rows, 0, lane);
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
             const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 < g.cend) {
-                x = game_dual_row(a.game, i0, k, call_id);
-                if (a.game.V_out) *reinterpret_cast<float4*>(a.game.V_out + kbase + i0) = x;
+            const GameOperands now = next;
+            if (r + 1 < kRows) next = load_game_operands(rows, r + 1, lane);
+            v[r] = game_noisy_row(a.game, game_operator_row(a.game, now), i0 < g.cend ? a.game.sigma : 0.0f, i0, k, call_id);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (a.game.V_out) {
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
+                if (i0 < g.cend) *reinterpret_cast<float4*>(a.game.V_out + kbase + i0) = v[r];
             }
-            v[r] = x;
         }
     }
     {
