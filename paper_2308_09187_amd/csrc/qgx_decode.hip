@@ -148,16 +148,15 @@ __device__ __forceinline__ void commit_half(uint32_t* stage, const uint4 (&pre)[
 }
 
 // LDS tables of the decoder in one array: level values first, then the decode table, so that the
-// level index of a reject entry (flag bit set) still lands inside the array.
-constexpr int kTabLvalBytes = kSymMax * 4;
-constexpr int kTabBytes = kTabLvalBytes + kDlut * 2;
+// level of a reject entry still lands inside the array.
+constexpr int kTabLevelsAt = 16, kTabDlutAt = kTabLevelsAt + kSymMax * 4;
+constexpr int kTabBytes = kTabDlutAt + kDlut * 2;
+static_assert(kTabLevelsAt + 4 * (kDlutReject >> 6) + 4 <= kTabBytes, "the level of a reject entry");
 
 // Symbols are parsed in groups of four from one 64-bit window (three LDS words): a symbol takes at most 14 bits with
 // its sign, so two leave the first word's last bits to shift from, and the fourth starts before bit 42 and has its 14 bits
 // in the window.  (Groups of three need a shift less and three windows more a run: first half-step of 8 x 2^24
-// coordinates 74.8 us, now 69.8; of 8 x 9.86 M 56.7, now 53.5; second 99.6, now 92.8.)  An entry of the
-// 13-bit table is the symbol's bits incl. sign less one | 4 idx << 4 with bits 4 and 5 clear, so sums of four entries
-// carry the consumed bits in their low six bits; the 8-byte table's entries are minus the symbol's bits.
+// coordinates 74.8 us, now 69.8; of 8 x 9.86 M 56.7, now 53.5; second 99.6, now 92.8.)
 constexpr int kGroup = 4;
 static_assert(kSub % kGroup == 0 && 2 * kMaxSymBits < 32 && 3 * kMaxSymBits + kMaxSymBits <= 63 && kGroup * kMaxSymBits < 64, "a group in a window");
 struct Window { uint32_t w0, w1, w2; };
@@ -171,10 +170,6 @@ __device__ __forceinline__ Window read_window(const uint32_t* stage, uint32_t p)
     return Window{lds_load_u32(at), lds_load_u32(at + 4u), lds_load_u32(at + 8u)};
 }
 
-// Minus the bits of a symbol (sign included) in the low six bits of sums of four, from its table entry.
-template <bool WIDE>
-__device__ __forceinline__ uint32_t negative_bits(uint32_t e) { return WIDE ? e : ~e; }
-
 // The dependent chain: window i needs the lengths of the symbols before it.  The cursor r is a bit position
 // in the buffer and moves DOWN, the three words from it give the 64 bits with the first stream bit on top by
 // two funnel shifts and nothing else.
@@ -184,38 +179,37 @@ __device__ __forceinline__ uint32_t negative_bits(uint32_t e) { return WIDE ? e 
 // AND-OR, no shift by its length: W[i + 1] for symbol i, the next group's W[0] for a group's last
 // symbol, and for the last group of a run (LAST) the window after its last symbol, W[4].
 // The table index sits one bit lower (bits 30..20 resp. 30..18).
-// `seen` gathers the AND of the (negative) bit counts of the groups' halves: a reject entry leaves a zero among bits
-// 15..31, valid entries never do, so no per-symbol flag is kept.
-// WIDE: the 8-byte table's entries are the negative counts themselves and only need adding up.
+// `seen` gathers the sums of the groups' halves: a reject entry leaves a one in bit 15 or 16, valid entries never do, so no
+// per-symbol flag is kept.
+// WIDE: the 8-byte table, which has the level beside the count.
 template <bool WIDE, bool LAST>
 __device__ __forceinline__ void parse_group(const Window& w, const unsigned char* tab, uint32_t& r,
                                             uint32_t (&W)[kGroup + 1], uint32_t (&e)[kGroup], float (&lv)[kGroup], uint32_t& seen)
 {
-    uint32_t half[2];
-    auto look_up = [&](int i, uint32_t& neg) __attribute__((always_inline)) {
+    auto look_up = [&](int i) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            const uint2 t = *reinterpret_cast<const uint2*>(tab + kTabLvalBytes + ((W[i] >> 17) & 0x3FF8u));
+            const uint2 t = *reinterpret_cast<const uint2*>(tab + kTabDlutAt + ((W[i] >> 17) & 0x3FF8u));
             e[i] = t.x;
             lv[i] = __uint_as_float(t.y);
-            neg = i % 2 == 0 ? t.x : neg + t.x;
         } else {
-            e[i] = *reinterpret_cast<const uint16_t*>(tab + kTabLvalBytes + ((W[i] >> 17) & 0x3FFEu));
-            neg = i % 2 == 0 ? negative_bits<false>(e[i]) : neg + negative_bits<false>(e[i]);
+            e[i] = *reinterpret_cast<const uint16_t*>(tab + kTabDlutAt + ((W[i] >> 17) & 0x3FFEu));
         }
     };
     const uint32_t nxt = __builtin_amdgcn_alignbit(w.w1, w.w0, r);
     W[0] = __builtin_amdgcn_alignbit(w.w2, w.w1, r);                          // shifts use r mod 32
-    look_up(0, half[0]);
-    W[1] = __builtin_amdgcn_alignbit(W[0], nxt, half[0]);                     // (W[0]:nxt) << used, upper word
-    look_up(1, half[0]);
-    W[2] = __builtin_amdgcn_alignbit(W[0], nxt, half[0]);
-    const uint32_t after = __builtin_amdgcn_alignbit(nxt, 0u, half[0]);       // what follows W[2]
-    look_up(2, half[1]);
-    W[3] = __builtin_amdgcn_alignbit(W[2], after, half[1]);
-    look_up(3, half[1]);
-    if constexpr (LAST) W[4] = __builtin_amdgcn_alignbit(W[2], after, half[1]);      // at least two bits used: never a shift by 0
-    seen &= half[0] & half[1];
-    r += (half[0] + half[1]) | 0xFFFFFFC0u;                                   // down by the bits used
+    look_up(0);
+    W[1] = __builtin_amdgcn_alignbit(W[0], nxt, e[0]);                        // (W[0]:nxt) << used, upper word
+    look_up(1);
+    const uint32_t half0 = e[0] + e[1];
+    W[2] = __builtin_amdgcn_alignbit(W[0], nxt, half0);
+    const uint32_t after = __builtin_amdgcn_alignbit(nxt, 0u, half0);         // what follows W[2]
+    look_up(2);
+    W[3] = __builtin_amdgcn_alignbit(W[2], after, e[2]);
+    look_up(3);
+    const uint32_t half1 = e[2] + e[3];
+    if constexpr (LAST) W[4] = __builtin_amdgcn_alignbit(W[2], after, half1);        // at least two bits used: never a shift by 0
+    seen |= half0 | half1;
+    r += (half0 + half1) | 0xFFFFFFC0u;                                       // down by the bits used
 }
 
 // norm with the sign of the symbol whose last bit is bit 31 of `w_next` (norms are not negative)
@@ -235,9 +229,11 @@ __device__ __forceinline__ float symbol_value(uint32_t w_next, float lv, float n
     return val;
 }
 
+// (64 less a symbol's bits has ones in bits 4 and 5: an entry over 16 is 4 idx + 3)
+static_assert(64 - kMaxSymBits >= 48, "bits 4 and 5");
 __device__ __forceinline__ float level_of(const unsigned char* tab, uint32_t e)
 {
-    return *reinterpret_cast<const float*>(tab + (e >> 4));                  // the entry holds 4 * idx
+    return *reinterpret_cast<const float*>(tab + (kTabLevelsAt - 3) + (e >> 4));
 }
 
 // Level values and decode table of one Tables object into the decoder's LDS array (WIDE: the table of
@@ -247,11 +243,12 @@ __device__ __forceinline__ void load_tables(unsigned char* s_tab, const Tables* 
 {
     static_assert(kWide * sizeof(uint2) == kDlut * sizeof(uint16_t), "the two decode tables share one LDS area");
     static_assert(offsetof(Tables, dlut) % 16 == 0 && offsetof(Tables, dlutw) % 16 == 0 && sizeof(Tables) % 16 == 0, "16-byte copies");
+    static_assert(kTabDlutAt % 16 == 0, "16-byte copies");
     if constexpr (!WIDE) {
-        for (int i = tid; i < kSymMax; i += nthreads) reinterpret_cast<float*>(s_tab)[i] = tab->lval[i];
+        for (int i = tid; i < kSymMax; i += nthreads) reinterpret_cast<float*>(s_tab + kTabLevelsAt)[i] = tab->lval[i];
     }
     const uint4* src = WIDE ? reinterpret_cast<const uint4*>(tab->dlutw) : reinterpret_cast<const uint4*>(tab->dlut);
-    for (int i = tid; i < kDlut / 8; i += nthreads) reinterpret_cast<uint4*>(s_tab + kTabLvalBytes)[i] = src[i];
+    for (int i = tid; i < kDlut / 8; i += nthreads) reinterpret_cast<uint4*>(s_tab + kTabDlutAt)[i] = src[i];
 }
 
 // First coordinate, length and bucket of chunk position c.
@@ -423,7 +420,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
 #pragma unroll
     for (int s = 0; s < kSub; ++s) acc[s] = 0.0f;
     double sdiff = 0.0;
-    uint32_t seen = 0xFFFFFFFFu;
+    uint32_t seen = 0;
     uint32_t bad = 0;                                    // not 0: malformed
 
     // RAG: a short half, or with two streams a half of a short position.  The symbols past a lane's count are parsed
@@ -526,22 +523,22 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                         lv[j] = level_of(s_tab, e[j]);
                         if constexpr (PAIR) lv_b[j] = level_of(s_tab_b, e_b[j]);
                     }
-                    if constexpr (RAG) {                                  // (a symbol past the count: minus one bit, no value)
+                    if constexpr (RAG) {                                  // (a symbol past the count: one bit, no value)
                         const bool in = s + j < cnt;
-                        e[j] = in ? negative_bits<WIDE>(e[j]) : 0xFFFFFFFFu;
+                        e[j] = in ? e[j] : 63u;
                         lv[j] = in ? lv[j] : 0.0f;
                         if constexpr (PAIR) {
-                            e_b[j] = in ? negative_bits<WIDE>(e_b[j]) : 0xFFFFFFFFu;
+                            e_b[j] = in ? e_b[j] : 63u;
                             lv_b[j] = in ? lv_b[j] : 0.0f;
                         }
                     }
                 }
                 if constexpr (RAG) {
                     used -= (e[0] + e[1] + e[2] + e[3]) | 0xFFFFFFC0u;
-                    seen &= (e[0] + e[1]) & (e[2] + e[3]);
+                    seen |= (e[0] + e[1]) | (e[2] + e[3]);
                     if constexpr (PAIR) {
                         used_b -= (e_b[0] + e_b[1] + e_b[2] + e_b[3]) | 0xFFFFFFC0u;
-                        seen &= (e_b[0] + e_b[1]) & (e_b[2] + e_b[3]);
+                        seen |= (e_b[0] + e_b[1]) | (e_b[2] + e_b[3]);
                     }
                 }
                 if (s > 0) emit(s - 1, W[0], held, W_b[0], held_b);
@@ -580,8 +577,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     };
     if (straight) all_workers(BoolTag<false>{});
     else all_workers(BoolTag<true>{});
-    // a reject entry leaves a zero among bits 15..31 of its group's negative bit count
-    bad |= (seen >> 15) ^ 0x1FFFFu;
+    bad |= seen >> 15;                                   // (a reject entry among those parsed)
     if (__any(bad != 0u) && lane == 0) raise_error(sc, QGX_EBIT_STREAM);
 
     // ---- aggregate and update ---------------------------------------------------------------------

@@ -45,18 +45,18 @@ constexpr int kDlut = 1 << kDlutBits;     // 8192 entries
 
 // The decode table is indexed by the next 13 stream bits read as a number with the FIRST bit on top,
 // so the windows that start with one code word are neighbours: lanes that parse the same symbol read
-// the same or adjacent entries, whatever follows the word in their streams.
-constexpr uint32_t kDlutReject = 0x8000u; // no code word starts this window: flag, one bit long, symbol 0
+// the same or adjacent entries, whatever follows the word in their streams.  An entry is idx << 6 | 64 - the symbol's bits
+// (sign included): sums of four entries hold minus the bits of the four in their low six bits, shift counts as they are.
+constexpr uint32_t kDlutReject = 0x803Fu; // no code word starts this window: flag, one bit long, symbol beyond the level table
 // When the first kWideBits bits of a code word always tell which word it is (every word at most that
 // long, or longer ones that differ from each other earlier: Elias' code up to 63 symbols), a second
 // table indexed by the next kWideBits stream bits (first bit on top as well) holds the level value
-// beside the bit count, so that one 8-byte look-up per symbol replaces the entry look-up and the level
-// look-up (same footprint: 2^11 entries of 8 bytes).  Its counts are MINUS the symbol's bits, sign
-// included, as a 32-bit number and nothing else: the parse counts downwards, and sums of these entries
-// are its shift counts as they are.  Its reject entry is minus one bit with bit 15 cleared.
+// beside the count, so that one 8-byte look-up per symbol replaces the entry look-up and the level
+// look-up (same footprint: 2^11 entries of 8 bytes).  (An 11-bit table of two-byte entries and a level look-up meet fewer of the
+// banks' conflicts, and cost an instruction and an access more: first half-step of 8 x 4.9 M coordinates, 17 exponential levels 32.1
+// us with eight bytes, 30.4 with two; 33 fitted 31.4 / 33.2; 8 in words of one width 32.5 / 33.4; 8 x 2^24, 17 fitted 66.9 / 73.6.)
 constexpr int kWideBits = 11;
 constexpr int kWide = 1 << kWideBits;
-constexpr uint32_t kWideReject = 0xFFFF7FFFu;
 
 // Device-resident tables: rebuilt on the device whenever the level table or the code changes.
 struct Tables {
@@ -75,11 +75,10 @@ struct Tables {
     uint32_t code_kind;
     uint32_t cell_exact;
     uint32_t pad_;
-    // dlut[next 13 stream bits, first bit on top] = (bits of the symbol incl. sign - 1) | (4 * idx) << 4,
-    // or kDlutReject
+    // dlut[next 13 stream bits, first bit on top] = entry, or kDlutReject
     uint16_t dlut[kDlut];
-    // dlutw[next 11 stream bits, first bit on top] = {-(bits of the symbol incl. sign), bits of l_idx}, or
-    // {kWideReject, 0}; wide_ok tells whether 11 bits identify every code word
+    // dlutw[next 11 stream bits, first bit on top] = {64 - the symbol's bits incl. sign, bits of l_idx}, or
+    // {kDlutReject, 0}; wide_ok tells whether 11 bits identify every code word
     uint2 dlutw[kWide];
     uint32_t wide_ok;
     uint32_t pad2_[3];

@@ -57,7 +57,7 @@ static __device__ void build_tables_block(Tables* tab)
     }
     constexpr uint32_t kTwoRejects = kDlutReject | (kDlutReject << 16);
     for (int i = tid; i < kDlut / 8; i += nt) reinterpret_cast<uint4*>(tab->dlut)[i] = make_uint4(kTwoRejects, kTwoRejects, kTwoRejects, kTwoRejects);
-    for (int i = tid; i < kWide / 2; i += nt) reinterpret_cast<uint4*>(tab->dlutw)[i] = make_uint4(kWideReject, 0u, kWideReject, 0u);
+    for (int i = tid; i < kWide / 2; i += nt) reinterpret_cast<uint4*>(tab->dlutw)[i] = make_uint4(kDlutReject, 0u, kDlutReject, 0u);
     __syncthreads();
 
     const int mant = cell_mant(n_sym), cells = cell_count(mant), cell_shift = 23 - mant;
@@ -110,16 +110,15 @@ static __device__ void build_tables_block(Tables* tab)
         if (len == 0 || len > (uint32_t)kMaxCode) continue;
         const uint32_t first = (__brev(bits) >> (32u - len)) << (kDlutBits - len);   // the word, first bit on top
         const uint32_t reps = 1u << (kDlutBits - len);
-        const uint32_t entry = (j << 6) | (len - (j != 0u ? 0u : 1u));               // symbol bits - 1: sign for j != 0
+        const uint32_t count = 64u - len - (j != 0u ? 1u : 0u), entry = (j << 6) | count;       // (a sign for j != 0)
         for (uint32_t s = lane; s < reps; s += kWave) tab->dlut[first + s] = (uint16_t)entry;
-        // the same run in the 11-bit table, with minus the symbol's bits (sign included) and the level; a
+        // the same run in the 11-bit table, with the level beside the count; a
         // longer word takes the one slot of its first 11 bits (no shorter word's run reaches it: the code is
         // prefix-free)
         const uint32_t first_w = first >> (kDlutBits - kWideBits);
         const uint32_t reps_w = len <= (uint32_t)kWideBits ? 1u << (kWideBits - len) : 1u;
-        const uint32_t entry_w = 0u - (len + (j != 0u ? 1u : 0u));
         for (uint32_t s = lane; s < reps_w; s += kWave)
-            tab->dlutw[first_w + s] = make_uint2(entry_w, __float_as_uint(lv[j]));
+            tab->dlutw[first_w + s] = make_uint2(count, __float_as_uint(lv[j]));
     }
     __syncthreads();
     // the 11-bit table is no use if two of the longer words begin with the same 11 bits: they would meet in
