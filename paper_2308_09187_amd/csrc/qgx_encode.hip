@@ -367,15 +367,14 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
 // GROUPED: the layout has shared chunks; a workgroup is four waves with a chunk each, and every wave
 // finds the norms of its chunk's buckets by itself.
 // CM: cell_mant of the level table, so that the rounding pass has the cell size as a constant.
-// Waves per SIMD: five where V is read; four where it is formed, whose second generator and transcendentals spill at five
-// (16 x 2^26 coordinates: 2.07 ms instead of 2.30).  kStaged: a row's four look-ups are asked for together, cells before the
-// generator and level rows after it: 16 x 2^26 coordinates 2.02 -> 1.93 ms (before its operands were asked for ahead).  Where V is read the registers of five waves do not
-// hold it (17 spilled: 8 x 2^24 148 us instead of 137), and at four waves it is no faster (137; buckets of 1024 88 instead of 86).
+// STAGED: a row's four look-ups are asked for together, cells before the generator and level rows after it, at four waves
+// per SIMD, whose registers hold it (at five 17 were spilled: 8 x 2^24 coordinates 148 us instead of 137).  The game's form, whose
+// second generator and transcendentals need the registers anyway, always: 16 x 2^26 coordinates 2.02 -> 1.93 ms.  Where V is
+// read, launches of few waves, which wait for their look-ups with little else to do (use_staged).
 template <EncMode MODE> constexpr bool kWaits = MODE != EncMode::EncodeOnly;     // for partners: it needs the bucket's norm
-template <EncMode MODE> constexpr int kSimdWaves = MODE == EncMode::Generate ? 4 : 5;
-template <EncMode MODE> constexpr bool kStaged = MODE == EncMode::Generate;
-template <EncMode MODE, bool GROUPED, int CM>
-__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(kSimdWaves<MODE>)))
+template <bool STAGED> constexpr int kSimdWaves = STAGED ? 4 : 5;
+template <EncMode MODE, bool GROUPED, int CM, bool STAGED>
+__global__ __launch_bounds__(GROUPED ? 256 : 1024) __attribute__((amdgpu_waves_per_eu(kSimdWaves<STAGED>)))
 void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
 {
     extern __shared__ __align__(16) unsigned char s_all[];
@@ -673,7 +672,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
                 e[q] = up ? t.w : t.z;
                 if (MODE == EncMode::QuantOnly) pk |= (j + (up ? 1u : 0u) + ((__float_as_uint(xs[q]) >> 31) << 7)) << (8 * q);
             };
-            if constexpr (kStaged<MODE>) {
+            if constexpr (STAGED) {
                 float u[4];
                 uint2 c[4];
 #pragma unroll
@@ -837,7 +836,7 @@ static size_t encode_lds_bytes(int waves, const EncodeArgs& a, bool with_stage, 
     return n;
 }
 
-template <EncMode MODE, bool GROUPED, int CM>
+template <EncMode MODE, bool GROUPED, int CM, bool STAGED = false>
 static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
 {
     EncodeArgs b = a;
@@ -846,7 +845,7 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     const int waves = (GROUPED || a.parts > 1u) ? 4 : (int)(b.group * lay.waves_per_bucket);
     const size_t lds = encode_lds_bytes(waves, a, MODE != EncMode::QuantOnly, GROUPED);
     static LdsLimit limit;
-    hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_encode<MODE, GROUPED, CM>), 160 * 1024);
+    hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_encode<MODE, GROUPED, CM, STAGED>), 160 * 1024);
     if (e != hipSuccess) return e;
     // one workgroup per bucket or group of buckets, per part of a bucket, or (shared chunks) per four chunks; in compact
     // placement and with split buckets each takes one ticket of its worker
@@ -854,25 +853,32 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     // Where the workgroups of a bucket wait for each other, no XCD may have more workers than leave it a place to
     // start one in (see worker_span).  The game's form puts the K workgroups of a unit on one XCD, which all K workers
     // then share, as long as that holds for K (42 workers with four workgroups to a compute unit, 31 with three).
-    const uint32_t held = held_per_xcd(kSimdWaves<MODE>, lds, a.n_cu);
+    const uint32_t held = held_per_xcd(kSimdWaves<STAGED>, lds, a.n_cu);
     b.span = kWaits<MODE> && a.parts > 1u ? worker_span(lay.K, a.parts, held) : lay.K;
     b.spread = ordered && a.parts == 1u && spread_workers(lay.K, b.units) ? 1u : 0u;
     b.by_unit = MODE == EncMode::Generate && (a.parts == 1u || (a.parts - 1u) * lay.K < held) ? 1u : 0u;
     const uint32_t grid = b.span * b.units;
-    hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM>), dim3(grid), dim3(waves * kWave), lds, st, lay, tab, sc, b);
+    hipLaunchKernelGGL((k_encode<MODE, GROUPED, CM, STAGED>), dim3(grid), dim3(waves * kWave), lds, st, lay, tab, sc, b);
     return hipGetLastError();
+}
+
+template <EncMode MODE, int CM>
+static hipError_t launch_size(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
+{
+    if (lay.shared_chunks) return launch_mode<MODE, true, CM>(lay, tab, sc, a, st);
+    if constexpr (MODE == EncMode::Fused) {
+        if (use_staged((uint64_t)lay.K * lay.NC, 4u * a.n_cu)) return launch_mode<MODE, false, CM, true>(lay, tab, sc, a, st);
+    }
+    return launch_mode<MODE, false, CM>(lay, tab, sc, a, st);
 }
 
 template <EncMode MODE>
 static hipError_t launch_kind(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
 {
     switch (a.cell_mant) {
-        case 4: return lay.shared_chunks ? launch_mode<MODE, true, 4>(lay, tab, sc, a, st)
-                                         : launch_mode<MODE, false, 4>(lay, tab, sc, a, st);
-        case 5: return lay.shared_chunks ? launch_mode<MODE, true, 5>(lay, tab, sc, a, st)
-                                         : launch_mode<MODE, false, 5>(lay, tab, sc, a, st);
-        default: return lay.shared_chunks ? launch_mode<MODE, true, 6>(lay, tab, sc, a, st)
-                                          : launch_mode<MODE, false, 6>(lay, tab, sc, a, st);
+        case 4: return launch_size<MODE, 4>(lay, tab, sc, a, st);
+        case 5: return launch_size<MODE, 5>(lay, tab, sc, a, st);
+        default: return launch_size<MODE, 6>(lay, tab, sc, a, st);
     }
 }
 
@@ -884,9 +890,9 @@ hipError_t launch_encode(EncMode mode, const Layout& lay, const Tables* tab, Sca
         case EncMode::Generate:
             if (lay.shared_chunks) return hipErrorInvalidValue;          // (the host side has refused this layout)
             switch (a.cell_mant) {
-                case 4: return launch_mode<EncMode::Generate, false, 4>(lay, tab, sc, a, st);
-                case 5: return launch_mode<EncMode::Generate, false, 5>(lay, tab, sc, a, st);
-                default: return launch_mode<EncMode::Generate, false, 6>(lay, tab, sc, a, st);
+                case 4: return launch_mode<EncMode::Generate, false, 4, true>(lay, tab, sc, a, st);
+                case 5: return launch_mode<EncMode::Generate, false, 5, true>(lay, tab, sc, a, st);
+                default: return launch_mode<EncMode::Generate, false, 6, true>(lay, tab, sc, a, st);
             }
         case EncMode::QuantOnly: return launch_kind<EncMode::QuantOnly>(lay, tab, sc, a, st);
         default: return launch_kind<EncMode::EncodeOnly>(lay, tab, sc, a, st);

@@ -95,6 +95,11 @@ inline uint32_t buckets_per_group(uint32_t waves_per_bucket, uint64_t chunks_of_
     return 4u / waves_per_bucket;
 }
 
+// The coding kernel's form with look-ups ahead at four waves per SIMD, or five waves: a wave per chunk, up to two rounds of four.
+// Measured, us, five waves / look-ups ahead: 256 chunks 10.6 / 9.6, 2048 15.9 / 15.2, 4096 27.7 / 27.0, 8192 46.7 / 45.4 (in order
+// 13.7 / 12.7, 19.9 / 19.7, 31.7 / 30.9, 59.8 / 58.0); 19328 84.0 / 85.5, 32768 137 / 137.
+inline bool use_staged(uint64_t chunks_of_all, uint32_t n_simd) { return chunks_of_all <= 8u * (uint64_t)n_simd; }
+
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
 // x = f * tasks against the wave slots (8 per SIMD with one stream, 4 with two).  A launch is bound by latency,
 // ceil(K / f) workers one after the other (a worker's chain of look-ups takes 2.2 us with one stream, 3.3 with two, however

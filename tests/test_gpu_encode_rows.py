@@ -70,3 +70,23 @@ def test_buckets_side_by_side(qgx, bucket, d, norm):
         else:
             assert_stream_equal(h, so, lay)
     ctx.close()
+
+
+@pytest.mark.parametrize("slotted", [False, True])
+@pytest.mark.parametrize("d", [1023 * 100 + 1, 1024 * 100 + 1, 4096 * 100])
+def test_both_sides_of_the_look_ups_ahead(qgx, d, slotted):
+    """8192 and 8200 chunks, where the kernel's form changes on 1024 SIMDs, and 32768 of them."""
+    K, seed, bucket = 8, 29, 100
+    levels = synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, K, bucket, oracle.NORM_L2, levels, seed=seed)
+    V = synth.student_t3(K, d, seed=d)
+    s = ctx.new_stream(slotted=slotted)
+    ctx.quantize_encode(dev(V), 3, s)
+    h = s.to_host()
+    _, _, _, so = oracle_stream(V, lay, oracle.NORM_L2, levels, seed, 3, h["norms"], ctx.worst_words)
+    if slotted:
+        assert_slotted_equal(h, so, lay, s.slot_words)
+    else:
+        assert_stream_equal(h, so, lay)
+    assert ctx.poll_error() == 0
+    ctx.close()

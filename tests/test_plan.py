@@ -29,6 +29,7 @@ extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint3
 extern "C" uint32_t worker_spread(uint32_t k, uint32_t unit, uint32_t span) { return qgx::worker_spread(k, unit, span); }
 extern "C" int spread_workers(uint32_t K, uint32_t units) { return qgx::spread_workers(K, units); }
 extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int ordered) { return qgx::buckets_per_group(waves, chunks, ordered != 0); }
+extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_staged(chunks, n_simd); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
 
@@ -151,3 +152,9 @@ def test_buckets_per_group_fills_four_waves(plan):
     for waves, chunks, ordered in itertools.product(range(1, 17), (1, 255, 256, 4095, 4096, 1 << 40), (0, 1)):
         n = plan.buckets_per_group(waves, chunks, ordered)
         assert n == (4 // waves if waves <= 2 and chunks >= (256 if ordered else 4096) else 1), (waves, chunks, ordered)
+
+
+def test_use_staged_up_to_two_rounds_of_four_waves(plan):
+    plan.use_staged.argtypes = [C.c_uint64, C.c_uint32]
+    for simds, chunks in itertools.product((4, 1024), (1, 32, 33, 8192, 8193, (1 << 32) + 1)):
+        assert plan.use_staged(chunks, simds) == (chunks <= 8 * simds), (simds, chunks)
