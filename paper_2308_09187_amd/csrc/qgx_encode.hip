@@ -36,6 +36,7 @@
 namespace qgx {
 
 constexpr unsigned kSpinLimit = 1u << 22;
+constexpr float kMaxF32 = 3.402823466e+38f;
 
 // Exclusive prefix of `agg` over buckets 0..b-1 of one worker (decoupled look-back, one wave).
 // state[] entries: high word = epoch << 2 | status (1 = aggregate, 2 = inclusive prefix), low word = value.
@@ -291,7 +292,7 @@ __device__ __forceinline__ ChunkGeom chunk_geom(const Layout& lay, uint32_t b, u
 // of whole rows, so the wave works out their norms by itself, one wave reduction at the last row of
 // every bucket, and leaves 1 / norm (0 for a bucket that is all zero or rejected) in LDS for the
 // rounding pass.  Returns whether the straight-line rounding path applies to the whole chunk: every
-// bucket live and no coordinate above its norm.
+// bucket live, no coordinate above its norm, and no norm so small that its reciprocal overflows.
 template <EncMode MODE>
 __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], const float* __restrict__ Vk,
                                                    const ChunkGeom& g, const Layout& lay, const EncodeArgs& a,
@@ -348,12 +349,13 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
             const bool bucket_bad = !(fabsf(n) <= 3.402823466e+38f);
             if (bucket_bad) n = 0.0f;
             const bool live = n > 0.0f;
+            const float rinv = live ? 1.0f / n : 0.0f;                    // one IEEE division per bucket
             if (lane == 0) {
                 if (bucket_bad) raise_error(sc, QGX_EBIT_NONFINITE);
                 if (a.norms_out) a.norms_out[(size_t)k * lay.NB + bucket0 + gb] = n;
-                rinv_out[gb] = live ? 1.0f / n : 0.0f;                    // one IEEE division per bucket
+                rinv_out[gb] = rinv;
             }
-            plain = plain && live && u_le_1;
+            plain = plain && live && u_le_1 && rinv <= kMaxF32;
         }
         p0 = p1 = p2 = p3 = 0.0f;
         mx = 0.0f;
@@ -651,8 +653,10 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         }
         const float rinv = GROUPED ? 0.0f : 1.0f / n;  // one IEEE division per bucket
         const bool live = GROUPED ? plain : n > 0.0f;
-        // (a chunk's last row, if short, always takes the general path)
-        const bool fast = live && (vec_ok || MODE != EncMode::QuantOnly) && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
+        // The straight path's look-ups lie inside the tables for u <= 1 up to a rounding only: a norm of 2^-128 or less, whose
+        // reciprocal overflows and makes u infinite or NaN, takes the general path, which clamps u (as a chunk's last
+        // row does, if short).
+        const bool fast = live && (GROUPED || rinv <= kMaxF32) && (vec_ok || MODE != EncMode::QuantOnly) && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
         const uint32_t rshift = GROUPED ? lay.bucket_shift - 8u : 0u;         // rows per bucket, as a shift
 
         // ---- per row: quantise, code, pack -------------------------------------------------------

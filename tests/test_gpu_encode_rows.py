@@ -90,3 +90,37 @@ def test_both_sides_of_the_look_ups_ahead(qgx, d, slotted):
         assert_stream_equal(h, so, lay)
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("slotted", [False, True])
+@pytest.mark.parametrize("norm", [oracle.NORM_L2, oracle.NORM_LINF, 3])
+@pytest.mark.parametrize("bucket,d,K,n_sym", [(8192, 5 * 8192 + 700, 2, 17), (1024, 3 * 4096 + 1500, 3, 17), (4096, 4 * 4096, 2, 65),
+                                              (16384, 3 * 16384, 2, 127), (32768, 3 * 32768, 2, 33), (516, 1030 * 516, 8, 17)])
+def test_norms_without_a_finite_reciprocal(qgx, bucket, d, K, n_sym, norm, slotted):
+    """Buckets of subnormal coordinates between ordinary ones: up to a norm of 2^-128 the reciprocal is infinite.  Their
+    coordinates go to the top level as the oracle's, and their neighbours are bit for bit what they are without them."""
+    seed = 31
+    levels = synth.levels_exponential(16) if n_sym == 17 else np.linspace(0, 1, n_sym).astype(np.float32)
+    ctx, lay = make_ctx(qgx, d, K, bucket, norm, levels, seed=seed)
+    V = synth.student_t3(K, d, seed=d)
+    for k, b, top in ((0, 1, 1e-41), (1, 0, 2.0 ** -128), (1, 2, 2.0 ** -128 + 2.0 ** -149), (K - 1, lay.NB - 1, 2.0 ** -149)):
+        at = slice(b * bucket, min(d, (b + 1) * bucket))
+        V[k, at] = (V[k, at].astype(np.float64) * (top / np.abs(V[k, at]).max())).astype(np.float32)
+        assert V[k, at].any() and np.abs(V[k, at]).max() < 2.0 ** -126
+    s = ctx.new_stream(slotted=slotted)
+    ctx.quantize_encode(dev(V), 2, s)
+    h = s.to_host()
+    norms_o = oracle.quantize(V, lay, norm, levels, seed, 2)[0]
+    np.testing.assert_allclose(h["norms"], norms_o, rtol=1e-6, atol=2.0 ** -149)     # (a subnormal's spacing)
+    with np.errstate(over="ignore"):
+        assert 2 <= np.isinf(np.float32(1) / h["norms"]).sum() <= 4
+    _, idx, neg, so = oracle_stream(V, lay, norm, levels, seed, 2, h["norms"], ctx.worst_words)
+    if slotted:
+        assert_slotted_equal(h, so, lay, s.slot_words)
+    else:
+        assert_stream_equal(h, so, lay)
+    norms, sym = ctx.quantize(dev(V), 2)
+    np.testing.assert_array_equal(norms.cpu().numpy(), h["norms"])
+    np.testing.assert_array_equal(sym.cpu().numpy(), (idx | (neg << 7)).astype(np.uint8))
+    assert ctx.poll_error() == 0
+    ctx.close()
