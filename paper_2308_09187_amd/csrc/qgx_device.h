@@ -206,7 +206,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* first, u
 }
 
 // A chunk's coordinates in registers: 16 rows of 256, four to a lane.  Its whole groups of four coordinates are a buffer, outside of
-// which a load gives zeros: no branch whatever the chunk's length, so that the compiler knows how many loads are under way.
+// which a load gives zeros (a row's place is part of the lane's offset, which the bounds apply to; the scalar one is not checked
+// by what the compiler promises): no branch whatever the chunk's length, so that the compiler knows how many loads are under way.
 // Vectors of an odd length put a worker's rows at any multiple of 4 bytes, which 16-byte loads take.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rows(const float* first, uint32_t len)
 {
@@ -216,7 +217,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rows(const float* first,
 __device__ __forceinline__ float4 load_row(__amdgpu_buffer_rsrc_t rows, int r, int lane)
 {
     constexpr int kNonTemporal = 2;                          // (read once: see nt_load4)
-    const nt_u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16, r * 1024, kNonTemporal);
+    const nt_u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rows, lane * 16 + r * 1024, 0, kNonTemporal);
     return make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
 }
 
@@ -277,9 +278,9 @@ __device__ __forceinline__ GameRows game_rows(const GameArgs& G, uint32_t first,
 
 __device__ __forceinline__ GameOperands load_game_operands(const GameRows& rows, int r, int lane)
 {
-    const nt_u32x4 z = __builtin_amdgcn_raw_buffer_load_b128(rows.z, lane * 16, r * 1024, 0);
-    const nt_u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rows.b, lane * 16, r * 1024, 0);
-    const lds_u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rows.a, lane * 8, r * 512, 0);
+    const nt_u32x4 z = __builtin_amdgcn_raw_buffer_load_b128(rows.z, lane * 16 + r * 1024, 0, 0);
+    const nt_u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rows.b, lane * 16 + r * 1024, 0, 0);
+    const lds_u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rows.a, lane * 8 + r * 512, 0, 0);
     auto f = [](uint32_t x) { return __uint_as_float(x); };
     return GameOperands{make_float4(f(z.x), f(z.y), f(z.z), f(z.w)), make_float4(f(b.x), f(b.y), f(b.z), f(b.w)), make_float2(f(a.x), f(a.y))};
 }
