@@ -470,15 +470,13 @@ __device__ __forceinline__ double stationary_between(const Tree& T, double a, do
     if (!same_in_all(right_all > 0.0)) return a;                       // no mass between the neighbours
     const double t = right_all / (c - a);
     // the smallest x with mass(a, x) >= t: x = from + share / of * span in the bin or piece that holds it
-    double from = a, share = t, of = m_a, span = a_hi - a, least = a;
+    double from = a, share = t, of = m_a, span = a_hi - a;
     if (!same_in_all(m_a >= t)) {
+        uint32_t bin = Q;
         // the first place in the first run in which the mass reaches t
         const unsigned long long there1 = __ballot(in1 && cum1 >= t), there2 = __ballot(in2 && cum2 >= t), there3 = __ballot(in3 && cum3 >= t);
         if ((there1 | there2 | there3) == 0ull) {
-            // the mass reaches t in the piece of c's bin, or t is a rounding above all the mass: then the answer
-            // is where the mass ends
-            if (!same_in_all(m_c > 0.0))
-                return fmin(fmax(last_mass_edge(T, P, Q, same_in_all(m_a > 0.0) ? a_hi : a), a), c);
+            // in the piece of c's bin
             from = c_e0; share = t - all; of = m_c; span = c - c_e0;
         } else {
             const unsigned long long there = there1 != 0ull ? there1 : there2 != 0ull ? there2 : there3;
@@ -486,7 +484,7 @@ __device__ __forceinline__ double stationary_between(const Tree& T, double a, do
             const double cum = there1 != 0ull ? cum1 : there2 != 0ull ? cum2 : cum3;
             const double base = there1 != 0ull ? m_a : there2 != 0ull ? base2 : base3;
             double prev = first > 0u ? lane_value(cum, first - 1u) : base;
-            uint32_t bin = there1 != 0ull ? P + first : Q1 + first;
+            bin = there1 != 0ull ? P + first : Q1 + first;
             if (there1 == 0ull && there2 != 0ull) {                    // into the node that holds it
                 const uint32_t b0 = (p1 + first) * kWave;
                 const double below = prev + wave_prefix(T.H[b0 + lane]);
@@ -498,10 +496,14 @@ __device__ __forceinline__ double stationary_between(const Tree& T, double a, do
                 bin = b0 + first;
             }
             from = bin_edge(bin, nb);
-            share = t - prev; of = T.H[bin]; span = bin_edge(bin + 1u, nb) - from; least = from;
+            share = t - prev; of = T.H[bin]; span = bin_edge(bin + 1u, nb) - from;
         }
+        // The sums of neighbouring lanes are rounded apart, so t can be reached in a bin without mass, or past all the mass, by a
+        // rounding (or be behind that place already): then the answer is where the mass before it ends.
+        if (!same_in_all(of > 0.0 && share > 0.0))
+            return fmin(fmax(last_mass_edge(T, P, bin, same_in_all(m_a > 0.0) ? a_hi : a), a), c);
     }
-    const double x = fmax(from + share / of * span, least);
+    const double x = fmin(from + share / of * span, from + span);        // (a little mass may be less than t's rounding)
     return fmin(fmax(x, a), c);
 }
 

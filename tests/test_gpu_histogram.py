@@ -41,3 +41,30 @@ def test_histogram(qgx, bucket, d, K, norm):
     assert abs(got.sum() - want.sum()) <= 1e-6 * want.sum()
     assert np.abs(np.cumsum(got) - np.cumsum(want)).max() <= 1e-5 * want.sum()
     ctx.close()
+
+
+@pytest.mark.parametrize("seed", [153, 299, 0, 1])
+def test_level_where_the_mass_ends(qgx, seed):
+    """All mass below the second level lies under 2^-63, so the update's share of it is the whole mass up to a rounding: the
+    level goes to where that mass ends, whatever the order its sums are rounded in (seeds 153 and 299: a bin without mass is the
+    first whose prefix sum reaches the share)."""
+    rng = np.random.default_rng(seed)
+    K, bucket, NB = 3, 64, 40
+    edges = oracle.bin_edges(4096)
+    m = rng.integers(2, 12)
+    bins = 1 + rng.choice(63, m, replace=False)
+    mids = (0.5 * (edges[bins] + edges[bins + 1])).astype(np.float32)
+    norms = (1 + rng.random((K, NB, 1))).astype(np.float32)
+    u = mids[rng.integers(0, m, (K, NB, bucket))]
+    u[:, :, 0] = 1
+    V = (u * norms).astype(np.float32).reshape(K, -1)
+    start = np.array([0, 0.25, 0.5, 1], np.float32)
+    ctx, lay = make_ctx(qgx, V.shape[1], K, bucket, oracle.NORM_LINF, start, seed=0)
+    hist = torch.empty(4096, dtype=torch.float64, device="cuda")
+    ctx.fit_levels(dev(V), 4, 4096, sweeps=1, hist_out=hist)
+    want = oracle.histogram(V, lay, oracle.NORM_LINF, 4096)
+    np.testing.assert_allclose(hist.cpu().numpy(), want, rtol=1e-12, atol=0)
+    # the second level rests on the smallest gap, 2^-24; the third differs by the histogram's roundings only
+    np.testing.assert_allclose(ctx.get_levels(), oracle.fit_levels(want, start, sweeps=1), rtol=1e-6, atol=1e-9)
+    assert ctx.poll_error() == 0
+    ctx.close()
