@@ -95,6 +95,13 @@ inline uint32_t buckets_per_group(uint32_t waves_per_bucket, uint64_t chunks_of_
     return 4u / waves_per_bucket;
 }
 
+// Waves of a workgroup of `group` buckets that have one: fewer in a worker's last workgroup.
+QGX_PLAN uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t waves_per_bucket, uint32_t NB)
+{
+    const uint32_t left = NB - unit * group;
+    return (left < group ? left : group) * waves_per_bucket;
+}
+
 // The coding kernel's form with look-ups ahead at four waves per SIMD, or five waves: a wave per chunk, up to two rounds of four.
 // Measured, us, five waves / look-ups ahead: 256 chunks 10.6 / 9.6, 2048 15.9 / 15.2, 4096 27.7 / 27.0, 8192 46.7 / 45.4 (in order
 // 13.7 / 12.7, 19.9 / 19.7, 31.7 / 30.9, 59.8 / 58.0); 19328 84.0 / 85.5, 32768 137 / 137.

@@ -29,6 +29,7 @@ extern "C" uint32_t waves_per_task(uint32_t n, uint32_t K, uint32_t simds, uint3
 extern "C" uint32_t worker_spread(uint32_t k, uint32_t unit, uint32_t span) { return qgx::worker_spread(k, unit, span); }
 extern "C" int spread_workers(uint32_t K, uint32_t units) { return qgx::spread_workers(K, units); }
 extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int ordered) { return qgx::buckets_per_group(waves, chunks, ordered != 0); }
+extern "C" uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t waves, uint32_t NB) { return qgx::waves_with_a_bucket(unit, group, waves, NB); }
 extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_staged(chunks, n_simd); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
@@ -158,3 +159,12 @@ def test_use_staged_up_to_two_rounds_of_four_waves(plan):
     plan.use_staged.argtypes = [C.c_uint64, C.c_uint32]
     for simds, chunks in itertools.product((4, 1024), (1, 32, 33, 8192, 8193, (1 << 32) + 1)):
         assert plan.use_staged(chunks, simds) == (chunks <= 8 * simds), (simds, chunks)
+
+
+def test_waves_without_a_bucket_are_a_workers_last(plan):
+    """The waves whose sums a workgroup of several buckets looks at: those whose bucket is one of the worker's."""
+    for waves, NB in itertools.product((1, 2), (1, 2, 3, 4, 5, 127, 128, 350)):
+        group = 4 // waves
+        for unit in range((NB + group - 1) // group):
+            want = sum(unit * group + w // waves < NB for w in range(4))
+            assert plan.waves_with_a_bucket(unit, group, waves, NB) == want, (waves, NB, unit)
