@@ -746,8 +746,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         }
     }
     // The scalar end in this launch, where it has no more workgroups than a wave has lanes (a.arrived): each leaves its sum and
-    // counts itself, and the last one to arrive adds up the sums.  A sum is written past the caches (agent scope) and is
-    // there before its workgroup is counted (the wait); it is read past the caches, too.
+    // counts itself (release), and the last one to arrive (acquire) adds up the sums.
     if constexpr (MODE == DecMode::Half1) {
         if (a.arrived != nullptr) {
             __syncthreads();
@@ -757,10 +756,10 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
                     double own = 0.0;
                     for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
                     __hip_atomic_store(&a.s_partial[blockIdx.x], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u == gridDim.x) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                     const double sum = wave_sum((uint32_t)lane < gridDim.x ? __hip_atomic_load(&a.s_partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0);
                     if (lane == 0) {
                         finish_scalars(sc, sum, lay.K);
@@ -790,8 +789,9 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     if (TWO && held(8) >= held(16)) per = 8;                 // (short codes: two of eight beside each other, 160 us to 164)
     for (uint32_t small = 4; small < per; small *= 2)
         if (nwaves <= held(small) * a.n_cu) { per = small; break; }
-    // The scalar end in the same launch: one bucket of 1024, 4 workers, an iteration 37.2 us with a launch of its own, 34.8 without.  With
-    // 751 workgroups (5 x 3000001 coordinates) their sums take the last one longer than the launch does, 116.5 us and 120.
+    // The scalar end in the same launch, as long as a wave has a lane for each workgroup.  Second half-step of 8 workers, us, in a
+    // launch of its own / in this one: 2 workgroups 15.8 / 14.5, 16 16.2 / 15.2, 64 16.4 / 15.6; with lanes that add up several sums
+    // 65 18.2 / 17.6, 128 16.9 / 17.9, 256 17.6 / 22.2.  (A release and an acquire around the count cost nothing beside relaxed accesses.)
     const uint64_t grid = (nwaves + per - 1u) / per;
     DecodeArgs b = a;
     b.arrived = MODE == DecMode::Half1 && grid <= kWave ? &sc->arrived : nullptr;

@@ -122,3 +122,34 @@ def test_two_tables_in_workgroups_of_sixteen_waves(qgx, monkeypatch, waves):
     assert abs(ctx.scalars()["S"] - st.S) <= REL * st.S
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("waves", [1, 4])
+@pytest.mark.parametrize("groups", [1, 2, 63, 64, 65, 130])
+def test_scalar_end_on_both_sides_of_its_line(qgx, monkeypatch, groups, waves):
+    """The second half-step of up to 64 workgroups leaves S, gamma and t itself, larger ones have a kernel for that: several
+    in a row without a wait between them, with and without a previous stream, a short last task, waves without one.  S is a sum of
+    non-negative terms from groups of six in binary32, Y and X of K + 1 and 2 roundings a step: within REL, as the parity tests."""
+    monkeypatch.setitem(WAVES_PER_POSITION, "waves", waves)
+    K, tasks = 4, groups if waves == 4 else 4 * groups - 1       # (four waves to a workgroup: a task each, or all on one)
+    d = 2048 * tasks - 300
+    levels = synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, K, 4096, oracle.NORM_L2, levels, seed=13)
+    ctx.state_init(None)
+    A, B = ctx.new_stream(slotted=True), ctx.new_stream(slotted=True)
+    X = torch.empty(d, device="cuda")
+    for call, s in ((0, A), (1, B)):
+        ctx.quantize_encode(dev(synth.student_t3(K, d, seed=40 + call)), call, s)
+    a, b = ctx.decode(A).double(), ctx.decode(B).double()
+    S, Y, t0 = 0.0, torch.zeros(d, dtype=torch.float64, device="cuda"), ctx.scalars()["t"]
+    for cur, prev, vc, vp in ((B, A, b, a), (A, B, a, b), (B, None, b, 0 * b), (B, A, b, a), (A, None, a, 0 * a)):
+        ctx.eg_step(1, cur, prev, X)
+        S += float(((vc - vp) ** 2).sum())
+        Y -= vc.mean(0)
+        X_o = K / math.sqrt(1.0 + S) * Y
+    assert rel_err(X.cpu().numpy(), X_o.cpu().numpy()) <= REL
+    sc = ctx.scalars()
+    assert sc["t"] == t0 + 5 and abs(sc["S"] - S) <= REL * S
+    assert abs(sc["gamma"] - K / math.sqrt(1.0 + S)) <= REL * sc["gamma"]
+    assert ctx.poll_error() == 0
+    ctx.close()
