@@ -73,9 +73,36 @@ def test_buckets_side_by_side(qgx, bucket, d, norm):
 
 
 @pytest.mark.parametrize("slotted", [False, True])
+@pytest.mark.parametrize("n_sym", [33, 65, 127])
+@pytest.mark.parametrize("bucket,d", [(516, 1024 * 516), (516, 1024 * 516 + 259), (4096, 1024 * 4096), (4096, 1024 * 4096 + 257),
+                                      (16384, 1025 * 4096 + 513)])
+def test_both_sides_of_the_look_ups_ahead(qgx, bucket, d, n_sym, slotted):
+    """8192 and 8200 chunks, where the kernel's form changes on 1024 SIMDs, with whole rows in every chunk (rows that are not
+    whole take a path of their own, the same in both forms), and tables of each cell size; no cell of a uniform one holds two levels, so
+    the rows are coded by the straight path."""
+    K, seed = 8, 29
+    levels = np.linspace(0, 1, n_sym).astype(np.float32)
+    ctx, lay = make_ctx(qgx, d, K, bucket, oracle.NORM_LINF, levels, seed=seed)
+    assert K * lay.NC in (8192, 8200, 8208)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    V = torch.randn((K, d), generator=g, device="cuda")
+    s = ctx.new_stream(slotted=slotted)
+    ctx.quantize_encode(V, 3, s)
+    h = s.to_host()
+    _, _, _, so = oracle_stream(V.cpu().numpy(), lay, oracle.NORM_LINF, levels, seed, 3, h["norms"], ctx.worst_words)
+    if slotted:
+        assert_slotted_equal(h, so, lay, s.slot_words)
+    else:
+        assert_stream_equal(h, so, lay)
+    assert ctx.poll_error() == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("slotted", [False, True])
 @pytest.mark.parametrize("d", [1023 * 100 + 1, 1024 * 100 + 1, 4096 * 100])
-def test_both_sides_of_the_look_ups_ahead(qgx, d, slotted):
-    """8192 and 8200 chunks, where the kernel's form changes on 1024 SIMDs, and 32768 of them."""
+def test_many_chunks_without_a_whole_row(qgx, d, slotted):
+    """8192, 8200 and 32768 chunks of 100 coordinates, four buckets to a workgroup."""
     K, seed, bucket = 8, 29, 100
     levels = synth.levels_exponential(16)
     ctx, lay = make_ctx(qgx, d, K, bucket, oracle.NORM_L2, levels, seed=seed)
