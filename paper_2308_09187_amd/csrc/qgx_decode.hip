@@ -289,8 +289,8 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // KSPLIT = 2 or 4: that many neighbouring waves share a task, each takes a run of the workers (as
 // equal as K allows, the longer runs first), and they add their sums through LDS before the update
 // (for layouts with too few tasks to fill the GPU's wave slots).
-// What bounds it: the parse, whose chains wait for their look-ups (vector ALUs busy for about 55 % of the time, LDS
-// for about half), and at the largest sizes of one stream the memory path (the update moves 6 TB/s).
+// What bounds it: the parse, whose chains wait for their look-ups (with two streams vector ALUs busy for 73 % of the time, LDS
+// for 55 %), and at the largest sizes of one stream the memory path.
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
 __global__ __launch_bounds__((most_waves<MODE, PREV, TWO>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>()) ? 4 : 8)))
 void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)

@@ -160,25 +160,12 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t x)
     return wave_join_u32<32>(x, [](uint32_t a, uint32_t b) { return a | b; });
 }
 
-__device__ __forceinline__ uint32_t bcast_lane(uint32_t x, int src)
-{
-    return (uint32_t)__shfl((int)x, src, kWave);
-}
-
 // A 16-byte load of data that is read once: marked non-temporal, so that it does not push what is
 // reused (the coded streams a later kernel reads back) out of the caches.
 typedef float nt_f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 nt_load4(const float* p)
 {
     const nt_f32x4 r = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4*>(p));
-    return make_float4(r.x, r.y, r.z, r.w);
-}
-
-// The same at any multiple of 4 bytes.
-typedef float nt_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 nt_load4_any(const float* p)
-{
-    const nt_f32x4_any r = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x4_any*>(p));
     return make_float4(r.x, r.y, r.z, r.w);
 }
 

@@ -2,8 +2,8 @@
 // bit packing through LDS, ordered placement of the chunks in the payload.
 // (Definition 1; Section 3.2; Appendix J "Encoding".)
 //
-// Work decomposition for 64-wide wavefronts: one workgroup per (worker, bucket), or several per
-// bucket when it is longer than four chunks (see exchange_parts); one wave per chunk of
+// Work decomposition for 64-wide wavefronts: one workgroup per (worker, bucket), per few short ones (buckets_per_group), or
+// several per bucket when it is longer than four chunks (see exchange_parts); one wave per chunk of
 // 4096 coordinates.  A wave holds its chunk in registers as 16 rows of 256 coordinates, lane L owning
 // the four consecutive coordinates 4L..4L+3 of every row, so that (a) every global load is a fully
 // coalesced 16-byte-per-lane access, (b) the bucket is read from HBM once and stays in registers
@@ -15,7 +15,7 @@
 // straight line: u -> cell (1/16, 1/32 or 1/64 of an octave, by the table's size) -> (boundary level, lower candidate level)
 // -> one 16-byte LDS row holding the level, the scaled gap and the two candidate code words with the sign
 // already appended -> compare against the Philox draw -> select.  A chunk's short last row, buckets
-// with a zero norm and level tables too fine for the cell table take a general path, row by row from memory.
+// whose norm is zero or has no finite reciprocal and level tables too fine for the cell table take a general path, row by row from memory.
 // Measured, us (120 instructions a row, tables waited for before a chunk is asked for, a workgroup per bucket -> now):
 // 8 x 2^24 coordinates 147 -> 138, 8 x 9.86 M in buckets of 8192 96 -> 83, of 1024 101 -> 86, 5 x 3000001 in buckets of 6000
 // 35 -> 28, 2^20 coordinates 11.7 -> 9.9.
@@ -93,7 +93,7 @@ __device__ uint32_t lookback_exclusive(unsigned long long* state, uint32_t b, ui
 }
 
 // Buckets longer than four chunks are shared by several workgroups of four waves (parts), which a
-// compute unit holds five of (four in the game's form) at different points of their life, where one workgroup of sixteen waves
+// compute unit holds five of (four in the forms with look-ups ahead) at different points of their life, where one workgroup of sixteen waves
 // would have the unit to itself and leave the memory system idle while it computes and the ALUs idle
 // while it loads.  What the parts must agree on is the bucket's norm: every part publishes its
 // partial sum (or maximum) and reads the others'.  A published value is two words, each tagged with
@@ -363,8 +363,8 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
     return plain;
 }
 
-// One workgroup per (worker, bucket).  Workgroups are short-lived on purpose: with five of them (four in
-// the game's form) per compute unit at different points of their life, the load, ticket and look-back latencies of one
+// One workgroup per (worker, bucket), group of short buckets or part of a long one.  Workgroups are short-lived on purpose: with five of
+// them (four with look-ups ahead) per compute unit at different points of their life, the load, ticket and look-back latencies of one
 // overlap the arithmetic of the others (a persistent, lock-stepped variant measured slower).
 // GROUPED: the layout has shared chunks; a workgroup is four waves with a chunk each, and every wave
 // finds the norms of its chunk's buckets by itself.

@@ -60,10 +60,12 @@ QGX_PLAN BlockWork block_by_unit(uint32_t i, uint32_t K, uint32_t units)
 
 // Where a worker's workgroups keep an order (compact placement, whole buckets) and K is a multiple of 8, the plain rows put each
 // worker on one XCD, whose workgroups then all wait for the same straggler, go on together and are in step from there on. Rows
-// turned against each other by 0, 2, 4 and 6 workers give a worker four XCDs.  8 workers in buckets of 16384, us, plain / turned:
-// 2^20 coordinates 20.1 / 20.7, 2^21 34.5 / 31.1, 2^22 64.9 / 56.7, 9.86 M 141 / 108, 2^24 224 / 166 (without an order 145);
-// 16 workers, 2^22 103 / 95, 2^23 201 / 162.  With more workers to an XCD each has fewer workgroups there and the wait is a
-// part of it: 24 workers of 2^21 70 / 80, 32 of 2^20 50 / 60, of 2^22 157 / 161.
+// turned against each other by 0, 2, 4 and 6 workers give a worker four XCDs.  What that gives grows with a worker's workgroups on an
+// XCD, and with few of them plain rows are the better; the two meet at about 16 for each worker.  Plain / turned, us, buckets of
+// 16384, 8 workers, 17 exponential levels: 2^21 coordinates (128 workgroups a worker) 31.1 / 29.2, 2^22 59.7 / 54.8, 2^24 219 / 167
+// (without an order 138); 33 uniform ones: 2^20 17.2 / 18.9, 2^21 26.8 / 27.8, 2^22 52.7 / 52.5, 9.86 M 125 / 108, 2^24 198 / 164.  33 uniform
+// levels, 16 workers: 128 workgroups 49.2 / 52.3, 256 91.5 / 92.1, 512 183 / 160; 24 workers: 192 92.2 / 97.2, 384 169 / 168, 576
+// 269 / 241; 32 workers: 256 149 / 154, 512 285 / 283; 64 workers: 256 274 / 280.
 QGX_PLAN uint32_t worker_spread(uint32_t k, uint32_t unit, uint32_t span) { return (k + 2u * (unit & 3u)) % span; }
 
 inline bool spread_workers(uint32_t K, uint32_t units) { return K % kXcds == 0u && units >= 16u * K; }
@@ -84,11 +86,13 @@ inline uint32_t worker_span(uint32_t K, uint32_t parts, uint32_t held)
 }
 
 // Whole buckets to a workgroup of the coding kernel, where buckets have few chunks (a wave each): four waves then share the
-// tables in LDS, and a compute unit holds twenty waves whatever the bucket.  A small launch is over sooner with more and
+// tables in LDS, and a compute unit's places hold as many waves whatever the bucket.  A small launch is over sooner with more and
 // smaller workgroups, unless they have to keep an order, which has the fewer members.  Measured, one bucket to a workgroup /
-// four waves, us, in slots: 256 chunks 9.9 / 10.6, 2048 15.8 / 16.3, 3665 24.2 / 24.5, 5005 (half of them short) 26.3 / 25.1,
-// 8192 47.1 / 45.6; in order: 256 chunks 13.7 / 13.8 and (a chunk to a bucket) 15.3 / 13.9, 2048 20.8 / 21.1 and 30.2 / 20.5,
-// 8192 81.6 / 68.3 and 88.4 / 69.1.
+// four waves, us, 8 workers in buckets of one chunk and of two.  In slots: 256 chunks 9.0 / 9.9 and 9.0 / 9.7, 2048 14.2 / 14.6
+// and 14.1 / 14.4, 4096 23.8 / 24.4 and 23.7 / 24.2, 8192 41.6 / 42.0 and 41.0 / 41.4, 16384 76.0 / 75.5 and 75.7 / 75.1, 19257
+// 84.5 / 83.1 and 83.0 / 83.0.  In order: 128 10.8 / 11.5 and 10.6 / 11.3, 256 11.4 / 11.7 and 11.0 / 11.5, 512 13.9 / 12.4 and
+// 11.6 / 12.2, 1024 15.9 / 13.0 and 14.6 / 12.9, 4096 37.3 / 29.7 and 32.1 / 29.4, 16384 123 / 95.9 and 105 / 95.0.  (The lines
+// were drawn at five waves per SIMD; with look-ups ahead, small launches in slots gain nothing from sharing up to twice the line.)
 inline uint32_t buckets_per_group(uint32_t waves_per_bucket, uint64_t chunks_of_all, bool ordered)
 {
     if (waves_per_bucket > 2u || chunks_of_all < (ordered ? 256u : 4096u)) return 1u;
@@ -103,8 +107,12 @@ QGX_PLAN uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t wa
 }
 
 // The coding kernel's form with look-ups ahead at four waves per SIMD, or five waves: a wave per chunk, up to two rounds of four.
-// Measured, us, five waves / look-ups ahead: 256 chunks 10.6 / 9.6, 2048 15.9 / 15.2, 4096 27.7 / 27.0, 8192 46.7 / 45.4 (in order
-// 13.7 / 12.7, 19.9 / 19.7, 31.7 / 30.9, 59.8 / 58.0); 19328 84.0 / 85.5, 32768 137 / 137.
+// Beyond that, chunks in order lose more with it than those in slots gain.  Five waves / look-ups ahead, us, 8 workers in buckets of
+// 16384, 17 levels, in slots: 512 chunks 10.6 / 9.6, 2048 14.7 / 14.0, 4096 24.5 / 23.7, 6144 32.1 / 31.6, 8192 41.2 / 41.0, 9216 45.0 /
+// 44.0, 10240 49.0 / 48.5, 12288 57.4 / 56.5, 16384 74.1 / 74.5, 24576 104 / 104; in order: 512 13.0 / 11.9, 2048 19.5 / 18.4, 4096
+// 29.3 / 28.6, 6144 46.1 / 46.5, 8192 56.8 / 54.4, 9216 59.2 / 64.6, 10240 62.0 / 69.5, 12288 77.0 / 76.1, 16384 92.5 / 96.5.  In slots,
+// 4096 and 8192 chunks, with 33 levels 23.8 / 22.7 and 39.5 / 38.5, 65 23.2 / 22.2 and 39.4 / 38.1, 127 24.8 / 23.2 and 42.9 /
+// 40.5; L-infinity norm 24.9 / 24.2 and 41.8 / 41.0, q = 3 59.5 / 58.6 and 116 / 114.
 inline bool use_staged(uint64_t chunks_of_all, uint32_t n_simd) { return chunks_of_all <= 8u * (uint64_t)n_simd; }
 
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
