@@ -36,7 +36,7 @@
 namespace qgx {
 
 constexpr unsigned kSpinLimit = 1u << 22;
-constexpr float kMaxF32 = 3.402823466e+38f;
+constexpr float kNoReciprocal = 0x1p-128f;        // 1 / n overflows binary32 for n up to this
 
 // Exclusive prefix of `agg` over buckets 0..b-1 of one worker (decoupled look-back, one wave).
 // state[] entries: high word = epoch << 2 | status (1 = aggregate, 2 = inclusive prefix), low word = value.
@@ -349,13 +349,12 @@ __device__ __forceinline__ bool shared_chunk_norms(const float4 (&v)[kRows], con
             const bool bucket_bad = !(fabsf(n) <= 3.402823466e+38f);
             if (bucket_bad) n = 0.0f;
             const bool live = n > 0.0f;
-            const float rinv = live ? 1.0f / n : 0.0f;                    // one IEEE division per bucket
             if (lane == 0) {
                 if (bucket_bad) raise_error(sc, QGX_EBIT_NONFINITE);
                 if (a.norms_out) a.norms_out[(size_t)k * lay.NB + bucket0 + gb] = n;
-                rinv_out[gb] = rinv;
+                rinv_out[gb] = live ? 1.0f / n : 0.0f;                    // one IEEE division per bucket
             }
-            plain = plain && live && u_le_1 && rinv <= kMaxF32;
+            plain = plain && n > kNoReciprocal && u_le_1;
         }
         p0 = p1 = p2 = p3 = 0.0f;
         mx = 0.0f;
@@ -662,7 +661,7 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
         // The straight path's look-ups lie inside the tables for u <= 1 up to a rounding only: a norm of 2^-128 or less, whose
         // reciprocal overflows and makes u infinite or NaN, takes the general path, which clamps u (as a chunk's last
         // row does, if short).
-        const bool fast = live && (GROUPED || rinv <= kMaxF32) && (vec_ok || MODE != EncMode::QuantOnly) && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
+        const bool fast = live && (GROUPED || n > kNoReciprocal) && (vec_ok || MODE != EncMode::QuantOnly) && u_le_1 && (cell_exact != 0u) && MODE != EncMode::EncodeOnly;
         const uint32_t rshift = GROUPED ? lay.bucket_shift - 8u : 0u;         // rows per bucket, as a shift
 
         // ---- per row: quantise, code, pack -------------------------------------------------------
