@@ -58,7 +58,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // 2, v_sin_f32 and v_cos_f32 take their argument in turns), good to about 1e-6, which is ample for noise.
 __device__ __forceinline__ float2 box_muller(uint32_t w_radius, uint32_t w_angle)
 {
-    const float u1 = (float)(2u * (w_radius >> 9) + 1u) * 0x1p-24f;
+    // (1 + m 2^-23 less 1 - 2^-24, m = w >> 9: exact, and two instructions where a conversion of 2 m + 1 takes four)
+    const float u1 = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w_radius, 9)) - 0x1.fffffep-1f;
     const float u2 = (float)(w_angle >> 8) * 0x1p-24f;
     const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));   // -2 ln 2 * log2 u1
     return make_float2(r * __builtin_amdgcn_cosf(u2), r * __builtin_amdgcn_sinf(u2));
@@ -274,21 +275,21 @@ __device__ __forceinline__ GameOperands load_game_operands(const GameRows& rows,
 
 // The same four coordinates of worker k's dual vector in call `call_id`: F(z) + sigma N, the noise from the
 // Philox block with key (seed_lo, seed_hi) and counter (i0 / 4, 1, k, call_id).  F: game_operator_row.
-__device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, float sigma, uint32_t i0, uint32_t k, uint32_t call_id)
+__device__ __forceinline__ float4 game_noisy_row(const GameArgs& G, float4 F, uint32_t i0, uint32_t k, uint32_t call_id)
 {
     uint32_t w[4];
     philox4x32_10(i0 >> 2, 1u, k, call_id, philox_keys(G.seed_lo, G.seed_hi), w);
     const float2 n01 = box_muller(w[0], w[1]), n23 = box_muller(w[2], w[3]);
-    F.x += sigma * n01.x;
-    F.y += sigma * n01.y;
-    F.z += sigma * n23.x;
-    F.w += sigma * n23.y;
+    F.x += G.sigma * n01.x;
+    F.y += G.sigma * n01.y;
+    F.z += G.sigma * n23.x;
+    F.w += G.sigma * n23.y;
     return F;
 }
 
 __device__ __forceinline__ float4 game_dual_row(const GameArgs& G, uint32_t i0, uint32_t k, uint32_t call_id)
 {
-    return game_noisy_row(G, game_operator_row(G, i0), G.sigma, i0, k, call_id);
+    return game_noisy_row(G, game_operator_row(G, i0), i0, k, call_id);
 }
 
 // t^q for a small positive integer q (the same q in every lane).

@@ -516,8 +516,15 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
             const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
             const GameOperands now = next;
             if (r + 1 < kRows) next = load_game_operands(rows, r + 1, lane);
-            v[r] = game_noisy_row(a.game, game_operator_row(a.game, now), i0 < g.cend ? a.game.sigma : 0.0f, i0, k, call_id);
+            v[r] = game_noisy_row(a.game, game_operator_row(a.game, now), i0, k, call_id);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!g.full) {                                 // no noise past the chunk's end (selected in every row: two of its 210 instructions)
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const uint32_t i0 = g.clo + (uint32_t)r * 256u + (uint32_t)lane * 4u;
+                if (i0 >= g.cend) v[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
         if (a.game.V_out) {
 #pragma unroll

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void k_game_dual_vectors(GameArgs G, uint32_t 
     const float4 F = game_operator_row(G, i0);
     float* __restrict__ out = V + (size_t)k0 * d + i0;
     for (uint32_t k = k0; k < k1; ++k, out += d)
-        *reinterpret_cast<float4*>(out) = game_noisy_row(G, F, G.sigma, i0, k, call);
+        *reinterpret_cast<float4*>(out) = game_noisy_row(G, F, i0, k, call);
 }
 
 hipError_t launch_game_dual_vectors(const GameArgs& g, uint32_t d, uint32_t K, uint32_t call_id, uint32_t call_mode,
