@@ -32,6 +32,7 @@
 // held by a running workgroup that needs nothing from later tickets; the wait is bounded all the same.
 #include "qgx_device.h"
 #include "qgx_plan.h"
+#include <algorithm>
 
 namespace qgx {
 
@@ -844,6 +845,431 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
     }
 }
 
+// The coding kernel where V is read and chunks are few: four waves to a chunk.  Such a launch takes as long as one wave lives, of
+// which a third is the straight line of its rows (a wave alone on its SIMD issues every 6.4 clocks, 5 us for sixteen rows), while most
+// of the GPU's places for waves are empty.
+// A wave has 16 of the 64 columns of four coordinates, lane 16 i + j rows 4 i .. 4 i + 3 of its column j (a short chunk: as
+// many rows as it takes, 4 i -> slots * i): a column's sums of squares thus go from row to row inside a wave, by lane
+// swaps, and are the sums of k_encode bit for bit.  The codes' lengths are summed across 16 lanes, and a row's four pieces
+// find their places through the chunk's 64 counts in LDS.
+// What bounds it is still latency: launch, tables and rows 2.3 us, the norm with its two barriers 1.2, a row at a time 0.4, flush 0.5.
+// Kernel alone, a wave per chunk -> four, us: 256 chunks in slots, buckets of 1024 13.1 -> 7.0, of 6000 9.8 -> 7.4, of 8192 (L-infinity
+// norm) 9.6 -> 7.7; one bucket of 1024 6.3 -> 5.0; in order, 16 chunks in buckets of 1024 14.2 -> 10.7, of 8192 11.0 -> 9.0; where not: use_columns.
+// (A quarter of the rows to a wave, the sums handed on through LDS with a barrier each: 6.1, 9.5, 7.2 and 6.8.)
+// Units, tickets and look-back are those of k_encode; a workgroup is a whole bucket (a.parts is 1), or with shared chunks a chunk, or
+// four where they keep an order.
+constexpr int kSlots = kRows / 4;       // rows of a lane
+struct ColumnLds {                      // LDS after the tables, in bytes, for a workgroup of `chunks` chunks
+    uint32_t sums, again, misc, rinv, fine, counts, totals, stage, buckets;
+    __host__ __device__ ColumnLds(uint32_t pieces, uint32_t chunks, bool grouped)
+    {
+        buckets = grouped ? 16u : 1u;                               // of a chunk
+        sums = pieces * 16u;                                        // [chunks][buckets][64] double: a bucket's columns
+        again = sums + chunks * buckets * (uint32_t)kWave * 8u;     // [4 * chunks] double
+        misc = again + 4u * chunks * 8u;                            // 4 words
+        rinv = misc + 16u;                                          // [chunks][16] float: 1 / norm of the buckets that share a chunk
+        fine = rinv + (grouped ? chunks * 64u : 0u);                // [chunks][16] words: the straight route applies to them
+        counts = fine + (grouped ? chunks * 64u : 0u);              // [chunks][64]: bits of row r's columns 16 q and on, at 4 r + q
+        totals = counts + chunks * 256u;                            // [4] words of the unit's chunks
+        stage = totals + 16u;
+    }
+};
+
+// From the lanes of a row of 16 to the lanes of the next row: FROM 0 -> 1 and 2 -> 3 (even), 1 -> 2 (odd).
+template <bool ODD>
+__device__ __forceinline__ float next_sixteen(float x)
+{
+    const LanePair p = lane_pair<16>(__float_as_uint(x));
+    if constexpr (!ODD) return __uint_as_float(p.a);
+    return __uint_as_float(lane_pair<32>(p.b).a);
+}
+
+template <bool GROUPED, int CM>
+__global__ __launch_bounds__(1024) void k_encode_columns(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArgs a)
+{
+    extern __shared__ __align__(16) unsigned char s_all[];
+    const int tid = (int)threadIdx.x, lane = lane_id();
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane(wave_id()), cw = w >> 2, part = w & 3u;
+    const uint32_t nthreads = blockDim.x, nchunks = nthreads >> 8;
+    uint32_t k = blockIdx.x % lay.K;
+    const uint32_t own_unit = blockIdx.x / lay.K;
+    if (a.spread) k = worker_spread(k, own_unit, lay.K);
+    const ColumnLds at(a.pieces, nchunks, GROUPED);
+    uint4* s_enc = reinterpret_cast<uint4*>(s_all);
+    double* s_sums = reinterpret_cast<double*>(s_all + at.sums);
+    double* s_again = reinterpret_cast<double*>(s_all + at.again);
+    uint32_t* s_misc = reinterpret_cast<uint32_t*>(s_all + at.misc);
+    float* s_rinv = reinterpret_cast<float*>(s_all + at.rinv) + cw * 16u;
+    uint32_t* s_fine = reinterpret_cast<uint32_t*>(s_all + at.fine) + cw * 16u;
+    uint32_t* s_counts = reinterpret_cast<uint32_t*>(s_all + at.counts) + cw * 64u;
+    uint32_t* s_totals = reinterpret_cast<uint32_t*>(s_all + at.totals);
+    uint32_t* stage = reinterpret_cast<uint32_t*>(s_all + at.stage + (size_t)cw * a.stage_bytes);
+    if (lds_address(s_all) != 0u) {                    // the look-ups address the tables by number (see k_encode)
+        if (tid == 0) raise_error(sc, QGX_EBIT_STATE);
+        return;
+    }
+    for (uint32_t i = (uint32_t)tid + 2u * nthreads; i < a.pieces; i += nthreads) s_enc[i] = tab->enc[i];
+    const uint32_t piece0 = min((uint32_t)tid, a.pieces - 1u), piece1 = min((uint32_t)tid + nthreads, a.pieces - 1u);
+    const nt_u32x4 ahead0 = reinterpret_cast<const nt_u32x4*>(tab->enc)[piece0];
+    const nt_u32x4 ahead1 = reinterpret_cast<const nt_u32x4*>(tab->enc)[piece1];
+
+    const bool ordered = a.slot_words == 0u;
+    if (ordered) {                                     // (the unit and the launch's number from the ticket: see k_encode)
+        if (tid == 0) {
+            const unsigned long long per_launch = a.units;
+            const unsigned long long raw = atomicAdd(a.tickets + k * kTicketStride, 1ull);
+            const unsigned long long launch = raw / per_launch;
+            s_misc[2] = (uint32_t)(raw - launch * per_launch);
+            s_misc[3] = (uint32_t)(launch % 0x3FFFFFFFull) + 1u;
+        }
+        __syncthreads();
+    }
+    const uint32_t unit = ordered ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_misc[2]) : own_unit;
+    const uint32_t epoch = ordered ? (uint32_t)__builtin_amdgcn_readfirstlane((int)s_misc[3]) : 0u;
+    if (unit >= a.units) return;                       // cannot happen
+    const uint32_t call_id = a.call_mode ? 2u * (scalar_load(&sc->t) - 1u) + (a.call_mode - 1u) : a.call_id;
+    const float* __restrict__ Vk = a.V + (size_t)k * lay.d;
+
+    // the wave's chunk and bucket (with shared chunks: the chunk's first)
+    ChunkGeom g;
+    uint32_t b;
+    if constexpr (GROUPED) {
+        g.c = unit * nchunks + cw;
+        const bool there = g.c < lay.NC;
+        g.clo = there ? scalar_load(lay.chunk_start + g.c) : 0u;
+        g.clen = there ? scalar_load(lay.chunk_start + g.c + 1) - g.clo : 0u;
+        g.cend = g.clo + g.clen;
+        g.nrows = (int)((g.clen + 255u) >> 8);
+        g.full = g.clen == (uint32_t)kChunk;
+        b = there ? scalar_load(lay.chunk_bucket + g.c) : 0u;
+    } else {
+        b = unit;
+        g = chunk_geom(lay, b, cw, true);
+    }
+    // rows to a lane: 4, 2 or 1
+    const int slots = g.nrows > 8 ? 4 : g.nrows > 4 ? 2 : 1;
+    const uint32_t column = 16u * part + ((uint32_t)lane & 15u);
+    const uint32_t row0 = ((uint32_t)lane >> 4) * (uint32_t)slots;
+    const uint32_t at0 = g.clo + row0 * 256u + column * 4u;            // the lane's first coordinate; slot s: 256 s further on
+
+    float4 v[kSlots];
+    {
+        const __amdgpu_buffer_rsrc_t rows = chunk_rows(Vk + g.clo, g.clen);
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (s < slots) v[s] = load_row(rows, s, (int)(row0 * 64u + column));
+        }
+    }
+    reinterpret_cast<nt_u32x4*>(s_enc)[piece0] = ahead0;
+    reinterpret_cast<nt_u32x4*>(s_enc)[piece1] = ahead1;
+    for (uint32_t i = part * kWave + (uint32_t)lane; i < a.stage_bytes / 16; i += 4u * kWave)
+        reinterpret_cast<uint4*>(stage)[i] = make_uint4(0, 0, 0, 0);
+    if (part == 0u) s_counts[lane] = 0u;
+    const uint32_t n_sym = tab->n_sym;
+    const bool cell_exact = tab->cell_exact != 0u && (uint32_t)cell_mant(n_sym) == a.cell_mant;
+    __syncthreads();
+    if ((g.clen & 3u) != 0u) {                         // the last one to three coordinates of an odd vector (load_rest)
+        const uint32_t rest = g.clo + (g.clen & ~3u);
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+        x.x = Vk[rest];
+        if ((g.clen & 3u) > 1u) x.y = Vk[rest + 1u];
+        if ((g.clen & 3u) > 2u) x.z = Vk[rest + 2u];
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)
+            if (s < slots && at0 + 256u * (uint32_t)s == rest) v[s] = x;
+    }
+
+    // ---- norms -----------------------------------------------------------------------------------
+    const bool l2 = a.norm_kind == QGX_NORM_L2;
+    const uint32_t rshift = GROUPED ? lay.bucket_shift - 8u : 4u;      // rows to a bucket of the chunk, as a shift
+    // A column's four runs of squares (largest magnitude) of a bucket's rows, in row order, to bucket t's columns in LDS.
+    auto leave = [&](uint32_t t, const float4& p, float mx) {
+        s_sums[(cw * at.buckets + t) * (uint32_t)kWave + column] =
+            l2 ? ((double)p.x + (double)p.y) + ((double)p.z + (double)p.w) : (double)mx;       // inf or NaN survive the conversion
+    };
+    auto add_slot = [&](float4& p, float& mx, int s) {
+        if (l2) {
+            p.x = fmaf(v[s].x, v[s].x, p.x);
+            p.y = fmaf(v[s].y, v[s].y, p.y);
+            p.z = fmaf(v[s].z, v[s].z, p.z);
+            p.w = fmaf(v[s].w, v[s].w, p.w);
+        } else {
+            mx = largest_of(v[s], mx);
+        }
+    };
+    if ((1 << rshift) <= slots) {                      // (shared chunks) a lane's rows are whole buckets
+        float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+        float mx = 0.0f;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            if (s >= slots) break;
+            add_slot(p, mx, s);
+            if ((((uint32_t)s + 1u) & ((1u << rshift) - 1u)) != 0u) continue;
+            leave((row0 + (uint32_t)s) >> rshift, p, mx);
+            p = make_float4(0.f, 0.f, 0.f, 0.f);
+            mx = 0.0f;
+        }
+    } else {
+        // from one row of 16 lanes to the next, but where a bucket begins
+        const uint32_t in_bucket = row0 & ((1u << rshift) - 1u);
+        float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+        float mx = 0.0f;
+#pragma unroll
+        for (int turn = 0; turn < 4; ++turn) {
+            if (turn > 0) {
+                auto pass = [&](float x) { return turn == 2 ? next_sixteen<true>(x) : next_sixteen<false>(x); };
+                p = make_float4(pass(p.x), pass(p.y), pass(p.z), pass(p.w));
+                mx = pass(mx);
+                if (in_bucket == 0u) { p = make_float4(0.f, 0.f, 0.f, 0.f); mx = 0.0f; }
+            }
+#pragma unroll
+            for (int s = 0; s < kSlots; ++s)
+                if (s < slots) add_slot(p, mx, s);
+            // (the lanes whose turn it is, where the bucket or the chunk ends)
+            if ((lane >> 4) == turn && (turn == 3 || in_bucket + (uint32_t)slots == (1u << rshift))) leave(row0 >> rshift, p, mx);
+        }
+    }
+    __syncthreads();
+    auto column_total = [&](uint32_t chunk, uint32_t t) -> double {    // (a whole wave)
+        const double x = s_sums[(chunk * at.buckets + t) * (uint32_t)kWave + (uint32_t)lane];
+        return l2 ? wave_sum(x) : (double)__uint_as_float(wave_max_u32(__float_as_uint((float)x)));
+    };
+    auto beyond = [&](double t) { return l2 && !(t >= 0x1p-60 && t <= 0x1p100); };
+    auto finite = [](float x) { return fabsf(x) <= 3.402823466e+38f; };
+    float n = 0.0f;
+    bool fast = cell_exact;                            // the straight route applies: see k_encode
+    if constexpr (GROUPED) {
+        // a wave to a bucket of its chunk
+        for (uint32_t t = part; t < 16u >> rshift; t += 4u) {
+            const uint32_t lo = g.clo + (t << lay.bucket_shift);
+            if (lo >= g.cend) break;
+            const uint32_t hi = min(lo + (1u << lay.bucket_shift), g.cend);
+            double tot = column_total(cw, t);
+            if (beyond(tot)) {
+                double acc = 0.0;
+#pragma unroll 1
+                for (uint32_t i = lo + (uint32_t)lane; i < hi; i += kWave) acc = fma((double)Vk[i], (double)Vk[i], acc);
+                tot = wave_sum(acc);
+            }
+            float nt = l2 ? (float)sqrt(tot) : (float)tot;
+            if (!l2 && a.norm_kind != QGX_NORM_LINF && tot > 0.0 && tot <= 3.402823466e+38) {
+                const double inv_m = 1.0 / tot;
+                double acc = 0.0;
+#pragma unroll 1
+                for (uint32_t i = lo + (uint32_t)lane; i < hi; i += kWave)
+                    acc += pow_int(fabs((double)Vk[i]) * inv_m, (uint32_t)a.norm_kind);
+                nt = (float)(tot * root_int(wave_sum(acc), (uint32_t)a.norm_kind));
+            }
+            bool u_le_1 = true;
+            if (a.norms_in) {
+                const float forced = a.norms_in[(size_t)k * lay.NB + b + t];
+                u_le_1 = forced >= nt;
+                nt = finite(nt) ? forced : nt;
+            }
+            const bool bad = !finite(nt);
+            if (bad) nt = 0.0f;
+            if (lane == 0) {
+                if (bad) raise_error(sc, QGX_EBIT_NONFINITE);
+                if (a.norms_out) a.norms_out[(size_t)k * lay.NB + b + t] = nt;
+                s_rinv[t] = nt > 0.0f ? 1.0f / nt : 0.0f;
+                s_fine[t] = nt > kNoReciprocal && u_le_1 ? 1u : 0u;
+            }
+        }
+        __syncthreads();
+    } else {
+        auto sum_again = [&](double acc) {             // (by all waves of the workgroup) the bucket's sum of acc
+            acc = wave_sum(acc);
+            if (lane == 0) s_again[w] = acc;
+            __syncthreads();
+            double t = 0.0;
+            for (uint32_t i = 0; i < 4u * nchunks; ++i) t += s_again[i];
+            return t;
+        };
+        const uint32_t quarter_lo = min(g.clo + part * (kChunk / 4u), g.cend), quarter_hi = min(quarter_lo + kChunk / 4u, g.cend);
+        double tot = 0.0;
+        for (uint32_t c = 0; c < nchunks; ++c) {       // the bucket's chunks, in order
+            const double x = column_total(c, 0u);
+            if (l2) tot += x;
+            else tot = (x > tot || x != x) ? x : tot;
+        }
+        if (beyond(tot)) {                             // as in k_encode: the sum again in binary64
+            double acc = 0.0;
+#pragma unroll 1
+            for (uint32_t i = quarter_lo + (uint32_t)lane; i < quarter_hi; i += kWave) { const double x = (double)Vk[i]; acc = fma(x, x, acc); }
+            tot = sum_again(acc);
+        }
+        n = l2 ? (float)sqrt(tot) : (float)tot;
+        if (!l2 && a.norm_kind != QGX_NORM_LINF) {
+            const bool sound = tot > 0.0 && tot <= 3.402823466e+38;
+            const double inv_m = 1.0 / tot;
+            double acc = 0.0;
+            if (sound) {
+#pragma unroll 1
+                for (uint32_t i = quarter_lo + (uint32_t)lane; i < quarter_hi; i += kWave)
+                    acc += pow_int(fabs((double)Vk[i]) * inv_m, (uint32_t)a.norm_kind);
+            }
+            const double sum = sum_again(acc);
+            if (sound) n = (float)(tot * root_int(sum, (uint32_t)a.norm_kind));
+        }
+        bool u_le_1 = true;
+        if (a.norms_in) {
+            const float forced = a.norms_in[(size_t)k * lay.NB + b];
+            u_le_1 = forced >= n;
+            n = finite(n) ? forced : n;
+        }
+        const bool bad = !finite(n);
+        if (bad) n = 0.0f;
+        if (tid == 0) {
+            if (bad) raise_error(sc, QGX_EBIT_NONFINITE);
+            if (a.norms_out) a.norms_out[(size_t)k * lay.NB + b] = n;
+        }
+        fast = fast && n > kNoReciprocal && u_le_1;
+    }
+    const float rinv = GROUPED ? 0.0f : 1.0f / n;
+    const bool live = n > 0.0f;
+
+    // ---- the rows: quantise, code ------------------------------------------------------------------
+    uint32_t first_cell = kCellKey0<CM> << kCellShift<CM>;
+    asm("" : "+v"(first_cell));
+    const PhiloxKeys keys = philox_keys(a.seed_lo, a.seed_hi);
+    float rinv_s[kSlots];
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        rinv_s[s] = rinv;
+        if constexpr (GROUPED) {
+            if (s < slots) {
+                const uint32_t t = (row0 + (uint32_t)s) >> rshift;
+                const bool inside = g.clo + (t << lay.bucket_shift) < g.cend;
+                rinv_s[s] = inside ? s_rinv[t] : 0.0f;
+                fast = fast && !__any(inside && s_fine[t] == 0u);
+            }
+        }
+    }
+    RowCode code[kSlots];
+    uint32_t length[kSlots], end[kSlots];
+    auto put_entries = [&](int s, uint32_t (&e)[4]) __attribute__((always_inline)) {
+        if (!g.full) {                                 // nothing past the chunk's end (wave-uniform)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = at0 + 256u * (uint32_t)s + (uint32_t)i < g.cend ? e[i] : 0u;
+        }
+        code[s] = join_row(e);
+    };
+    auto fast_row = [&](int s) __attribute__((always_inline)) {
+        const float xs[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
+        float u[4];
+        uint2 c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { u[i] = fabsf(xs[i]) * rinv_s[s]; c[i] = cell_of<CM>(u[i], first_cell); }
+        uint32_t rnd[4], e[4];
+        philox4x32_10((at0 >> 2) + 64u * (uint32_t)s, 0u, k, call_id, keys, rnd);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 t = level_row<CM>(level_in_cell(u[i], c[i]), xs[i]);
+            e[i] = rounds_up(u[i], t, rnd[i]) ? t.w : t.z;
+        }
+        put_entries(s, e);
+    };
+    if (fast && slots == kSlots) {
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) fast_row(s);
+    } else {
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            code[s] = RowCode{0u, 0u, 0u};
+            if (s >= slots) continue;
+            if (fast) {
+                fast_row(s);
+            } else {                                   // a norm of zero or without a reciprocal, u above 1, crowded cells
+                const float xs[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
+                const bool live_s = GROUPED ? rinv_s[s] != 0.0f : live;
+                uint32_t rnd[4], e[4];
+                philox4x32_10((at0 >> 2) + 64u * (uint32_t)s, 0u, k, call_id, keys, rnd);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t idx = 0;
+                    const uint32_t neg = __float_as_uint(xs[i]) >> 31;
+                    if (live_s) {
+                        const float u = fminf(fabsf(xs[i]) * rinv_s[s], 1.0f);
+                        const uint32_t j = level_general<CM>(u, n_sym);
+                        idx = j + (rounds_up(u, level_row<CM>(j, xs[i]), rnd[i]) ? 1u : 0u);
+                    }
+                    uint32_t entry = lds_load_u32(kLevAt<CM> + 8u + (2u * idx + neg) * 16u);
+                    asm("" : "+v"(entry));
+                    e[i] = entry;
+                }
+                put_entries(s, e);
+            }
+        }
+    }
+    // each lane's place among its row's 16 columns, two slots to a scan; the rows' pieces through LDS
+#pragma unroll
+    for (int s = 0; s < kSlots; s += 2) {
+        const uint32_t both = __builtin_amdgcn_perm(code[s + 1].sum, code[s].sum, 0x0C050C01u);
+        uint32_t incl = both;
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x112, 0xf, 0xf, false);
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x114, 0xf, 0xf, false);
+        incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x118, 0xf, 0xf, false);
+        length[s] = both & 0xFFFFu;
+        length[s + 1] = both >> 16;
+        end[s] = incl & 0xFFFFu;
+        end[s + 1] = incl >> 16;
+        if ((lane & 15) == 15) {
+            if (s < slots) s_counts[4u * (row0 + (uint32_t)s) + part] = end[s];
+            if (s + 1 < slots) s_counts[4u * (row0 + (uint32_t)s + 1u) + part] = end[s + 1];
+        }
+    }
+    __syncthreads();
+    const uint32_t count = s_counts[lane], upto = wave_incl_scan(count);
+    const uint32_t total_bits = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+    const uint32_t words = (((total_bits + 31u) >> 5) + (kAlignWords - 1)) & ~(uint32_t)(kAlignWords - 1);
+    if (ordered && part == 0u && lane == 0) s_totals[cw] = words;
+    if (g.clen != 0u) {
+        uint16_t* __restrict__ sub_g = a.sub_end + ((size_t)k * lay.NC + g.c) * kSubs;
+        const __amdgpu_buffer_rsrc_t ends = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_address(sub_g)), 0, kSubs * (int)sizeof(uint16_t), 0x00027000);
+        const uint32_t stage0 = 8u * (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_address(stage)) - 1u;      // (see place_row)
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            if (s >= slots) break;
+            const uint32_t row = row0 + (uint32_t)s;
+            const uint32_t base = (uint32_t)__shfl((int)(upto - count), (int)(4u * row + part), kWave);
+            place_row(stage0 + base + end[s] - length[s], code[s]);
+            // a run's last lane stores where it ends, the others outside the buffer; a row without symbols: where the chunk ends
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(base + end[s]), ends, (lane & 7) == 7 ? (int)(16u * row + 2u * (column >> 3)) : 0x40000000, 0, 0);
+        }
+        // the rows that no slot stands for
+        for (uint32_t i = 32u * (uint32_t)slots + part * kWave + (uint32_t)lane; i < (uint32_t)kSubs; i += 4u * kWave) sub_g[i] = (uint16_t)total_bits;
+    }
+    uint32_t words_before = 0;
+    if (ordered) {
+        __syncthreads();
+        uint32_t unit_words = 0;
+        for (uint32_t c = 0; c < nchunks; ++c) {
+            if (c == cw) words_before = unit_words;
+            unit_words += s_totals[c];
+        }
+        if (w == 0u) {
+            const uint32_t excl = lookback_exclusive(a.scan_state + (size_t)k * lay.NB * a.parts, unit, unit_words, epoch, sc);
+            if (lane == 0) s_misc[1] = excl;
+        }
+    }
+    __syncthreads();                                   // the chunk's codes are all there
+    if (g.clen == 0u) return;
+    const uint32_t off = ordered ? s_misc[1] + words_before : g.c * a.slot_words;
+    if (part == 0u && lane == 0) {
+        a.chunk_off[(size_t)k * (lay.NC + 1) + g.c] = off;
+        if (g.c + 1 == lay.NC) a.chunk_off[(size_t)k * (lay.NC + 1) + lay.NC] = off + (ordered ? words : a.slot_words);
+    }
+    if ((uint64_t)off + words > a.cap_words) {
+        if (part == 0u && lane == 0) raise_error(sc, QGX_EBIT_CAPACITY);
+    } else {
+        uint4* __restrict__ dst = reinterpret_cast<uint4*>(a.payload + (size_t)k * a.cap_words + off);
+        const uint4* src = reinterpret_cast<const uint4*>(stage);
+        for (uint32_t i = part * kWave + (uint32_t)lane; i < (words >> 2); i += 4u * kWave) dst[i] = src[i];
+    }
+}
+
 static size_t encode_lds_bytes(int waves, const EncodeArgs& a, bool with_stage, bool grouped)
 {
     size_t n = (size_t)a.pieces * sizeof(uint4) + (grouped ? (size_t)waves * 64 : 0) +
@@ -878,9 +1304,31 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
     return hipGetLastError();
 }
 
+template <bool GROUPED, int CM>
+static hipError_t launch_columns(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
+{
+    EncodeArgs b = a;
+    const bool ordered = a.slot_words == 0u;
+    // (where units are ticketed these are those of k_encode: a context's launches share the counters)
+    b.group = 1u;
+    const uint32_t chunks = GROUPED ? (ordered ? 4u : 1u) : std::min(lay.waves_per_bucket, lay.NC);
+    b.units = GROUPED ? (lay.NC + chunks - 1u) / chunks : lay.NB;
+    b.spread = ordered && spread_workers(lay.K, b.units) ? 1u : 0u;
+    const size_t lds = ColumnLds(a.pieces, chunks, GROUPED).stage + (size_t)chunks * a.stage_bytes;
+    static LdsLimit limit;
+    const hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_encode_columns<GROUPED, CM>), 160 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_encode_columns<GROUPED, CM>), dim3(lay.K * b.units), dim3(chunks * 4u * kWave), lds, st, lay, tab, sc, b);
+    return hipGetLastError();
+}
+
 template <EncMode MODE, int CM>
 static hipError_t launch_size(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
 {
+    if constexpr (MODE == EncMode::Fused) {
+        if (a.parts == 1u && use_columns((uint64_t)lay.K * lay.NC, std::min(lay.waves_per_bucket, lay.NC), lay.shared_chunks != 0u, a.slot_words == 0u, 4u * a.n_cu))
+            return lay.shared_chunks ? launch_columns<true, CM>(lay, tab, sc, a, st) : launch_columns<false, CM>(lay, tab, sc, a, st);
+    }
     if (lay.shared_chunks) return launch_mode<MODE, true, CM>(lay, tab, sc, a, st);
     if constexpr (MODE == EncMode::Fused) {
         if (use_staged((uint64_t)lay.K * lay.NC, 4u * a.n_cu)) return launch_mode<MODE, false, CM, true>(lay, tab, sc, a, st);

@@ -115,6 +115,20 @@ QGX_PLAN uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t wa
 // 40.5; L-infinity norm 24.9 / 24.2 and 41.8 / 41.0, q = 3 59.5 / 58.6 and 116 / 114.
 inline bool use_staged(uint64_t chunks_of_all, uint32_t n_simd) { return chunks_of_all <= 8u * (uint64_t)n_simd; }
 
+// The coding kernel's form with four waves to a chunk, `per_bucket` chunks to a workgroup where buckets do not share chunks: as long as the
+// waves find places, and no more than eight of them on one compute unit while others are empty.  A wave per chunk / four,
+// us, kernel alone, 8 workers and 17 levels if not said otherwise.  In slots, shared chunks (buckets of 1024): 512 chunks 13.3 / 8.1,
+// 1024 14.4 / 11.1, 2048 19.8 / 18.7, 4096 31.6 / 29.6, 8192 49.2 / 51.7; of 256: 4096 39.2 / 36.9, 8192 63.6 / 66.3.  One or
+// two chunks to a bucket: buckets of 8192, 512 10.0 / 8.2, 1024 13.5 / 11.9, 1280 15.0 / 14.8, 2048 17.4 / 19.2; of 6000, 816 11.6 / 9.6,
+// 1408 12.8 / 13.5.  Four: 256 10.0 / 10.6, 1024 11.8 / 12.7, but one of a vector of 1024 coordinates 5.7 / 5.1.  In order, shared
+// chunks, four to a workgroup: 256 15.4 / 12.2, 1024 18.5 / 14.6, 1280 20.8 / 25.0, 2048 22.8 / 27.6; one or two to a bucket: 16 11.0 / 9.0,
+// 128 11.1 / 9.4, from 256 on a workgroup has four: 13.0 / 13.6.
+inline bool use_columns(uint64_t chunks_of_all, uint32_t per_bucket, bool shared, bool ordered, uint32_t n_simd)
+{
+    if (shared) return chunks_of_all <= (ordered ? 1u : 4u) * (uint64_t)n_simd;
+    return per_bucket <= 2u && (ordered ? chunks_of_all < 256u : chunks_of_all <= n_simd);
+}
+
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
 // x = f * tasks against the wave slots (8 per SIMD with one stream, 4 with two).  A launch is bound by latency,
 // ceil(K / f) workers one after the other (a worker's chain of look-ups takes 2.2 us with one stream, 3.3 with two, however

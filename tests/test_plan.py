@@ -31,6 +31,7 @@ extern "C" int spread_workers(uint32_t K, uint32_t units) { return qgx::spread_w
 extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int ordered) { return qgx::buckets_per_group(waves, chunks, ordered != 0); }
 extern "C" uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t waves, uint32_t NB) { return qgx::waves_with_a_bucket(unit, group, waves, NB); }
 extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_staged(chunks, n_simd); }
+extern "C" int use_columns(uint64_t chunks, uint32_t per_bucket, int shared, int ordered, uint32_t n_simd) { return qgx::use_columns(chunks, per_bucket, shared != 0, ordered != 0, n_simd); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
 
@@ -168,3 +169,18 @@ def test_waves_without_a_bucket_are_a_workers_last(plan):
         for unit in range((NB + group - 1) // group):
             want = sum(unit * group + w // waves < NB for w in range(4))
             assert plan.waves_with_a_bucket(unit, group, waves, NB) == want, (waves, NB, unit)
+
+
+def test_four_waves_to_a_chunk_fit_a_workgroup(plan):
+    """Whatever the rule sends to that form has at most two chunks to a workgroup (four where shared chunks keep an order), and where
+    it keeps an order its units are those of the other form, a bucket each: tickets of both come from one counter."""
+    plan.use_columns.argtypes = [C.c_uint64, C.c_uint32, C.c_int, C.c_int, C.c_uint32]
+    plan.buckets_per_group.argtypes = [C.c_uint32, C.c_uint64, C.c_int]
+    for chunks in (1, 15, 255, 256, 257, 1023, 1024, 1025, 4096, 4097, 1 << 20):
+        for per_bucket in range(1, 17):
+            for ordered in (0, 1):
+                if plan.use_columns(chunks, per_bucket, 0, ordered, 1024):
+                    assert per_bucket <= 2 and chunks <= 1024
+                    assert not ordered or plan.buckets_per_group(per_bucket, chunks, 1) == 1
+        assert plan.use_columns(chunks, 1, 1, 1, 1024) == (chunks <= 1024)
+        assert plan.use_columns(chunks, 1, 1, 0, 1024) == (chunks <= 4096)
