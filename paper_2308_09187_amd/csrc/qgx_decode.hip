@@ -266,15 +266,30 @@ __device__ __forceinline__ void chunk_geometry(const Layout& lay, uint32_t c, ui
     }
 }
 
-// S, gamma_{t+1}, t at the end of the second half-step.
-__device__ __forceinline__ void finish_scalars(Scalars* sc, double sum, uint32_t K)
+// S, gamma_{t+1}, t at the end of the second half-step, from S; what the update multiplies by comes back.
+__device__ __forceinline__ float step_size(double S, uint32_t K) { return (float)((double)K / sqrt(1.0 + S)); }      // Theorem 3: gamma_t = K (1 + sum ...)^(-1/2)
+
+__device__ __forceinline__ void finish_scalars(Scalars* sc, double S, uint32_t K)
 {
-    const double S = sum + sc->S;
-    const double gamma = (double)K / sqrt(1.0 + S);           // Theorem 3: gamma_t = K (1 + sum ...)^(-1/2)
     sc->S = S;
-    sc->gamma = gamma;
-    sc->gamma_f = (float)gamma;
+    sc->gamma = (double)K / sqrt(1.0 + S);
+    sc->gamma_f = step_size(S, K);
     sc->t += 1ull;
+}
+
+// X_{t+1} = X_1 + gamma Y by threads `at` of `step`: four coordinates at a time (X, Y and the anchor are 16-byte aligned), the last
+// d mod 4 by the first threads.
+__device__ __forceinline__ void x_from_y(float gam, uint32_t d, const float* Y, const float* anchor, float* X, uint32_t at, uint32_t step)
+{
+    const uint32_t quads = d / 4u;
+    for (uint32_t q = at; q < quads; q += step) {
+        const float4 y = reinterpret_cast<const float4*>(Y)[q];
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (anchor) x = reinterpret_cast<const float4*>(anchor)[q];
+        x.x += gam * y.x; x.y += gam * y.y; x.z += gam * y.z; x.w += gam * y.w;
+        reinterpret_cast<float4*>(X)[q] = x;
+    }
+    if (at < (d & 3u)) X[4u * quads + at] = (anchor ? anchor[4u * quads + at] : 0.0f) + gam * Y[4u * quads + at];
 }
 
 template <bool B> struct BoolTag { static constexpr bool value = B; };
@@ -401,7 +416,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     for (uint32_t q = (uint32_t)lane; q < kBufs * stage_stride; q += kWave) stage[q] = 0;
     __syncthreads();
     if constexpr (KSPLIT == 1) {
-        if (!mine && (MODE != DecMode::Half1 || a.arrived == nullptr)) return;
+        if (!mine && MODE != DecMode::Half1) return;
     }                                                    // (else: the waves meet at workgroup barriers below)
 
     // From bit t of the staged words to the buffer bit r with the bit before t on top of the 64 bits
@@ -644,7 +659,6 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     if constexpr (MODE == DecMode::Half1) {
         sdiff = wave_sum(sdiff);
         if (lane == 0) s_sd[w] = mine ? sdiff : 0.0;      // joined below, after a barrier
-        if (KSPLIT == 1 && mine && lane == 0 && a.arrived == nullptr) a.s_partial[task] = sdiff;
     }
     // KSPLIT: all waves of the group put their sums there, and after a barrier each of them adds them
     // up (in the order of the workers' runs) for its share of the rows and does the update for those.
@@ -671,11 +685,6 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
         wave_lds_fence();                                     // the rows are read by other lanes than wrote them
         if constexpr (KSPLIT > 1) {
             __syncthreads();
-            if (MODE == DecMode::Half1 && q == 0 && mine && part == 0 && lane == 0 && a.arrived == nullptr) {
-                double sd = s_sd[w];
-                for (int j = 1; j < KSPLIT; ++j) sd += s_sd[w + j];
-                a.s_partial[task] = sd;
-            }
         }
         if (mine && full) {
 #pragma unroll
@@ -745,26 +754,31 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
-    // The scalar end in this launch, where it has no more workgroups than a wave has lanes (a.arrived): each leaves its sum and
-    // counts itself (release), and the last one to arrive (acquire) adds up the sums.
+    // The workgroup's sum of S, and as much of the scalar end as the launch has been given (Half1End).
     if constexpr (MODE == DecMode::Half1) {
-        if (a.arrived != nullptr) {
-            __syncthreads();
-            if (w == 0) {
-                uint32_t before = 0;
+        const double S_before = sc->S;
+        __syncthreads();
+        double own = 0.0;
+        for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
+        if (a.end == kEndAll) {                               // one workgroup: Y is its own work
+            const double S = own + S_before;
+            if (tid == 0) finish_scalars(sc, S, lay.K);
+            x_from_y(step_size(S, lay.K), lay.d, a.Y, a.anchor, a.x_out, (uint32_t)tid, blockDim.x);
+        } else if (a.end == kEndSums) {
+            if (tid == 0) a.s_partial[blockIdx.x] = own;
+        } else if (w == 0) {
+            // each leaves its sum and counts itself (release), and the last one to arrive (acquire) adds up the sums
+            uint32_t before = 0;
+            if (lane == 0) {
+                __hip_atomic_store(&a.s_partial[blockIdx.x], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                before = __hip_atomic_fetch_add(&sc->arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u == gridDim.x) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                const double sum = wave_sum((uint32_t)lane < gridDim.x ? __hip_atomic_load(&a.s_partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0);
                 if (lane == 0) {
-                    double own = 0.0;
-                    for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
-                    __hip_atomic_store(&a.s_partial[blockIdx.x], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    before = __hip_atomic_fetch_add(a.arrived, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u == gridDim.x) {
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                    const double sum = wave_sum((uint32_t)lane < gridDim.x ? __hip_atomic_load(&a.s_partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0);
-                    if (lane == 0) {
-                        finish_scalars(sc, sum, lay.K);
-                        __hip_atomic_store(a.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
+                    finish_scalars(sc, sum + sc->S, lay.K);
+                    __hip_atomic_store(&sc->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }
@@ -773,7 +787,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
 }
 
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, bool* finished)
+static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, Half1End* left)
 {
     const uint64_t nwaves = MODE == DecMode::Decode ? (uint64_t)lay.n_tasks * ((lay.K + 1u) / 2u) : (uint64_t)lay.n_tasks * (uint32_t)KSPLIT;
     // Workgroups of four waves spread over the compute units and are replaced as soon as four waves are done, but
@@ -792,10 +806,11 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     // The scalar end in the same launch, as long as a wave has a lane for each workgroup.  Second half-step of 8 workers, us, in a
     // launch of its own / in this one: 2 workgroups 15.8 / 14.5, 16 16.2 / 15.2, 64 16.4 / 15.6; with lanes that add up several sums
     // 65 18.2 / 17.6, 128 16.9 / 17.9, 256 17.6 / 22.2.  (A release and an acquire around the count cost nothing beside relaxed accesses.)
+    // One workgroup, whose coordinates are all its own, writes X_{t+1} as well: an iteration of one bucket 30.9 us, now 28.0.
     const uint64_t grid = (nwaves + per - 1u) / per;
     DecodeArgs b = a;
-    b.arrived = MODE == DecMode::Half1 && grid <= kWave ? &sc->arrived : nullptr;
-    if (finished) *finished = b.arrived != nullptr;
+    b.end = grid == 1u && a.x_out ? kEndAll : grid <= kWave ? kEndScalars : kEndSums;
+    if (left) *left = Half1End{(uint32_t)grid, b.end};
     const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
@@ -806,82 +821,71 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
 }
 
 template <DecMode MODE, bool PREV, bool TWO = false>
-static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, bool* finished)
+static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, Half1End* left)
 {
     if constexpr (MODE != DecMode::Decode) {
         if (a.ksplit == 2u) {
-            if (a.wide) return launch_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st, finished);
-            return launch_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st, finished);
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 2>(lay, tab, sc, a, st, left);
+            return launch_as<MODE, PREV, TWO, false, 2>(lay, tab, sc, a, st, left);
         }
         if (a.ksplit == 4u) {
-            if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st, finished);
-            return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st, finished);
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st, left);
+            return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st, left);
         }
     }
-    if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st, finished);
-    return launch_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st, finished);
+    if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st, left);
+    return launch_as<MODE, PREV, TWO, false, 1>(lay, tab, sc, a, st, left);
 }
 
 hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a,
-                         hipStream_t st, bool* finished)
+                         hipStream_t st, Half1End* left)
 {
     switch (mode) {
-        case DecMode::Decode: return launch_mode<DecMode::Decode, false>(lay, tab, sc, a, st, finished);
-        case DecMode::Average: return launch_mode<DecMode::Average, false>(lay, tab, sc, a, st, finished);
-        case DecMode::Half0: return launch_mode<DecMode::Half0, false>(lay, tab, sc, a, st, finished);
+        case DecMode::Decode: return launch_mode<DecMode::Decode, false>(lay, tab, sc, a, st, left);
+        case DecMode::Average: return launch_mode<DecMode::Average, false>(lay, tab, sc, a, st, left);
+        case DecMode::Half0: return launch_mode<DecMode::Half0, false>(lay, tab, sc, a, st, left);
         default:
-            if (a.payload_p == nullptr) return launch_mode<DecMode::Half1, false>(lay, tab, sc, a, st, finished);
-            return a.tab_p ? launch_mode<DecMode::Half1, true, true>(lay, tab, sc, a, st, finished)
-                           : launch_mode<DecMode::Half1, true>(lay, tab, sc, a, st, finished);
+            if (a.payload_p == nullptr) return launch_mode<DecMode::Half1, false>(lay, tab, sc, a, st, left);
+            return a.tab_p ? launch_mode<DecMode::Half1, true, true>(lay, tab, sc, a, st, left)
+                           : launch_mode<DecMode::Half1, true>(lay, tab, sc, a, st, left);
     }
 }
 
-// ---- the scalar end of the second half-step: S, gamma_{t+1}, t; then X_{t+1} on request -----------
+// ---- the scalar end of the second half-step: S, gamma_{t+1}, t; and X_{t+1} on request -----------
 constexpr uint32_t kFinishThreads = 1024;
-__global__ __launch_bounds__(kFinishThreads) void k_finish_half1(uint32_t n_tasks, uint32_t K, Scalars* sc,
-                                                                  const double* __restrict__ s_partial)
+__global__ __launch_bounds__(kFinishThreads) void k_finish_half1(uint32_t n_sums, uint32_t K, Scalars* sc, const double* __restrict__ sums)
 {
     __shared__ double s_red[kFinishThreads / kWave];
     double acc = 0.0;
 #pragma unroll 4
-    for (uint32_t i = threadIdx.x; i < n_tasks; i += kFinishThreads) acc += s_partial[i];     // fixed order: reproducible
+    for (uint32_t i = threadIdx.x; i < n_sums; i += kFinishThreads) acc += sums[i];     // fixed order: reproducible
     acc = wave_sum(acc);
     if (lane_id() == 0) s_red[wave_id()] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double S = 0.0;
         for (uint32_t w = 0; w < kFinishThreads / kWave; ++w) S += s_red[w];
-        finish_scalars(sc, S, K);
+        finish_scalars(sc, S + sc->S, K);
     }
 }
 
-// Four coordinates at a time (X, Y and the anchor are 16-byte aligned), the last d mod 4 by the first threads.
 __global__ __launch_bounds__(256) void k_x_from_y(uint32_t d, const Scalars* sc, const float* __restrict__ Y,
                                                   const float* __restrict__ anchor, float* __restrict__ X)
 {
-    const float gam = sc->gamma_f;
-    const uint32_t quads = d / 4u, at = blockIdx.x * 256u + threadIdx.x;
-    for (uint32_t q = at; q < quads; q += gridDim.x * 256u) {
-        const float4 y = reinterpret_cast<const float4*>(Y)[q];
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (anchor) x = reinterpret_cast<const float4*>(anchor)[q];
-        x.x += gam * y.x; x.y += gam * y.y; x.z += gam * y.z; x.w += gam * y.w;
-        reinterpret_cast<float4*>(X)[q] = x;
-    }
-    if (at < (d & 3u)) X[4u * quads + at] = (anchor ? anchor[4u * quads + at] : 0.0f) + gam * Y[4u * quads + at];
+    x_from_y(sc->gamma_f, d, Y, anchor, X, blockIdx.x * 256u + threadIdx.x, gridDim.x * 256u);
 }
 
-// Two launches, or the second only (`finished`: the half-step has left the scalars already).  One, with the sum done by every workgroup and the scalars put down by the last to arrive, was no
-// faster: iterations of 5 x 3 M 140.8 us (136.8 with two), of 8 x 9.86 M 389.9 (389.5).
+// Two launches, the second only, or none, by what the half-step has left.  (In one launch, each workgroup of the second adding up the
+// sums, one of the half-step's workgroups each, by itself: no faster, iterations of 5 x 3 M 115.6 us, 115.7 with two, of 8 x 9.86 M 328.7 and 328.4.)
 hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_partial, const float* Y,
-                               const float* anchor, float* X_out, bool finished, hipStream_t st)
+                               const float* anchor, float* X_out, const Half1End& left, hipStream_t st)
 {
     hipError_t e = hipSuccess;
-    if (!finished) {
-        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, lay.n_tasks, lay.K, sc, s_partial);
+    if (left.end == kEndSums) {
+        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, left.sums, lay.K, sc, s_partial);
         e = hipGetLastError();
     }
-    if (e != hipSuccess || X_out == nullptr) return e;
+    if (e != hipSuccess || X_out == nullptr || left.end == kEndAll) return e;
     const uint32_t grid = min(lay.d / 1024u + 1u, 16384u);
     hipLaunchKernelGGL(k_x_from_y, dim3(grid), dim3(256), 0, st, lay.d, sc, Y, anchor, X_out);
     return hipGetLastError();

@@ -176,8 +176,9 @@ struct DecodeArgs {
     float* out;                 // Decode: Vhat [K][d]; Average: mean [d]; Half0: X_{t+1/2} [d]
     float* Y;                   // [d] dual state (Half0 reads, Half1 updates)
     const float* anchor;        // [d] or null
-    double* s_partial;          // [n_tasks] per-task partial of S (Half1), or per workgroup with `arrived`
-    unsigned int* arrived;      // filled in by the launch: where workgroups count themselves, or null
+    double* s_partial;          // a partial sum of S per workgroup (Half1; no more of them than tasks)
+    float* x_out;               // [d] or null: X_{t+1}, for a Half1 of one workgroup to write as well
+    uint32_t end;               // filled in by the launch: how much of the scalar end a Half1 does (Half1End)
     double* x_sum;              // [d] running sum of the X_{t+1/2} or null (Half0 adds its output)
     uint32_t stage_words;       // most words half a chunk of the code in use touches (multiple of 4)
     uint32_t stage_stride;      // words of one LDS staging buffer (padded layout plus slack)
@@ -210,13 +211,17 @@ struct LdsLimit {
     }
 };
 
+// What the second half-step has left: `sums` partial sums of S; S, gamma and t already (kEndScalars); X_{t+1} as well (kEndAll).
+constexpr uint32_t kEndSums = 0, kEndScalars = 1, kEndAll = 2;
+struct Half1End { uint32_t sums = 0, end = kEndSums; };
+
 hipError_t launch_build_tables(Tables* tab, hipStream_t st);
 hipError_t launch_encode(EncMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a,
                          hipStream_t st);
 hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a,
-                         hipStream_t st, bool* finished = nullptr);      // finished: whether Half1 has left S, gamma and t, too
+                         hipStream_t st, Half1End* left = nullptr);
 hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_partial, const float* Y,
-                               const float* anchor, float* X_out, bool finished, hipStream_t st);
+                               const float* anchor, float* X_out, const Half1End& left, hipStream_t st);
 hipError_t launch_state_init(const Layout& lay, Scalars* sc, float* Y, float* anchor, const float* X1,
                              hipStream_t st);
 hipError_t launch_average(uint32_t d, const double* x_sum, const Scalars* sc, float* out, hipStream_t st);

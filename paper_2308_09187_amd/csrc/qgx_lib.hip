@@ -757,9 +757,10 @@ static qgx_status eg_step_with(qgx_ctx* ctx, int half, const qgx_stream* cur, co
     }
     fill_decode_args(ctx, a, cur, prev);
     a.s_partial = s_partial;
-    bool finished = false;
-    QGX_HIP(ctx, launch_decode(DecMode::Half1, ctx->lay, tab_of(ctx), ctx->d_sc, a, st, &finished));
-    QGX_HIP(ctx, launch_finish_half1(ctx->lay, ctx->d_sc, s_partial, ctx->d_Y, a.anchor, X_out, finished, st));
+    a.x_out = X_out;
+    Half1End left;
+    QGX_HIP(ctx, launch_decode(DecMode::Half1, ctx->lay, tab_of(ctx), ctx->d_sc, a, st, &left));
+    QGX_HIP(ctx, launch_finish_half1(ctx->lay, ctx->d_sc, s_partial, ctx->d_Y, a.anchor, X_out, left, st));
     return QGX_OK;
 }
 
