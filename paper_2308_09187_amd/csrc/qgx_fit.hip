@@ -268,7 +268,7 @@ constexpr uint32_t kRedSegs = 16;
 
 __global__ __launch_bounds__(kRedBins * kRedSegs) void k_hist_reduce(uint32_t n_bins, uint32_t n_partial,
                                                                      const double* __restrict__ partial,
-                                                                     double* __restrict__ hist)
+                                                                     double* __restrict__ hist, double* __restrict__ copy)
 {
     __shared__ double s_run[kRedSegs][kRedBins];
     const uint32_t bl = threadIdx.x & (kRedBins - 1u), seg = threadIdx.x / kRedBins;
@@ -291,6 +291,7 @@ __global__ __launch_bounds__(kRedBins * kRedSegs) void k_hist_reduce(uint32_t n_
         double tot = 0.0;
         for (uint32_t q = 0; q < kRedSegs; ++q) tot += s_run[q][bl];
         hist[i] = tot;
+        if (copy) copy[i] = tot;
     }
 }
 
@@ -304,7 +305,7 @@ uint32_t histogram_groups(const Layout& lay)
 }
 
 hipError_t launch_histogram(const Layout& lay, const float* V, int norm_kind, uint32_t n_bins, double* partial,
-                            uint32_t n_partial, double* hist, Scalars* sc, hipStream_t st)
+                            uint32_t n_partial, double* hist, double* copy, Scalars* sc, hipStream_t st)
 {
     if (lay.shared_chunks) {                              // buckets of 256 << s coordinates, s = 0..3
         const size_t lds = (size_t)n_bins * (sizeof(double) + 4 * sizeof(uint16_t));
@@ -326,7 +327,7 @@ hipError_t launch_histogram(const Layout& lay, const float* V, int norm_kind, ui
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_hist_reduce, dim3((n_bins + kRedBins - 1u) / kRedBins), dim3(kRedBins * kRedSegs), 0, st, n_bins, n_partial,
-                       partial, hist);
+                       partial, hist, copy);
     return hipGetLastError();
 }
 

@@ -229,7 +229,7 @@ hipError_t launch_average_reset(uint32_t d, double* x_sum, Scalars* sc, hipStrea
 hipError_t launch_state_set(Scalars* sc, double S, unsigned long long t, uint32_t K, hipStream_t st);
 hipError_t launch_sum_bits(const Layout& lay, const uint16_t* sub_end, Scalars* sc, hipStream_t st);
 hipError_t launch_histogram(const Layout& lay, const float* V, int norm_kind, uint32_t n_bins, double* partial,
-                            uint32_t n_partial, double* hist, Scalars* sc, hipStream_t st);
+                            uint32_t n_partial, double* hist, double* copy, Scalars* sc, hipStream_t st);
 hipError_t launch_compact(const Layout& lay, const uint16_t* sub_end, const uint32_t* in_off, const uint32_t* in_payload,
                           uint64_t in_cap, uint32_t* out_off, uint32_t* out_payload, uint64_t out_cap, Scalars* sc,
                           hipStream_t st);

@@ -73,7 +73,8 @@ struct qgx_ctx {
     double* d_static_scratch = nullptr;   // this device's copy of the file-scope scratch array (not owned)
     double* d_hpartial = nullptr;
     double* d_hist = nullptr;
-    FitCodeResult* d_prob = nullptr;   // what the last qgx_fit_code left for the host
+    FitCodeResult* h_fit = nullptr;    // what the last qgx_fit_code left for the host: pinned memory, which the kernel writes (QGX_CODE_TABLE)
+    FitCodeResult* d_fit = nullptr;    // the same as the device sees it
     double* d_norm = nullptr;       // [2 kNormBlocks + 2] partial sums and results of qgx_norm2 and qgx_game_gap
     double* d_metrics = nullptr;    // [K][3][kMetricBlocks] partial sums, then [K][3] results of qgx_quantization_metrics
     double* d_xsum = nullptr;       // [d] sum of the X_{t+1/2} since qgx_average_reset (allocated there)
@@ -145,6 +146,15 @@ bool wide_table_ok(const uint32_t* packed, uint32_t n_sym)
     return true;
 }
 
+// A kernel on the context's device may write doubles there.
+bool writable_here(const qgx_ctx* ctx, const double* p)
+{
+    hipPointerAttribute_t at{};
+    if ((reinterpret_cast<uintptr_t>(p) & 7u) != 0) return false;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return at.type == hipMemoryTypeDevice && at.device == ctx->device;
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 qgx_status check_stream(qgx_ctx* ctx, const qgx_stream* s, const char* what)
@@ -187,8 +197,9 @@ qgx_status need_levels(qgx_ctx* ctx) { return need_levels(ctx, ctx->sel); }
 
 void free_all(qgx_ctx* c)
 {
-    void* all[] = {c->d_layout, c->d_tabs, c->d_sc, c->d_Y, c->d_anchor, c->d_scan, c->d_xch, c->d_tickets, c->d_spartial, c->d_hpartial, c->d_hist, c->d_prob, c->d_norm, c->d_metrics, c->d_xsum};
+    void* all[] = {c->d_layout, c->d_tabs, c->d_sc, c->d_Y, c->d_anchor, c->d_scan, c->d_xch, c->d_tickets, c->d_spartial, c->d_hpartial, c->d_hist, c->d_norm, c->d_metrics, c->d_xsum};
     for (void* p : all) (void)hipFree(p);
+    if (c->h_fit) (void)hipHostFree(c->h_fit);
 }
 
 }  // namespace
@@ -311,7 +322,10 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     ok = ok && hipMalloc(&c->d_spartial, (size_t)c->lay.n_tasks * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hpartial, (size_t)c->h_groups * QGX_MAX_BINS * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_hist, QGX_MAX_BINS * sizeof(double)) == hipSuccess;
-    ok = ok && hipMalloc(&c->d_prob, sizeof(FitCodeResult)) == hipSuccess;
+    if (cfg->code == QGX_CODE_TABLE) {                     // (50 us, which a context without a fitted code is spared)
+        ok = ok && hipHostMalloc(reinterpret_cast<void**>(&c->h_fit), sizeof(FitCodeResult), hipHostMallocMapped) == hipSuccess;
+        ok = ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&c->d_fit), c->h_fit, 0) == hipSuccess;
+    }
     ok = ok && hipMalloc(&c->d_norm, (2 * kNormBlocks + 2) * sizeof(double)) == hipSuccess;
     ok = ok && hipMalloc(&c->d_metrics, (size_t)cfg->K * 3 * (kMetricBlocks + 1) * sizeof(double)) == hipSuccess;
     ok = ok && hipMemcpy(c->d_layout, flat.data(), n_lay * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess;
@@ -685,9 +699,11 @@ qgx_status qgx_fit_levels(qgx_ctx* ctx, const float* V, uint32_t n_sym, uint32_t
     if (n_bins == 0 || (n_bins & 63u) || n_bins > QGX_MAX_BINS)
         return fail(ctx, QGX_ERR_ARG, "qgx_fit_levels: n_bins must be a multiple of 64, at most 4096");
     hipStream_t st = (hipStream_t)stream;
+    // The caller's histogram is written by the kernel that has it; through a copy where it is no memory of this device's.
+    const bool direct = hist_out && writable_here(ctx, hist_out);
     QGX_HIP(ctx, launch_histogram(ctx->lay, V, ctx->cfg.norm, n_bins, ctx->d_hpartial, ctx->h_groups, ctx->d_hist,
-                                  ctx->d_sc, st));
-    if (hist_out)
+                                  direct ? hist_out : nullptr, ctx->d_sc, st));
+    if (hist_out && !direct)
         QGX_HIP(ctx, hipMemcpyAsync(hist_out, ctx->d_hist, n_bins * sizeof(double), hipMemcpyDeviceToDevice, st));
     QGX_HIP(ctx, launch_fit(tab_of(ctx), ctx->d_hist, n_bins, sweeps, st));
     ctx->hist_bins = n_bins;
@@ -704,10 +720,10 @@ qgx_status qgx_fit_code(qgx_ctx* ctx, double* p_host, uint8_t* code_len_host, ui
     while ((1u << need) < T(ctx).n_sym) ++need;
     if (need > QGX_FIT_CODE_BITS) return fail(ctx, QGX_ERR_ARG, "too many symbols for the longest code word");
     hipStream_t st = (hipStream_t)stream;
-    QGX_HIP(ctx, launch_fit_code(tab_of(ctx), ctx->d_hist, ctx->hist_bins, QGX_FIT_CODE_BITS, ctx->d_prob, st));
-    FitCodeResult host;                                   // probabilities and code words in one copy
-    QGX_HIP(ctx, hipMemcpyAsync(&host, ctx->d_prob, sizeof(host), hipMemcpyDeviceToHost, st));
+    // (a copy of the result took 4 us of the stream and the host's staging of it: an update step of 8 x 2^20 208.6 us, now 183.0, of which the copy of the histogram 4)
+    QGX_HIP(ctx, launch_fit_code(tab_of(ctx), ctx->d_hist, ctx->hist_bins, QGX_FIT_CODE_BITS, ctx->d_fit, st));
     QGX_HIP(ctx, hipStreamSynchronize(st));
+    const FitCodeResult& host = *ctx->h_fit;
     const uint32_t* packed = host.code;
     if (p_host) std::memcpy(p_host, host.p, T(ctx).n_sym * sizeof(double));
     T(ctx).max_code_len = 0;

@@ -68,3 +68,28 @@ def test_level_where_the_mass_ends(qgx, seed):
     np.testing.assert_allclose(ctx.get_levels(), oracle.fit_levels(want, start, sweeps=1), rtol=1e-6, atol=1e-9)
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("n_bins", [64, 192, 4096])
+def test_where_the_histogram_goes(qgx, n_bins):
+    """The caller's buffer: device memory, device memory at an odd word, pinned host memory, none; all the same values, and a buffer's end
+    stays as it was."""
+    d, K = 70001, 3
+    V = dev(synth.student_t3(K, d, seed=4))
+    ctx, _ = make_ctx(qgx, d, K, 4096, oracle.NORM_L2, synth.levels_exponential(8), seed=1)
+    room = torch.full((2 * (n_bins + 4),), -1.0, dtype=torch.float32, device="cuda")
+    buffers = [torch.full((n_bins + 2,), -1.0, dtype=torch.float64, device="cuda"), room[1:],
+               torch.full((n_bins + 2,), -1.0, dtype=torch.float64, pin_memory=True), None]
+    got = []
+    for b in buffers:
+        ctx.fit_levels(V, 9, n_bins, sweeps=0, hist_out=b)
+        torch.cuda.synchronize()
+        if b is not None:
+            h = b.cpu().numpy()
+            got.append(h[: 2 * n_bins].copy().view(np.float64) if h.dtype == np.float32 else h[:n_bins])
+            assert (h[2 * n_bins:] == -1.0).all() if h.dtype == np.float32 else (h[n_bins:] == -1.0).all()
+    assert got[0].sum() > 0
+    for h in got[1:]:
+        np.testing.assert_array_equal(h, got[0])
+    assert ctx.poll_error() == 0
+    ctx.close()
