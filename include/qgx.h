@@ -195,7 +195,7 @@ qgx_status qgx_decode(qgx_ctx* ctx, const qgx_stream* in, float* Vhat, void* str
 
 /* Aggregate of Algorithm 1: mean DEVICE [d] = (1/K) sum_k DEQ(CODE_k), decoded on the fly.
  * The K values of a coordinate are added in binary32, in worker order; on layouts whose chunks fill
- * the GPU badly the workers are split in two or four runs (as equal as K allows, the
+ * the GPU badly the workers are split in two, four or eight runs (as equal as K allows, the
  * longer ones first), each added in order, and the runs' sums added in order (the same in
  * qgx_eg_step).  The number of runs follows from the layout, K and the device, so results repeat bit
  * for bit (qgx_debug_set_waves_per_position overrides the choice, for tests and timing). */

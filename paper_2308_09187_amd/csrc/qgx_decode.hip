@@ -301,18 +301,18 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // TWO: those were coded with another level table and code (a.tab_p) than the current ones.
 // WIDE: the first kWideBits bits of a code word always tell which one it is, so the 8-byte decode table
 // is there (of both codes, with TWO).
-// KSPLIT = 2 or 4: that many neighbouring waves share a task, each takes a run of the workers (as
+// KSPLIT = 2, 4 or 8: that many neighbouring waves share a task, each takes a run of the workers (as
 // equal as K allows, the longer runs first), and they add their sums through LDS before the update
 // (for layouts with too few tasks to fill the GPU's wave slots).
 // What bounds it: the parse, whose chains wait for their look-ups (with two streams vector ALUs busy for 73 % of the time, LDS
 // for 55 %), and at the largest sizes of one stream the memory path.
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
-__global__ __launch_bounds__((most_waves<MODE, PREV, TWO>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>()) ? 4 : 8)))
+__global__ __launch_bounds__((most_waves<MODE, PREV, TWO>()) * kWave) __attribute__((amdgpu_waves_per_eu((two_chains<MODE, PREV>() || KSPLIT == 8) ? 4 : 8)))
 void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArgs a)
 {
     static_assert(!PREV || MODE == DecMode::Half1, "only the second half-step reads two streams");
     static_assert(!TWO || PREV, "a second table only comes with a second stream");
-    static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "the waves of a workgroup in groups of 1, 2 or 4");
+    static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4 || KSPLIT == 8, "the waves of a workgroup in groups of 1, 2, 4 or 8");
     static_assert(KSPLIT == 1 || MODE != DecMode::Decode, "plain decoding has nothing to add up");
     extern __shared__ __align__(16) uint32_t s_dyn[];    // [waves][2][stage_stride]
     __shared__ double s_sd[KSPLIT > 1 || MODE == DecMode::Half1 ? most_waves<MODE, PREV, TWO>() : 1];
@@ -801,7 +801,7 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     };
     uint32_t per = (uint32_t)most_waves<MODE, PREV, TWO>();
     if (TWO && held(8) >= held(16)) per = 8;                 // (short codes: two of eight beside each other, 160 us to 164)
-    for (uint32_t small = 4; small < per; small *= 2)
+    for (uint32_t small = KSPLIT > 4 ? (uint32_t)KSPLIT : 4u; small < per; small *= 2)
         if (nwaves <= held(small) * a.n_cu) { per = small; break; }
     // The scalar end in the same launch, as long as a wave has a lane for each workgroup.  Second half-step of 8 workers, us, in a
     // launch of its own / in this one: 2 workgroups 15.8 / 14.5, 16 16.2 / 15.2, 64 16.4 / 15.6; with lanes that add up several sums
@@ -831,6 +831,10 @@ static hipError_t launch_mode(const Layout& lay, const Tables* tab, Scalars* sc,
         if (a.ksplit == 4u) {
             if (a.wide) return launch_as<MODE, PREV, TWO, true, 4>(lay, tab, sc, a, st, left);
             return launch_as<MODE, PREV, TWO, false, 4>(lay, tab, sc, a, st, left);
+        }
+        if (a.ksplit == 8u) {
+            if (a.wide) return launch_as<MODE, PREV, TWO, true, 8>(lay, tab, sc, a, st, left);
+            return launch_as<MODE, PREV, TWO, false, 8>(lay, tab, sc, a, st, left);
         }
     }
     if (a.wide) return launch_as<MODE, PREV, TWO, true, 1>(lay, tab, sc, a, st, left);

@@ -184,7 +184,7 @@ struct DecodeArgs {
     uint32_t stage_stride;      // words of one LDS staging buffer (padded layout plus slack)
     uint32_t sym_bits;          // most bits a symbol can take with the codes in use (longest word + sign)
     uint32_t wide;              // the 8-byte decode table of the current streams' code is valid (Tables::wide_ok)
-    uint32_t ksplit;            // fused modes: 1, 2 or 4 waves per task, a run of the workers each
+    uint32_t ksplit;            // fused modes: 1, 2, 4 or 8 waves per task, a run of the workers each
     uint32_t n_cu;              // compute units of the device
 };
 

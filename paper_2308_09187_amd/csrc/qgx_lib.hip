@@ -653,6 +653,7 @@ static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream
     if (a.stage_stride < 576u) a.stage_stride = 576u;     // a buffer also turns the output (16 rows of 36 floats)
     a.wide = (T(ctx).wide && (!prev || ctx->ts[ctx->sel_prev].wide)) ? 1u : 0u;   // one kernel variant reads both streams
     a.ksplit = waves_per_task(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u);
+    if (eight_waves(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u)) a.ksplit = 8;
     if (ctx->ksplit_forced >= 0 && (uint32_t)ctx->ksplit_forced <= ctx->lay.K) a.ksplit = (uint32_t)ctx->ksplit_forced;
     a.n_cu = ctx->n_simd / 4u;
     a.norms = cur->norms; a.chunk_off = cur->chunk_off; a.sub_end = cur->sub_end; a.payload = cur->payload;

@@ -154,4 +154,14 @@ inline uint32_t waves_per_task(uint32_t n_tasks, uint32_t workers, uint32_t n_si
     return best;
 }
 
+// Eight waves to a task instead, for eight workers and more: where even so a SIMD has no more than two or three of them, the workers
+// that a wave goes through one after the other are all that counts.  At four waves per SIMD also with one stream (at eight the join spilled 140
+// bytes a lane and took what it gave).  Four waves / eight, us: first half-step, 4 tasks of 8 workers 9.7 / 7.7, 128 11.8 / 8.6, 256 11.6 /
+// 9.0, 512 12.9 / 12.4, 768 14.1 / 19.0, of 12 256 12.5 / 11.2, 512 14.3 / 15.0, of 32 256 23.2 / 17.0, 512 26.5 / 22.2; second, 4 of 8
+// 12.4 / 10.6, 32 12.8 / 11.2, 256 12.2 / 11.6, 512 15.4 / 17.6, of 16 256 19.1 / 15.4, 512 24.1 / 25.8, of 32 32.0 / 23.6 and 40.2 / 42.6.
+inline bool eight_waves(uint32_t n_tasks, uint32_t workers, uint32_t n_simd, uint32_t streams)
+{
+    return workers >= 8u && n_tasks <= (streams == 2u ? n_simd / 4u : n_simd / 8u * 3u);
+}
+
 }  // namespace qgx

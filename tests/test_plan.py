@@ -32,6 +32,7 @@ extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int order
 extern "C" uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t waves, uint32_t NB) { return qgx::waves_with_a_bucket(unit, group, waves, NB); }
 extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_staged(chunks, n_simd); }
 extern "C" int use_columns(uint64_t chunks, uint32_t per_bucket, int shared, int ordered, uint32_t n_simd) { return qgx::use_columns(chunks, per_bucket, shared != 0, ordered != 0, n_simd); }
+extern "C" int eight_waves(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::eight_waves(n, K, simds, streams); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
 
@@ -184,3 +185,9 @@ def test_four_waves_to_a_chunk_fit_a_workgroup(plan):
                     assert not ordered or plan.buckets_per_group(per_bucket, chunks, 1) == 1
         assert plan.use_columns(chunks, 1, 1, 1, 1024) == (chunks <= 1024)
         assert plan.use_columns(chunks, 1, 1, 0, 1024) == (chunks <= 4096)
+
+
+def test_eight_waves_to_a_task_have_a_worker_each_and_a_place(plan):
+    for tasks, K, streams in itertools.product((1, 256, 257, 384, 385, (1 << 32) - 1), (1, 7, 8, 65535), (1, 2)):
+        got = plan.eight_waves(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(streams))
+        assert bool(got) == (K >= 8 and tasks <= (256 if streams == 2 else 384))
