@@ -860,13 +860,12 @@ void k_encode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, EncodeArg
 // four where they keep an order.
 constexpr int kSlots = kRows / 4;       // rows of a lane
 struct ColumnLds {                      // LDS after the tables, in bytes, for a workgroup of `chunks` chunks
-    uint32_t sums, again, misc, rinv, fine, counts, totals, stage, buckets;
+    uint32_t sums, misc, rinv, fine, counts, totals, stage, buckets;
     __host__ __device__ ColumnLds(uint32_t pieces, uint32_t chunks, bool grouped)
     {
         buckets = grouped ? 16u : 1u;                               // of a chunk
         sums = pieces * 16u;                                        // [chunks][buckets][64] double: a bucket's columns
-        again = sums + chunks * buckets * (uint32_t)kWave * 8u;     // [4 * chunks] double
-        misc = again + 4u * chunks * 8u;                            // 4 words
+        misc = sums + chunks * buckets * (uint32_t)kWave * 8u;      // 4 words
         rinv = misc + 16u;                                          // [chunks][16] float: 1 / norm of the buckets that share a chunk
         fine = rinv + (grouped ? chunks * 64u : 0u);                // [chunks][16] words: the straight route applies to them
         counts = fine + (grouped ? chunks * 64u : 0u);              // [chunks][64]: bits of row r's columns 16 q and on, at 4 r + q
@@ -897,7 +896,6 @@ __global__ __launch_bounds__(1024) void k_encode_columns(Layout lay, const Table
     const ColumnLds at(a.pieces, nchunks, GROUPED);
     uint4* s_enc = reinterpret_cast<uint4*>(s_all);
     double* s_sums = reinterpret_cast<double*>(s_all + at.sums);
-    double* s_again = reinterpret_cast<double*>(s_all + at.again);
     uint32_t* s_misc = reinterpret_cast<uint32_t*>(s_all + at.misc);
     float* s_rinv = reinterpret_cast<float*>(s_all + at.rinv) + cw * 16u;
     uint32_t* s_fine = reinterpret_cast<uint32_t*>(s_all + at.fine) + cw * 16u;
@@ -1078,39 +1076,45 @@ __global__ __launch_bounds__(1024) void k_encode_columns(Layout lay, const Table
         }
         __syncthreads();
     } else {
-        auto sum_again = [&](double acc) {             // (by all waves of the workgroup) the bucket's sum of acc
-            acc = wave_sum(acc);
-            if (lane == 0) s_again[w] = acc;
-            __syncthreads();
+        // The bucket's sum of term(v) over its coordinates, from memory, by all waves of the workgroup, in the order of k_encode (an order of
+        // its own would turn a norm between two binary32 numbers the other way): a lane of a chunk adds the coordinates 64 apart.  Each
+        // wave works out a quarter of them, and the quarters are added one after the other.
+        auto sum_again = [&](auto term) {
+            constexpr int kTerms = kChunk / 4 / kWave;
+            double x[kTerms], acc = 0.0;
+#pragma unroll
+            for (int j = 0; j < kTerms; ++j) {
+                const uint32_t i = g.clo + part * (kChunk / 4u) + (uint32_t)(j * kWave + lane);
+                x[j] = i < g.cend ? term(Vk[i]) : 0.0;
+            }
+            double* sums = s_sums + cw * (uint32_t)kWave + (uint32_t)lane;
+            __syncthreads();                           // (the columns' sums have been read)
+            for (uint32_t turn = 0; turn < 4u; ++turn) {
+                if (part == turn) {
+                    if (turn > 0u) acc = *sums;
+#pragma unroll
+                    for (int j = 0; j < kTerms; ++j) acc += x[j];
+                    *sums = acc;
+                }
+                __syncthreads();
+            }
             double t = 0.0;
-            for (uint32_t i = 0; i < 4u * nchunks; ++i) t += s_again[i];
+            for (uint32_t c = 0; c < nchunks; ++c) t += wave_sum(s_sums[c * (uint32_t)kWave + (uint32_t)lane]);
             return t;
         };
-        const uint32_t quarter_lo = min(g.clo + part * (kChunk / 4u), g.cend), quarter_hi = min(quarter_lo + kChunk / 4u, g.cend);
         double tot = 0.0;
         for (uint32_t c = 0; c < nchunks; ++c) {       // the bucket's chunks, in order
             const double x = column_total(c, 0u);
             if (l2) tot += x;
             else tot = (x > tot || x != x) ? x : tot;
         }
-        if (beyond(tot)) {                             // as in k_encode: the sum again in binary64
-            double acc = 0.0;
-#pragma unroll 1
-            for (uint32_t i = quarter_lo + (uint32_t)lane; i < quarter_hi; i += kWave) { const double x = (double)Vk[i]; acc = fma(x, x, acc); }
-            tot = sum_again(acc);
-        }
+        // as in k_encode: the sum again in binary64 (where a square is exact)
+        if (beyond(tot)) tot = sum_again([](float v) { return (double)v * (double)v; });
         n = l2 ? (float)sqrt(tot) : (float)tot;
-        if (!l2 && a.norm_kind != QGX_NORM_LINF) {
-            const bool sound = tot > 0.0 && tot <= 3.402823466e+38;
+        if (!l2 && a.norm_kind != QGX_NORM_LINF && tot > 0.0 && tot <= 3.402823466e+38) {
             const double inv_m = 1.0 / tot;
-            double acc = 0.0;
-            if (sound) {
-#pragma unroll 1
-                for (uint32_t i = quarter_lo + (uint32_t)lane; i < quarter_hi; i += kWave)
-                    acc += pow_int(fabs((double)Vk[i]) * inv_m, (uint32_t)a.norm_kind);
-            }
-            const double sum = sum_again(acc);
-            if (sound) n = (float)(tot * root_int(sum, (uint32_t)a.norm_kind));
+            const double sum = sum_again([&](float v) { return pow_int(fabs((double)v) * inv_m, (uint32_t)a.norm_kind); });
+            n = (float)(tot * root_int(sum, (uint32_t)a.norm_kind));
         }
         bool u_le_1 = true;
         if (a.norms_in) {

@@ -79,3 +79,29 @@ def test_table_sizes_and_given_norms(qgx, n_sym):
             for call in range(2):
                 for x, y in zip(a[call], b[call]):
                     np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("norm,scale", [(1, 1.0), (oracle.NORM_L2, 2.0 ** 60), (oracle.NORM_L2, 2.0 ** -40)])
+@pytest.mark.parametrize("bucket,d,first", [(4096, 4096, 0), (4096, 3000, 0), (8192, 8192, 0), (8192, 8192, 4096), (6000, 12000, 6000)])
+def test_norms_summed_from_memory_have_one_order(qgx, bucket, d, first, norm, scale):
+    """The sums that are formed from memory in binary64 (q norms; squares beyond binary32): terms below half a unit in the last place
+    of a sum that lies between two binary32 norms.  One at a time they are lost, added to each other first they turn the norm up."""
+    V = np.zeros((2, d), np.float32)
+    at = first + 64 * np.arange(4)                           # (all in the coordinates of one lane)
+    V[:, at] = [1.0, 2.0 ** -24, 0.0, 0.0] if norm == 1 else [1.0, 2.0 ** -12, 2.0 ** -12, 2.0 ** -24]
+    small = 2.0 ** -54 if norm == 1 else 2.0 ** -27
+    V[0, first + 1024 + 64 * np.arange(16)] = small
+    V[1, first + 1 + 64 * np.arange(16)] = 64 * small        # (in another lane: they count)
+    V *= np.float32(scale)
+    levels = synth.levels_exponential(16)
+    ctx, lay = make_ctx(qgx, d, 2, bucket, norm, levels, seed=77)
+    norms, sym = ctx.quantize(dev(V), 3)
+    want = norms.cpu().numpy()
+    b = first // bucket
+    np.testing.assert_array_equal(want[:, b], np.float32(scale) * np.float32([1.0, 1.0 + 2.0 ** -23]))
+    for slotted in (False, True):
+        s = ctx.new_stream(slotted=slotted)
+        ctx.quantize_encode(dev(V), 3, s)
+        np.testing.assert_array_equal(s.norms.cpu().numpy(), want)
+    assert ctx.poll_error() == 0
+    ctx.close()
