@@ -1330,7 +1330,7 @@ template <EncMode MODE, int CM>
 static hipError_t launch_size(const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a, hipStream_t st)
 {
     if constexpr (MODE == EncMode::Fused) {
-        if (a.parts == 1u && use_columns((uint64_t)lay.K * lay.NC, std::min(lay.waves_per_bucket, lay.NC), lay.shared_chunks != 0u, a.slot_words == 0u, 4u * a.n_cu))
+        if (a.columns)
             return lay.shared_chunks ? launch_columns<true, CM>(lay, tab, sc, a, st) : launch_columns<false, CM>(lay, tab, sc, a, st);
     }
     if (lay.shared_chunks) return launch_mode<MODE, true, CM>(lay, tab, sc, a, st);

@@ -149,6 +149,7 @@ struct EncodeArgs {
     uint32_t parts;             // workgroups per bucket: 1, or ceil(waves_per_bucket / 4) when that exceeds 4
     unsigned long long* tickets;   // [K] ever-increasing tickets, kTicketStride counters apart
     uint32_t n_cu;              // compute units of the device
+    uint32_t columns;           // Fused: the form with four waves to a chunk (use_columns, columns_pay)
     // filled in by the launch: which worker's which unit a block takes
     uint32_t units;             // workgroups per worker
     uint32_t group;             // whole buckets per workgroup

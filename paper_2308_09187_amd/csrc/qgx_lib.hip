@@ -49,12 +49,14 @@ struct TableState {
     uint32_t max_code_len = 0;      // longest code word of the code in use (without the sign bit)
     bool levels_set = false, code_set = false;
     bool wide = false;              // 11 bits identify every code word: the decoders may use the 8-byte table
+    bool crowded = false;           // levels too close for the encoder's cells, as far as the host knows (not of fitted ones)
 };
 
 struct qgx_ctx {
     qgx_config cfg{};
     std::vector<uint64_t> seg;
     int device = 0;
+    uint32_t rows = 0;               // of the longest bucket's last chunk, or with shared chunks of a bucket (columns_pay)
     uint32_t n_simd = 1024;          // SIMDs of the device (four per compute unit)
     int ksplit_forced = -1;          // qgx_debug_set_waves_per_position: 1, 2 or 4, else -1: by the rule
     Layout lay{};
@@ -295,6 +297,7 @@ qgx_status qgx_create(qgx_ctx** out, const qgx_config* cfg)
     uint32_t max_len = 0;
     for (uint32_t b = 0; b < NB; ++b) max_len = bstart[b + 1] - bstart[b] > max_len ? bstart[b + 1] - bstart[b] : max_len;
     c->lay.waves_per_bucket = (max_len + kChunk - 1) / kChunk;
+    c->rows = shared ? cfg->bucket / 256u : ((max_len - 1u) % (uint32_t)kChunk) / 256u + 1u;
     c->lay.uniform_bucket = (c->seg.size() == 1 && !shared) ? cfg->bucket : 0u;
     c->lay.shared_chunks = shared ? 1u : 0u;
     c->lay.bucket_shift = 31u;
@@ -425,6 +428,7 @@ qgx_status qgx_set_levels(qgx_ctx* ctx, const float* levels_host, uint32_t n_sym
     QGX_HIP(ctx, hipStreamSynchronize(st));
     T(ctx).n_sym = n_sym;
     T(ctx).levels_set = true;
+    T(ctx).crowded = levels_crowded(levels_host, n_sym, cell_mant(n_sym), kCellOct);
     if (ctx->cfg.code == QGX_CODE_ELIAS_OMEGA) {
         T(ctx).max_code_len = omega_length(n_sym);
         T(ctx).wide = n_sym <= 63u;     // the words of 1..63 differ within their first 11 bits, those of 64 and 65 do not
@@ -509,6 +513,10 @@ static qgx_status run_encode(qgx_ctx* ctx, EncMode mode, const float* V, uint32_
     a.parts = ctx->parts;
     a.xch = ctx->d_xch;
     a.n_cu = ctx->n_simd / 4u;
+    const bool powers = ctx->cfg.norm != QGX_NORM_L2 && ctx->cfg.norm != QGX_NORM_LINF;
+    const uint64_t chunks = (uint64_t)ctx->lay.K * ctx->lay.NC;
+    a.columns = a.parts == 1u && use_columns(chunks, ctx->lay.waves_per_bucket, ctx->lay.shared_chunks != 0u, a.slot_words == 0u, ctx->n_simd) &&
+                columns_pay(chunks, ctx->lay.waves_per_bucket, ctx->rows, ctx->lay.shared_chunks != 0u, a.slot_words == 0u, powers, T(ctx).crowded, T(ctx).n_sym, ctx->n_simd);
     a.tickets = ctx->d_tickets;
     hipError_t le = launch_encode(mode, ctx->lay, tab_of(ctx), ctx->d_sc, a, (hipStream_t)stream);
     if (le != hipSuccess) return fail(ctx, QGX_ERR_HIP, "encode launch: %s", hipGetErrorString(le));
@@ -707,6 +715,7 @@ qgx_status qgx_fit_levels(qgx_ctx* ctx, const float* V, uint32_t n_sym, uint32_t
     if (hist_out && !direct)
         QGX_HIP(ctx, hipMemcpyAsync(hist_out, ctx->d_hist, n_bins * sizeof(double), hipMemcpyDeviceToDevice, st));
     QGX_HIP(ctx, launch_fit(tab_of(ctx), ctx->d_hist, n_bins, sweeps, st));
+    if (sweeps != 0u) T(ctx).crowded = false;             // (not known)
     ctx->hist_bins = n_bins;
     return QGX_OK;
 }

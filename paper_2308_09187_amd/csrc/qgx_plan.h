@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 
 #ifdef __HIPCC__
 #define QGX_PLAN __host__ __device__ __forceinline__
@@ -127,6 +128,62 @@ inline bool use_columns(uint64_t chunks_of_all, uint32_t per_bucket, bool shared
 {
     if (shared) return chunks_of_all <= (ordered ? 1u : 4u) * (uint64_t)n_simd;
     return per_bucket <= 2u && (ordered ? chunks_of_all < 256u : chunks_of_all <= n_simd);
+}
+
+// What that form gives depends on the work in a chunk besides.  Its lanes have 16 rows in 4, 2 or 1 of their own (`rows`: those of the
+// longest bucket's last chunk, of 256 coordinates each), and lanes past the chunk's end work for nothing: quarters of n_simd up to which it
+// is no slower, L2 and L-infinity norms on the left, q norms (powers in binary64, row by row from memory) on the right.  A wave per chunk /
+// four, us, 8 workers in slots, 17 exponential levels: 1 row, 248 chunks 5.4 / 5.3, 512 5.7 / 6.3, 1024 6.1 / 7.9, q = 3 6.3 / 6.7 and
+// 7.1 / 9.8; 2 rows, 512 1 / 0.98 of the time, 1024 1 / 1.13, q = 3, 256 1 / 1.0, 384 1 / 1.10; 5 rows, 640 1 / 1.10; 9 rows, 192 1 / 1.02, 384 1 / 1.25; 10
+// rows, 256 1 / 1.0, 384 1 / 1.05, 640 1 / 1.22; 12 rows, 512 1 / 0.93, 1024 1 / 1.13, q = 3 1 / 0.83; 14 rows, 1024 1 / 1.0; 16 and 9,
+// 512 1 / 0.92, 640 1 / 1.08.  (15 uniform levels, nearly all zeros after L2, 1 / 1.08 where others have 1 / 0.95.)  In order
+// (below 256 chunks): 1 row 1 / 0.98, q = 3 1 / 1.07, 9 rows 1 / 1.07, the others gain.
+// Four waves load a large table sooner (127 levels, 1 row, 248 chunks 7.1 / 5.4, 512 7.3 / 6.4, 1024 1 / 1.02, 2 rows, 1024 1 / 0.93, 10 rows, 512
+// 1 / 0.87, 640 1 / 1.03; 34 to 65 levels, 1 row, 256 1 / 0.87, 384 1 / 0.98, 3 rows, 1024 1 / 0.9), and where the levels are too close for the cells
+// (`crowded`, known of tables that were set), a row takes several times as long: 1 / 0.8 to 1 / 0.6 from 3 rows on, but 1 / 1.13 with one row.
+// Fitted tables of 18 to 33 levels can be such: 1 row 1 / 1.11, 9 rows 1 / 0.63.
+// Shared chunks in slots, with buckets of 8 rows, which go through all the lanes' turns: 1536 chunks 1 / 0.87, 2048 1 / 1.06, 4096 1 / 1.09, q = 3 1 / 0.69, 1 / 1.11
+// and 1 / 1.31; 127 levels (LDS for fewer workgroups) 1280 1 / 0.97, 1536 1 / 1.04, 4096 1 / 1.18, in shorter buckets 1536 1 / 0.9, 3072 1 / 1.11; crowded 4096 1 / 0.8,
+// q = 3 1 / 1.13 (2560 1 / 0.89).
+inline bool columns_pay(uint64_t chunks_of_all, uint32_t per_bucket, uint32_t rows, bool shared, bool ordered, bool powers, bool crowded, uint32_t n_sym, uint32_t n_simd)
+{
+    const bool large = n_sym > 65u;
+    uint32_t quarters = 16u;
+    if (shared) {                                      // (rows: of a bucket)
+        if (ordered) return true;
+        if (crowded) quarters = rows == 8u && powers ? 12u : 16u;
+        else if (large) quarters = rows == 8u ? 5u : powers ? 16u : 6u;
+        else if (rows == 8u) quarters = 6u;
+    } else if (per_bucket == 2u) {
+        quarters = !powers && !crowded && (rows == 9u || rows == 10u) ? 2u : 4u;
+    } else if (!(crowded && rows > 2u)) {
+        constexpr uint8_t kQuarters[17][2] = {{0, 0}, {0, 0}, {2, 1}, {3, 2}, {4, 4}, {2, 2}, {3, 4}, {4, 4}, {4, 4}, {0, 2}, {1, 4}, {2, 4}, {2, 4}, {3, 4}, {4, 4}, {4, 4}, {4, 4}};
+        quarters = kQuarters[rows < 16u ? rows : 16u][powers ? 1 : 0];
+        if (!crowded) {
+            quarters += large ? (rows > 8u ? 1u : 2u) : n_sym > 33u && rows <= 8u ? 1u : 0u;
+            if (quarters == 0u && (rows == 9u ? n_sym > 17u : n_sym <= 17u && !powers)) quarters = 1u;
+        }
+        if (quarters > 4u) quarters = 4u;
+    }
+    return 4u * chunks_of_all <= (uint64_t)quarters * n_simd;
+}
+
+// Two levels strictly inside one cell of the look-up (qgx_tables.hip): rows then go through the levels one by one.
+inline bool levels_crowded(const float* levels, uint32_t n_sym, int cell_mant, int octaves)
+{
+    auto cell_of = [&](float x, bool* edge) {
+        uint32_t u;
+        std::memcpy(&u, &x, sizeof(u));
+        const int64_t c = (int64_t)(u >> (23 - cell_mant)) - ((int64_t)(127 - octaves) << cell_mant);
+        *edge = c > 0 && (u & ((1u << (23 - cell_mant)) - 1u)) == 0u;
+        return c > 0 ? c : 0;
+    };
+    for (uint32_t j = 1; j + 2u < n_sym; ++j) {
+        bool at_edge, unused;
+        const int64_t a = cell_of(levels[j], &at_edge), b = cell_of(levels[j + 1u], &unused);
+        if (a == b && !at_edge) return true;
+    }
+    return false;
 }
 
 // ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --

@@ -105,3 +105,29 @@ def test_norms_summed_from_memory_have_one_order(qgx, bucket, d, first, norm, sc
         np.testing.assert_array_equal(s.norms.cpu().numpy(), want)
     assert ctx.poll_error() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("slotted", [False, True])
+@pytest.mark.parametrize("bucket,d", [(128, 2051), (300, 3001), (2304, 9000)])
+def test_forms_change_with_the_table(qgx, bucket, d, slotted):
+    """Calls of one context take one form or the other by the table in use (order and tickets go on from call to call): each stream is
+    that of the symbols quantised and coded on their own."""
+    V = dev(np.random.default_rng(d).standard_normal((4, d), dtype=np.float32))
+    ctx, lay = make_ctx(qgx, d, 4, bucket, oracle.NORM_L2, synth.levels_exponential(16), seed=7)
+    for call, levels in enumerate((synth.levels_uniform(126), synth.levels_exponential(32), synth.levels_uniform(32), synth.levels_exponential(16),
+                                   synth.levels_exponential(40), synth.levels_uniform(64))):
+        ctx.set_levels(levels)
+        one, two = ctx.new_stream(slotted=slotted), ctx.new_stream(slotted=slotted)
+        for _ in range(2):
+            ctx.quantize_encode(V, call, one)
+        norms, sym = ctx.quantize(V, call)
+        ctx.encode(norms, sym, two)
+        a, b = one.to_host(), two.to_host()
+        for name in ("norms", "sub_end", "chunk_off"):
+            np.testing.assert_array_equal(a[name], b[name])
+        for k in range(4):
+            for c in range(lay.NC):
+                at, words = int(a["chunk_off"][k, c]), (int(a["sub_end"][k, c, -1]) + 31) // 32
+                np.testing.assert_array_equal(a["payload"][k, at: at + words], b["payload"][k, at: at + words])
+    assert ctx.poll_error() == 0
+    ctx.close()

@@ -32,6 +32,8 @@ extern "C" uint32_t buckets_per_group(uint32_t waves, uint64_t chunks, int order
 extern "C" uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t waves, uint32_t NB) { return qgx::waves_with_a_bucket(unit, group, waves, NB); }
 extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_staged(chunks, n_simd); }
 extern "C" int use_columns(uint64_t chunks, uint32_t per_bucket, int shared, int ordered, uint32_t n_simd) { return qgx::use_columns(chunks, per_bucket, shared != 0, ordered != 0, n_simd); }
+extern "C" int columns_pay(uint64_t chunks, uint32_t per_bucket, uint32_t rows, int shared, int ordered, int powers, int crowded, uint32_t n_sym, uint32_t n_simd) { return qgx::columns_pay(chunks, per_bucket, rows, shared != 0, ordered != 0, powers != 0, crowded != 0, n_sym, n_simd); }
+extern "C" int levels_crowded(const float* levels, uint32_t n_sym, int mant) { return qgx::levels_crowded(levels, n_sym, mant, 24); }
 extern "C" int eight_waves(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::eight_waves(n, K, simds, streams); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
@@ -191,3 +193,79 @@ def test_eight_waves_to_a_task_have_a_worker_each_and_a_place(plan):
     for tasks, K, streams in itertools.product((1, 256, 257, 384, 385, (1 << 32) - 1), (1, 7, 8, 65535), (1, 2)):
         got = plan.eight_waves(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024), C.c_uint32(streams))
         assert bool(got) == (K >= 8 and tasks <= (256 if streams == 2 else 384))
+
+
+@pytest.mark.parametrize("what,yes,no", [
+    # (chunks to a bucket, rows, shared, ordered, powers, crowded, levels): chunks where four waves to one are no slower, and where they are
+    ((1, 1, 0, 0, 0, 0, 17), (1, 256), (320, 1024)),
+    ((1, 1, 0, 0, 1, 0, 17), (), (1, 1024)),
+    ((1, 1, 0, 0, 0, 0, 33), (), (1, 1024)),
+    ((1, 1, 0, 0, 0, 1, 41), (), (1, 1024)),
+    ((1, 1, 0, 0, 0, 0, 127), (512,), (1024,)),
+    ((1, 1, 0, 0, 1, 0, 127), (1, 512), (640,)),
+    ((1, 1, 0, 0, 0, 0, 65), (256,), (512,)),
+    ((1, 2, 0, 0, 0, 0, 127), (1024,), ()),
+    ((1, 3, 0, 0, 0, 0, 65), (1024,), ()),
+    ((1, 9, 0, 0, 0, 0, 127), (256,), (384,)),
+    ((1, 10, 0, 0, 0, 0, 127), (512,), (640,)),
+    ((1, 16, 0, 0, 0, 0, 127), (1024,), ()),
+    ((1, 1, 0, 1, 1, 0, 17), (), (1, 248)),
+    ((1, 1, 0, 1, 0, 0, 17), (1, 248), ()),
+    ((1, 2, 0, 0, 0, 0, 17), (512,), (640, 1024)),
+    ((1, 2, 0, 0, 1, 0, 17), (256,), (384,)),
+    ((1, 5, 0, 0, 0, 0, 17), (512,), (640,)),
+    ((1, 9, 0, 0, 0, 0, 17), (), (192, 1024)),
+    ((1, 9, 0, 1, 0, 0, 17), (), (192,)),
+    ((1, 9, 0, 0, 0, 0, 33), (256,), (384,)),
+    ((1, 10, 0, 0, 0, 0, 17), (), (384, 1024)),
+    ((1, 10, 0, 0, 1, 0, 17), (1024,), ()),
+    ((1, 10, 0, 0, 0, 1, 33), (1024,), ()),
+    ((1, 12, 0, 0, 0, 0, 17), (512,), (640, 1024)),
+    ((1, 16, 0, 0, 1, 0, 17), (1024,), ()),
+    ((2, 16, 0, 0, 0, 0, 17), (1024,), ()),
+    ((2, 9, 0, 0, 0, 0, 17), (512,), (640, 1024)),
+    ((2, 9, 0, 0, 1, 0, 17), (1024,), ()),
+    ((2, 2, 0, 0, 0, 0, 17), (1024,), ()),
+    ((1, 4, 1, 0, 0, 0, 17), (1, 4096), ()),
+    ((1, 4, 1, 0, 0, 0, 127), (1536,), (2048, 4096)),
+    ((1, 8, 1, 0, 0, 0, 17), (1536,), (2048, 4096)),
+    ((1, 8, 1, 0, 1, 0, 17), (1536,), (2048, 4096)),
+    ((1, 8, 1, 0, 0, 0, 127), (1280,), (1536, 4096)),
+    ((1, 8, 1, 0, 0, 1, 33), (4096,), ()),
+    ((1, 4, 1, 0, 0, 1, 127), (4096,), ()),
+    ((1, 8, 1, 0, 1, 1, 33), (2560,), (4096,)),
+    ((1, 8, 1, 1, 1, 0, 127), (1, 1024), ()),
+])
+def test_four_waves_to_a_chunk_where_they_are_no_slower(plan, what, yes, no):
+    per_bucket, rows, shared, ordered, powers, crowded, n_sym = what
+    for chunks, want in [(c, 1) for c in yes] + [(c, 0) for c in no]:
+        got = plan.columns_pay(C.c_uint64(chunks), *(C.c_uint32(x) for x in (per_bucket, rows)), shared, ordered, powers, crowded, C.c_uint32(n_sym), C.c_uint32(1024))
+        assert got == want, (what, chunks)
+
+
+def test_crowded_levels_by_the_cells_themselves(plan):
+    """Cell edges of 1/16, 1/32 and 1/64 octave, written out in binary64: two interior levels strictly between two of them."""
+    plan.levels_crowded.argtypes = [C.c_void_p, C.c_uint32, C.c_int]
+    rng = np.random.default_rng(3)
+    seen = set()
+    for n_sym in (2, 3, 4, 17, 33, 34, 65, 66, 127):
+        mant = 4 if n_sym <= 33 else 5 if n_sym <= 65 else 6
+        edges = np.concatenate([[0.0], np.outer(2.0 ** np.arange(-24, 0), 1.0 + np.arange(1 << mant) / (1 << mant)).ravel()[1:], [1.0, np.inf]])
+        tables = [np.arange(n_sym) / (n_sym - 1), np.concatenate([[0.0], 2.0 ** np.arange(-(n_sym - 2.0), 1.0)])]
+        for _ in range(60):
+            t = np.sort(rng.uniform(size=n_sym) ** rng.integers(1, 9))
+            if n_sym > 3:                                        # levels on edges, and between them
+                t[rng.integers(1, n_sym - 1, size=n_sym // 2)] = rng.choice(edges[1:-2], size=n_sym // 2)
+            t[0], t[-1] = 0.0, 1.0
+            tables.append(np.sort(t))
+        for t in tables:
+            t = t.astype(np.float32)
+            if (np.diff(t) <= 0).any():
+                continue
+            inner = t[1:-1].astype(np.float64)
+            cell = np.searchsorted(edges, inner, side="right") - 1
+            inside = inner > edges[cell]
+            want = bool((np.bincount(cell[inside], minlength=1) > 1).any()) if len(inner) else False
+            assert bool(plan.levels_crowded(t.ctypes.data, n_sym, mant)) == want, (n_sym, t)
+            seen.add(want)
+    assert seen == {False, True}
