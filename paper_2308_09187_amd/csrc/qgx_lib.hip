@@ -653,7 +653,7 @@ qgx_status qgx_quantization_metrics(qgx_ctx* ctx, const float* V, const float* V
     return QGX_OK;
 }
 
-static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream* cur, const qgx_stream* prev)
+static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream* cur, const qgx_stream* prev, bool second_half = false)
 {
     a.sym_bits = longest_code(ctx) + 1;
     a.stage_words = (uint32_t)(kChunk / 2) * a.sym_bits / 32u + 8u;      // half a chunk, from a multiple of 4 words to one
@@ -661,7 +661,7 @@ static void fill_decode_args(const qgx_ctx* ctx, DecodeArgs& a, const qgx_stream
     if (a.stage_stride < 576u) a.stage_stride = 576u;     // a buffer also turns the output (16 rows of 36 floats)
     a.wide = (T(ctx).wide && (!prev || ctx->ts[ctx->sel_prev].wide)) ? 1u : 0u;   // one kernel variant reads both streams
     a.ksplit = waves_per_task(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u);
-    if (eight_waves(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u)) a.ksplit = 8;
+    if (eight_waves(ctx->lay.n_tasks, ctx->lay.K, ctx->n_simd, prev ? 2u : 1u, second_half)) a.ksplit = 8;
     if (ctx->ksplit_forced >= 0 && (uint32_t)ctx->ksplit_forced <= ctx->lay.K) a.ksplit = (uint32_t)ctx->ksplit_forced;
     a.n_cu = ctx->n_simd / 4u;
     a.norms = cur->norms; a.chunk_off = cur->chunk_off; a.sub_end = cur->sub_end; a.payload = cur->payload;
@@ -781,7 +781,7 @@ static qgx_status eg_step_with(qgx_ctx* ctx, int half, const qgx_stream* cur, co
         QGX_HIP(ctx, launch_decode(DecMode::Half0, ctx->lay, tab_of(ctx), ctx->d_sc, a, st));
         return QGX_OK;
     }
-    fill_decode_args(ctx, a, cur, prev);
+    fill_decode_args(ctx, a, cur, prev, true);
     a.s_partial = s_partial;
     a.x_out = X_out;
     Half1End left;

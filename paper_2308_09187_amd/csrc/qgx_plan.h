@@ -216,9 +216,13 @@ inline uint32_t waves_per_task(uint32_t n_tasks, uint32_t workers, uint32_t n_si
 // bytes a lane and took what it gave).  Four waves / eight, us: first half-step, 4 tasks of 8 workers 9.7 / 7.7, 128 11.8 / 8.6, 256 11.6 /
 // 9.0, 512 12.9 / 12.4, 768 14.1 / 19.0, of 12 256 12.5 / 11.2, 512 14.3 / 15.0, of 32 256 23.2 / 17.0, 512 26.5 / 22.2; second, 4 of 8
 // 12.4 / 10.6, 32 12.8 / 11.2, 256 12.2 / 11.6, 512 15.4 / 17.6, of 16 256 19.1 / 15.4, 512 24.1 / 25.8, of 32 32.0 / 23.6 and 40.2 / 42.6.
-inline bool eight_waves(uint32_t n_tasks, uint32_t workers, uint32_t n_simd, uint32_t streams)
+// Between 256 and 384 tasks of one stream: means of 8 workers, 320 10.4 / 11.0 and 384 10.2 / 11.1, of 12 12.6 / 13.0 and 12.5 / 13.2, of 16 14.8 / 14.1 and
+// 14.8 / 14.3, of 32 24.3 / 20.6 and 24.5 / 21.2; first half-steps (which have the means' rule) of 8 11.2 / 11.3 and 11.2 / 11.4, of 12 13.4 / 13.4 and
+// 13.8 / 13.4; second ones without a previous stream (`second`) of 8 17.0 / 16.6 and 17.4 / 17.2, of 12 20.2 / 18.7 and 19.9 / 19.0.
+inline bool eight_waves(uint32_t n_tasks, uint32_t workers, uint32_t n_simd, uint32_t streams, bool second = true)
 {
-    return workers >= 8u && n_tasks <= (streams == 2u ? n_simd / 4u : n_simd / 8u * 3u);
+    const bool longer = streams == 1u && (second || workers >= 16u);
+    return workers >= 8u && n_tasks <= (longer ? n_simd / 8u * 3u : n_simd / 4u);
 }
 
 }  // namespace qgx

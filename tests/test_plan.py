@@ -34,6 +34,7 @@ extern "C" int use_staged(uint64_t chunks, uint32_t n_simd) { return qgx::use_st
 extern "C" int use_columns(uint64_t chunks, uint32_t per_bucket, int shared, int ordered, uint32_t n_simd) { return qgx::use_columns(chunks, per_bucket, shared != 0, ordered != 0, n_simd); }
 extern "C" int columns_pay(uint64_t chunks, uint32_t per_bucket, uint32_t rows, int shared, int ordered, int powers, int crowded, uint32_t n_sym, uint32_t n_simd) { return qgx::columns_pay(chunks, per_bucket, rows, shared != 0, ordered != 0, powers != 0, crowded != 0, n_sym, n_simd); }
 extern "C" int levels_crowded(const float* levels, uint32_t n_sym, int mant) { return qgx::levels_crowded(levels, n_sym, mant, 24); }
+extern "C" int eight_waves_first(uint32_t n, uint32_t K, uint32_t simds) { return qgx::eight_waves(n, K, simds, 1, false); }
 extern "C" int eight_waves(uint32_t n, uint32_t K, uint32_t simds, uint32_t streams) { return qgx::eight_waves(n, K, simds, streams); }
 extern "C" uint32_t held_per_xcd(uint32_t waves, size_t lds, uint32_t n_cu) { return qgx::held_per_xcd(waves, lds, n_cu); }
 """
@@ -269,3 +270,9 @@ def test_crowded_levels_by_the_cells_themselves(plan):
             assert bool(plan.levels_crowded(t.ctypes.data, n_sym, mant)) == want, (n_sym, t)
             seen.add(want)
     assert seen == {False, True}
+
+
+def test_means_and_first_half_steps_have_eight_waves_where_they_gain(plan):
+    for tasks, K in itertools.product((1, 256, 257, 320, 384, 385), (1, 7, 8, 12, 15, 16, 32, 65535)):
+        got = plan.eight_waves_first(C.c_uint32(tasks), C.c_uint32(K), C.c_uint32(1024))
+        assert bool(got) == (K >= 8 and tasks <= (384 if K >= 16 else 256))
