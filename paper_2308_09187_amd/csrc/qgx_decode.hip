@@ -416,7 +416,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     for (uint32_t q = (uint32_t)lane; q < kBufs * stage_stride; q += kWave) stage[q] = 0;
     __syncthreads();
     if constexpr (KSPLIT == 1) {
-        if (!mine && MODE != DecMode::Half1) return;
+        if (!mine && (MODE != DecMode::Half1 || a.end == kEndSums)) return;
     }                                                    // (else: the waves meet at workgroup barriers below)
 
     // From bit t of the staged words to the buffer bit r with the bit before t on top of the 64 bits
@@ -661,6 +661,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     if constexpr (MODE == DecMode::Half1) {
         sdiff = wave_sum(sdiff);
         if (lane == 0) s_sd[w] = mine ? sdiff : 0.0;      // joined below, after a barrier
+        if (KSPLIT == 1 && lane == 0 && a.end == kEndSums) a.s_partial[task] = sdiff;
     }
     // KSPLIT: all waves of the group put their sums there, and after a barrier each of them adds them
     // up (in the order of the workers' runs) for its share of the rows and does the update for those.
@@ -756,8 +757,19 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
-    // The workgroup's sum of S, and as much of the scalar end as the launch has been given (Half1End).
+    // As much of the scalar end as the launch has been given (Half1End).  Where that is none of it, a task's sum (KSPLIT 1: left above; else its
+    // waves have put theirs down since the first of the barriers), and the waves go one by one: with a sum per workgroup, which all of them wait for,
+    // a worker of 19.7 M coordinates took 51.4 us, now 48.5, and two of 1 M 11.0, now 10.5 (fewer sums for the next launch to read gave 0.5 us at most,
+    // of 50).
     if constexpr (MODE == DecMode::Half1) {
+        if (a.end == kEndSums) {
+            if (KSPLIT > 1 && mine && part == 0 && lane == 0) {
+                double sd = s_sd[w];
+                for (int j = 1; j < KSPLIT; ++j) sd += s_sd[w + j];
+                a.s_partial[task] = sd;
+            }
+            return;
+        }
         __syncthreads();
         double own = 0.0;
         for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
@@ -765,8 +777,6 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             const double S = own + S_before;
             if (tid == 0) finish_scalars(sc, S, lay.K);
             x_from_y(step_size(S, lay.K), lay.d, a.Y, a.anchor, a.x_out, (uint32_t)tid, blockDim.x);
-        } else if (a.end == kEndSums) {
-            if (tid == 0) a.s_partial[blockIdx.x] = own;
         } else if (w == 0) {
             // each leaves its sum and counts itself (release), and the last one to arrive (acquire) adds up the sums
             uint32_t before = 0;
@@ -811,7 +821,7 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     const uint64_t grid = (nwaves + per - 1u) / per;
     DecodeArgs b = a;
     b.end = grid == 1u && a.x_out ? kEndAll : grid <= kWave ? kEndScalars : kEndSums;
-    if (left) *left = Half1End{(uint32_t)grid, b.end};
+    if (left) *left = Half1End{b.end};
     const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
@@ -887,7 +897,7 @@ hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_p
 {
     hipError_t e = hipSuccess;
     if (left.end == kEndSums) {
-        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, left.sums, lay.K, sc, s_partial);
+        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, lay.n_tasks, lay.K, sc, s_partial);
         e = hipGetLastError();
     }
     if (e != hipSuccess || X_out == nullptr || left.end == kEndAll) return e;

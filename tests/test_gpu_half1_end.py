@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("anchor", [False, True])
-@pytest.mark.parametrize("K,d", [(1, 255), (2, 2047), (3, 4099), (4, 1024), (4, 8191), (4, 8193), (1, 32769), (8, 130001), (2, 600002)])
+@pytest.mark.parametrize("K,d", [(1, 255), (2, 2047), (3, 4099), (4, 1024), (4, 8191), (4, 8193), (1, 32769), (8, 130001), (2, 600002), (1, 1200002), (5, 9000001)])
 def test_end_of_an_iteration(qgx, K, d, anchor):
     """X_{t+1} with and without being asked for it, S and gamma against the oracle; the static entry point the same bit for bit."""
     levels = synth.levels_exponential(16)
