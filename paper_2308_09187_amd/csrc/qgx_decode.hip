@@ -757,16 +757,23 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
-    // As much of the scalar end as the launch has been given (Half1End).  Where that is none of it, a task's sum (KSPLIT 1: left above; else its
-    // waves have put theirs down since the first of the barriers), and the waves go one by one: with a sum per workgroup, which all of them wait for,
-    // a worker of 19.7 M coordinates took 51.4 us, now 48.5, and two of 1 M 11.0, now 10.5 (fewer sums for the next launch to read gave 0.5 us at most,
-    // of 50).
+    // As much of the scalar end as the launch has been given (Half1End).  Where that is only sums (KSPLIT 1: left above; else the waves have put
+    // theirs down since the first of the barriers), the waves go one by one: with a barrier here a worker of 19.7 M coordinates took 51.4 us, now
+    // 48.5, and two of 1 M 11.0, now 10.5.
     if constexpr (MODE == DecMode::Half1) {
         if (a.end == kEndSums) {
             if (KSPLIT > 1 && mine && part == 0 && lane == 0) {
                 double sd = s_sd[w];
                 for (int j = 1; j < KSPLIT; ++j) sd += s_sd[w + j];
                 a.s_partial[task] = sd;
+            }
+            return;
+        }
+        if (KSPLIT > 1 && a.end == kEndGroupSums) {
+            if (tid == 0) {
+                double sd = 0.0;
+                for (uint32_t i = 0; i < nwaves; ++i) sd += s_sd[i];
+                a.s_partial[blockIdx.x] = sd;
             }
             return;
         }
@@ -797,6 +804,8 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
     }
 }
 
+constexpr uint32_t kFinishThreads = 1024;      // of k_finish_half1
+
 template <DecMode MODE, bool PREV, bool TWO, bool WIDE, int KSPLIT>
 static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, const DecodeArgs& a, hipStream_t st, Half1End* left)
 {
@@ -820,8 +829,10 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     // One workgroup, whose coordinates are all its own, writes X_{t+1} as well: an iteration of one bucket 30.9 us, now 28.0.
     const uint64_t grid = (nwaves + per - 1u) / per;
     DecodeArgs b = a;
-    b.end = grid == 1u && a.x_out ? kEndAll : grid <= kWave ? kEndScalars : kEndSums;
-    if (left) *left = Half1End{b.end};
+    // A sum per workgroup (where its waves meet anyway) as soon as the next launch's threads would have more than one each to read: iterations of
+    // 8 x 2^22 coordinates 146.0 us, with a sum per task 147.2.
+    b.end = grid == 1u && a.x_out ? kEndAll : grid <= kWave ? kEndScalars : KSPLIT > 1 && lay.n_tasks > kFinishThreads ? kEndGroupSums : kEndSums;
+    if (left) *left = Half1End{b.end == kEndSums ? lay.n_tasks : (uint32_t)grid, b.end};
     const size_t lds = (size_t)per * wave_lds;
     static LdsLimit limit;
     hipError_t e = limit.ensure(reinterpret_cast<const void*>(&k_decode<MODE, PREV, TWO, WIDE, KSPLIT>), lds);
@@ -867,7 +878,6 @@ hipError_t launch_decode(DecMode mode, const Layout& lay, const Tables* tab, Sca
 }
 
 // ---- the scalar end of the second half-step: S, gamma_{t+1}, t; and X_{t+1} on request -----------
-constexpr uint32_t kFinishThreads = 1024;
 __global__ __launch_bounds__(kFinishThreads) void k_finish_half1(uint32_t n_sums, uint32_t K, Scalars* sc, const double* __restrict__ sums)
 {
     __shared__ double s_red[kFinishThreads / kWave];
@@ -896,8 +906,8 @@ hipError_t launch_finish_half1(const Layout& lay, Scalars* sc, const double* s_p
                                const float* anchor, float* X_out, const Half1End& left, hipStream_t st)
 {
     hipError_t e = hipSuccess;
-    if (left.end == kEndSums) {
-        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, lay.n_tasks, lay.K, sc, s_partial);
+    if (left.end == kEndSums || left.end == kEndGroupSums) {
+        hipLaunchKernelGGL(k_finish_half1, dim3(1), dim3(kFinishThreads), 0, st, left.sums, lay.K, sc, s_partial);
         e = hipGetLastError();
     }
     if (e != hipSuccess || X_out == nullptr || left.end == kEndAll) return e;

@@ -177,7 +177,7 @@ struct DecodeArgs {
     float* out;                 // Decode: Vhat [K][d]; Average: mean [d]; Half0: X_{t+1/2} [d]
     float* Y;                   // [d] dual state (Half0 reads, Half1 updates)
     const float* anchor;        // [d] or null
-    double* s_partial;          // partial sums of S (Half1): a task's with kEndSums, a workgroup's with kEndScalars (no more of them than tasks)
+    double* s_partial;          // partial sums of S (Half1), each a task's (kEndSums) or a workgroup's (no more of them than tasks)
     float* x_out;               // [d] or null: X_{t+1}, for a Half1 of one workgroup to write as well
     uint32_t end;               // filled in by the launch: how much of the scalar end a Half1 does (Half1End)
     double* x_sum;              // [d] running sum of the X_{t+1/2} or null (Half0 adds its output)
@@ -212,9 +212,10 @@ struct LdsLimit {
     }
 };
 
-// What the second half-step has left: a partial sum of S per task; S, gamma and t already (kEndScalars); X_{t+1} as well (kEndAll).
-constexpr uint32_t kEndSums = 0, kEndScalars = 1, kEndAll = 2;
-struct Half1End { uint32_t end = kEndSums; };
+// What the second half-step has left: `sums` partial sums of S, per task (kEndSums) or per workgroup (kEndGroupSums); S, gamma and t already
+// (kEndScalars); X_{t+1} as well (kEndAll).
+constexpr uint32_t kEndSums = 0, kEndScalars = 1, kEndAll = 2, kEndGroupSums = 3;
+struct Half1End { uint32_t sums = 0, end = kEndSums; };
 
 hipError_t launch_build_tables(Tables* tab, hipStream_t st);
 hipError_t launch_encode(EncMode mode, const Layout& lay, const Tables* tab, Scalars* sc, const EncodeArgs& a,
