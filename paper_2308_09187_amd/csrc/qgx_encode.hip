@@ -1089,7 +1089,9 @@ __global__ __launch_bounds__(1024) void k_encode_columns(Layout lay, const Table
             }
             double* sums = s_sums + cw * (uint32_t)kWave + (uint32_t)lane;
             __syncthreads();                           // (the columns' sums have been read)
-            for (uint32_t turn = 0; turn < 4u; ++turn) {
+            // (a short chunk of a workgroup's own: only the quarters that it reaches into)
+            const uint32_t turns = nchunks > 1u ? 4u : (g.clen + kChunk / 4u - 1u) / (kChunk / 4u);
+            for (uint32_t turn = 0; turn < turns; ++turn) {
                 if (part == turn) {
                     if (turn > 0u) acc = *sums;
 #pragma unroll
