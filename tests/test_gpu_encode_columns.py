@@ -1,5 +1,6 @@
 """The coding kernel with four waves to a chunk, against the one with a wave per chunk: the same vectors coded by a few workers
-(few chunks) and by the first of many (more chunks than the former takes).  Every bit of the streams and every norm are the same."""
+(few chunks; with some tables and norms the rule has short chunks coded by the latter all the same) and by the first of many (more chunks
+than the former takes).  Every bit of the streams and every norm are the same."""
 import numpy as np
 import pytest
 import torch
@@ -107,13 +108,14 @@ def test_norms_summed_from_memory_have_one_order(qgx, bucket, d, first, norm, sc
     ctx.close()
 
 
+@pytest.mark.parametrize("norm", [oracle.NORM_L2, 3])
 @pytest.mark.parametrize("slotted", [False, True])
 @pytest.mark.parametrize("bucket,d", [(128, 2051), (300, 3001), (2304, 9000)])
-def test_forms_change_with_the_table(qgx, bucket, d, slotted):
+def test_forms_change_with_the_table(qgx, bucket, d, slotted, norm):
     """Calls of one context take one form or the other by the table in use (order and tickets go on from call to call): each stream is
     that of the symbols quantised and coded on their own."""
     V = dev(np.random.default_rng(d).standard_normal((4, d), dtype=np.float32))
-    ctx, lay = make_ctx(qgx, d, 4, bucket, oracle.NORM_L2, synth.levels_exponential(16), seed=7)
+    ctx, lay = make_ctx(qgx, d, 4, bucket, norm, synth.levels_exponential(16), seed=7)
     for call, levels in enumerate((synth.levels_uniform(126), synth.levels_exponential(32), synth.levels_uniform(32), synth.levels_exponential(16),
                                    synth.levels_exponential(40), synth.levels_uniform(64))):
         ctx.set_levels(levels)
