@@ -32,7 +32,6 @@
 // held by a running workgroup that needs nothing from later tickets; the wait is bounded all the same.
 #include "qgx_device.h"
 #include "qgx_plan.h"
-#include <algorithm>
 
 namespace qgx {
 
@@ -1316,8 +1315,7 @@ static hipError_t launch_columns(const Layout& lay, const Tables* tab, Scalars* 
     EncodeArgs b = a;
     const bool ordered = a.slot_words == 0u;
     // (where units are ticketed these are those of k_encode: a context's launches share the counters)
-    b.group = 1u;
-    const uint32_t chunks = GROUPED ? (ordered ? 4u : 1u) : std::min(lay.waves_per_bucket, lay.NC);
+    const uint32_t chunks = GROUPED ? (ordered ? 4u : 1u) : lay.waves_per_bucket;
     b.units = GROUPED ? (lay.NC + chunks - 1u) / chunks : lay.NB;
     b.spread = ordered && spread_workers(lay.K, b.units) ? 1u : 0u;
     const size_t lds = ColumnLds(a.pieces, chunks, GROUPED).stage + (size_t)chunks * a.stage_bytes;
