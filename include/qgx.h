@@ -316,7 +316,7 @@ qgx_status qgx_stream_bits(qgx_ctx* ctx, const qgx_stream* coded, uint64_t* tota
 
 /* Test and timing hook: the number of waves that share a task, half a chunk position, short ones
  * included, in qgx_decode_average and the half-steps (1, 2 or 4; ignored when above K), or 0 to go back to
- * the library's own rule.  Host-side only. */
+ * the library's own rule (which takes eight as well).  Host-side only. */
 qgx_status qgx_debug_set_waves_per_position(qgx_ctx* ctx, int waves);
 
 /* Copies the dual state out (checkpoint) or in (resume).  Y, anchor DEVICE [d]; NULL skips. */

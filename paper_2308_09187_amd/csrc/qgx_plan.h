@@ -117,11 +117,12 @@ QGX_PLAN uint32_t waves_with_a_bucket(uint32_t unit, uint32_t group, uint32_t wa
 inline bool use_staged(uint64_t chunks_of_all, uint32_t n_simd) { return chunks_of_all <= 8u * (uint64_t)n_simd; }
 
 // The coding kernel's form with four waves to a chunk, `per_bucket` chunks to a workgroup where buckets do not share chunks: as long as the
-// waves find places, and no more than eight of them on one compute unit while others are empty.  A wave per chunk / four,
+// waves find places, in slots and with unshared chunks with at most eight of them to a workgroup, so that no compute unit has more while others are
+// empty (shared chunks in order come four to a ticket, and thus sixteen waves to a workgroup).  A wave per chunk / four,
 // us, kernel alone, 8 workers and 17 levels if not said otherwise.  In slots, shared chunks (buckets of 1024): 512 chunks 13.3 / 8.1,
 // 1024 14.4 / 11.1, 2048 19.8 / 18.7, 4096 31.6 / 29.6, 8192 49.2 / 51.7; of 256: 4096 39.2 / 36.9, 8192 63.6 / 66.3.  One or
 // two chunks to a bucket: buckets of 8192, 512 10.0 / 8.2, 1024 13.5 / 11.9, 1280 15.0 / 14.8, 2048 17.4 / 19.2; of 6000, 816 11.6 / 9.6,
-// 1408 12.8 / 13.5.  Four: 256 10.0 / 10.6, 1024 11.8 / 12.7, but one of a vector of 1024 coordinates 5.7 / 5.1.  In order, shared
+// 1408 12.8 / 13.5.  Four: 256 10.0 / 10.6, 1024 11.8 / 12.7.  One chunk of 1024 coordinates 5.7 / 5.1.  In order, shared
 // chunks, four to a workgroup: 256 15.4 / 12.2, 1024 18.5 / 14.6, 1280 20.8 / 25.0, 2048 22.8 / 27.6; one or two to a bucket: 16 11.0 / 9.0,
 // 128 11.1 / 9.4, from 256 on a workgroup has four: 13.0 / 13.6.
 inline bool use_columns(uint64_t chunks_of_all, uint32_t per_bucket, bool shared, bool ordered, uint32_t n_simd)
@@ -133,8 +134,8 @@ inline bool use_columns(uint64_t chunks_of_all, uint32_t per_bucket, bool shared
 // What that form gives depends on the work in a chunk besides.  Its lanes have 16 rows in 4, 2 or 1 of their own (`rows`: those of the
 // longest bucket's last chunk, of 256 coordinates each), and lanes past the chunk's end work for nothing: quarters of n_simd up to which it
 // is no slower, L2 and L-infinity norms on the left, q norms (powers in binary64, row by row from memory) on the right.  A wave per chunk /
-// four, us, 8 workers in slots, 17 exponential levels: 1 row, 248 chunks 5.4 / 5.3, 512 5.7 / 6.3, 1024 6.1 / 7.9, q = 3 6.3 / 6.7 and
-// 7.1 / 9.8; 2 rows, 512 1 / 0.98 of the time, 1024 1 / 1.13, q = 3, 256 1 / 1.0, 384 1 / 1.10; 5 rows, 640 1 / 1.10; 9 rows, 192 1 / 1.02, 384 1 / 1.25; 10
+// four, us or as 1 / the ratio, 8 workers in slots, 17 exponential levels: 1 row, 248 chunks 5.4 / 5.3, 512 5.7 / 6.3, 1024 6.1 / 7.9, q = 3 6.3 / 6.7 and
+// 7.1 / 9.8; 2 rows, 512 1 / 0.98, 1024 1 / 1.13, q = 3, 256 1 / 1.0, 384 1 / 1.10; 5 rows, 640 1 / 1.10; 9 rows, 192 1 / 1.02, 384 1 / 1.25; 10
 // rows, 256 1 / 1.0, 384 1 / 1.05, 640 1 / 1.22; 12 rows, 512 1 / 0.93, 1024 1 / 1.13, q = 3 1 / 0.83; 14 rows, 1024 1 / 1.0; 16 and 9,
 // 512 1 / 0.92, 640 1 / 1.08.  (15 uniform levels, nearly all zeros after L2, 1 / 1.08 where others have 1 / 0.95.)  In order
 // (below 256 chunks): 1 row 1 / 0.98, q = 3 1 / 1.07, 9 rows 1 / 1.07, the others gain.
@@ -186,7 +187,7 @@ inline bool levels_crowded(const float* levels, uint32_t n_sym, int cell_mant, i
     return false;
 }
 
-// ---- waves to a task of the fused decoders (1, 2 or 4): each takes a run of the K workers, and they join their sums --
+// ---- waves to a task of the fused decoders (1, 2 or 4, and see eight_waves): each takes a run of the K workers, and they join their sums --
 // x = f * tasks against the wave slots (8 per SIMD with one stream, 4 with two).  A launch is bound by latency,
 // ceil(K / f) workers one after the other (a worker's chain of look-ups takes 2.2 us with one stream, 3.3 with two, however
 // few waves there are), or by throughput, x K / f of the time that full slots take for a worker (7.7 and 7.1 us, the unit
