@@ -757,7 +757,7 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             if (q + 1 < kPasses) __syncthreads();             // the partners have read these rows
         }
     }
-    // As much of the scalar end as the launch has been given (Half1End).  Where that is a sum per task (KSPLIT 1: left above; else the waves have put
+    // As much of the scalar end as the launch has been given (Half1End).  Where that is only sums (KSPLIT 1: left above; else the waves have put
     // theirs down since the first of the barriers), the waves go one by one: with a barrier here a worker of 19.7 M coordinates took 51.4 us, now
     // 48.5, and two of 1 M 11.0, now 10.5.
     if constexpr (MODE == DecMode::Half1) {
@@ -769,6 +769,14 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             }
             return;
         }
+        if (KSPLIT > 1 && a.end == kEndGroupSums) {
+            if (tid == 0) {
+                double sd = 0.0;
+                for (uint32_t i = 0; i < nwaves; ++i) sd += s_sd[i];
+                a.s_partial[blockIdx.x] = sd;
+            }
+            return;
+        }
         __syncthreads();
         double own = 0.0;
         for (uint32_t i = 0; i < nwaves; ++i) own += s_sd[i];
@@ -776,8 +784,6 @@ void k_decode(Layout lay, const Tables* __restrict__ tab, Scalars* sc, DecodeArg
             const double S = own + S_before;
             if (tid == 0) finish_scalars(sc, S, lay.K);
             x_from_y(step_size(S, lay.K), lay.d, a.Y, a.anchor, a.x_out, (uint32_t)tid, blockDim.x);
-        } else if (KSPLIT > 1 && a.end == kEndGroupSums) {
-            if (tid == 0) a.s_partial[blockIdx.x] = own;
         } else if (w == 0) {
             // each leaves its sum and counts itself (release), and the last one to arrive (acquire) adds up the sums
             uint32_t before = 0;
@@ -824,7 +830,7 @@ static hipError_t launch_as(const Layout& lay, const Tables* tab, Scalars* sc, c
     const uint64_t grid = (nwaves + per - 1u) / per;
     DecodeArgs b = a;
     // A sum per workgroup (where its waves meet anyway) as soon as the next launch's threads would have more than one each to read: iterations of
-    // 8 x 2^22 coordinates 146.0 us, with a sum per task 147.2 (without the barrier for it, 0.2 more).
+    // 8 x 2^22 coordinates 146.0 us, with a sum per task 147.2.
     b.end = grid == 1u && a.x_out ? kEndAll : grid <= kWave ? kEndScalars : KSPLIT > 1 && lay.n_tasks > kFinishThreads ? kEndGroupSums : kEndSums;
     if (left) *left = Half1End{b.end == kEndSums ? lay.n_tasks : (uint32_t)grid, b.end};
     const size_t lds = (size_t)per * wave_lds;
